@@ -7,8 +7,19 @@
 // Design (gfx950):
 //   1. validate : the data-error flags, a sweep over the whole input.
 //   2. in-links : the reverse of the port graph -- per switch v the (u, port)
-//                 pairs of the links u -> v -- counted, scanned and filled.
-//   3. search   : one workgroup per request.  Its usable-switch bitset,
+//                 pairs of the links u -> v -- counted, scanned and filled --
+//                 and packed link records for the directed search.
+//   3. bounds   : with many more legs than switches, for every switch that a
+//                 leg ends at, a lower bound of every switch's distance to
+//                 it: the distances of the whole port graph, which no
+//                 request's restrictions can shorten.
+//   4. goal     : one wavefront per request.  A leg relaxes only switches
+//                 whose distance plus bound stays within a limit, which starts
+//                 at the bound of the leg's source and grows until the leg's
+//                 end is reached; the few dozen switches that pass it live in
+//                 a small LDS hash table.  A request that outgrows its table or
+//                 its work limit is left for 5.
+//   5. search   : one workgroup per request.  Its usable-switch bitset,
 //                 distances and frontier queues live in LDS.  Each leg is
 //                 a chaotic relaxation in rounds: a wavefront takes 64
 //                 frontier switches at a time (one lane each reads the
@@ -27,7 +38,9 @@
 //                 The legs' switches collect in an LDS walk; the rules are
 //                 written from it, one wavefront per switch finding the port
 //                 of least (weight, index) to the next switch.
+#include <algorithm>
 #include <climits>
+#include <type_traits>
 
 #include "pc_internal.h"
 
@@ -95,16 +108,21 @@ __device__ __forceinline__ uint32_t link_weight(const int32_t *__restrict__ port
     return weight ? weight[p] : 1u;
 }
 
-// In-link counts: one thread per switch u, +1 at the peer of each link.
+// Lanes per switch of the in-link kernels: a switch's ports are read
+// together (one thread per switch walked 48 ports one after another: 181 and
+// 162 us for 138,240 ports, against 7 and 8 us).
+constexpr int kInLanes = 16;
+
+// In-link counts: kInLanes lanes per switch u, +1 at the peer of each link.
 __global__ __launch_bounds__(256) void k_ps_in_count(int32_t V, const int32_t *__restrict__ port_off,
                                                      const int32_t *__restrict__ port_peer, int64_t n_ports,
                                                      const uint32_t *__restrict__ weight, int32_t *__restrict__ cnt)
 {
-    const int32_t u = blockIdx.x * blockDim.x + threadIdx.x;
+    const int32_t u = (blockIdx.x * blockDim.x + threadIdx.x) / kInLanes;
     if (u >= V) return;
     const int64_t b = port_off[u], e = port_off[u + 1];
     if (!pc_range_ok(b, e, n_ports)) return;
-    for (int64_t p = b; p < e; ++p)
+    for (int64_t p = b + threadIdx.x % kInLanes; p < e; p += kInLanes)
         if (link_weight(port_peer, weight, V, p)) atomicAdd(&cnt[port_peer[p]], 1);
 }
 
@@ -116,16 +134,567 @@ __global__ __launch_bounds__(256) void k_ps_in_fill(int32_t V, const int32_t *__
                                                     const uint32_t *__restrict__ weight,
                                                     int32_t *__restrict__ cursor, int2 *__restrict__ rin)
 {
-    const int32_t u = blockIdx.x * blockDim.x + threadIdx.x;
+    const int32_t u = (blockIdx.x * blockDim.x + threadIdx.x) / kInLanes;
     if (u >= V) return;
     const int64_t b = port_off[u], e = port_off[u + 1];
     if (!pc_range_ok(b, e, n_ports)) return;
-    for (int64_t p = b; p < e; ++p) {
+    for (int64_t p = b + threadIdx.x % kInLanes; p < e; p += kInLanes) {
         const uint32_t w = link_weight(port_peer, weight, V, p);
         if (w) {
             const int32_t pos = atomicAdd(&cursor[port_peer[p]], 1);
             rin[pos] = make_int2(u, static_cast<int32_t>(w));  // the weight's bits
         }
+    }
+}
+
+// ---------------------------------------------------------------- directed search
+constexpr uint32_t kNoLink = 0xFFFF0000u;  // bounds' links: slot 0 at the weight that saturates every sum
+constexpr uint32_t kNoPeer = 0xFFFFu;  // packed links: the port is no link (switch ids stay below 12,288)
+
+// The links' largest weight and the complement of their smallest
+// (wspan[0], wspan[1], both maxima), and the switches that some leg ends at
+// (every target and waypoint that is a switch).
+__global__ __launch_bounds__(256) void k_ps_survey(int32_t V, const int32_t *__restrict__ port_peer, int64_t n_ports,
+                                                   const uint32_t *__restrict__ weight, int32_t Q,
+                                                   const int32_t *__restrict__ target, const int32_t *__restrict__ via,
+                                                   int32_t Kv, int32_t *__restrict__ need,
+                                                   uint32_t *__restrict__ wspan)
+{
+    __shared__ uint32_t top[2];
+    if (threadIdx.x < 2) top[threadIdx.x] = 0;
+    __syncthreads();
+    const int64_t nv = static_cast<int64_t>(Q) * Kv;
+    int64_t tot = n_ports > nv ? n_ports : nv;
+    if (Q > tot) tot = Q;
+    uint32_t mine = 0, least = ~0u;
+    for (int64_t x = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; x < tot;
+         x += static_cast<int64_t>(gridDim.x) * blockDim.x) {
+        if (x < n_ports) {
+            const uint32_t w = link_weight(port_peer, weight, V, x);
+            mine = mine > w ? mine : w;
+            if (w) least = least < w ? least : w;
+        }
+        if (x < Q && target[x] >= 0 && target[x] < V) need[target[x]] = 1;
+        if (x < nv && via[x] >= 0 && via[x] < V) need[via[x]] = 1;
+    }
+    if (mine) {
+        atomicMax(&top[0], mine);
+        atomicMax(&top[1], ~least);
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 && top[threadIdx.x]) atomicMax(wspan + threadIdx.x, top[threadIdx.x]);
+}
+
+// Links of one weight only (or none at all): equally short paths are the
+// rule, a fat-tree's edge switches have one through every core, and a
+// directed search would keep most of the graph.  The workgroup search takes
+// every request then (2,880 switches, 32,768 requests at weight 1: 2.4 ms,
+// directed 3.1 ms; weights 1-2: 2.5 ms, directed 0.8 ms).
+__device__ __forceinline__ bool one_weight(const uint32_t *wspan) { return wspan[0] == ~wspan[1] || wspan[0] == 0; }
+
+// Bounds are kept in 16 bits, in units of 2^shift: a largest weight of up
+// to 12 bits leaves room for sixteen such links before a bound saturates.
+// Weights are rounded down, so the sums stay lower bounds.
+__device__ __forceinline__ uint32_t bound_shift(const uint32_t *wspan)
+{
+    const int bits = 32 - __builtin_clz(wspan[0] | 1u);
+    return bits > 12 ? static_cast<uint32_t>(bits - 12) : 0u;
+}
+
+// The LDS slot of switch v in the bounds kernel: switches 16 apart fall in
+// different banks (the peers of a fat-tree's core are a pod apart).
+__device__ __forceinline__ int32_t bslot(int32_t v) { return v ^ ((v >> 4) & 15); }
+
+// Packed forms of the port graph: per port (peer | region << 16, weight)
+// and (peer's slot | scaled weight << 16), per switch its port range (empty when
+// its offsets are bad), and the list of the switches that legs end at.
+__global__ __launch_bounds__(256) void k_ps_links(int32_t V, const int32_t *__restrict__ port_off,
+                                                  const int32_t *__restrict__ port_peer, int64_t n_ports,
+                                                  const uint32_t *__restrict__ weight,
+                                                  const uint8_t *__restrict__ region,
+                                                  const int32_t *__restrict__ need, const int32_t *__restrict__ row,
+                                                  const uint32_t *__restrict__ wspan, int2 *__restrict__ link,
+                                                  uint32_t *__restrict__ blink, int2 *__restrict__ range,
+                                                  int32_t *__restrict__ ends)
+{
+    const uint32_t shift = bound_shift(wspan);
+    const int64_t tot = n_ports > V ? n_ports : V;
+    for (int64_t x = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; x < tot;
+         x += static_cast<int64_t>(gridDim.x) * blockDim.x) {
+        if (x < n_ports) {
+            const uint32_t w = link_weight(port_peer, weight, V, x);
+            const uint32_t u = w ? static_cast<uint32_t>(port_peer[x]) : kNoPeer;
+            const uint32_t r = w ? region[u] : 32u;
+            const uint32_t ws = w >> shift;
+            link[x] = make_int2(static_cast<int>(u | (r < 32 ? r : 32u) << 16), static_cast<int>(w));
+            blink[x] = w ? static_cast<uint32_t>(bslot(static_cast<int32_t>(u))) | (ws < 0xFFFFu ? ws : 0xFFFFu) << 16 : kNoLink;
+        }
+        if (x < V) {
+            const int64_t b = port_off[x], e = port_off[x + 1];
+            range[x] = pc_range_ok(b, e, n_ports) ? make_int2(static_cast<int>(b), static_cast<int>(e)) : make_int2(0, 0);
+            if (need[x]) ends[row[x]] = static_cast<int32_t>(x);
+        }
+    }
+}
+
+// Distances of the whole port graph to 2 * kW of the listed switches per
+// workgroup, two 16-bit values a word: every switch takes the minimum over
+// its links of weight + the peer's values until nothing changes.  A quad of
+// lanes shares a switch's links, kBv switches and kBu links of each in flight
+// at once, the next switches' ranges read ahead (wider groups spend more
+// instructions on the minimum over the group than on the links: 0.63 ms with
+// 16 lanes instead of 0.34 ms).  Values only fall, and each entry is written by one
+// lane, so sweeps read whatever is newest.  Saturated sums (0xFFFF) are lower
+// bounds like the rest.  A graph that needs more than kSweeps sweeps is too
+// long for this: its rows are marked as missing.
+// Bound by vector instructions (two packed adds and minima per link, word and
+// sweep): 2,880 rows over 138,240 links, 7-8 sweeps, in 0.31 ms with eight
+// rows per workgroup, 0.33 ms with four.
+constexpr int kSweeps = 40;
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u16x2 pk_min(u16x2 a, u16x2 b) { return __builtin_elementwise_min(a, b); }
+
+// Minimum over a quad of lanes, in each of them.
+__device__ __forceinline__ u16x2 quad_pk_min(u16x2 x)
+{
+    const auto dpp = [](u16x2 a, auto ctrl) {
+        const int v = __builtin_bit_cast(int, a);
+        return __builtin_bit_cast(
+            u16x2, __builtin_amdgcn_update_dpp(v, v, decltype(ctrl)::value, 0xF, 0xF, false));
+    };
+    x = pk_min(x, dpp(x, std::integral_constant<int, 0xB1>{}));     // quad_perm 1,0,3,2
+    return pk_min(x, dpp(x, std::integral_constant<int, 0x4E>{}));  // quad_perm 2,3,0,1
+}
+
+template <int kW>
+struct __align__(4 * kW) BoundWords {
+    u16x2 w[kW];
+};
+
+template <int kBv, int kBu, int kW>
+__global__ __launch_bounds__(256 * kW) void k_ps_bound(int32_t V, const int2 *__restrict__ range,
+                                                            const uint32_t *__restrict__ blink,
+                                                            const int32_t *__restrict__ ends,
+                                                            const int32_t *__restrict__ n_ends,
+                                                            const uint32_t *__restrict__ wspan,
+                                                            uint16_t *__restrict__ bound, int32_t *__restrict__ row_ok)
+{
+    using Words = BoundWords<kW>;
+    constexpr int kRows = 2 * kW, kBoundThreads = 256 * kW;
+    extern __shared__ uint4 ps_bound_lds[];
+    Words *dd = reinterpret_cast<Words *>(ps_bound_lds);  // [V rounded up to 16], at bslot(v)
+    const int32_t n = *n_ends;
+    const int32_t r0 = blockIdx.x * kRows;
+    if (r0 >= n || one_weight(wspan)) return;
+    const int tid = threadIdx.x;
+    const u16x2 far = {0xFFFF, 0xFFFF};
+    Words none;
+#pragma unroll
+    for (int k = 0; k < kW; ++k) none.w[k] = far;
+    for (int32_t v = tid; v < ((V + 15) & ~15); v += kBoundThreads) dd[v] = none;
+    __syncthreads();
+    if (tid < kRows && r0 + tid < n) reinterpret_cast<uint16_t *>(&dd[bslot(ends[r0 + tid])])[tid] = 0;
+    __syncthreads();
+    constexpr int GS = 4, kStep = kBoundThreads / GS * kBv;
+    const int grp = tid / GS, gl = tid % GS;
+    auto ranges = [&](int32_t v0, int2 (&r)[kBv]) {
+#pragma unroll
+        for (int k = 0; k < kBv; ++k) r[k] = range[min(v0 + k, V - 1)];
+    };
+    bool done = false;
+    for (int sweep = 0; sweep < kSweeps && !done; ++sweep) {
+        bool changed = false;
+        int2 rn[kBv];
+        ranges(grp * kBv, rn);
+        for (int32_t v0 = grp * kBv; v0 < V; v0 += kStep) {
+            int2 r[kBv];
+#pragma unroll
+            for (int k = 0; k < kBv; ++k) r[k] = rn[k];
+            uint32_t L[kBv][kBu];
+#pragma unroll
+            for (int k = 0; k < kBv; ++k)
+#pragma unroll
+                for (int j = 0; j < kBu; ++j) {
+                    const int32_t p = r[k].x + j * GS + gl;
+                    L[k][j] = p < r[k].y ? blink[p] : kNoLink;
+                }
+            ranges(v0 + kStep, rn);
+#pragma unroll
+            for (int k = 0; k < kBv; ++k) {
+                if (v0 + k >= V) break;
+                Words acc = none;
+                auto take = [&](uint32_t link) {  // (no link: weight 0xFFFF, which saturates)
+                    const Words x = dd[link & 0xFFFFu];
+                    const uint16_t w = static_cast<uint16_t>(link >> 16);
+                    const u16x2 ww = {w, w};
+#pragma unroll
+                    for (int i = 0; i < kW; ++i) acc.w[i] = pk_min(acc.w[i], __builtin_elementwise_add_sat(x.w[i], ww));
+                };
+#pragma unroll
+                for (int j = 0; j < kBu; ++j) take(L[k][j]);
+                for (int32_t p = r[k].x + kBu * GS; p < r[k].y; p += GS)
+                    take(p + gl < r[k].y ? blink[p + gl] : kNoLink);
+#pragma unroll
+                for (int i = 0; i < kW; ++i) acc.w[i] = quad_pk_min(acc.w[i]);
+                if (gl == 0) {
+                    const Words old = dd[bslot(v0 + k)];
+                    bool less = false;
+#pragma unroll
+                    for (int i = 0; i < kW; ++i) {
+                        acc.w[i] = pk_min(acc.w[i], old.w[i]);
+                        less |= __builtin_bit_cast(uint32_t, acc.w[i]) != __builtin_bit_cast(uint32_t, old.w[i]);
+                    }
+                    if (less) {
+                        dd[bslot(v0 + k)] = acc;
+                        changed = true;
+                    }
+                }
+            }
+        }
+        done = !__syncthreads_or(changed);
+    }
+    for (int k = 0; k < kRows; ++k) {
+        if (r0 + k >= n) break;
+        uint16_t *row = bound + static_cast<int64_t>(r0 + k) * V;
+        for (int32_t v = tid; v < V; v += kBoundThreads) row[v] = reinterpret_cast<const uint16_t *>(&dd[bslot(v)])[k];
+        if (tid == 0) row_ok[r0 + k] = done;
+    }
+}
+
+// One wavefront per request, directed by the bounds.  A switch u relaxed to
+// distance d is kept only while d + bound(u) <= limit, the smaller of B and
+// the distance found for the leg's end.  Every switch on a minimum-weight
+// path of the request's own graph passes that test once B reaches the path's
+// weight, with its exact distance, since the bounds never exceed the
+// restricted distances; so do all of its equally short predecessors, which
+// is what the walk-back compares.  B starts at the source's bound; while
+// the end lies beyond it, every kept switch is relaxed again with B raised to
+// the smallest value that was turned away, and at least by half of its excess
+// over the start, so that the passes stay few under weights of any size
+// (doubling the excess kept so many more switches that about 1 request in 50
+// outgrew its table: 597 + 207 us instead of 541 + 6 for both searches).
+// Kept switches: an LDS hash table of distance << 16 | switch (forbidden
+// switches sit in it with bit 15 set) and a ring of the slots to relax.  GS
+// lanes share a switch's links, so 64 / GS switches are relaxed at once, kUn
+// links per lane in flight.  Requests that need more than kFull slots or
+// max_steps rounds of links go to the list `hard`.
+// Bound by the latency of the link and bound reads, so the wave slots have
+// to fill: 512 slots keep 5 KB of LDS per wavefront (1,024 slots: 0.96 ms
+// instead of 0.60 at the time).  Three links per lane in flight and 16 lanes a
+// switch fit 48-port switches (0.51 ms; four links 0.54, 8 lanes 0.64, 32 lanes
+// 0.52).  65,536 weighted requests with a waypoint each over 2,880 switches:
+// 10.44 ms by the workgroup search, 0.51 + 0.31 ms (bounds) directed.
+constexpr int kSlots = 512;
+constexpr int kFull = 384;
+constexpr uint32_t kForbid = 0x8000u;
+constexpr int kUn = 3;
+
+template <int GS>
+__global__ __launch_bounds__(64) void k_ps_goal(
+    int32_t V, const int2 *__restrict__ range, const int2 *__restrict__ link, const uint8_t *__restrict__ region,
+    const int32_t *__restrict__ rin_off, const int2 *__restrict__ rin, const int32_t *__restrict__ row,
+    const int32_t *__restrict__ row_ok, const uint16_t *__restrict__ bound, const uint32_t *__restrict__ wspan,
+    const int32_t *__restrict__ src, const int32_t *__restrict__ target, const uint32_t *__restrict__ allowed,
+    const int32_t *__restrict__ via, int32_t Kv, const int32_t *__restrict__ forbid, int32_t Kf,
+    const pc_key *__restrict__ key, const int32_t *__restrict__ out_port, int32_t prio, int32_t max_hops,
+    int32_t *__restrict__ hops_out, int32_t *__restrict__ path_out, pc_rule *__restrict__ rules_out, int32_t max_steps,
+    int32_t *__restrict__ hard, int32_t *__restrict__ n_hard)
+{
+    constexpr unsigned long long kEmpty = ~0ull;
+    __shared__ __align__(16) unsigned long long tab[kSlots];
+    __shared__ uint32_t inq[kSlots / 32];
+    __shared__ uint16_t ring[kSlots];
+    extern __shared__ uint16_t ps_walk[];  // the walk, one leg backwards, the walk's ports: max_hops + 2 each
+    uint16_t *walk = ps_walk, *leg = walk + max_hops + 2, *act = leg + max_hops + 2;
+    const int lane = threadIdx.x, grp = lane / GS, gl = lane % GS;
+    constexpr int kNG = 64 / GS;
+    auto wave_sync = [] {  // LDS written by other lanes of this wavefront
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    auto slot_of = [](uint32_t u) { return (u * 40503u >> 7) & (kSlots - 1); };
+    if (one_weight(wspan)) return;
+    const int32_t q = blockIdx.x;
+    const int32_t s = src[q], t = target[q];
+    bool fail = s < 0 || s >= V || t < 0 || t >= V;
+    if (!fail) {
+        const int2 r = range[t];
+        fail = out_port[q] < 0 || out_port[q] >= r.y - r.x;
+    }
+    const uint32_t A = allowed[q];
+    const int32_t *fl = forbid + static_cast<int64_t>(q) * Kf;
+    const int32_t *vl = via + static_cast<int64_t>(q) * Kv;
+    auto usable = [&](int32_t v) {
+        const uint32_t r = region[v];
+        if (r >= 32 || !((A >> r) & 1u)) return false;
+        for (int32_t k = 0; k < Kf; ++k)
+            if (fl[k] == v) return false;
+        return true;
+    };
+    int32_t m = 0;  // waypoints: the list ends at its first -1
+    while (m < Kv && vl[m] != -1) ++m;
+    const uint32_t shift = bound_shift(wspan);
+    // every stop is a usable switch, or the request fails before any search
+    if (!fail) fail = !usable(s) || !usable(t);
+    for (int32_t k = 0; k < m && !fail; ++k) fail = vl[k] < 0 || vl[k] >= V || !usable(vl[k]);
+
+    int32_t total = 0, steps = 0;
+    bool hard_q = false;
+    int32_t from = s;
+    if (lane == 0 && !fail) walk[0] = static_cast<uint16_t>(s);
+    for (int32_t li = 0; li <= m && !fail && !hard_q; ++li) {
+        const int32_t to = li < m ? vl[li] : t;
+        const int32_t rw = row[to];
+        if (!row_ok[rw]) {
+            hard_q = true;
+            break;
+        }
+        const uint16_t *bt = bound + static_cast<int64_t>(rw) * V;
+        // the empty table with the forbidden switches and the leg's source
+        for (int i = lane; i < kSlots / 2; i += 64) reinterpret_cast<ulonglong2 *>(tab)[i] = make_ulonglong2(kEmpty, kEmpty);
+        if (lane < kSlots / 32) inq[lane] = 0;
+        wave_sync();
+        int32_t stored = 1;
+        if (lane < Kf && fl[lane] >= 0 && fl[lane] < V) {
+            const uint32_t f = static_cast<uint32_t>(fl[lane]);
+            uint32_t h = slot_of(f);
+            while (true) {
+                const unsigned long long o = atomicCAS(&tab[h], kEmpty, static_cast<unsigned long long>(f | kForbid));
+                if (o == kEmpty || (o & 0x7FFFu) == f) break;
+                h = (h + 1) & (kSlots - 1);
+            }
+        }
+        wave_sync();
+        stored += Kf;
+        uint32_t s_slot = slot_of(static_cast<uint32_t>(from));
+        while (tab[s_slot] != kEmpty) s_slot = (s_slot + 1) & (kSlots - 1);
+        wave_sync();
+        if (lane == 0) {
+            tab[s_slot] = static_cast<unsigned long long>(from);
+            ring[0] = static_cast<uint16_t>(s_slot);
+            inq[s_slot >> 5] = 1u << (s_slot & 31);
+        }
+        wave_sync();
+        uint32_t head = 0, tail = 1;
+        const uint32_t base = static_cast<uint32_t>(bt[from]) << shift;
+        uint64_t B = base;  // limits and sums in 64 bits: a bound may exceed 2^31
+        uint32_t dto = from == to ? 0u : static_cast<uint32_t>(kInf);
+        while (true) {
+            uint32_t turned = ~0u;  // the smallest distance + bound beyond B (below 2^32 - 1, or saturated)
+            while (head != tail && !hard_q) {
+                // 64 / GS switches of the ring; one lane group each
+                const uint32_t n = tail - head;
+                const bool mine = static_cast<uint32_t>(grp) < n;
+                uint32_t v = 0, dv = 0;
+                int2 r = make_int2(0, 0);
+                if (mine) {
+                    const uint32_t sl = ring[(head + grp) & (kSlots - 1)];
+                    if (gl == 0) atomicAnd(&inq[sl >> 5], ~(1u << (sl & 31)));
+                    const unsigned long long e = tab[sl];
+                    v = static_cast<uint32_t>(e & 0x7FFFu);
+                    dv = static_cast<uint32_t>(e >> 16);
+                    r = range[v];
+                }
+                head += n < kNG ? n : kNG;
+                wave_sync();
+                for (int32_t p0 = 0; __ballot(r.x + p0 < r.y) != 0; p0 += GS * kUn) {
+                    ++steps;
+                    int2 L[kUn];
+                    uint32_t hb[kUn];
+#pragma unroll
+                    for (int k = 0; k < kUn; ++k) {
+                        const int32_t p = r.x + p0 + k * GS + gl;
+                        L[k] = p < r.y ? link[p] : make_int2(static_cast<int>(kNoPeer | 32u << 16), 0);
+                    }
+#pragma unroll
+                    for (int k = 0; k < kUn; ++k) {
+                        const uint32_t x = static_cast<uint32_t>(L[k].x), g = x >> 16;
+                        const bool ok = g < 32 && ((A >> (g & 31)) & 1u);
+                        if (!ok) L[k].x = static_cast<int>(kNoPeer);
+                        hb[k] = ok ? bt[x & 0xFFFFu] : 0u;
+                    }
+#pragma unroll
+                    for (int k = 0; k < kUn; ++k) {
+                        const uint32_t u = static_cast<uint32_t>(L[k].x) & 0xFFFFu;
+                        // distances are below 2^31 - 1; a heavier sum is no path
+                        const uint32_t nd = dv + min(static_cast<uint32_t>(L[k].y), static_cast<uint32_t>(kInf));
+                        const uint64_t f = static_cast<uint64_t>(nd) + (static_cast<uint64_t>(hb[k]) << shift);
+                        bool keep = u != kNoPeer && nd < static_cast<uint32_t>(kInf) && f <= dto;
+                        if (keep && f > B) {
+                            turned = min(turned, static_cast<uint32_t>(f < 0xFFFFFFFEull ? f : 0xFFFFFFFEull));
+                            keep = false;
+                        }
+                        bool fresh = false, push = false;
+                        uint32_t h = 0;
+                        if (keep) {
+                            const unsigned long long want = static_cast<unsigned long long>(nd) << 16 | u;
+                            h = slot_of(u);
+                            while (true) {
+                                unsigned long long e = tab[h];
+                                if (e == kEmpty) {
+                                    e = atomicCAS(&tab[h], kEmpty, want);
+                                    if (e == kEmpty) {
+                                        fresh = push = true;
+                                        break;
+                                    }
+                                }
+                                if ((e & 0x7FFFu) == u) {
+                                    // (a forbidden switch's entry is below every distance)
+                                    if (!(e & kForbid) && want < e) push = atomicMin(&tab[h], want) > want;
+                                    break;
+                                }
+                                h = (h + 1) & (kSlots - 1);
+                            }
+                        }
+                        if (push) push = !((atomicOr(&inq[h >> 5], 1u << (h & 31)) >> (h & 31)) & 1u);
+                        if (__ballot(keep && u == static_cast<uint32_t>(to))) {
+                            uint32_t d = keep && u == static_cast<uint32_t>(to) ? nd : static_cast<uint32_t>(kInf);
+#pragma unroll
+                            for (int off = 32; off > 0; off >>= 1) d = min(d, static_cast<uint32_t>(__shfl_xor(d, off, 64)));
+                            dto = min(dto, d);
+                        }
+                        const uint64_t pm = __ballot(push);
+                        if (push) {
+                            const uint32_t below = __builtin_amdgcn_mbcnt_hi(
+                                static_cast<uint32_t>(pm >> 32),
+                                __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(pm), 0u));
+                            ring[(tail + below) & (kSlots - 1)] = static_cast<uint16_t>(h);
+                        }
+                        tail += static_cast<uint32_t>(__popcll(pm));
+                        stored += static_cast<int32_t>(__popcll(__ballot(fresh)));
+                        if (stored > kFull) break;  // room for one more round of 64 is left either way
+                    }
+                    wave_sync();
+                    if (stored > kFull || steps > max_steps) {
+                        hard_q = true;
+                        break;
+                    }
+                }
+            }
+            if (hard_q || dto <= B) break;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) turned = min(turned, static_cast<uint32_t>(__shfl_xor(turned, off, 64)));
+            if (turned == ~0u) break;  // nothing was turned away: no path (or the end's distance stands)
+            const uint64_t wider = B + (B - base) / 2;
+            B = turned > wider ? turned : wider;
+            // every kept switch again, with the wider limit
+            head = 0;
+            tail = 0;
+            for (int i = 0; i < kSlots / 64; ++i) {
+                const int sl = i * 64 + lane;
+                const unsigned long long e = tab[sl];
+                const bool in = e != kEmpty && !(e & kForbid);
+                const uint64_t pm = __ballot(in);
+                if (in) {
+                    const uint32_t below = __builtin_amdgcn_mbcnt_hi(
+                        static_cast<uint32_t>(pm >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(pm), 0u));
+                    ring[tail + below] = static_cast<uint16_t>(sl);
+                }
+                if (lane < 2) inq[2 * i + lane] = static_cast<uint32_t>(pm >> (32 * lane));
+                tail += static_cast<uint32_t>(__popcll(pm));
+            }
+            wave_sync();
+        }
+        if (hard_q) break;
+        if (dto == static_cast<uint32_t>(kInf)) {
+            fail = true;
+            break;
+        }
+        // walk back from `to`: the lowest-numbered predecessor on a minimum-weight path
+        int32_t c = to, n = 1;
+        uint32_t dc = dto;
+        if (lane == 0) leg[0] = static_cast<uint16_t>(to);
+        while (c != from) {
+            if (total + n > max_hops) {
+                fail = true;
+                break;
+            }
+            int32_t best = INT32_MAX;
+            uint32_t bd = 0;
+            for (int32_t k = rin_off[c] + lane; k < rin_off[c + 1]; k += 64) {
+                const int2 in = rin[k];
+                const uint32_t w = min(static_cast<uint32_t>(in.y), static_cast<uint32_t>(kInf));
+                if (w > dc || in.x >= best) continue;
+                uint32_t h = slot_of(static_cast<uint32_t>(in.x));
+                while (true) {
+                    const unsigned long long e = tab[h];
+                    if (e == kEmpty) break;
+                    if ((e & 0x7FFFu) == static_cast<uint32_t>(in.x)) {
+                        if (!(e & kForbid) && static_cast<uint32_t>(e >> 16) + w == dc) {
+                            best = in.x;
+                            bd = dc - w;
+                        }
+                        break;
+                    }
+                    h = (h + 1) & (kSlots - 1);
+                }
+            }
+            const int32_t least = wave_min_i32(best);
+            if (least == INT32_MAX) {
+                fail = true;
+                break;
+            }
+            const int who = static_cast<int>(__builtin_ctzll(__ballot(best == least)));
+            c = least;
+            dc = __builtin_amdgcn_readlane(bd, who);
+            if (lane == 0) leg[n] = static_cast<uint16_t>(c);
+            ++n;
+        }
+        wave_sync();
+        if (fail) break;
+        for (int32_t i = 1 + lane; i < n; i += 64) walk[total + i] = leg[n - 1 - i];
+        total += n - 1;
+        wave_sync();
+        from = to;
+    }
+    if (hard_q) {
+        if (lane == 0) hard[atomicAdd(n_hard, 1)] = q;
+        return;
+    }
+    const int32_t slots = max_hops + 1;
+    if (lane == 0) hops_out[q] = fail ? -1 : total;
+    int32_t *pq = path_out + static_cast<int64_t>(q) * slots;
+    for (int32_t k = lane; k < slots; k += 64) pq[k] = (!fail && k <= total) ? walk[k] : -1;
+    // the port of least (weight, index) to the next switch: one lane group per switch of the walk
+    for (int32_t k0 = 0; !fail && k0 < total; k0 += kNG) {
+        const int32_t k = k0 + grp;
+        uint64_t best = UINT64_MAX;  // (weight << 32) | local port
+        if (k < total) {
+            const int2 r = range[walk[k]];
+            const uint32_t nx = walk[k + 1];
+            for (int32_t p = r.x + gl; p < r.y; p += GS) {
+                const int2 L = link[p];
+                if ((static_cast<uint32_t>(L.x) & 0xFFFFu) == nx) {
+                    const uint64_t x = static_cast<uint64_t>(static_cast<uint32_t>(L.y)) << 32 |
+                                       static_cast<uint32_t>(p - r.x);
+                    best = x < best ? x : best;
+                }
+            }
+        }
+#pragma unroll
+        for (int off = GS / 2; off > 0; off >>= 1) {
+            const uint64_t o = __shfl_xor(best, off, 64);
+            best = o < best ? o : best;
+        }
+        if (gl == 0 && k < total) act[k] = static_cast<uint16_t>(best & 0xFFFFu);
+    }
+    if (lane == 0 && !fail) act[total] = static_cast<uint16_t>(out_port[q]);
+    wave_sync();
+    // 10 dwords per slot: value[4], mask[4], priority | action << 16, rsv
+    const pc_key kq = key[q];
+    uint32_t *rq = reinterpret_cast<uint32_t *>(rules_out + static_cast<int64_t>(q) * slots);
+    for (int32_t i = lane; i < slots * 10; i += 64) {
+        const int32_t k = i / 10, d = i - 10 * k;
+        uint32_t x = 0;
+        if (!fail && k <= total) {
+            x = d < 4 ? (d < 2 ? (d ? kq.w[1] : kq.w[0]) : (d == 2 ? kq.w[2] : kq.w[3]))
+              : d < 7 ? 0xFFFFFFFFu
+              : d == 7 ? 0xFFu
+              : d == 8 ? static_cast<uint32_t>(prio) | static_cast<uint32_t>(act[k]) << 16
+                       : 0u;
+        }
+        rq[i] = x;
     }
 }
 
@@ -139,7 +708,8 @@ __global__ __launch_bounds__(kPsThreads) void k_ps_search(
     const uint32_t *__restrict__ allowed, const int32_t *__restrict__ via, int32_t Kv,
     const int32_t *__restrict__ forbid, int32_t Kf, const pc_key *__restrict__ key,
     const int32_t *__restrict__ out_port, int32_t prio, int32_t max_hops, int32_t *__restrict__ hops_out,
-    int32_t *__restrict__ path_out, pc_rule *__restrict__ rules_out)
+    int32_t *__restrict__ path_out, pc_rule *__restrict__ rules_out, int32_t Q,
+    const int32_t *__restrict__ list, const int32_t *__restrict__ n_list, const uint32_t *__restrict__ wspan)
 {
     extern __shared__ int32_t ps_lds[];
     const int32_t VW = (V + 31) >> 5;
@@ -152,10 +722,13 @@ __global__ __launch_bounds__(kPsThreads) void k_ps_search(
     int32_t *leg = walk + max_hops + 2;
     __shared__ int32_t s_nf, s_fail, s_total;
 
-    const int32_t q = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t slots = max_hops + 1;
+    if (list && one_weight(wspan)) list = nullptr;  // the directed search took none
+    const int32_t n_req = list ? *n_list : Q;
+    for (int32_t at = blockIdx.x; at < n_req; at += gridDim.x) {
+    const int32_t q = list ? list[at] : at;
     const int32_t s = src[q], t = target[q];
     bool fail = s < 0 || s >= V || t < 0 || t >= V;
     if (!fail) {
@@ -398,6 +971,8 @@ __global__ __launch_bounds__(kPsThreads) void k_ps_search(
             rq[static_cast<int64_t>(k) * 10 + lane] = d;
         }
     }
+    __syncthreads();  // the next request reuses the LDS
+    }
 }
 
 }  // namespace
@@ -408,34 +983,68 @@ int run_synthesize(pc_ctx *ctx, int32_t V, const int32_t *port_off, const int32_
                    const pc_key *key, const int32_t *out_port, int32_t prio, int32_t max_hops, int32_t *hops,
                    int32_t *path, pc_rule *rules, hipStream_t stream)
 {
-    int32_t *cnt, *rin_off, *cursor;
-    int2 *rin;
-    auto carve = [&](Carver &cv) {
-        cnt = cv.take<int32_t>(static_cast<size_t>(V) + 1);
+    // The directed search pays for its bounds (a row per switch that legs end
+    // at, at most V, each about as dear as one undirected leg) and for four
+    // more launches, about 25 million links' worth of undirected search.
+    // Undirected / directed at weights 1-10, one leg per request: 138,240
+    // ports and 1,440 legs 357 / 328 us, 5,760 legs 939 / 343 us; 17,280 ports
+    // and 720 legs 87 / 139 us, 1,440 legs 132 / 144 us, 2,880 legs 201 / 160 us;
+    // 2,160 ports and 1,440 legs 65 / 106 us.
+    const int64_t legs = static_cast<int64_t>(Q) * (Kv + 1);
+    bool directed = weight != nullptr && V > 0 && n_ports > 0 && n_ports < (int64_t(1) << 30) &&
+                    legs >= V + 25'000'000 / n_ports;
+    const size_t n_rows = directed ? static_cast<size_t>(V) : 0;
+    // zeroed together: in-link counts, needed rows, the hard requests' count, the weights' span
+    int32_t *cnt, *need, *n_hard, *rin_off, *cursor, *row, *ends, *row_ok, *hard;
+    int2 *rin, *link, *range;
+    uint32_t *blink, *wspan;
+    uint16_t *bound;
+    const size_t n_zero = static_cast<size_t>(V) * 2 + 4;
+    auto carve = [&](Carver &cv, bool with) {
+        cnt = cv.take<int32_t>(with ? n_zero : static_cast<size_t>(V) + 1);
         rin_off = cv.take<int32_t>(static_cast<size_t>(V) + 1);
         cursor = cv.take<int32_t>(static_cast<size_t>(V) + 1);
         rin = cv.take<int2>(static_cast<size_t>(n_ports) + 1);
+        if (!with) return;
+        need = cnt + V + 1;
+        n_hard = need + V;
+        wspan = reinterpret_cast<uint32_t *>(n_hard + 1);
+        row = cv.take<int32_t>(static_cast<size_t>(V) + 1);
+        ends = cv.take<int32_t>(static_cast<size_t>(V));
+        row_ok = cv.take<int32_t>(static_cast<size_t>(V));
+        hard = cv.take<int32_t>(static_cast<size_t>(Q));
+        link = cv.take<int2>(static_cast<size_t>(n_ports) + 1);
+        blink = cv.take<uint32_t>(static_cast<size_t>(n_ports) + 1);
+        range = cv.take<int2>(static_cast<size_t>(V));
+        bound = cv.take<uint16_t>(n_rows * V);
     };
     Carver dry{nullptr, 0};
-    carve(dry);
+    carve(dry, directed);
     int rc = pc_ensure_arena(ctx, dry.off);
+    if (rc == PC_ENOMEM && directed) {  // no room for the bounds: the undirected search needs none
+        directed = false;
+        dry.off = 0;
+        carve(dry, false);
+        rc = pc_ensure_arena(ctx, dry.off);
+        if (rc == PC_OK) ctx->msg[0] = 0;
+    }
     if (rc) return rc;
     Carver real{ctx->arena, 0};
-    carve(real);
+    carve(real, directed);
 
     int64_t tot = std::max<int64_t>({static_cast<int64_t>(V), n_ports, static_cast<int64_t>(Q) * std::max(Kv, 1),
                                      static_cast<int64_t>(Q) * std::max(Kf, 1)});
+    const unsigned g_all = static_cast<unsigned>(std::min<int64_t>((tot + 255) / 256, 8192));
     if (tot > 0) {
-        const unsigned g = static_cast<unsigned>(std::min<int64_t>((tot + 255) / 256, 8192));
         PC_TIMED(ctx, "k_ps_validate", stream,
-                 hipLaunchKernelGGL(k_ps_validate, dim3(g), dim3(256), 0, stream, V, port_off, port_peer, n_ports,
+                 hipLaunchKernelGGL(k_ps_validate, dim3(g_all), dim3(256), 0, stream, V, port_off, port_peer, n_ports,
                                     weight, region, Q, src, target, out_port, via, Kv, forbid, Kf, ctx->d_err));
         PC_LAUNCH_CHECK(ctx);
     }
     if (Q == 0) return PC_OK;
     if (V > 0) {
-        launch_fill_u32(reinterpret_cast<uint32_t *>(cnt), static_cast<size_t>(V) + 1, 0, stream);
-        const unsigned g = static_cast<unsigned>((V + 255) / 256);
+        launch_fill_u32(reinterpret_cast<uint32_t *>(cnt), directed ? n_zero : static_cast<size_t>(V) + 1, 0, stream);
+        const unsigned g = static_cast<unsigned>((static_cast<int64_t>(V) * kInLanes + 255) / 256);
         PC_TIMED(ctx, "k_ps_in_count", stream,
                  hipLaunchKernelGGL(k_ps_in_count, dim3(g), dim3(256), 0, stream, V, port_off, port_peer, n_ports,
                                     weight, cnt));
@@ -447,15 +1056,61 @@ int run_synthesize(pc_ctx *ctx, int32_t V, const int32_t *port_off, const int32_
                                     weight, cursor, rin));
         PC_LAUNCH_CHECK(ctx);
     }
+    if (directed) {
+        const unsigned g = static_cast<unsigned>(std::min<int64_t>((std::max<int64_t>(n_ports, V) + 255) / 256, 4096));
+        PC_TIMED(ctx, "k_ps_survey", stream,
+                 hipLaunchKernelGGL(k_ps_survey, dim3(std::min(g_all, 1024u)), dim3(256), 0, stream, V, port_peer,
+                                    n_ports, weight, Q, target, via, Kv, need, wspan));
+        launch_scan_i32(need, V, row, nullptr, nullptr, stream);
+        PC_TIMED(ctx, "k_ps_links", stream,
+                 hipLaunchKernelGGL(k_ps_links, dim3(g), dim3(256), 0, stream, V, port_off, port_peer, n_ports,
+                                    weight, region, need, row, wspan, link, blink,
+                                    range, ends));
+        PC_LAUNCH_CHECK(ctx);
+        // lanes per switch: a power of two near a third of the mean degree
+        const int64_t avg = n_ports / V;
+        const int gs = avg <= 12 ? 4 : avg <= 24 ? 8 : 16;
+        // eight rows per workgroup where two such workgroups fit a CU's LDS and
+        // enough of them remain to fill the chip, else four
+        const int words = V > 1024 && V <= 4800 ? 4 : 2;
+        const size_t lds_b = ((static_cast<size_t>(V) + 15) & ~size_t(15)) * 4 * words;
+        const size_t lds_g = static_cast<size_t>(max_hops + 2) * 3 * sizeof(uint16_t);
+        // a request that relaxes more links than the whole graph holds (a few
+        // times over) is not being directed: the workgroup search takes it
+        const int32_t max_steps = static_cast<int32_t>(std::min<int64_t>(64 + n_ports / 64, INT32_MAX / 2));
+        auto launch = [&](auto bk, auto gk) -> int {
+            PC_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(bk),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_b)));
+            PC_TIMED(ctx, "k_ps_bound", stream,
+                     hipLaunchKernelGGL(bk, dim3(static_cast<unsigned>((V + 2 * words - 1) / (2 * words))), dim3(256 * words), lds_b,
+                                        stream, V, range, blink, ends, row + V, wspan, bound, row_ok));
+            PC_TIMED(ctx, "k_ps_goal", stream,
+                     hipLaunchKernelGGL(gk, dim3(static_cast<unsigned>(Q)), dim3(64), lds_g, stream, V, range, link,
+                                        region, rin_off, rin, row, row_ok, bound,
+                                        wspan, src, target, allowed, via, Kv,
+                                        forbid, Kf, key, out_port, prio, max_hops, hops, path, rules, max_steps,
+                                        hard, n_hard));
+            PC_LAUNCH_CHECK(ctx);
+            return PC_OK;
+        };
+        const auto goal = gs == 4 ? k_ps_goal<4> : gs == 8 ? k_ps_goal<8> : k_ps_goal<16>;
+        rc = avg <= 12 ? (words == 4 ? launch(k_ps_bound<4, 3, 4>, goal) : launch(k_ps_bound<4, 3, 2>, goal))
+                       : (words == 4 ? launch(k_ps_bound<1, 12, 4>, goal) : launch(k_ps_bound<1, 12, 2>, goal));
+        if (rc) return rc;
+    }
     const int32_t VW = (V + 31) / 32;
     const size_t lds = (static_cast<size_t>(V) * 3 + static_cast<size_t>(VW) * 2 +
                         2 * static_cast<size_t>(max_hops + 2)) * 4;
     PC_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(k_ps_search),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
+    // after the directed search: the requests it left, by a grid that walks their list
+    const unsigned grid = static_cast<unsigned>(directed ? std::min(Q, 16384) : Q);
     PC_TIMED(ctx, "k_ps_search", stream,
-             hipLaunchKernelGGL(k_ps_search, dim3(static_cast<unsigned>(Q)), dim3(kPsThreads), lds, stream, V,
+             hipLaunchKernelGGL(k_ps_search, dim3(grid), dim3(kPsThreads), lds, stream, V,
                                 port_off, port_peer, n_ports, weight, region, rin_off, rin, src, target, allowed, via,
-                                Kv, forbid, Kf, key, out_port, prio, max_hops, hops, path, rules));
+                                Kv, forbid, Kf, key, out_port, prio, max_hops, hops, path, rules,
+                                Q, directed ? hard : nullptr, directed ? n_hard : nullptr,
+                                directed ? wspan : nullptr));
     PC_LAUNCH_CHECK(ctx);
     return PC_OK;
 }

@@ -152,3 +152,49 @@ def test_synthesized_rules_deliver_on_the_gpu(g, orc, weighted):
     assert np.array_equal(tr["last_port"].astype(np.int32), req["out_port"][ok])
     assert np.array_equal(tr["hops"].astype(np.int32), hops[ok])
     assert ((tr["jmask"] & ~req["allowed"][ok]) == 0).all()
+
+
+def _line(V, rng):
+    """A line of V switches with one host port each (a search runs through hundreds of switches)."""
+    peer, off = [], [0]
+    for s in range(V):
+        p = [x for x in (s - 1, s + 1) if 0 <= x < V] + [-1]
+        peer += p
+        off.append(len(peer))
+    host = np.arange(V)
+    return dict(S=V, J=4, H=V, port_off=np.array(off, np.int32), port_peer=np.array(peer, np.int32),
+                jur=(host // 7 % 4).astype(np.uint8), host_switch=host.astype(np.int32),
+                host_port=(np.diff(off) - 1).astype(np.int32))
+
+
+# enough legs for the bounds to pay: the directed search with its fallbacks (a full table: sparse1500, line; rows
+# missing: line900; one weight)
+@pytest.mark.parametrize("kind,Kv,Kf,hops,wmax", [
+    ("random", 2, 3, 40, 9), ("random", 0, 0, 255, 3), ("fat_tree", 1, 32, 16, 10), ("fat_tree", 3, 1, 1, 1),
+    ("fat_tree", 1, 2, 40, 2), ("random", 1, 2, 40, 2**32 - 1), ("fat_tree", 1, 2, 40, 1 << 20),
+    ("sparse1500", 1, 2, 64, 10), ("line900", 1, 1, 255, 5), ("malformed", 2, 2, 40, 9)])
+def test_directed_search(g, orc, kind, Kv, Kf, hops, wmax):
+    rng = np.random.default_rng(21)
+    if kind == "fat_tree":
+        topo = synth.fat_tree(12, 6)
+    elif kind == "line900":
+        topo = _line(900, rng)
+    else:
+        V = 1500 if kind == "sparse1500" else 300
+        topo = synth.random_graph(rng, V, 2 * V + V // 3, 2, 6)
+    n_ports = topo["port_peer"].shape[0]
+    Q = (topo["S"] + 25_000_000 // n_ports) // (Kv + 1) + 40
+    weight = np.random.default_rng(5).integers(1, wmax + 1, size=n_ports).astype(np.uint32)
+    req = synth.synthesis_requests(5, topo, Q, Kv=max(Kv, 1), Kf=max(Kf, 1), p_other_jur=0.8)
+    if Kv == 0:
+        req["via"] = np.full((Q, 1), -1, np.int32)
+    off, peer, jur = topo["port_off"].copy(), topo["port_peer"].copy(), topo["jur"].copy()
+    if kind == "malformed":
+        off[17] = off[18] + 1
+        peer[rng.integers(0, n_ports, 40)] = 1 << 20
+        weight[rng.integers(0, n_ports, 40)] = 0
+        jur[rng.integers(0, 300, 9)] = 77
+        req["src"][::50], req["target"][7::50], req["out_port"][9::50] = -3, 300, 99
+        req["via"][11::50, 0], req["forbid"][13::50, 0] = 4000, -9
+    ho, _, _ = _check(g, orc, topo["S"], off, peer, jur, req, 4321, hops, weight)
+    assert (ho == -1).sum() > 0 and (hops < 2 or (ho >= 0).sum() > 50)
