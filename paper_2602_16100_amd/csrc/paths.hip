@@ -110,7 +110,7 @@ __device__ __forceinline__ uint32_t link_weight(const int32_t *__restrict__ port
 
 // Lanes per switch of the in-link kernels: a switch's ports are read
 // together (one thread per switch walked 48 ports one after another: 181 and
-// 162 us for 138,240 ports, against 7 and 8 us).
+// 162 us for 138,240 ports, against 15 and 20 us).
 constexpr int kInLanes = 16;
 
 // In-link counts: kInLanes lanes per switch u, +1 at the peer of each link.
@@ -128,12 +128,20 @@ __global__ __launch_bounds__(256) void k_ps_in_count(int32_t V, const int32_t *_
 
 // In-link lists: (u, link weight) pairs in rin[rin_off[v] ..); cursor starts as a
 // copy of rin_off.  The order within a list is arbitrary (only minima are
-// taken over it).
+// taken over it).  rin holds n_ports entries: switches whose port ranges
+// overlap can have more links than that, and then no list is written (the
+// searches test in_lists).
+__device__ __forceinline__ bool in_lists(const int32_t *rin_off, int32_t V, int64_t n_ports)
+{
+    return rin_off[V] >= 0 && rin_off[V] <= n_ports;
+}
 __global__ __launch_bounds__(256) void k_ps_in_fill(int32_t V, const int32_t *__restrict__ port_off,
                                                     const int32_t *__restrict__ port_peer, int64_t n_ports,
                                                     const uint32_t *__restrict__ weight,
+                                                    const int32_t *__restrict__ rin_off,
                                                     int32_t *__restrict__ cursor, int2 *__restrict__ rin)
 {
+    if (!in_lists(rin_off, V, n_ports)) return;
     const int32_t u = (blockIdx.x * blockDim.x + threadIdx.x) / kInLanes;
     if (u >= V) return;
     const int64_t b = port_off[u], e = port_off[u + 1];
@@ -142,7 +150,7 @@ __global__ __launch_bounds__(256) void k_ps_in_fill(int32_t V, const int32_t *__
         const uint32_t w = link_weight(port_peer, weight, V, p);
         if (w) {
             const int32_t pos = atomicAdd(&cursor[port_peer[p]], 1);
-            rin[pos] = make_int2(u, static_cast<int32_t>(w));  // the weight's bits
+            if (pos >= 0 && pos < n_ports) rin[pos] = make_int2(u, static_cast<int32_t>(w));  // the weight's bits
         }
     }
 }
@@ -391,7 +399,7 @@ constexpr int kUn = 3;
 
 template <int GS>
 __global__ __launch_bounds__(64) void k_ps_goal(
-    int32_t V, const int2 *__restrict__ range, const int2 *__restrict__ link, const uint8_t *__restrict__ region,
+    int32_t V, int64_t n_ports, const int2 *__restrict__ range, const int2 *__restrict__ link, const uint8_t *__restrict__ region,
     const int32_t *__restrict__ rin_off, const int2 *__restrict__ rin, const int32_t *__restrict__ row,
     const int32_t *__restrict__ row_ok, const uint16_t *__restrict__ bound, const uint32_t *__restrict__ wspan,
     const int32_t *__restrict__ src, const int32_t *__restrict__ target, const uint32_t *__restrict__ allowed,
@@ -414,7 +422,7 @@ __global__ __launch_bounds__(64) void k_ps_goal(
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
     auto slot_of = [](uint32_t u) { return (u * 40503u >> 7) & (kSlots - 1); };
-    if (one_weight(wspan)) return;
+    if (one_weight(wspan) || !in_lists(rin_off, V, n_ports)) return;
     const int32_t q = blockIdx.x;
     const int32_t s = src[q], t = target[q];
     bool fail = s < 0 || s >= V || t < 0 || t >= V;
@@ -725,7 +733,8 @@ __global__ __launch_bounds__(kPsThreads) void k_ps_search(
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t slots = max_hops + 1;
-    if (list && one_weight(wspan)) list = nullptr;  // the directed search took none
+    const bool lists = in_lists(rin_off, V, n_ports);
+    if (list && (one_weight(wspan) || !lists)) list = nullptr;  // the directed search took none
     const int32_t n_req = list ? *n_list : Q;
     for (int32_t at = blockIdx.x; at < n_req; at += gridDim.x) {
     const int32_t q = list ? list[at] : at;
@@ -890,13 +899,26 @@ __global__ __launch_bounds__(kPsThreads) void k_ps_search(
                 }
                 int32_t best = INT32_MAX;
                 const int32_t dc = dist[c];
-                for (int32_t k = rin_off[c] + lane; k < rin_off[c + 1]; k += 64) {
-                    const int2 in = rin[k];
-                    const int32_t du = dist[in.x];
-                    if (du != kInf &&
-                        static_cast<uint32_t>(du) + min(static_cast<uint32_t>(in.y), static_cast<uint32_t>(kInf)) ==
-                            static_cast<uint32_t>(dc))
-                        best = min(best, in.x);
+                auto pred = [&](int32_t u, uint32_t w) {
+                    const int32_t du = dist[u];
+                    if (du != kInf && static_cast<uint32_t>(du) + min(w, static_cast<uint32_t>(kInf)) ==
+                                          static_cast<uint32_t>(dc))
+                        best = min(best, u);
+                };
+                if (lists) {
+                    for (int32_t k = rin_off[c] + lane; k < rin_off[c + 1]; k += 64) {
+                        const int2 in = rin[k];
+                        pred(in.x, static_cast<uint32_t>(in.y));
+                    }
+                } else {  // overlapping port ranges: every switch's links
+                    for (int32_t u = lane; u < V; u += 64) {
+                        const int64_t b = port_off[u], e = port_off[u + 1];
+                        if (!pc_range_ok(b, e, n_ports)) continue;
+                        for (int64_t p = b; p < e; ++p) {
+                            const uint32_t w = link_weight(port_peer, weight, V, p);
+                            if (w && port_peer[p] == c) pred(u, w);
+                        }
+                    }
                 }
                 best = wave_min_i32(best);
                 if (best == INT32_MAX) {
@@ -1053,7 +1075,7 @@ int run_synthesize(pc_ctx *ctx, int32_t V, const int32_t *port_off, const int32_
         PC_LAUNCH_CHECK(ctx);
         PC_TIMED(ctx, "k_ps_in_fill", stream,
                  hipLaunchKernelGGL(k_ps_in_fill, dim3(g), dim3(256), 0, stream, V, port_off, port_peer, n_ports,
-                                    weight, cursor, rin));
+                                    weight, rin_off, cursor, rin));
         PC_LAUNCH_CHECK(ctx);
     }
     if (directed) {
@@ -1085,8 +1107,8 @@ int run_synthesize(pc_ctx *ctx, int32_t V, const int32_t *port_off, const int32_
                      hipLaunchKernelGGL(bk, dim3(static_cast<unsigned>((V + 2 * words - 1) / (2 * words))), dim3(256 * words), lds_b,
                                         stream, V, range, blink, ends, row + V, wspan, bound, row_ok));
             PC_TIMED(ctx, "k_ps_goal", stream,
-                     hipLaunchKernelGGL(gk, dim3(static_cast<unsigned>(Q)), dim3(64), lds_g, stream, V, range, link,
-                                        region, rin_off, rin, row, row_ok, bound,
+                     hipLaunchKernelGGL(gk, dim3(static_cast<unsigned>(Q)), dim3(64), lds_g, stream, V, n_ports, range,
+                                        link, region, rin_off, rin, row, row_ok, bound,
                                         wspan, src, target, allowed, via, Kv,
                                         forbid, Kf, key, out_port, prio, max_hops, hops, path, rules, max_steps,
                                         hard, n_hard));

@@ -198,3 +198,17 @@ def test_directed_search(g, orc, kind, Kv, Kf, hops, wmax):
         req["via"][11::50, 0], req["forbid"][13::50, 0] = 4000, -9
     ho, _, _ = _check(g, orc, topo["S"], off, peer, jur, req, 4321, hops, weight)
     assert (ho == -1).sum() > 0 and (hops < 2 or (ho >= 0).sum() > 50)
+
+
+@pytest.mark.parametrize("weighted,Q", [(False, 60), (True, 60), (True, 24_000)])
+def test_overlapping_port_ranges(g, orc, weighted, Q):
+    """Every other switch owns all ports (the offset pairs between are bad), so there are many times more links
+    than ports: no in-link list can hold them."""
+    topo = synth.random_graph(np.random.default_rng(3), 40, 520, 2, 4)
+    n = topo["port_peer"].shape[0]
+    off = np.where(np.arange(41) % 2 == 0, 0, n).astype(np.int32)
+    req = synth.synthesis_requests(2, topo, Q, Kv=1, Kf=1)
+    req["target"] = (req["target"] // 2 * 2).astype(np.int32)
+    w = synth.port_weights(4, n, 9) if weighted else None
+    ho, _, _ = _check(g, orc, 40, off, topo["port_peer"], topo["jur"], req, 5, 20, w)
+    assert (ho > 0).any()
