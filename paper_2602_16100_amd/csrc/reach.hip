@@ -21,7 +21,14 @@
 //            slots: vertices 16 apart map to different LDS banks (unswizzled,
 //            a fat-tree core's pushes to its per-pod peers, 48 apart, all
 //            hit one bank pair).
-//   queue  : larger graphs: one workgroup per query, frontier queue in
+//   map    : larger graphs whose visited bits fit in LDS (1.2 million
+//            vertices): one workgroup per query.  Narrow frontiers, which a
+//            sparse graph has for hundreds of levels, are one wavefront's work
+//            without barriers, one memory latency per level: a vertex's first
+//            16 neighbours and their regions sit in one 64-byte record.
+//            Meanwhile the other wavefronts write the row's -1s.  Wide
+//            frontiers take the whole workgroup.
+//   queue  : still larger graphs: one workgroup per query, frontier queue in
 //            scratch, the distance row itself (or a scratch row, with
 //            targets) as the visited set claimed with compare-and-swap.
 #include <algorithm>
@@ -411,6 +418,284 @@ __global__ __launch_bounds__(kBitsetThreads) void k_rc_bitset(int32_t V, const i
     if (target && tid < 64 && lane < nq) dist[qid[lane]] = res;
 }
 
+// Neighbour records for the map search: word j of a vertex's 64 bytes is
+// its j-th neighbour and that neighbour's region (vertex | region << 26; kHole
+// where there is none, or none that any query may enter).  A vertex of more
+// than kEll entries has kUseLists in word 0.
+constexpr int kEll = 16;
+constexpr int kVertexBits = 26;
+constexpr uint32_t kHole = 0xFFFFFFFFu, kUseLists = 0xFFFFFFFEu;
+
+__global__ __launch_bounds__(256) void k_rc_records(int32_t V, const int32_t *__restrict__ adj_off,
+                                                    const int32_t *__restrict__ adj, int64_t n_adj,
+                                                    const uint8_t *__restrict__ region, uint32_t *__restrict__ ell)
+{
+    // four lanes per vertex, four words each
+    const int64_t x = blockIdx.x * 256ll + threadIdx.x;
+    const int32_t v = static_cast<int32_t>(x / 4), j0 = static_cast<int32_t>(x % 4) * 4;
+    if (v >= V) return;
+    const int64_t b = adj_off[v], e = adj_off[v + 1];
+    uint32_t r[4] = {kHole, kHole, kHole, kHole};
+    if (pc_range_ok(b, e, n_adj)) {
+        if (e - b > kEll) {
+            if (j0 == 0) r[0] = kUseLists;
+        } else {
+            int32_t u[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) u[k] = b + j0 + k < e ? adj[b + j0 + k] : -1;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const uint32_t g = u[k] >= 0 && u[k] < V ? region[u[k]] : 32u;
+                if (g < 32) r[k] = static_cast<uint32_t>(u[k]) | g << kVertexBits;
+            }
+        }
+    }
+    reinterpret_cast<uint4 *>(ell)[x] = make_uint4(r[0], r[1], r[2], r[3]);
+}
+
+// One workgroup per query (grid-stride over queries).  LDS: a visited bit
+// per vertex (forbidden vertices start out visited).  list: every visited
+// vertex of the query in BFS order, so a level is a range of it.
+// While wavefront 0 walks the first levels, whose vertices it only lists
+// (and the levels' starts), the others fill the row with -1; then the listed
+// vertices get their distances.  After that a frontier of at most kNarrow
+// vertices is again wavefront 0's, from an LDS copy, and a wider one takes a
+// barrier per level.
+// GS lanes share a vertex: with the records (kRecords) four, each reading 16 bytes.
+// Bound by the deepest query's levels, one record latency each, and by
+// the -1 fill: 256 rows of a million vertices (mean degree 4, deepest search
+// 196 levels) in 325 us, the -1s alone about 200 us; the queue search took
+// 1,210 us after a fill of 207 us.  At mean degree 6 (one component, 1,800
+// levels) 8.4 ms against 39 ms; 8,191 vertices of mean degree 60, 256 rows
+// 0.28 ms against 2.0 ms.
+constexpr int kMapThreads = 1024;
+constexpr int kNarrow = 256;
+constexpr int kDeferred = 1024;  // levels walked at most while the row is filled
+template <int GS, bool kRecords>
+__global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t *__restrict__ adj_off,
+                                                        const int32_t *__restrict__ adj, int64_t n_adj,
+                                                        const uint8_t *__restrict__ region,
+                                                        const uint32_t *__restrict__ ell, int32_t Q,
+                                                        const int32_t *__restrict__ src,
+                                                        const uint32_t *__restrict__ allowed,
+                                                        const int32_t *__restrict__ target, int32_t *__restrict__ dist,
+                                                        int32_t *__restrict__ list_all,
+                                                        const int32_t *__restrict__ forbid, int32_t Kf, int32_t qdiv)
+{
+    static_assert(!kRecords || GS == 4, "four lanes read a record");
+    extern __shared__ uint4 map_lds[];
+    uint32_t *bm = reinterpret_cast<uint32_t *>(map_lds);  // [ceil(V / 128) * 4]
+    __shared__ int32_t near_q[2][kNarrow];  // a narrow frontier and the next one
+    __shared__ int32_t starts[kDeferred + 1];
+    __shared__ int32_t s_lo, s_hi, s_d, s_tail;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool rows = target == nullptr;
+    int32_t *list = list_all + static_cast<int64_t>(blockIdx.x) * V;
+    auto bit = [&](int32_t v) { return (bm[v >> 5] >> (v & 31)) & 1u; };
+    auto rank_in = [](uint64_t m) {
+        return static_cast<int32_t>(__builtin_amdgcn_mbcnt_hi(
+            static_cast<uint32_t>(m >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u)));
+    };
+    for (int32_t q = blockIdx.x; q < Q; q += gridDim.x) {
+        int32_t *row = rows ? dist + static_cast<int64_t>(q) * V : nullptr;
+        const uint32_t A = allowed[q / qdiv];
+        const int32_t s = src[q];
+        const int32_t tgt = rows ? -1 : target[q];
+        for (int32_t i = tid; i < (V + 127) / 128; i += kMapThreads) map_lds[i] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+        if (tid < Kf) {
+            const int32_t f = forbid[static_cast<int64_t>(q / qdiv) * Kf + tid];
+            if (f >= 0 && f < V) atomicOr(&bm[f >> 5], 1u << (f & 31));
+        }
+        __syncthreads();
+        // a target that is not allowed, or forbidden, is never reached
+        const bool go = s >= 0 && s < V && allowed_v(region, A, s) && !bit(s) &&
+                        (rows || (tgt >= 0 && tgt < V && allowed_v(region, A, tgt) && !bit(tgt)));
+        __syncthreads();
+        if (tid == 0) {
+            s_lo = 0;
+            s_hi = go ? 1 : 0;
+            s_d = 0;
+            starts[0] = 0;
+            if (go) {
+                list[0] = s;
+                near_q[0][0] = s;
+                atomicOr(&bm[s >> 5], 1u << (s & 31));
+            }
+        }
+        __syncthreads();
+        // Narrow levels, by wavefront 0: the frontier in near_q[0], ids
+        // list[lo .. hi).  Ends with the frontier empty, too wide, the target
+        // reached, or (deferred) kDeferred levels behind it.
+        auto narrow = [&](bool deferred) {
+            int32_t lo = s_lo, hi = s_hi, d = s_d, cur = 0;
+            while (hi > lo && hi - lo <= kNarrow && !(deferred && d >= kDeferred) && !(!rows && bit(tgt))) {
+                const int32_t n = hi - lo;
+                int32_t *nq = near_q[cur ^ 1];
+                int32_t nn = 0;
+                auto claim = [&](uint32_t r) {
+                    const bool ok = !(r >> 31) && ((A >> (r >> kVertexBits)) & 1u);
+                    const uint32_t u = r & ((1u << kVertexBits) - 1);
+                    if (!__ballot(ok)) return;
+                    bool fresh = false;
+                    if (ok) fresh = !((atomicOr(&bm[u >> 5], 1u << (u & 31)) >> (u & 31)) & 1u);
+                    const uint64_t m = __ballot(fresh);
+                    if (fresh) {
+                        const int32_t pos = nn + rank_in(m);
+                        list[hi + pos] = static_cast<int32_t>(u);
+                        if (pos < kNarrow) nq[pos] = static_cast<int32_t>(u);
+                        if (rows && !deferred) row[u] = d + 1;
+                    }
+                    nn += static_cast<int32_t>(__popcll(m));
+                };
+                constexpr int kSteps = 4;  // 16 vertices each, their records in flight together
+                for (int32_t i0 = 0; i0 < n; i0 += 16 * kSteps) {
+                    uint4 R[kSteps];
+                    int32_t v[kSteps];
+#pragma unroll
+                    for (int k = 0; k < kSteps; ++k) {
+                        const int32_t i = i0 + 16 * k + lane / 4;
+                        v[k] = i < n ? near_q[cur][i] : -1;
+                        R[k] = make_uint4(kHole, kHole, kHole, kHole);
+                        if (v[k] >= 0) R[k] = reinterpret_cast<const uint4 *>(ell)[static_cast<int64_t>(v[k]) * 4 + (lane & 3)];
+                    }
+#pragma unroll
+                    for (int k = 0; k < kSteps; ++k) {
+                        if (i0 + 16 * k >= n) break;
+                        uint64_t big = __ballot((lane & 3) == 0 && R[k].x == kUseLists);
+                        claim(R[k].x);
+                        claim(R[k].y);
+                        claim(R[k].z);
+                        claim(R[k].w);
+                        while (big) {  // a vertex of many entries: its list, across the wavefront
+                            const int32_t w = __builtin_amdgcn_readlane(v[k], static_cast<int>(__builtin_ctzll(big)));
+                            big &= big - 1;
+                            const int64_t e = adj_off[w + 1];
+                            for (int64_t p = adj_off[w]; p < e; p += 64) {
+                                const int32_t u = p + lane < e ? adj[p + lane] : -1;
+                                const uint32_t g = u >= 0 && u < V ? region[u] : 32u;
+                                claim(g < 32 ? static_cast<uint32_t>(u) | g << kVertexBits : kHole);
+                            }
+                        }
+                    }
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                lo = hi;
+                hi += nn;
+                ++d;
+                if (deferred && lane == 0) starts[d] = lo;
+                cur ^= 1;
+            }
+            if (lane == 0) {
+                s_lo = lo;
+                s_hi = hi;
+                s_d = d;
+            }
+        };
+        auto fill = [&](int32_t first, int32_t step) {  // -1 over the row: 16-byte stores between its unaligned ends
+            const int32_t head = min(V, static_cast<int32_t>((16 - (reinterpret_cast<uintptr_t>(row) & 15)) & 15) / 4);
+            const int32_t quads = (V - head) / 4;
+            typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+            i32x4 *body = reinterpret_cast<i32x4 *>(row + head);
+            // (non-temporal: the records stay in L2, 389 -> 325 us at a million vertices)
+            for (int32_t i = first; i < quads; i += step) __builtin_nontemporal_store(i32x4{-1, -1, -1, -1}, body + i);
+            for (int32_t i = first; i < head; i += step) row[i] = -1;
+            for (int32_t i = head + quads * 4 + first; i < V; i += step) row[i] = -1;
+        };
+        if (rows) {
+            if (!kRecords) fill(tid, kMapThreads);
+            else if (wave == 0) narrow(true);
+            else fill(tid - 64, kMapThreads - 64);
+            __syncthreads();
+            const int32_t hi = s_hi, d_end = s_d;
+            for (int32_t i = tid; i < hi; i += kMapThreads) {  // level of entry i: the last d with starts[d] <= i
+                int32_t a = 0, b = d_end + 1;
+                while (b - a > 1) {
+                    const int32_t mid = (a + b) >> 1;
+                    if (starts[mid] <= i) a = mid;
+                    else b = mid;
+                }
+                row[list[i]] = a;
+            }
+            __syncthreads();
+        }
+        while (true) {
+            const int32_t lo = s_lo, hi = s_hi, d = s_d;
+            if (hi <= lo || (!rows && bit(tgt))) break;
+            __syncthreads();
+            if (kRecords && hi - lo <= kNarrow / 2) {
+                if (wave == 0) {
+                    for (int32_t i = lane; i < hi - lo; i += 64) near_q[0][i] = list[lo + i];
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                    __builtin_amdgcn_wave_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+                    narrow(false);
+                }
+                __syncthreads();
+                continue;
+            }
+            if (tid == 0) s_tail = hi;
+            __syncthreads();
+            auto claim = [&](uint32_t r) {
+                const bool ok = !(r >> 31) && ((A >> (r >> kVertexBits)) & 1u);
+                const uint32_t u = r & ((1u << kVertexBits) - 1);
+                if (!__ballot(ok)) return;
+                bool fresh = false;
+                if (ok && !bit(static_cast<int32_t>(u)))
+                    fresh = !((atomicOr(&bm[u >> 5], 1u << (u & 31)) >> (u & 31)) & 1u);
+                const uint64_t m = __ballot(fresh);
+                if (!m) return;
+                const int lead = static_cast<int>(__builtin_ctzll(m));
+                int32_t at = 0;
+                if (lane == lead) at = atomicAdd(&s_tail, static_cast<int32_t>(__popcll(m)));
+                at = __builtin_amdgcn_readlane(at, lead);
+                if (fresh) {
+                    list[at + rank_in(m)] = static_cast<int32_t>(u);
+                    if (rows) row[u] = d + 1;
+                }
+            };
+            constexpr int kPerWave = 64 / GS;
+            for (int32_t i0 = lo + wave * kPerWave; i0 < hi; i0 += kMapThreads / GS) {
+                const int32_t i = i0 + lane / GS;
+                const int32_t w = i < hi ? list[i] : -1;
+                bool lists = !kRecords && w >= 0;
+                if constexpr (kRecords) {
+                    uint4 R = make_uint4(kHole, kHole, kHole, kHole);
+                    if (w >= 0) R = reinterpret_cast<const uint4 *>(ell)[static_cast<int64_t>(w) * 4 + (lane & 3)];
+                    lists = __shfl(R.x == kUseLists ? 1 : 0, lane & ~3, 64) != 0;
+                    claim(R.x);
+                    claim(R.y);
+                    claim(R.z);
+                    claim(R.w);
+                }
+                int64_t p = 0, e = 0;
+                if (lists) {
+                    p = adj_off[w];
+                    e = adj_off[w + 1];
+                    if (!pc_range_ok(p, e, n_adj)) e = p;
+                }
+                for (p += lane % GS; __ballot(p < e); p += GS) {
+                    const int32_t u = p < e ? adj[p] : -1;
+                    const uint32_t g = u >= 0 && u < V ? region[u] : 32u;
+                    claim(g < 32 ? static_cast<uint32_t>(u) | g << kVertexBits : kHole);
+                }
+            }
+            __syncthreads();
+            if (tid == 0) {
+                s_lo = hi;
+                s_hi = s_tail;
+                s_d = d + 1;
+            }
+            __syncthreads();
+        }
+        if (!rows && tid == 0) dist[q] = go && bit(tgt) ? s_d : -1;
+        __syncthreads();
+    }
+}
+
 // One workgroup per query (grid-stride over queries).
 __global__ __launch_bounds__(kQueueThreads) void k_rc_queue(int32_t V, const int32_t *__restrict__ adj_off,
                                                             const int32_t *__restrict__ adj, int64_t n_adj,
@@ -512,7 +797,6 @@ int bfs(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj, int6
         int32_t Q, const int32_t *src, const uint32_t *allowed, const int32_t *target, int32_t *dist,
         const int32_t *forbid, int32_t Kf, int32_t qdiv, const int32_t *sym, hipStream_t stream)
 {
-    if (!target) launch_fill_u32(reinterpret_cast<uint32_t *>(dist), static_cast<size_t>(Q) * V, 0xFFFFFFFFu, stream);
     if (V == 0) {
         if (target) launch_fill_u32(reinterpret_cast<uint32_t *>(dist), static_cast<size_t>(Q), 0xFFFFFFFFu, stream);
         PC_LAUNCH_CHECK(ctx);
@@ -525,9 +809,19 @@ int bfs(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj, int6
                        ((static_cast<size_t>(V) + 3) & ~size_t(3)) + static_cast<size_t>(V) * 2;
     hipFuncAttributes fa{};
     PC_HIP(ctx, hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(k_rc_bitset<16>)));  // static LDS
-    if (V <= kMaxBitsetV && lds + fa.sharedSizeBytes <= static_cast<size_t>(max_lds)) {
+    // Few queries on a sparse graph: the bitset search would leave most of the
+    // chip idle and pass over every vertex on each of many levels (bitset /
+    // map, rows: 6,000 vertices of mean degree 4, 256 queries 272 / 80 us, 1,024
+    // queries 280 / 145 us, 4,096 queries 309 / 424 us; 1,000 vertices, 64 queries
+    // 46 / 33 us, 1,024 queries 75 / 77 us; 100 vertices, 64 queries 20 / 33 us).
+    // Denser graphs have few levels (1,280 switches of degree 32, 64 queries
+    // 41 / 36 us; 2,880 of degree 48 80 / 84 us): the bitset search keeps them.
+    const int64_t avg = n_adj / V;
+    const bool deep = avg <= kEll / 2 && V >= 512 && Q <= 1024;
+    if (V <= kMaxBitsetV && !deep && lds + fa.sharedSizeBytes <= static_cast<size_t>(max_lds)) {
         if (!sym && target) sym = symcheck(ctx, V, adj_off, adj, n_adj, stream);
         if (!sym) sym = ctx->d_small + 5;  // full rows: no look-ahead reads it
+        if (!target) launch_fill_u32(reinterpret_cast<uint32_t *>(dist), static_cast<size_t>(Q) * V, 0xFFFFFFFFu, stream);
         PC_LAUNCH_CHECK(ctx);
         // more than one workgroup: order the queries by source
         int32_t *perm = nullptr;
@@ -557,7 +851,6 @@ int bfs(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj, int6
             PC_LAUNCH_CHECK(ctx);
         }
         // lanes per vertex: a power of two near a third of the mean degree
-        const int64_t avg = n_adj / V;
         const int gs = avg <= 12 ? 4 : avg <= 24 ? 8 : avg <= 48 ? 16 : 32;
         const dim3 grid_b(static_cast<unsigned>((Q + 63) / 64));
         auto launch = [&](auto kern) -> int {
@@ -574,6 +867,44 @@ int bfs(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj, int6
         if (gs == 16) return launch(k_rc_bitset<16>);
         return launch(k_rc_bitset<32>);
     }
+    const size_t lds_m = (static_cast<size_t>(V) + 127) / 128 * 16;
+    hipFuncAttributes fm{};
+    PC_HIP(ctx, hipFuncGetAttributes(&fm, reinterpret_cast<const void *>(k_rc_map<4, true>)));
+    if (V < (1 << kVertexBits) && lds_m + fm.sharedSizeBytes <= static_cast<size_t>(max_lds)) {
+        // records for sparse graphs: up to a mean of kEll / 2 entries nearly all vertices fit one
+        const bool records = avg <= kEll / 2;
+        const int per_cu = 2 * (lds_m + fm.sharedSizeBytes) <= static_cast<size_t>(max_lds) ? 2 : 1;
+        const int32_t grid = std::min(Q, 256 * per_cu);
+        int32_t *list;
+        uint32_t *ell;
+        auto carve = [&](Carver &c) {
+            list = c.take<int32_t>(static_cast<size_t>(grid) * V);
+            ell = c.take<uint32_t>(records ? static_cast<size_t>(V) * kEll : 1);
+        };
+        Carver dry{nullptr, 0};
+        carve(dry);
+        int rc = pc_ensure_arena(ctx, dry.off);
+        if (rc) return rc;
+        Carver real{ctx->arena, 0};
+        carve(real);
+        if (records)
+            PC_TIMED(ctx, "k_rc_records", stream,
+                     hipLaunchKernelGGL(k_rc_records, dim3(static_cast<unsigned>((static_cast<int64_t>(V) * 4 + 255) / 256)), dim3(256), 0,
+                                        stream, V, adj_off, adj, n_adj, region, ell));
+        auto launch = [&](auto kern) -> int {
+            PC_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_m)));
+            PC_TIMED(ctx, "k_rc_map", stream,
+                     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(kMapThreads), lds_m, stream, V,
+                                        adj_off, adj, n_adj, region, ell, Q, src, allowed, target, dist, list, forbid,
+                                        Kf, qdiv));
+            PC_LAUNCH_CHECK(ctx);
+            return PC_OK;
+        };
+        if (records) return launch(k_rc_map<4, true>);
+        return avg <= 24 ? launch(k_rc_map<8, false>) : launch(k_rc_map<32, false>);
+    }
+    if (!target) launch_fill_u32(reinterpret_cast<uint32_t *>(dist), static_cast<size_t>(Q) * V, 0xFFFFFFFFu, stream);
     int32_t grid = Q < 256 ? Q : 256;
     int32_t *qbuf, *rows;
     auto carve = [&](Carver &c) {

@@ -1,0 +1,72 @@
+"""Parity of the map search of pc_masked_reach / pc_masked_reach_via (graphs past the 6,016 vertices of the bitset
+search, and few queries on smaller sparse ones) with the CPU oracle: narrow and wide frontiers and the hand-over between them, more levels than are
+deferred while the row is filled, vertices of more neighbours than a record holds, dense graphs without
+records, rows of every alignment, invalid entries, and the largest size of its range and the first beyond it."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def g():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_run
+    return gpu_run
+
+
+def _csr(V, pairs):
+    pairs = np.unique(np.concatenate([pairs, pairs[:, ::-1]]), axis=0)
+    off = np.zeros(V + 1, np.int32)
+    off[1:] = np.cumsum(np.bincount(pairs[:, 0], minlength=V))
+    return off, pairs[:, 1].astype(np.int32)
+
+
+def _graph(kind, V, rng):
+    v = np.arange(V)
+    if kind == "line":      # a vertex a level: thousands of narrow levels
+        return _csr(V, np.stack([v[:-1], v[1:]], 1))
+    if kind == "blocks":    # short lines of ten
+        return _csr(V, np.stack([v[:-1], v[1:]], 1)[(v[1:] % 10) != 0])
+    if kind == "hubs":      # a line with hubs of 17-400 entries
+        hubs = rng.integers(0, V, 40)
+        spokes = np.concatenate([np.stack([np.full(n, h), rng.integers(0, V, n)], 1)
+                                 for h, n in zip(hubs, rng.integers(17, 400, 40))])
+        return _csr(V, np.concatenate([np.stack([v[:-1], v[1:]], 1), spokes[spokes[:, 0] != spokes[:, 1]]]))
+    deg = {"sparse": 3, "mixed": 8, "mean20": 20, "dense": 60}[kind]  # random: wide levels
+    return _csr(V, np.stack([rng.integers(0, V, V * deg // 2), rng.integers(0, V, V * deg // 2)], 1))
+
+
+@pytest.mark.parametrize("kind,V,Q", [
+    ("line", 6017, 5), ("line", 7003, 3), ("hubs", 9001, 9), ("sparse", 20001, 300), ("mixed", 12007, 40),
+    ("mean20", 8191, 20), ("dense", 6100, 12), ("sparse", 512, 1000), ("sparse", 4001, 1024), ("sparse", 4001, 1025), ("blocks", 1_259_000, 4), ("blocks", 1_300_001, 4)])
+def test_map_rows_and_targets(g, orc, kind, V, Q):
+    rng = np.random.default_rng(V)
+    off, adj = _graph(kind, V, rng)
+    region = (np.arange(V) // 64 % 5 if kind in ("line", "hubs") else rng.integers(0, 5, V)).astype(np.uint8)
+    region[rng.integers(0, V, 5)] = 40
+    bad = rng.integers(0, adj.shape[0], 7)
+    adj[bad] = [-1, V, V + 9, -7, 1 << 30, -(1 << 31), V]
+    src = rng.integers(0, V, Q).astype(np.int32)
+    src[1] = V
+    allowed = rng.integers(1, 32, Q).astype(np.uint32)
+    allowed[::2] = 31
+    target = rng.integers(0, V, Q).astype(np.int32)
+    target[0] = src[0]
+    target[Q // 2] = -1
+    near = np.flatnonzero(np.arange(Q) % 3 == 2)
+    target[near] = np.minimum(np.clip(src[near], 0, V - 1) + rng.integers(0, 900, near.shape[0]), V - 1)
+    rows = slice(0, min(Q, 24))
+    _, flags = orc.reach(V, off, adj, region, src, allowed, target)
+    for t, part in ((None, rows), (target, slice(0, Q))):
+        tt = None if t is None else t[part]
+        dg = g.reach(V, off, adj, region, src[part], allowed[part], tt)
+        do, _ = orc.reach(V, off, adj, region, src[part], allowed[part], tt)
+        assert np.array_equal(dg, do), (kind, t is None, np.argwhere(dg != do)[:3])
+    via = rng.integers(-1, V, (Q, 2)).astype(np.int32)
+    forbid = rng.integers(-1, V, (Q, 3)).astype(np.int32)
+    dg = g.reach_via(V, off, adj, region, src, allowed, target, via, forbid)
+    do, _ = orc.reach_via(V, off, adj, region, src, allowed, target, via, forbid)
+    assert np.array_equal(dg, do), kind
