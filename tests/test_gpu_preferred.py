@@ -203,3 +203,18 @@ def test_preferred_full_size_sampled(g, orc):
     rows = np.concatenate([rows, np.array([0, I - 1], np.int32)])
     bo, so, co = _check(g, orc, wl["labels"], row_off, term_off, weight, preds, feasible=feas, rows=rows)
     assert (so > 0).sum() > 300
+
+
+@pytest.mark.parametrize("I,N,wmax,p_tile", [(1, 64, 100, 1.0), (5, 8193, 1, 0.5), (63, 8192, 2, 0.3),
+                                             (257, 16385, 3, 0.5), (1500, 200, 2, 0.7), (300, 30000, 4, 0.2)])
+def test_preferred_term_sets_and_batches(g, orc, I, N, wmax, p_tile):
+    """Rows of one to three terms with small weights (sums of different term sets often equal), whole tiles
+    without a feasible node, and row counts at the edges of the evaluator's batches."""
+    wl = synth.affinity_workload(I, N, 6, 1, card_choices=(2, 3, 4), absent_p=0.1)
+    row_off, term_off, preds, weight = synth.preferred_rows(I, wl.meta["cards"], I, tmin=1, tmax=3, kmin=1, kmax=2)
+    rng = np.random.default_rng(I)
+    weight = rng.integers(1, wmax + 1, weight.shape[0]).astype(np.uint32)
+    tiles = rng.random((I, (N + 8191) // 8192)) < p_tile
+    feas = _pack((rng.random((I, N)) < 0.02) & np.repeat(tiles, 8192, axis=1)[:, :N])
+    _check(g, orc, wl["labels"], row_off, term_off, weight, preds, feasible=feas)
+    _check(g, orc, wl["labels"], row_off, term_off, weight, preds)
