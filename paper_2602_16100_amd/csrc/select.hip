@@ -51,6 +51,57 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t x)
     return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
+// Which values each label has: labels is read as one flat array in 16-byte
+// pieces (from the first 16-byte boundary on; the bytes before it and after
+// the last piece one by one), a byte at a time tested against, and if new
+// OR-ed into, the workgroup's LDS table (L x 256 bits), which is OR-ed into
+// present32 at the end.  After the first nodes nearly every byte is only an
+// LDS read.  100,000 nodes x 64 labels (6.4 MB): 38 us by single bytes, now 16.
+constexpr int32_t kPresenceLdsL = 1024;  // labels whose table fits 32 KB
+__global__ __launch_bounds__(256) void k_sel_presence_flat(const uint8_t *__restrict__ labels, int64_t n_bytes,
+                                                           int32_t L, uint32_t *present32)
+{
+    extern __shared__ uint32_t ptab[];  // [L][8]
+    for (int32_t i = threadIdx.x; i < L * 8; i += 256) ptab[i] = 0;
+    __syncthreads();
+    auto put = [&](uint32_t l, uint32_t x) {
+        uint32_t *w = ptab + l * 8 + (x >> 5);
+        const uint32_t bit = 1u << (x & 31);
+        if (!(*w & bit)) atomicOr(w, bit);
+    };
+    const int64_t head = min(n_bytes, static_cast<int64_t>((16 - (reinterpret_cast<uintptr_t>(labels) & 15)) & 15));
+    const int64_t pieces = (n_bytes - head) / 16;
+    const uint4 *body = reinterpret_cast<const uint4 *>(labels + head);
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * 256;
+    constexpr int kAhead = 4;
+    for (int64_t i0 = blockIdx.x * 256ll + threadIdx.x; i0 < pieces; i0 += stride * kAhead) {
+        uint4 v[kAhead];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k)
+            if (i0 + k * stride < pieces) v[k] = body[i0 + k * stride];
+#pragma unroll
+        for (int k = 0; k < kAhead; ++k) {
+            if (i0 + k * stride >= pieces) break;
+            uint32_t l = static_cast<uint32_t>((head + (i0 + k * stride) * 16) % L);
+            const uint32_t w[4] = {v[k].x, v[k].y, v[k].z, v[k].w};
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                put(l, (w[j / 4] >> (8 * (j % 4))) & 0xFFu);
+                l = l + 1 == static_cast<uint32_t>(L) ? 0 : l + 1;
+            }
+        }
+    }
+    if (blockIdx.x == 0) {
+        const int64_t tail = head + pieces * 16;
+        for (int64_t o = threadIdx.x; o < head; o += 256) put(static_cast<uint32_t>(o % L), labels[o]);
+        for (int64_t o = tail + threadIdx.x; o < n_bytes; o += 256) put(static_cast<uint32_t>(o % L), labels[o]);
+    }
+    __syncthreads();
+    for (int32_t i = threadIdx.x; i < L * 8; i += 256)
+        if (ptab[i] & ~present32[i]) atomicOr(&present32[i], ptab[i]);  // (mostly known by then: no contended atomics)
+}
+
+// The same for more labels than the table holds: a tile of 64 labels per workgroup column.
 __global__ __launch_bounds__(256) void k_sel_presence(const uint8_t *__restrict__ labels, int32_t N, int32_t L,
                                                       int64_t chunk, uint32_t *__restrict__ present32)
 {
@@ -130,30 +181,89 @@ __global__ __launch_bounds__(1024) void k_sel_label_scan(const uint64_t *__restr
     if (tid == 0) *d_P = static_cast<int32_t>(carry_s);
 }
 
-// One wavefront per (64-node word w, label l): a ballot per present value.
+// A wavefront builds kPlaneWords words (1,024 nodes) of one label's planes, so
+// that what it writes of a plane is a whole 128-byte line, four values'
+// lines to a store.  A lane keeps its nodes' values of the label.  Few
+// values: per value and word a ballot gives the word, which moves into the
+// lane that stores it.  More than kBallots of a 64-value word: every node sets
+// its bit in an LDS tile (one atomic per node and label instead of a ballot
+// per value).  A workgroup's wavefronts take four neighbouring labels, whose
+// bytes arrive together (kWide: as one aligned word, L a multiple of 4).
 // Word w of plane p lives at planes[p * Wp + kPad + w].
+// 100,000 nodes x 64 labels: 78 us with a word per wavefront (8 bytes of a line
+// written at a time), now 25; 50,000 nodes 44 us, now 16.
+constexpr int kPlaneWords = 16;
+constexpr int kBallots = 8;
+template <bool kWide>
 __global__ __launch_bounds__(256) void k_sel_planes(const uint8_t *__restrict__ labels, int32_t N, int32_t L,
                                                     const uint64_t *__restrict__ present,
                                                     const uint32_t *__restrict__ wbase, uint64_t *__restrict__ planes,
                                                     int64_t Wp)
 {
+    constexpr int kRow = 2 * kPlaneWords + 2;  // dwords per value of the tile: neighbouring values in other banks
+    __shared__ __align__(8) uint32_t tiles[4][64 * kRow];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int32_t w = blockIdx.x;
+    const int32_t w0 = blockIdx.x * kPlaneWords;
     const int32_t l = blockIdx.y * 4 + wave;
     if (l >= L) return;
-    uint64_t *col = planes + kPad + w;
-    const int64_t n = static_cast<int64_t>(w) * 64 + lane;
-    const uint32_t x = n < N ? labels[n * L + l] : 0x100u;  // 0x100 equals no value
-    for (int k = 0; k < 4; ++k) {
-        uint64_t m = uniform_u64(present[static_cast<int64_t>(l) * 4 + k]);
-        uint32_t pid = __builtin_amdgcn_readfirstlane(wbase[static_cast<int64_t>(l) * 4 + k]);
-        while (m) {
-            const uint32_t v = static_cast<uint32_t>(k * 64 + __builtin_ctzll(m));
-            const uint64_t word = __ballot(x == v);
-            if (lane == 0) col[static_cast<int64_t>(pid) * Wp] = word;
-            ++pid;
-            m &= m - 1;
+    const int32_t W = static_cast<int32_t>((static_cast<int64_t>(N) + 63) / 64);
+    uint32_t *tile = tiles[wave];
+    uint32_t x[kPlaneWords];
+#pragma unroll
+    for (int k = 0; k < kPlaneWords; ++k) {
+        const int64_t n = static_cast<int64_t>(w0 + k) * 64 + lane;
+        x[k] = 0x100u;  // equals no value
+        if (n < N) {
+            if constexpr (kWide)
+                x[k] = (*reinterpret_cast<const uint32_t *>(labels + n * L + blockIdx.y * 4) >> (8 * wave)) & 0xFFu;
+            else
+                x[k] = labels[n * L + l];
+        }
+    }
+    const int col = lane & (kPlaneWords - 1), slot = lane / kPlaneWords;
+    const bool store = w0 + col < W;
+    for (int k4 = 0; k4 < 4; ++k4) {
+        const uint64_t here = uniform_u64(present[static_cast<int64_t>(l) * 4 + k4]);
+        const int n = __popcll(here);
+        uint64_t *out = planes + static_cast<int64_t>(__builtin_amdgcn_readfirstlane(wbase[static_cast<int64_t>(l) * 4 + k4])) * Wp +
+                        kPad + w0;
+        if (n > kBallots) {
+            for (int i = lane; i < n * kRow; i += 64) tile[i] = 0;
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int k = 0; k < kPlaneWords; ++k)
+                if (x[k] >> 6 == static_cast<uint32_t>(k4)) {
+                    const int r = __popcll(here & ((1ull << (x[k] & 63)) - 1));
+                    atomicOr(&tile[r * kRow + 2 * k + (lane >> 5)], 1u << (lane & 31));
+                }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            for (int v = slot; v < n; v += 4)
+                if (store)
+                    out[static_cast<int64_t>(v) * Wp + col] =
+                        *reinterpret_cast<const uint64_t *>(tile + v * kRow + 2 * col);
+            __builtin_amdgcn_wave_barrier();
+            continue;
+        }
+        uint64_t m = here;
+        for (int v0 = 0; v0 < n; v0 += 4) {
+            uint64_t word = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (m == 0) break;
+                const uint32_t v = static_cast<uint32_t>(k4 * 64 + __builtin_ctzll(m));
+                m &= m - 1;
+#pragma unroll
+                for (int k = 0; k < kPlaneWords; ++k) {
+                    const uint64_t b = __ballot(x[k] == v);
+                    word = lane == j * kPlaneWords + k ? b : word;
+                }
+            }
+            if (store && v0 + slot < n)
+                out[static_cast<int64_t>(v0 + slot) * Wp + col] = word;
         }
     }
 }
@@ -340,15 +450,37 @@ __device__ __forceinline__ bool aff_valid(const pc_pred &q, int32_t L)
     return true;
 }
 
-// One thread per row, two passes over its predicates: validate and size
-// the program, then emit it -- inline in the row record when it has at most
-// 15 entries, else at prog[4 * pred_off[i] ...] (at most 4 entries per
-// predicate; longer programs are decoded at evaluation time).
-// One thread per row.  Each row's record is built in LDS and written as
-// four 16-byte stores instead of a store per entry.  (Staging a pass's
-// predicates in LDS as well measured slower: the 50 KB it takes leaves two
-// workgroups per CU.)
+// A group of G lanes compiles one row: the lanes' own bits of a ballot, and
+// the exclusive sum of x over the group's lower lanes with the group's total.
+template <int G>
+__device__ __forceinline__ uint32_t group_bits(bool x)
+{
+    return static_cast<uint32_t>(__ballot(x) >> ((threadIdx.x & 63) & ~(G - 1))) & ((1u << G) - 1);
+}
+
+template <int G>
+__device__ __forceinline__ uint32_t group_scan(uint32_t x, uint32_t &total)
+{
+    uint32_t s = x;
+#pragma unroll
+    for (int off = 1; off < G; off <<= 1) {
+        const uint32_t y = __shfl_up(s, off, G);
+        if (static_cast<int>(threadIdx.x % G) >= off) s += y;
+    }
+    total = __shfl(s, G - 1, G);
+    return s - x;
+}
+
+// kSelLanes lanes per row, one predicate each: validate and size the
+// predicates, then emit the program -- inline in the row record when it has
+// at most 15 entries, else at prog[4 * pred_off[i] ...] (at most 4 entries
+// per predicate; longer programs are decoded at evaluation time).  The record
+// is built in LDS and written by the group.
+// Bound by the chain offsets -> predicate -> presence words of a row, which
+// the lanes walk together (a thread per row walked it once per predicate:
+// 16,384 rows 22 us, now 7.5; 699,051 rows 113 us, now 81).
 constexpr int kCompThreads = 256;
+constexpr int kSelLanes = 8;
 __global__ __launch_bounds__(kCompThreads) void k_sel_compile(const int32_t *__restrict__ pred_off,
                                                               const pc_pred *__restrict__ preds, int64_t n_preds,
                                                               int32_t I, int32_t L,
@@ -357,79 +489,89 @@ __global__ __launch_bounds__(kCompThreads) void k_sel_compile(const int32_t *__r
                                                               uint32_t *__restrict__ prog, uint32_t *__restrict__ rec,
                                                               uint32_t *__restrict__ d_err)
 {
-    __shared__ uint32_t srec[kCompThreads][kRecWords + 1];  // each thread's row record (padded row)
-    uint32_t *R = srec[threadIdx.x];
+    constexpr int G = kSelLanes;
+    __shared__ uint32_t srec[kCompThreads / G][kRecWords + 2];  // each group's row record (padded)
+    uint32_t *R = srec[threadIdx.x / G];
+    const int gl = threadIdx.x % G;
     uint32_t errs = 0;
-    for (int64_t i0 = static_cast<int64_t>(blockIdx.x) * kCompThreads; i0 < I;
-         i0 += static_cast<int64_t>(gridDim.x) * kCompThreads) {
-        const int64_t i = i0 + threadIdx.x;
-        if (i >= I) continue;
-        const int64_t b = pred_off[i], e = pred_off[i + 1];
-        // the row's record, in LDS until it is complete
-        [&] {
-            if (!pc_range_ok(b, e, n_preds)) {
-                errs |= PC_DERR_OFFSETS;
-                R[0] = static_cast<uint32_t>(kRowFalse);
-                return;
-            }
-            // one pass: validity, sizes and the inline entries together
-            // (counted past the inline area; a longer program is written
-            // again into prog below)
-            bool empty = false;
-            int64_t n = 0;
-            auto emit = [&](const pc_pred &q, uint32_t *out, int64_t &k_out, bool bounded) {
-                const uint64_t *pres = present + static_cast<int64_t>(q.label) * 4;
-                const uint32_t *wb = wbase + static_cast<int64_t>(q.label) * 4;
-                uint64_t sel[4];
-                bool neg;
-                const uint32_t cnt0 = pred_clause(q, pres, sel, neg);
-                uint32_t cnt = cnt0;
-                for (int k = 0; k < 4; ++k) {
-                    uint64_t m = sel[k];
-                    while (m) {
-                        const uint32_t v = static_cast<uint32_t>(k * 64 + __builtin_ctzll(m));
-                        m &= m - 1;
-                        uint32_t ent = plane_id(pres, wb, v);
-                        if (--cnt == 0) ent |= kLast | (neg ? kNeg : 0u);
-                        if (!bounded || k_out < kInline) out[k_out] = ent;
-                        ++k_out;
+    for (int64_t i0 = static_cast<int64_t>(blockIdx.x) * (kCompThreads / G); i0 < I;
+         i0 += static_cast<int64_t>(gridDim.x) * (kCompThreads / G)) {
+        const int64_t i = i0 + threadIdx.x / G;
+        int64_t b = 0, e = 0;
+        bool good = false;
+        if (i < I) {
+            b = pred_off[i];
+            e = pred_off[i + 1];
+            good = pc_range_ok(b, e, n_preds);
+            if (!good) errs |= PC_DERR_OFFSETS;
+        }
+        if (!good) b = e = 0;
+        // the entries of the row's predicates in order; k0: the first one's place
+        auto pass = [&](auto &&emit, bool &empty) {
+            int64_t k0 = 0;
+            empty = false;
+            for (int64_t p0 = b; __ballot(p0 < e) != 0; p0 += G) {
+                const int64_t p = p0 + gl;
+                uint64_t sel[4] = {0, 0, 0, 0};
+                const uint64_t *pres = nullptr;
+                const uint32_t *wb = nullptr;
+                uint32_t cnt = 0;
+                bool neg = true;
+                if (p < e) {
+                    const pc_pred q = preds[p];
+                    if (!pred_valid(q.label, q.op, q.rsv0, q.rsv1, q.vals[3], L)) {
+                        errs |= PC_DERR_PRED;
+                        neg = false;  // as an empty OR: no node
+                    } else {
+                        pres = present + static_cast<int64_t>(q.label) * 4;
+                        wb = wbase + static_cast<int64_t>(q.label) * 4;
+                        cnt = pred_clause(q, pres, sel, neg);
                     }
                 }
-                return cnt0 == 0 && !neg;  // an empty OR: no node (a negated empty OR is every node)
-            };
-            int64_t k_in = 0;
-            for (int64_t p = b; p < e; ++p) {
-                const pc_pred q = preds[p];
-                if (!pred_valid(q.label, q.op, q.rsv0, q.rsv1, q.vals[3], L)) {
-                    errs |= PC_DERR_PRED;
-                    empty = true;
-                    continue;
+                empty |= group_bits<G>(cnt == 0 && !neg) != 0;
+                uint32_t total;
+                int64_t k = k0 + group_scan<G>(cnt, total);
+                k0 += total;
+                for (int w = 0; w < 4; ++w) {
+                    uint64_t m = sel[w];
+                    while (m) {
+                        const uint32_t v = static_cast<uint32_t>(w * 64 + __builtin_ctzll(m));
+                        m &= m - 1;
+                        emit(k++, plane_id(pres, wb, v) | (--cnt == 0 ? kLast | (neg ? kNeg : 0u) : 0u));
+                    }
                 }
-                if (empty) continue;
-                if (emit(q, R + 1, k_in, true)) empty = true;
             }
-            n = k_in;
-            if (empty) {
-                R[0] = static_cast<uint32_t>(kRowFalse);
-                return;
+            return k0;
+        };
+        bool empty;
+        const int64_t n = pass([&](int64_t k, uint32_t ent) {
+            if (k < kInline) R[1 + k] = ent;
+        }, empty);
+        const bool fits = n <= 4 * (e - b);
+        const bool indirect = good && !empty && n > kInline && fits;
+        if (gl == 0) {
+            // (the evaluator reads entries 1..n of an inline program only)
+            if (!good || empty) R[0] = static_cast<uint32_t>(kRowFalse);
+            else if (n <= kInline) R[0] = static_cast<uint32_t>(n);
+            else if (!fits) R[0] = static_cast<uint32_t>(kRowLong);
+            else {
+                R[0] = static_cast<uint32_t>(kRowIndirect);
+                R[1] = static_cast<uint32_t>(b);
+                R[2] = static_cast<uint32_t>(n);
             }
-            if (n <= kInline) {
-                R[0] = static_cast<uint32_t>(n);  // the evaluator reads entries 1..n only
-                return;
-            }
-            if (n > 4 * (e - b)) {
-                R[0] = static_cast<uint32_t>(kRowLong);
-                return;
-            }
-            int64_t k_out = 0;
-            for (int64_t p = b; p < e; ++p) emit(preds[p], prog + 4 * b, k_out, false);
-            R[0] = static_cast<uint32_t>(kRowIndirect);
-            R[1] = static_cast<uint32_t>(b);
-            R[2] = static_cast<uint32_t>(n);
-        }();
-        uint4 *dst = reinterpret_cast<uint4 *>(rec + i * kRecWords);
-#pragma unroll
-        for (int k = 0; k < kRecWords / 4; ++k) dst[k] = make_uint4(R[4 * k], R[4 * k + 1], R[4 * k + 2], R[4 * k + 3]);
+        }
+        if (__ballot(indirect)) {  // (rows of the wavefront that are not take part with no predicates)
+            uint32_t *out = prog + 4 * b;
+            const int64_t e_all = e;
+            if (!indirect) e = b;
+            pass([&](int64_t k, uint32_t ent) { out[k] = ent; }, empty);
+            e = e_all;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (i < I) reinterpret_cast<uint2 *>(rec + i * kRecWords)[gl] = make_uint2(R[2 * gl], R[2 * gl + 1]);
+        __builtin_amdgcn_wave_barrier();
     }
     if (errs) atomicOr(d_err, errs);
 }
@@ -502,13 +644,183 @@ __device__ __forceinline__ bool aff_term(const pc_pred *__restrict__ preds, int6
     return ok;
 }
 
-// One thread per affinity row: inventory flags, then the program.  Terms
-// that hold nowhere are dropped; a term with an empty program holds
-// everywhere, and so does a row without terms (header 0); a row with no
-// term left admits no node.  The last entry of each term carries
-// kTermEnd.  Programs of at most 15 entries sit inline in the row record;
-// longer ones take a slice of prog through a bump counter and, when it is
-// exhausted, are decoded at evaluation time (kRowLong).
+// One affinity row, on one lane (rows that k_aff_compile's groups do not
+// take): the record in rr, the inventory flags in unknown[i].
+__device__ __forceinline__ void aff_compile_row(const int32_t *__restrict__ row_off, int32_t i, const int32_t *__restrict__ term_off,
+                                int32_t n_terms, const pc_pred *__restrict__ preds, int64_t n_preds, int32_t L,
+                                const uint64_t *__restrict__ present, const uint32_t *__restrict__ wbase,
+                                uint32_t *__restrict__ prog, int64_t prog_cap,
+                                unsigned long long *__restrict__ prog_used, uint32_t *rr,
+                                uint8_t *__restrict__ unknown, uint32_t pfx0)
+{
+    const int64_t tb = row_off[i], te = row_off[i + 1];
+    if (!pc_range_ok(tb, te, n_terms)) {
+        rr[0] = static_cast<uint32_t>(kRowFalse);
+        unknown[i] = 0;
+        return;
+    }
+    // One pass over the row's expressions: the inventory flags (every
+    // well-formed expression of every term with valid offsets), and
+    // each term's entries emitted into the record's inline area as
+    // they come (counted past its end) and taken back when the term
+    // turns out to hold nowhere (a malformed expression, an empty
+    // clause).  A live term with no entries holds everywhere, and so
+    // does the row.
+    uint32_t unk = 0;
+    bool all = tb == te;
+    int64_t n = 0, live = 0, k_out = 0;
+    uint32_t *in_out = rr + 1;
+    for (int64_t t = tb; t < te; ++t) {
+        const int64_t b = term_off[t], e = term_off[t + 1];
+        if (!pc_range_ok(b, e, n_preds)) continue;
+        bool ok = b != e;
+        const int64_t start = k_out;
+        int64_t len = 0;
+        for (int64_t p = b; p < e; ++p) {
+            const pc_pred q = preds[p];
+            if (!aff_valid(q, L)) {
+                ok = false;
+                continue;
+            }
+            const uint64_t *pres = present + static_cast<int64_t>(q.label) * 4;
+            unk |= aff_unknown(q, pres);
+            if (!ok || all) continue;
+            bool neg;
+            const uint32_t cnt = aff_entries(q, pres, wbase + static_cast<int64_t>(q.label) * 4, pfx0, neg,
+                                             [&](uint32_t ent) {
+                                                 if (k_out < kInline) in_out[k_out] = ent;
+                                                 ++k_out;
+                                             });
+            if (cnt == 0 && !neg) ok = false;
+            len += cnt;
+        }
+        if (all) continue;
+        if (!ok) {
+            k_out = start;
+            continue;
+        }
+        if (len == 0) {
+            all = true;
+            continue;
+        }
+        if (k_out <= kInline) in_out[k_out - 1] |= kTermEnd;
+        n += len;
+        ++live;
+    }
+    unknown[i] = static_cast<uint8_t>(unk);
+    if (all) {
+        rr[0] = 0;
+        return;
+    }
+    if (live == 0) {
+        rr[0] = static_cast<uint32_t>(kRowFalse);
+        return;
+    }
+    if (n <= kInline) {
+        rr[0] = static_cast<uint32_t>(n);
+        return;
+    }
+    // longer than the inline area: a slice of prog, written by a
+    // second pass (slices are whole multiples of 4 entries: the
+    // record stores off / 4)
+    const unsigned long long off = atomicAdd(prog_used, static_cast<unsigned long long>((n + 3) & ~int64_t(3)));
+    if (static_cast<int64_t>(off) + n > prog_cap) {
+        rr[0] = static_cast<uint32_t>(kRowLong);
+        return;
+    }
+    uint32_t *out = prog + off;
+    rr[0] = static_cast<uint32_t>(kRowIndirect);
+    rr[1] = static_cast<uint32_t>(off / 4);
+    rr[2] = static_cast<uint32_t>(n);
+    int64_t k2 = 0;
+    for (int64_t t = tb; t < te; ++t) {
+        const int64_t b = term_off[t], e = term_off[t + 1];
+        int64_t len;
+        if (!aff_term(preds, b, e, n_preds, L, present, len)) continue;
+        for (int64_t p = b; p < e; ++p) {
+            const pc_pred q = preds[p];
+            bool neg;
+            aff_entries(q, present + static_cast<int64_t>(q.label) * 4, wbase + static_cast<int64_t>(q.label) * 4,
+                        pfx0, neg, [&](uint32_t ent) { out[k2++] = ent; });
+        }
+        out[k2 - 1] |= kTermEnd;
+    }
+}
+
+// The expressions of a row whose terms a group of G lanes can take at once:
+// at most G terms, all of valid offsets (which makes them adjacent), and at
+// most G expressions.  Term t is lane t's: expressions [b, e).
+struct GroupTerms {
+    bool fits;       // (group-uniform)
+    int32_t nt;      // terms
+    int64_t first;   // the row's first expression
+    int32_t n;       // expressions
+    int32_t b, e;    // lane t: term t's expressions, from `first`
+    uint32_t mask;   // lane t: them as lanes
+};
+
+template <int G>
+__device__ __forceinline__ GroupTerms group_terms(int64_t tb, int64_t te, const int32_t *__restrict__ term_off,
+                                                  int64_t n_preds, bool live)
+{
+    const int gl = threadIdx.x % G;
+    GroupTerms g{false, 0, 0, 0, 0, 0, 0};
+    const bool few = live && te - tb <= G;
+    int64_t b = 0, e = 0;
+    bool ok = true;
+    if (few && tb + gl < te) {
+        b = term_off[tb + gl];
+        e = term_off[tb + gl + 1];
+        ok = pc_range_ok(b, e, n_preds);
+    }
+    const bool all_ok = group_bits<G>(!ok) == 0;
+    g.nt = few ? static_cast<int32_t>(te - tb) : 0;
+    g.first = __shfl(b, 0, G);
+    const int64_t end = __shfl(e, max(g.nt - 1, 0), G);
+    g.fits = few && all_ok && end - g.first <= G;
+    if (g.fits) {
+        g.n = static_cast<int32_t>(end - g.first);
+        if (gl < g.nt) {
+            g.b = static_cast<int32_t>(b - g.first);
+            g.e = static_cast<int32_t>(e - g.first);
+            g.mask = ((1u << g.e) - 1) & ~((1u << g.b) - 1);
+        }
+    }
+    return g;
+}
+
+// Lane j's term among the group's (the last one that begins at or before
+// its expression; a term without expressions never is).
+template <int G>
+__device__ __forceinline__ int group_term_of(const GroupTerms &g)
+{
+    const int gl = threadIdx.x % G;
+    int mine = 0;
+    for (int t = 1; t < G; ++t) {
+        if (!__ballot(t < g.nt)) break;
+        const int32_t bt = __shfl(g.b, t, G);
+        if (t < g.nt && bt <= gl) mine = t;
+    }
+    return mine;
+}
+
+// A group of kAffLanes lanes per affinity row, one expression each:
+// inventory flags, then the program.  Terms that hold nowhere are dropped; a
+// term with an empty program holds everywhere, and so does a row without
+// terms (header 0); a row with no term left admits no node.  The last entry
+// of each term carries kTermEnd.  Programs of at most 15 entries sit inline in
+// the row record; longer ones take a slice of prog through a bump counter
+// and, when it is exhausted, are decoded at evaluation time (kRowLong).  Rows
+// that group_terms does not take are compiled by one lane.
+// Bound by the chain offsets -> expression -> presence words, which a thread
+// per row walked once per expression (3,001 rows 67 us, now 9); of many rows a
+// thread each (G = 1) has the better throughput.
+constexpr int kAffLanes = 16;
+// rows below which the groups win (a thread per row / groups, at 64 labels:
+// affinity 80,000 rows 56 / 37 us, 160,000 rows 69 / 67, 699,051 rows 147 / 266;
+// preferred 40,000 rows 46 / 40 us, 80,000 rows 52 / 54, 699,051 rows 195 / 343)
+constexpr int32_t kAffGroupRows = 131072, kPrefGroupRows = 65536;
+template <int G>
 __global__ __launch_bounds__(256) void k_aff_compile(const int32_t *__restrict__ row_off, int32_t I,
                                                      const int32_t *__restrict__ term_off, int32_t n_terms,
                                                      const pc_pred *__restrict__ preds, int64_t n_preds, int32_t L,
@@ -519,108 +831,107 @@ __global__ __launch_bounds__(256) void k_aff_compile(const int32_t *__restrict__
                                                      uint32_t *__restrict__ rec, uint8_t *__restrict__ unknown,
                                                      uint32_t pfx0)
 {
-    // each row's record is built in LDS and written as 16-byte stores
-    __shared__ uint32_t srec[256][kRecWords + 1];
-    uint32_t *rr = srec[threadIdx.x];
-    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < I; i += gridDim.x * blockDim.x) {
-        [&] {  // the row's record, in LDS until it is complete
-            const int64_t tb = row_off[i], te = row_off[i + 1];
-            if (!pc_range_ok(tb, te, n_terms)) {
+    __shared__ uint32_t srec[256 / G][kRecWords + 1];
+    uint32_t *rr = srec[threadIdx.x / G];
+    if constexpr (G == 1) {
+        for (int32_t i = blockIdx.x * 256 + threadIdx.x; i < I; i += gridDim.x * 256) {
+            aff_compile_row(row_off, i, term_off, n_terms, preds, n_preds, L, present, wbase, prog, prog_cap,
+                            prog_used, rr, unknown, pfx0);
+            uint4 *dst = reinterpret_cast<uint4 *>(rec + static_cast<int64_t>(i) * kRecWords);
+#pragma unroll
+            for (int k = 0; k < kRecWords / 4; ++k)
+                dst[k] = make_uint4(rr[4 * k], rr[4 * k + 1], rr[4 * k + 2], rr[4 * k + 3]);
+        }
+        return;
+    } else {
+    const int gl = threadIdx.x % G;
+    for (int64_t i0 = static_cast<int64_t>(blockIdx.x) * (256 / G); i0 < I;
+         i0 += static_cast<int64_t>(gridDim.x) * (256 / G)) {
+        const int64_t i = i0 + threadIdx.x / G;
+        int64_t tb = 0, te = 0;
+        bool good = false;
+        if (i < I) {
+            tb = row_off[i];
+            te = row_off[i + 1];
+            good = pc_range_ok(tb, te, n_terms);
+            if (!good && gl == 0) {
                 rr[0] = static_cast<uint32_t>(kRowFalse);
                 unknown[i] = 0;
-                return;
             }
-            // One pass over the row's expressions: the inventory flags (every
-            // well-formed expression of every term with valid offsets), and
-            // each term's entries emitted into the record's inline area as
-            // they come (counted past its end) and taken back when the term
-            // turns out to hold nowhere (a malformed expression, an empty
-            // clause).  A live term with no entries holds everywhere, and so
-            // does the row.
-            uint32_t unk = 0;
-            bool all = tb == te;
-            int64_t n = 0, live = 0, k_out = 0;
-            uint32_t *in_out = rr + 1;
-            for (int64_t t = tb; t < te; ++t) {
-                const int64_t b = term_off[t], e = term_off[t + 1];
-                if (!pc_range_ok(b, e, n_preds)) continue;
-                bool ok = b != e;
-                const int64_t start = k_out;
-                int64_t len = 0;
-                for (int64_t p = b; p < e; ++p) {
-                    const pc_pred q = preds[p];
-                    if (!aff_valid(q, L)) {
-                        ok = false;
-                        continue;
-                    }
-                    const uint64_t *pres = present + static_cast<int64_t>(q.label) * 4;
-                    unk |= aff_unknown(q, pres);
-                    if (!ok || all) continue;
-                    bool neg;
-                    const uint32_t cnt = aff_entries(q, pres, wbase + static_cast<int64_t>(q.label) * 4, pfx0, neg,
-                                                     [&](uint32_t ent) {
-                                                         if (k_out < kInline) in_out[k_out] = ent;
-                                                         ++k_out;
-                                                     });
-                    if (cnt == 0 && !neg) ok = false;
-                    len += cnt;
+        }
+        const GroupTerms g = group_terms<G>(tb, te, term_off, n_preds, good);
+        if (good && !g.fits && gl == 0)
+            aff_compile_row(row_off, static_cast<int32_t>(i), term_off, n_terms, preds, n_preds, L, present, wbase,
+                            prog, prog_cap, prog_used, rr, unknown, pfx0);
+        // this lane's expression
+        pc_pred q{};
+        const uint64_t *pres = nullptr;
+        const uint32_t *wb = nullptr;
+        uint32_t cnt = 0, unk = 0;
+        bool neg = true, valid = false;
+        const bool mine = g.fits && gl < g.n;
+        if (mine) {
+            q = preds[g.first + gl];
+            valid = aff_valid(q, L);
+            if (valid) {
+                pres = present + static_cast<int64_t>(q.label) * 4;
+                wb = wbase + static_cast<int64_t>(q.label) * 4;
+                unk = aff_unknown(q, pres);
+                if (q.op == PC_OP_GT || q.op == PC_OP_LT) {
+                    cnt = cmp_count(q.op, static_cast<int64_t>(q.vals[0]), pres, neg);
+                } else {
+                    uint64_t sel[4];
+                    cnt = expr_clause(q.op, q.vals, pres, sel, neg);
                 }
-                if (all) continue;
-                if (!ok) {
-                    k_out = start;
-                    continue;
-                }
-                if (len == 0) {
-                    all = true;
-                    continue;
-                }
-                if (k_out <= kInline) in_out[k_out - 1] |= kTermEnd;
-                n += len;
-                ++live;
             }
-            unknown[i] = static_cast<uint8_t>(unk);
-            if (all) {
-                rr[0] = 0;
-                return;
+        }
+        const uint32_t bad = group_bits<G>(mine && (!valid || (cnt == 0 && !neg)));
+        const uint32_t some = group_bits<G>(cnt != 0);
+        const uint32_t u0 = group_bits<G>((unk & 1) != 0), u1 = group_bits<G>((unk & 2) != 0);
+        // lane t: whether term t can hold, and whether it holds everywhere
+        const bool term_ok = g.mask != 0 && !(bad & g.mask);
+        const uint32_t live = group_bits<G>(term_ok);
+        const bool all = group_bits<G>(term_ok && !(some & g.mask)) != 0 || (g.fits && g.nt == 0);
+        const int term = group_term_of<G>(g);
+        const bool keep = mine && ((live >> term) & 1u);
+        uint32_t n;
+        const uint32_t k0 = group_scan<G>(keep ? cnt : 0u, n);
+        const bool write = g.fits && !all && live != 0;
+        unsigned long long off = 0;
+        if (write && n > kInline && gl == 0) off = atomicAdd(prog_used, static_cast<unsigned long long>((n + 3) & ~3u));
+        off = __shfl(off, 0, G);
+        const bool inl = n <= kInline;
+        const bool room = static_cast<int64_t>(off) + n <= prog_cap;
+        const uint32_t tmask = __shfl(g.mask, term, G);
+        if (write && keep && cnt && (inl || room)) {
+            uint32_t *out = inl ? rr + 1 : prog + off;
+            uint32_t k = k0;
+            // the term's last entry is in its last expression with any
+            const bool closes = (some & tmask) >> (gl + 1) == 0;
+            const uint32_t end = k0 + cnt - 1;
+            aff_entries(q, pres, wb, pfx0, neg, [&](uint32_t ent) {
+                out[k] = ent | (closes && k == end ? kTermEnd : 0u);
+                ++k;
+            });
+        }
+        if (g.fits && gl == 0) {
+            unknown[i] = static_cast<uint8_t>((u0 ? 1u : 0u) | (u1 ? 2u : 0u));
+            if (all) rr[0] = 0;
+            else if (live == 0) rr[0] = static_cast<uint32_t>(kRowFalse);
+            else if (inl) rr[0] = n;
+            else if (!room) rr[0] = static_cast<uint32_t>(kRowLong);
+            else {
+                rr[0] = static_cast<uint32_t>(kRowIndirect);
+                rr[1] = static_cast<uint32_t>(off / 4);
+                rr[2] = n;
             }
-            if (live == 0) {
-                rr[0] = static_cast<uint32_t>(kRowFalse);
-                return;
-            }
-            if (n <= kInline) {
-                rr[0] = static_cast<uint32_t>(n);
-                return;
-            }
-            // longer than the inline area: a slice of prog, written by a
-            // second pass (slices are whole multiples of 4 entries: the
-            // record stores off / 4)
-            const unsigned long long off = atomicAdd(prog_used, static_cast<unsigned long long>((n + 3) & ~int64_t(3)));
-            if (static_cast<int64_t>(off) + n > prog_cap) {
-                rr[0] = static_cast<uint32_t>(kRowLong);
-                return;
-            }
-            uint32_t *out = prog + off;
-            rr[0] = static_cast<uint32_t>(kRowIndirect);
-            rr[1] = static_cast<uint32_t>(off / 4);
-            rr[2] = static_cast<uint32_t>(n);
-            int64_t k2 = 0;
-            for (int64_t t = tb; t < te; ++t) {
-                const int64_t b = term_off[t], e = term_off[t + 1];
-                int64_t len;
-                if (!aff_term(preds, b, e, n_preds, L, present, len)) continue;
-                for (int64_t p = b; p < e; ++p) {
-                    const pc_pred q = preds[p];
-                    bool neg;
-                    aff_entries(q, present + static_cast<int64_t>(q.label) * 4, wbase + static_cast<int64_t>(q.label) * 4,
-                                pfx0, neg, [&](uint32_t ent) { out[k2++] = ent; });
-                }
-                out[k2 - 1] |= kTermEnd;
-            }
-        }();
-        uint4 *dst = reinterpret_cast<uint4 *>(rec + static_cast<int64_t>(i) * kRecWords);
-#pragma unroll
-        for (int k = 0; k < kRecWords / 4; ++k)
-            dst[k] = make_uint4(rr[4 * k], rr[4 * k + 1], rr[4 * k + 2], rr[4 * k + 3]);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (i < I) rec[i * kRecWords + gl] = rr[gl];
+        __builtin_amdgcn_wave_barrier();
+    }
     }
 }
 
@@ -1042,7 +1353,7 @@ __global__ __launch_bounds__(256) void k_pref_validate(const int32_t *__restrict
 // One row of k_pref_compile: its record, and its class (3: at most three
 // live terms, including none; 0: scores fit 8 bits, 1: 16 bits; 2: decoded
 // on the fly).
-__device__ uint32_t pref_compile_row(const int32_t *__restrict__ row_off, int32_t i,
+__device__ __forceinline__ uint32_t pref_compile_row(const int32_t *__restrict__ row_off, int32_t i,
                                      const int32_t *__restrict__ term_off, int32_t n_terms,
                                      const uint32_t *__restrict__ weight, const pc_pred *__restrict__ preds,
                                      int64_t n_preds, int32_t L, const uint64_t *__restrict__ present,
@@ -1130,13 +1441,16 @@ __device__ uint32_t pref_compile_row(const int32_t *__restrict__ row_off, int32_
     return bit_length(sum) <= 8 ? 0u : 1u;
 }
 
-// One thread per row: the row's live terms (weight in range, and able to
+// A group of kAffLanes lanes per row, one expression each (rows that
+// group_terms does not take: one lane): the row's live terms (weight in range, and able to
 // hold somewhere) as a program of term headers, each followed by its clause
 // entries (kLast / kNeg as in selector programs), inline in the row record
 // when it has at most 14 words, else in a slice of prog taken through a
 // bump counter.  When the slice does not fit, or a term has more than 2^24
 // entries, the row is decoded at evaluation time.
 // Each row is appended to the list of its class.
+// Bound as k_aff_compile (3,001 rows 57 us, now 11).
+template <int G>
 __global__ __launch_bounds__(256) void k_pref_compile(const int32_t *__restrict__ row_off, int32_t I,
                                                       const int32_t *__restrict__ term_off, int32_t n_terms,
                                                       const uint32_t *__restrict__ weight,
@@ -1145,36 +1459,128 @@ __global__ __launch_bounds__(256) void k_pref_compile(const int32_t *__restrict_
                                                       const uint32_t *__restrict__ wbase, uint32_t *__restrict__ prog,
                                                       int64_t prog_cap, unsigned long long *__restrict__ prog_used,
                                                       uint32_t *__restrict__ rec, int32_t *__restrict__ list,
-                                                      uint32_t *__restrict__ list_len, uint32_t pfx0)
+                                                      uint32_t *__restrict__ list_len, uint32_t pfx0, int32_t rpb)
 {
-    // each row's record is built in LDS and written as 16-byte stores
-    __shared__ uint32_t srec[256][kPrefRec + 1];
-    uint32_t *R = srec[threadIdx.x];
+    static_assert(G == 1 || G == kPrefRec, "a lane per record word");
+    __shared__ uint32_t srec[256 / G][kPrefRec + 1];
+    __shared__ uint8_t scls[256];  // the classes of the workgroup's rows
+    uint32_t *rr = srec[threadIdx.x / G];
+    const int gl = threadIdx.x % G;
     const int lane = threadIdx.x & 63;
-    for (int64_t base = static_cast<int64_t>(blockIdx.x) * blockDim.x; base < I;
-         base += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        const int32_t i = static_cast<int32_t>(base + threadIdx.x);
-        uint32_t cls = kPrefClasses;
+    const int64_t block0 = static_cast<int64_t>(blockIdx.x) * rpb;
+    if constexpr (G == 1) {
+        const int64_t i = block0 + threadIdx.x;
         if (i < I) {
-            cls = pref_compile_row(row_off, i, term_off, n_terms, weight, preds, n_preds, L, present, wbase, prog,
-                                   prog_cap, prog_used, R, pfx0);
-            uint4 *dst = reinterpret_cast<uint4 *>(rec + static_cast<int64_t>(i) * kPrefRec);
+            scls[threadIdx.x] = static_cast<uint8_t>(
+                pref_compile_row(row_off, static_cast<int32_t>(i), term_off, n_terms, weight, preds, n_preds, L,
+                                 present, wbase, prog, prog_cap, prog_used, rr, pfx0));
+            uint4 *dst = reinterpret_cast<uint4 *>(rec + i * kPrefRec);
 #pragma unroll
             for (int k = 0; k < kPrefRec / 4; ++k)
-                dst[k] = make_uint4(R[4 * k], R[4 * k + 1], R[4 * k + 2], R[4 * k + 3]);
+                dst[k] = make_uint4(rr[4 * k], rr[4 * k + 1], rr[4 * k + 2], rr[4 * k + 3]);
+        } else {
+            scls[threadIdx.x] = kPrefClasses;
         }
-        // append i to its class list: one counter update per class and wavefront
-        for (uint32_t c = 0; c < kPrefClasses; ++c) {
-            const uint64_t mask = __ballot(cls == c);
-            if (mask == 0) continue;
-            const int leader = __builtin_ctzll(mask);
-            uint32_t off = 0;
-            if (lane == leader) off = atomicAdd(list_len + c, static_cast<uint32_t>(__popcll(mask)));
-            off = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(off), leader));
-            const uint32_t below = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
-                                                             __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
-            if (cls == c) list[static_cast<int64_t>(c) * I + off + below] = i;
+    } else
+    for (int32_t at = threadIdx.x / G; at < rpb; at += 256 / G) {
+        const int64_t i = block0 + at;
+        int64_t tb = 0, te = 0;
+        bool good = false;
+        if (i < I) {
+            good = pref_row_ok(row_off, i, n_terms);
+            tb = row_off[i];
+            te = row_off[i + 1];
         }
+        uint32_t cls = i < I ? 3u : kPrefClasses;  // (a bad row has no terms)
+        const GroupTerms g = group_terms<G>(tb, te, term_off, n_preds, good);
+        if (good && !g.fits && gl == 0)
+            cls = pref_compile_row(row_off, static_cast<int32_t>(i), term_off, n_terms, weight, preds, n_preds, L,
+                                   present, wbase, prog, prog_cap, prog_used, rr, pfx0);
+        // this lane's expression
+        pc_pred q{};
+        const uint64_t *pres = nullptr;
+        const uint32_t *wb = nullptr;
+        uint32_t cnt = 0;
+        bool neg = true, valid = false;
+        const bool mine = g.fits && gl < g.n;
+        if (mine) {
+            q = preds[g.first + gl];
+            valid = aff_valid(q, L);
+            if (valid) {
+                pres = present + static_cast<int64_t>(q.label) * 4;
+                wb = wbase + static_cast<int64_t>(q.label) * 4;
+                if (q.op == PC_OP_GT || q.op == PC_OP_LT) {
+                    cnt = cmp_count(q.op, static_cast<int64_t>(q.vals[0]), pres, neg);
+                } else {
+                    uint64_t sel[4];
+                    cnt = expr_clause(q.op, q.vals, pres, sel, neg);
+                }
+            }
+        }
+        // this lane's term
+        const uint32_t wt = g.fits && gl < g.nt ? weight[tb + gl] : 0u;
+        const uint32_t bad = group_bits<G>(mine && (!valid || (cnt == 0 && !neg)));
+        const bool term_ok = g.mask != 0 && !(bad & g.mask) && pref_weight_ok(wt);
+        const uint32_t live = group_bits<G>(term_ok);
+        const int term = group_term_of<G>(g);
+        const bool keep = mine && ((live >> term) & 1u);
+        uint32_t entries, sum;
+        const uint32_t e0 = group_scan<G>(keep ? cnt : 0u, entries);
+        group_scan<G>(term_ok ? wt : 0u, sum);
+        const uint32_t n = entries + __popc(live);
+        const uint32_t n_live = __popc(live);
+        // entries ahead of term gl (its first expression's), and in it
+        const uint32_t t0 = __shfl(e0, g.b & (G - 1), G);
+        const uint32_t after = __shfl(e0 + (keep ? cnt : 0u), (g.e - 1) & (G - 1), G);
+        const bool inl = n <= static_cast<uint32_t>(kPrefInlineWords);
+        const bool write = g.fits && n_live != 0;
+        unsigned long long off = 0;
+        if (write && !inl && gl == 0) off = atomicAdd(prog_used, static_cast<unsigned long long>(n));
+        off = __shfl(off, 0, G);
+        const bool room = static_cast<int64_t>(off) + n <= prog_cap;
+        uint32_t *out = inl ? rr + 2 : prog + off;
+        if (write && (inl || room)) {
+            if (term_ok) out[t0 + __popc(live & ((1u << gl) - 1))] = wt << kPrefLenBits | (after - t0);
+            if (keep && cnt) {
+                uint32_t k = e0 + __popc(live & ((2u << term) - 1));  // past its own term's header too
+                aff_entries(q, pres, wb, pfx0, neg, [&](uint32_t ent) { out[k++] = ent; });
+            }
+        }
+        if (gl == 0 && i < I && (g.fits || !good)) {
+            rr[0] = kPrefNone << 24;
+            if (write) {
+                const uint32_t head = n_live | bit_length(sum) << 16;
+                if (!inl && !room) {
+                    rr[0] = head | kPrefDecode << 24;
+                    cls = 2;
+                } else {
+                    rr[0] = head | (inl ? kPrefInline : kPrefIndirect) << 24;
+                    if (!inl) rr[1] = static_cast<uint32_t>(off);
+                    cls = n_live <= kPrefFewTerms ? 3u : (bit_length(sum) <= 8 ? 0u : 1u);
+                }
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (i < I) rec[i * kPrefRec + gl] = rr[gl];
+        __builtin_amdgcn_wave_barrier();
+        if (gl == 0) scls[at] = static_cast<uint8_t>(cls);
+    }
+    __syncthreads();
+    // append the rows to their class lists: one counter update per class and
+    // wavefront (one per four rows would keep the counters busy for 11 ns each)
+    const uint32_t cls = static_cast<int>(threadIdx.x) < rpb ? scls[threadIdx.x] : kPrefClasses;
+    for (uint32_t c = 0; c < kPrefClasses; ++c) {
+        const uint64_t mask = __ballot(cls == c);
+        if (mask == 0) continue;
+        const int leader = __builtin_ctzll(mask);
+        uint32_t off = 0;
+        if (lane == leader) off = atomicAdd(list_len + c, static_cast<uint32_t>(__popcll(mask)));
+        off = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(off), leader));
+        const uint32_t below = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
+        if (cls == c) list[static_cast<int64_t>(c) * I + off + below] = static_cast<int32_t>(block0 + threadIdx.x);
     }
 }
 
@@ -1638,12 +2044,21 @@ __global__ __launch_bounds__(256) void k_aff_prefix(const uint64_t *__restrict__
     for (int k = 0; k < 4; ++k) {
         uint64_t m = pres[k];
         if (k == 3) m &= ~(1ull << 63);  // the absent value has no prefix plane
-        while (m) {
-            const uint32_t v = static_cast<uint32_t>(k * 64 + __builtin_ctzll(m));
-            m &= m - 1;
-            const uint32_t pid = plane_id(pres, wb, v);
-            acc |= planes[static_cast<int64_t>(pid) * Wp + w];
-            planes[static_cast<int64_t>(pfx0 + pid) * Wp + w] = acc;
+        // the present values of one 64-value word have consecutive planes:
+        // eight loads in flight (one at a time: 31 us for 64 labels over 5,037
+        // nodes, now 10)
+        const int n = __popcll(m);
+        const uint64_t *in = planes + static_cast<int64_t>(wb[k]) * Wp + w;
+        uint64_t *out = planes + static_cast<int64_t>(pfx0 + wb[k]) * Wp + w;
+        for (int j0 = 0; j0 < n; j0 += 8) {
+            uint64_t x[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = j0 + j < n ? in[(j0 + j) * Wp] : 0ull;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                acc |= x[j];
+                if (j0 + j < n) out[(j0 + j) * Wp] = acc;
+            }
         }
     }
 }
@@ -1658,16 +2073,25 @@ int build_planes(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, int64
     if (L == 0) launch_fill_u32(reinterpret_cast<uint32_t *>(d_P), 1, 0, stream);
     PC_LAUNCH_CHECK(ctx);
     if (N > 0 && L > 0) {
-        // about 2048 workgroups: a few hundred nodes each
-        const int64_t ltiles = (L + 63) / 64;
-        int64_t chunk = (static_cast<int64_t>(N) * ltiles + 2047) / 2048;
-        chunk = chunk < 64 ? 64 : (chunk + 3) / 4 * 4;
-        while ((N + chunk - 1) / chunk > 65535) chunk *= 2;
-        dim3 gp((L + 63) / 64, static_cast<unsigned>((N + chunk - 1) / chunk));
-        PC_TIMED(ctx, "k_sel_presence", stream,
-                 hipLaunchKernelGGL(k_sel_presence, gp, dim3(256), 0, stream, labels, N, L, chunk,
-                                    reinterpret_cast<uint32_t *>(present)));
-        PC_LAUNCH_CHECK(ctx);
+        if (L <= kPresenceLdsL) {
+            const int64_t n_bytes = static_cast<int64_t>(N) * L;
+            const unsigned blocks = static_cast<unsigned>(std::min<int64_t>((n_bytes + (4 << 10) - 1) / (4 << 10), 1024));
+            PC_TIMED(ctx, "k_sel_presence", stream,
+                     hipLaunchKernelGGL(k_sel_presence_flat, dim3(blocks), dim3(256), static_cast<size_t>(L) * 32,
+                                        stream, labels, n_bytes, L, reinterpret_cast<uint32_t *>(present)));
+            PC_LAUNCH_CHECK(ctx);
+        } else {
+            // about 2048 workgroups: a few hundred nodes each
+            const int64_t ltiles = (L + 63) / 64;
+            int64_t chunk = (static_cast<int64_t>(N) * ltiles + 2047) / 2048;
+            chunk = chunk < 64 ? 64 : (chunk + 3) / 4 * 4;
+            while ((N + chunk - 1) / chunk > 65535) chunk *= 2;
+            dim3 gp((L + 63) / 64, static_cast<unsigned>((N + chunk - 1) / chunk));
+            PC_TIMED(ctx, "k_sel_presence", stream,
+                     hipLaunchKernelGGL(k_sel_presence, gp, dim3(256), 0, stream, labels, N, L, chunk,
+                                        reinterpret_cast<uint32_t *>(present)));
+            PC_LAUNCH_CHECK(ctx);
+        }
     }
     if (L > 0) {
         PC_TIMED(ctx, "k_sel_label_scan", stream,
@@ -1675,9 +2099,11 @@ int build_planes(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, int64
         PC_LAUNCH_CHECK(ctx);
     }
     if (N > 0 && L > 0) {
-        dim3 gb(static_cast<unsigned>(W), static_cast<unsigned>((L + 3) / 4));
+        dim3 gb(static_cast<unsigned>((W + kPlaneWords - 1) / kPlaneWords), static_cast<unsigned>((L + 3) / 4));
+        const bool wide = L % 4 == 0 && (reinterpret_cast<uintptr_t>(labels) & 3) == 0;
+        const auto kern = wide ? k_sel_planes<true> : k_sel_planes<false>;
         PC_TIMED(ctx, "k_sel_planes", stream,
-                 hipLaunchKernelGGL(k_sel_planes, gb, dim3(256), 0, stream, labels, N, L, present, wbase, planes, Wp));
+                 hipLaunchKernelGGL(kern, gb, dim3(256), 0, stream, labels, N, L, present, wbase, planes, Wp));
         PC_LAUNCH_CHECK(ctx);
     }
     return PC_OK;
@@ -1807,7 +2233,8 @@ int run_selectors(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, cons
     if (W == 0) launch_fill_u32(popcnt, static_cast<size_t>(I), 0, stream);
     rc = build_planes(ctx, labels, N, L, W, Wp, pmax, present, wbase, planes, d_P, stream);
     if (rc) return rc;
-    const unsigned rgrid = static_cast<unsigned>(std::min<int64_t>((I + 255) / 256, 8192));
+    constexpr int kRows = kCompThreads / kSelLanes;  // rows per workgroup
+    const unsigned rgrid = static_cast<unsigned>(std::min<int64_t>((I + kRows - 1) / kRows, 65536));
     PC_TIMED(ctx, "k_sel_compile", stream,
              hipLaunchKernelGGL(k_sel_compile, dim3(rgrid), dim3(256), 0, stream, pred_off, preds, n_preds, I, L,
                                 present, wbase, prog, rec, ctx->d_err));
@@ -1869,9 +2296,12 @@ int run_affinity(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, const
     if (rc) return rc;
     rc = build_prefix(ctx, L, Wp, pmax, present, wbase, planes, stream);
     if (rc) return rc;
-    const unsigned rgrid = static_cast<unsigned>(std::min<int64_t>((I + 255) / 256, 8192));
+    const bool groups = I < kAffGroupRows;
+    const int64_t rows = groups ? 256 / kAffLanes : 256;  // per workgroup
+    const unsigned rgrid = static_cast<unsigned>(std::min<int64_t>((I + rows - 1) / rows, 8192));
+    const auto kern = groups ? k_aff_compile<kAffLanes> : k_aff_compile<1>;
     PC_TIMED(ctx, "k_aff_compile", stream,
-             hipLaunchKernelGGL(k_aff_compile, dim3(rgrid), dim3(256), 0, stream, row_off, I, term_off, n_terms,
+             hipLaunchKernelGGL(kern, dim3(rgrid), dim3(256), 0, stream, row_off, I, term_off, n_terms,
                                 preds, n_preds, L, present, wbase, prog, prog_cap,
                                 prog_used, rec, unknown, static_cast<uint32_t>(pmax + 1)));
     PC_LAUNCH_CHECK(ctx);
@@ -1937,11 +2367,17 @@ int run_preferred(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, cons
     if (rc) return rc;
     rc = build_prefix(ctx, L, Wp, pmax, present, wbase, planes, stream);
     if (rc) return rc;
-    const unsigned rgrid = static_cast<unsigned>(std::min<int64_t>((I + 255) / 256, 8192));
+    // rows per workgroup: all 256 threads', or 16 at a time (up to 256, so that
+    // the class lists' counters are not updated too often)
+    const bool groups = I < kPrefGroupRows;
+    const int32_t rpb =
+        groups ? static_cast<int32_t>(std::min<int64_t>(256, std::max<int64_t>(16, I / 2048 / 16 * 16))) : 256;
+    const unsigned rgrid = static_cast<unsigned>((static_cast<int64_t>(I) + rpb - 1) / rpb);
+    const auto kern = groups ? k_pref_compile<kAffLanes> : k_pref_compile<1>;
     PC_TIMED(ctx, "k_pref_compile", stream,
-             hipLaunchKernelGGL(k_pref_compile, dim3(rgrid), dim3(256), 0, stream, row_off, I, term_off, n_terms,
+             hipLaunchKernelGGL(kern, dim3(rgrid), dim3(256), 0, stream, row_off, I, term_off, n_terms,
                                 weight, preds, n_preds, L, present, wbase, prog, prog_cap, prog_used, rec, list,
-                                list_len, static_cast<uint32_t>(pmax + 1)));
+                                list_len, static_cast<uint32_t>(pmax + 1), rpb));
     PC_LAUNCH_CHECK(ctx);
     if (W > 0) {
         const RowSplit sp = row_split(I, ntiles);

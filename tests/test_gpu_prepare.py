@@ -1,0 +1,100 @@
+"""Parity of the selector, affinity and preferred calls with the CPU oracle where their preparation kernels change
+form: label arrays of every alignment and of more labels than the presence table holds, labels of few and of
+many values, node counts at the edges of the plane builder's 1,024-node pieces, and rows at the edges of what a
+group of lanes compiles (terms, expressions, inline program words, row counts)."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def g():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import gpu_run
+    return gpu_run
+
+
+@pytest.mark.parametrize("N,L,shift", [(1, 1, 0), (1023, 3, 1), (1024, 4, 4), (1025, 5, 15), (2049, 64, 3),
+                                       (3000, 16, 8), (300, 1024, 2), (300, 1025, 0), (5037, 7, 0)])
+def test_label_layouts(g, orc, N, L, shift):
+    import torch
+    import paper_2602_16100_amd as pc
+    rng = np.random.default_rng(N)
+    cards = rng.choice([1, 2, 8, 9, 64, 65, 255], size=L)
+    labels = synth.gen_labels(rng, N, cards, 0.05)
+    off, preds = synth.gen_preds(rng, 300, cards, 0, 6, mmax=4)
+    flat = torch.zeros(N * L + shift, dtype=torch.uint8, device="cuda")
+    flat[shift:] = torch.from_numpy(labels.reshape(-1)).cuda()
+    f, p = pc.pc_eval_selectors(flat[shift:].view(N, L), g.dev(off), g.dev(preds))
+    torch.cuda.synchronize()
+    fo, po, _ = orc.selectors(labels, off, preds)
+    assert np.array_equal(f.cpu().numpy().view(np.uint64), fo)
+    assert np.array_equal(p.cpu().numpy().view(np.uint32), po)
+
+
+def _rows(rng, cards, counts):
+    """Affinity rows whose terms have the given expression counts (a list of lists)."""
+    row_off = np.concatenate([[0], np.cumsum([len(r) for r in counts])]).astype(np.int32)
+    k = np.array([x for r in counts for x in r], np.int64)
+    term_off = np.concatenate([[0], np.cumsum(k)]).astype(np.int32)
+    P = int(term_off[-1])
+    lab = rng.integers(0, len(cards), P)
+    op = rng.integers(0, 6, P)
+    preds = np.zeros(P, synth.PRED_DT)
+    preds["label"], preds["op"] = lab, op
+    vals = synth.distinct_values(rng, cards[lab], np.minimum(rng.integers(1, 5, P), cards[lab]), 4)
+    bm = synth.values_to_bitmap(vals)
+    bm[op > 1] = 0
+    thr = rng.integers(-1, cards[lab] + 1)
+    bm[op > 3, 0] = thr[op > 3].astype(np.int64).view(np.uint64)
+    preds["vals"] = bm
+    return row_off, term_off, preds
+
+
+@pytest.mark.parametrize("kind", ["terms", "expressions", "inline", "malformed"])
+def test_compiled_rows(g, orc, kind):
+    rng = np.random.default_rng(len(kind))
+    cards = rng.choice([2, 5, 16, 64], size=20)
+    labels = synth.gen_labels(rng, 700, cards, 0.1)
+    if kind == "terms":          # 0 to 18 terms, empty ones among them
+        counts = [[int(x) for x in rng.integers(0, 2, n)] for n in range(19) for _ in range(8)]
+    elif kind == "expressions":  # 14 to 18 expressions, and many
+        counts = [[1] * 2 + [n - 2] for n in list(range(14, 19)) + [40, 200] for _ in range(12)] + [[16], [17], [0, 16, 0]]
+    else:                        # programs around the inline sizes
+        counts = [[int(x) for x in rng.integers(1, 5, int(rng.integers(1, 4)))] for _ in range(900)]
+    row_off, term_off, preds = _rows(rng, cards, counts)
+    weight = rng.integers(1, 101, term_off.shape[0] - 1).astype(np.uint32)
+    if kind == "malformed":
+        at = rng.integers(0, preds.shape[0], 60)
+        preds["op"][at[:20]], preds["label"][at[20:40]], preds["rsv1"][at[40:]] = 9, 20, 1
+        weight[rng.integers(0, weight.shape[0], 40)] = [0, 101] * 20
+        term_off = term_off.copy()
+        term_off[rng.integers(1, term_off.shape[0] - 1, 12)] += 7
+        row_off = row_off.copy()
+        row_off[rng.integers(1, row_off.shape[0] - 1, 6)] += 5
+    fg, pg, ug, eg = g.affinity(labels, row_off, term_off, preds)
+    fo, po, uo, eo = orc.affinity(labels, row_off, term_off, preds)
+    assert np.array_equal(fg, fo) and np.array_equal(pg, po) and np.array_equal(ug, uo) and eg == eo
+    bg, sg, cg, eg = g.preferred(labels, row_off, term_off, weight, preds)
+    bo, so, co, eo = orc.preferred(labels, row_off, term_off, weight, preds)
+    assert np.array_equal(bg, bo) and np.array_equal(sg, so) and np.array_equal(cg, co) and eg == eo
+
+
+@pytest.mark.parametrize("I", [65535, 65536, 131071, 131072])
+def test_row_counts_at_the_compile_rules(g, orc, I):
+    rng = np.random.default_rng(I)
+    cards = rng.choice([2, 4, 16], size=8)
+    labels = synth.gen_labels(rng, 100, cards, 0.1)
+    row_off, term_off, preds = synth.gen_affinity(rng, I, cards, 0, 3, 1, 3)
+    weight = rng.integers(1, 101, term_off.shape[0] - 1).astype(np.uint32)
+    fg, pg, ug, eg = g.affinity(labels, row_off, term_off, preds)
+    fo, po, uo, eo = orc.affinity(labels, row_off, term_off, preds)
+    assert np.array_equal(fg, fo) and np.array_equal(pg, po) and np.array_equal(ug, uo) and eg == eo
+    bg, sg, cg, eg = g.preferred(labels, row_off, term_off, weight, preds)
+    bo, so, co, eo = orc.preferred(labels, row_off, term_off, weight, preds)
+    assert np.array_equal(bg, bo) and np.array_equal(sg, so) and np.array_equal(cg, co) and eg == eo
