@@ -38,7 +38,7 @@
 //            own share of the list, grouped by port.
 //   tail   : once few traces are left in flight, one workgroup per trace
 //            walks it to its end, reading only the chunk-set words its
-//            header selects.
+//            header selects, and skipping whole turns of a loop.
 #include <stdlib.h>
 
 #include <algorithm>
@@ -133,16 +133,46 @@ __global__ void k_tr_port_check(int64_t n_ports, const int32_t *__restrict__ por
     if (bad) atomicOr(d_err, PC_DERR_SWITCH);
 }
 
+// What a lookup at a switch starts from, in one 32-byte record.
+struct __align__(32) SwInfo {
+    int32_t G;      // 32-rule groups
+    int32_t gofs;   // the first one's place in the chunk sets
+    uint32_t cpos;  // filter chunks
+    int32_t rb;     // first rule
+    int32_t pb;     // first port
+    int32_t np;     // ports, -1 when the port range is invalid
+    int32_t pad[2];
+};
+
 // Per port: its peer and the peer's jurisdiction bit (0 unless the peer is a
-// switch), read by the match with one load per port.
-__global__ void k_tr_port_info(int64_t n_ports, const int32_t *__restrict__ port_peer, int32_t S,
-                               const uint8_t *__restrict__ jur, int2 *__restrict__ pinfo)
+// switch), read by the match and the walk with one load per port; per
+// switch: its record.
+__global__ void k_tr_port_info(int64_t n_ports, const int32_t *__restrict__ port_off,
+                               const int32_t *__restrict__ port_peer, int32_t S, const uint8_t *__restrict__ jur,
+                               const int32_t *__restrict__ rule_off, const int32_t *__restrict__ gcount,
+                               const int32_t *__restrict__ gofs, const uint32_t *__restrict__ cpos,
+                               int2 *__restrict__ pinfo, SwInfo *__restrict__ sinfo)
 {
-    for (int64_t p = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; p < n_ports;
+    const int64_t tot = n_ports > S ? n_ports : S;
+    for (int64_t p = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; p < tot;
          p += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        const int32_t v = port_peer[p];
-        const uint32_t j = v >= 0 && v < S ? jur[v] : 32u;
-        pinfo[p] = make_int2(v, j < 32 ? static_cast<int32_t>(1u << j) : 0);
+        if (p < n_ports) {
+            const int32_t v = port_peer[p];
+            const uint32_t j = v >= 0 && v < S ? jur[v] : 32u;
+            pinfo[p] = make_int2(v, j < 32 ? static_cast<int32_t>(1u << j) : 0);
+        }
+        if (p < S) {
+            const int64_t pb = port_off[p], pe = port_off[p + 1];
+            SwInfo x;
+            x.G = gcount[p];
+            x.gofs = gofs[p];
+            x.cpos = cpos[p];
+            x.rb = rule_off[p];
+            x.pb = static_cast<int32_t>(pb);
+            x.np = pc_range_ok(pb, pe, n_ports) ? static_cast<int32_t>(pe - pb) : -1;
+            x.pad[0] = x.pad[1] = 0;
+            sinfo[p] = x;
+        }
     }
 }
 
@@ -579,16 +609,6 @@ __device__ __forceinline__ int apply_key(int32_t S, int32_t ttl, int64_t np, con
     return -1;
 }
 
-// The same, with switch s's ports read from port_off / port_peer.
-__device__ __forceinline__ int apply_rule(int32_t S, const int32_t *__restrict__ port_off,
-                                          const int32_t *__restrict__ port_peer, int64_t n_ports, int32_t ttl,
-                                          int32_t s, uint64_t key, int32_t hops, int32_t *next, uint16_t *port)
-{
-    const int64_t pb = port_off[s], pe = port_off[s + 1];
-    const int64_t np = pc_range_ok(pb, pe, n_ports) ? pe - pb : -1;
-    return apply_key(S, ttl, np, [&](uint32_t a) { return port_peer[pb + a]; }, key, hops, next, port);
-}
-
 __device__ __forceinline__ void write_out(pc_trace_out *out, int32_t t, uint32_t jm, int32_t s, uint16_t port,
                                           int32_t hops, int state)
 {
@@ -605,10 +625,8 @@ __device__ __forceinline__ void write_out(pc_trace_out *out, int32_t t, uint32_t
 struct Level {
     int32_t S;
     int32_t T;              // capacity of the live list
-    const int32_t *port_off;
     const int32_t *port_peer;
     const int2 *pinfo;      // per port: (peer, the peer's jurisdiction bit)
-    int64_t n_ports;
     const uint8_t *jur;
     int32_t ttl;
     int32_t hops;           // hops every trace of this level has made (the level's index)
@@ -786,10 +804,9 @@ __device__ __forceinline__ void filter_quad(const uint32_t (&x)[kChunks][4], con
 // lookups of its bucket).  Items are dealt to XCDs in contiguous ranges, so
 // the chunks of one switch share an L2.
 __global__ __launch_bounds__(kMatchThreads, 4) void k_tr_match(
-    int32_t S, const int32_t *__restrict__ rule_off, const pc_rule *__restrict__ rules,
-    const int32_t *__restrict__ gcount, const int32_t *__restrict__ gofs, const uint32_t *__restrict__ filt,
+    int32_t S, const SwInfo *__restrict__ sinfo, const pc_rule *__restrict__ rules, const uint32_t *__restrict__ filt,
     const int32_t *__restrict__ boff, const int32_t *__restrict__ ioff, const int2 *__restrict__ imap,
-    const BRec *__restrict__ bucket, const uint32_t *__restrict__ cpos, Level lv)
+    const BRec *__restrict__ bucket, Level lv)
 {
     __shared__ uint64_t best[kMaxChunk];
     __shared__ __align__(16) uint32_t cidx[kChunks][kMaxChunk];  // each lookup's values of the switch's filter chunks
@@ -818,18 +835,20 @@ __global__ __launch_bounds__(kMatchThreads, 4) void k_tr_match(
     const int2 im = imap[item];
     const int32_t s = im.x;
     if (static_cast<uint32_t>(s) >= static_cast<uint32_t>(S)) return;
-    const int32_t chunk = item_lookups(gcount[s], boff[s + 1] - boff[s]);
-    const int32_t bb = boff[s] + im.y * chunk;
-    const int32_t tn = min(chunk, min(boff[s + 1], lv.T) - bb);  // bucket holds at most T entries
+    const SwInfo si = sinfo[s];
+    const int32_t b0 = boff[s], b1 = boff[s + 1];
+    const int32_t chunk = item_lookups(si.G, b1 - b0);
+    const int32_t bb = b0 + im.y * chunk;
+    const int32_t tn = min(chunk, min(b1, lv.T) - bb);  // bucket holds at most T entries
     if (tn <= 0) return;
     const int32_t tn4 = (tn + 3) & ~3;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int32_t G = gcount[s];
-    const int64_t rb = rule_off[s];
-    const uint32_t *fs = filt + static_cast<int64_t>(gofs[s]) * kPlaneWords;
+    const int32_t G = si.G;
+    const int64_t rb = si.rb;
+    const uint32_t *fs = filt + static_cast<int64_t>(si.gofs) * kPlaneWords;
     const int32_t nslices = max(1, (G + kSliceGroups - 1) / kSliceGroups);
-    const uint32_t cp = cpos[s];
+    const uint32_t cp = si.cpos;
     uint2 *q = queue[wave];
     // A table of fewer than kSliceGroups groups fills gws wavefronts; the
     // workgroup's other wavefronts take further shares of the lookups: wave
@@ -843,8 +862,7 @@ __global__ __launch_bounds__(kMatchThreads, 4) void k_tr_match(
     const int32_t jb = st < streams ? min(tn4, 4 * st * per_stream) : tn4;
     const int32_t je = st < streams ? min(tn4, 4 * (st + 1) * per_stream) : tn4;
     // the switch's ports (np < 0: its port range is invalid)
-    const int64_t pb = lv.port_off[s], pe = lv.port_off[s + 1];
-    const int64_t np = pc_range_ok(pb, pe, lv.n_ports) ? pe - pb : -1;
+    const int64_t pb = si.pb, np = si.np;
     // A lane's chunk sets of group g: buffer loads with the lane's group as
     // the vector offset (clamped into the table) and the plane as a scalar
     // offset; an opaque copy of the plane stride keeps the 96 offsets from
@@ -1060,53 +1078,85 @@ __global__ __launch_bounds__(kMatchThreads, 4) void k_tr_match(
 // Sparse tail: one workgroup per trace still in flight walks it to its end,
 // filtering each switch's rule groups with only the kChunks chunk-set words
 // its header selects (coalesced over groups) and reducing the first match in
-// LDS.
-__global__ __launch_bounds__(256) void k_tr_walk(int32_t S, const int32_t *__restrict__ port_off,
-                                                 const int32_t *__restrict__ port_peer, int64_t n_ports,
-                                                 const uint8_t *__restrict__ jur, const int32_t *__restrict__ rule_off,
-                                                 const pc_rule *__restrict__ rules, const int32_t *__restrict__ gcount,
-                                                 const int32_t *__restrict__ gofs, const uint32_t *__restrict__ filt,
+// LDS.  Bound by the latency of a hop: the switch's record, its ports
+// together with the chunk-set words of two groups per lane, the survivors'
+// rules.  Where 5,200 of 500,009 traces loop until a TTL of 32, 329 us with a hop
+// per link, now 46; 6,001 traces over 777 rules per switch 54 us, now 22.
+__global__ __launch_bounds__(256) void k_tr_walk(int32_t S, const SwInfo *__restrict__ sinfo,
+                                                 const int2 *__restrict__ pinfo, const uint8_t *__restrict__ jur,
+                                                 const pc_rule *__restrict__ rules, const uint32_t *__restrict__ filt,
                                                  int32_t ttl,
                                                  const LRec *__restrict__ live, const int32_t *__restrict__ len,
                                                  int32_t hops0, pc_trace_out *__restrict__ out,
                                                  const int32_t *__restrict__ watch, int32_t K,
                                                  uint32_t *__restrict__ visit, uint64_t *__restrict__ vsum,
-                                                 int32_t *__restrict__ walk, const uint32_t *__restrict__ cpos)
+                                                 int32_t *__restrict__ walk)
 {
     __shared__ unsigned long long best;
     const int32_t n = *len;
-    for (int32_t i = blockIdx.x; i < n; i += gridDim.x) {
-        const LRec e = live[i];
-        if (e.next < 0 || e.next >= S) continue;  // the slot of a trace that has ended
+    const int lane = threadIdx.x & 63;
+    // Every gridDim-th entry is this workgroup's, 64 of them looked at
+    // together (most are the slots of traces that have ended).
+    const int64_t grid = gridDim.x;
+    for (int64_t i0 = blockIdx.x; i0 < n; i0 += 64 * grid) {
+    const int64_t il = i0 + lane * grid;
+    const int32_t at = il < n ? live[il].next : -1;
+    uint64_t flying = __ballot(at >= 0 && at < S);
+    while (flying) {
+        const LRec e = live[i0 + __builtin_ctzll(flying) * grid];
+        flying &= flying - 1;
         const int32_t t = e.t;
         const pc_key h = e.key;
-        int32_t s = e.next;
+        int32_t s = __builtin_amdgcn_readfirstlane(e.next);
         uint32_t jm = e.jm;
         uint32_t vis = visit ? visit[t] : 0u;
         uint64_t vs = vsum ? vsum[t] : 0ull;
         int32_t hops = hops0;
+        // A walk is a function of the switch (its header does not change): once
+        // a switch comes again, the walk repeats until its TTL, and whole
+        // turns of the cycle are skipped, their switches being in every mask
+        // already.  The switch two hops back finds the ping-pong of two
+        // switches at once, an anchor that moves on at doubled distances
+        // (Brent) any other cycle.
+        int32_t back1 = -1, back2 = -1, anchor = s, anchor_hops = hops, span = 1;
         for (;;) {
             if (threadIdx.x == 0) best = kNoMatch;
             __syncthreads();
-            const int32_t G = gcount[s];
-            const uint32_t *fs = filt + static_cast<int64_t>(gofs[s]) * kPlaneWords;
-            const int64_t rb = rule_off[s];
-            const uint32_t cp = cpos[s];
-            uint32_t x[kChunks];
+            const SwInfo si = sinfo[s];
+            const int32_t G = si.G;
+            const uint32_t *fs = filt + static_cast<int64_t>(si.gofs) * kPlaneWords;
+            const pc_rule *rs = rules + si.rb;
+            // this lane's of the switch's first 64 ports
+            const int2 port_lane = lane < si.np ? pinfo[si.pb + lane] : make_int2(-2, 0);
+            int64_t row[kChunks];
 #pragma unroll
-            for (int c = 0; c < kChunks; ++c) x[c] = key_nibble(h.w[0], h.w[1], h.w[2], h.w[3], chunk_pos(cp, c));
-            for (int32_t g = threadIdx.x; g < G; g += blockDim.x) {
-                uint32_t surv = ~0u;
+            for (int c = 0; c < kChunks; ++c)
+                row[c] = static_cast<int64_t>(c * 16 + key_nibble(h.w[0], h.w[1], h.w[2], h.w[3], chunk_pos(si.cpos, c))) * G;
+            for (int32_t g = threadIdx.x; g < G; g += 2 * blockDim.x) {
+                const int32_t g2 = g + static_cast<int32_t>(blockDim.x);
+                uint32_t surv = ~0u, surv2 = g2 < G ? ~0u : 0u;
 #pragma unroll
-                for (int c = 0; c < kChunks; ++c) surv &= fs[static_cast<int64_t>(c * 16 + x[c]) * G + g];
-                if (surv) verify_group(surv, rules + rb + static_cast<int64_t>(g) * 32, static_cast<uint32_t>(g) * 32, h,
-                                       &best);
+                for (int c = 0; c < kChunks; ++c) {
+                    surv &= fs[row[c] + g];
+                    surv2 &= fs[row[c] + min(g2, G - 1)];
+                }
+                if (surv) verify_group(surv, rs + static_cast<int64_t>(g) * 32, static_cast<uint32_t>(g) * 32, h, &best);
+                if (surv2)
+                    verify_group(surv2, rs + static_cast<int64_t>(g2) * 32, static_cast<uint32_t>(g2) * 32, h, &best);
             }
             __syncthreads();
             const uint64_t key = best;
             int32_t next = -1;
+            uint32_t jb = 0;
             uint16_t port = PC_NO_PORT;
-            const int state = apply_rule(S, port_off, port_peer, n_ports, ttl, s, key, hops, &next, &port);
+            const int state = apply_key(S, ttl, si.np, [&](uint32_t a) {
+                const uint32_t ua = __builtin_amdgcn_readfirstlane(a);
+                const int2 p = ua < 64 ? make_int2(__builtin_amdgcn_readlane(port_lane.x, static_cast<int>(ua)),
+                                                   __builtin_amdgcn_readlane(port_lane.y, static_cast<int>(ua)))
+                                       : pinfo[si.pb + static_cast<int64_t>(ua)];
+                jb = static_cast<uint32_t>(p.y);
+                return p.x;
+            }, key, hops, &next, &port);
             __syncthreads();  // everyone has read `best` before it is reset
             if (state >= 0) {
                 if (threadIdx.x == 0) {
@@ -1116,13 +1166,26 @@ __global__ __launch_bounds__(256) void k_tr_walk(int32_t S, const int32_t *__res
                 }
                 break;
             }
-            s = next;
+            back2 = back1;
+            back1 = s;
+            s = __builtin_amdgcn_readfirstlane(next);
             hops += 1;
-            jm |= jur_bit(jur, s);
+            jm |= jb;
             if (visit) vis |= watch_bits(watch, K, t, s);
             if (vsum) vs |= sum_bit(s);
             if (walk && hops < kWalkSlots && threadIdx.x == 0) walk[static_cast<int64_t>(t) * kWalkSlots + hops] = s;
+            const int32_t period = s == back2 ? 2 : s == anchor ? hops - anchor_hops : 0;
+            if (period > 0 && !(walk && hops < kWalkSlots)) {
+                hops += (ttl - hops) / period * period;  // (hops <= ttl: a forward at hops == ttl has ended the walk)
+                back2 = anchor = -1;                      // less than a turn is left
+                span = INT32_MAX;
+            } else if (hops - anchor_hops >= span) {
+                anchor = s;
+                anchor_hops = hops;
+                span = span < (1 << 20) ? 2 * span : span;
+            }
         }
+    }
     }
 }
 
@@ -1304,6 +1367,7 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         BRec *bucket;
         LRec *live0, *live1;
         int2 *pinfo, *imap;
+        SwInfo *sinfo;
         uint32_t *filt, *cpos, *hh;
     } B;
     // work items of a level: at most T / kItemCap + S (see the match launch)
@@ -1323,6 +1387,7 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         B.live1 = c.take<LRec>(T + 1);
         B.bucket = c.take<BRec>(T + 1);
         B.pinfo = c.take<int2>(static_cast<size_t>(n_ports) + 1);
+        B.sinfo = c.take<SwInfo>(static_cast<size_t>(S) + 1);
         B.imap = c.take<int2>(static_cast<size_t>(icap));
     };
     Carver dry{nullptr, 0};
@@ -1376,13 +1441,9 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         }
     }
     if (T == 0) return PC_OK;
-    // the tail walk's workgroup: about two rule groups per lane of a mean
-    // table (64-256 threads; 256 when the table sizes are not at hand)
-    int walk_threads = 256;
-    if (pre == nullptr && S > 0) {
-        const int64_t mean_groups = ctx->h_small[0] / S;
-        walk_threads = mean_groups <= 128 ? 64 : mean_groups <= 256 ? 128 : 256;
-    }
+    // the tail walk's workgroup: about two rule groups per lane of a mean table
+    const int64_t mean_groups = S > 0 ? (pre != nullptr ? pre->groups : ctx->h_small[0]) / S : 0;
+    const int walk_threads = mean_groups <= 128 ? 64 : mean_groups <= 256 ? 128 : 256;
     if (visit && K > 0) {
         PC_TIMED(ctx, "k_tr_watch_check", stream,
                  hipLaunchKernelGGL(k_tr_port_check, dim3(grid_for(static_cast<int64_t>(T) * K, 256)), dim3(256), 0,
@@ -1390,10 +1451,12 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         PC_LAUNCH_CHECK(ctx);
     }
     if (!visit) K = 0;
-    if (n_ports > 0) {
+    if (std::max<int64_t>(n_ports, S) > 0) {
+        const int64_t n_info = std::max<int64_t>(n_ports, S);
         PC_TIMED(ctx, "k_tr_port_info", stream,
-                 hipLaunchKernelGGL(k_tr_port_info, dim3(static_cast<unsigned>(std::min<int64_t>((n_ports + 255) / 256, 4096))),
-                                    dim3(256), 0, stream, n_ports, port_peer, S, jur, B.pinfo));
+                 hipLaunchKernelGGL(k_tr_port_info, dim3(static_cast<unsigned>(std::min<int64_t>((n_info + 255) / 256, 4096))),
+                                    dim3(256), 0, stream, n_ports, port_off, port_peer, S, jur, rule_off, B.gcount,
+                                    B.gofs, B.cpos, B.pinfo, B.sinfo));
         PC_LAUNCH_CHECK(ctx);
     }
 
@@ -1420,9 +1483,15 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
     LRec *live_cur = B.live0, *live_nxt = B.live1;
     int32_t *cnt_cur = B.counts0, *cnt_nxt = B.counts1;
     int32_t *n_cur = d_n, *n_nxt = d_n + 1;
-    // Levels with few traces in flight are cheaper as independent walks than
-    // as bucketed passes (tunable with PC_TRACE_WALK_MAX, 0 = never walk).
-    int64_t walk_max = 8192;
+    // Levels with few traces in flight are cheaper as independent walks than as
+    // bucketed passes (tunable with PC_TRACE_WALK_MAX, 0 = never walk): a walk
+    // skips its loops, a level costs three launches and a pass over its
+    // tables.  Large tables make a walk's hop dearer (24 bytes per 32 rules).
+    // Calls that walk from the start / from 8,192 traces on: 60,000 traces over
+    // 512 rules per switch (k = 16) 231 / 258 us, over 2,048 (k = 32) 275 / 302,
+    // over 32,768 (k = 16) 908 / 835, 30,000 traces there 527 / 803; 4,194,304
+    // traces, of which 8,900 loop until their TTL, 2.4 / 3.2 ms.
+    int64_t walk_max = mean_groups <= 128 ? 65536 : 32768;
     if (const char *env = getenv("PC_TRACE_WALK_MAX")) walk_max = atoll(env);
     // The host does not wait for a level before queueing the next one: live
     // counts only shrink, so level L is launched with the latest count the
@@ -1447,9 +1516,9 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         if (known <= walk_max) {
             const unsigned wb = static_cast<unsigned>(known < 8192 ? known : 8192);
             PC_TIMED(ctx, "k_tr_walk", stream,
-                     hipLaunchKernelGGL(k_tr_walk, dim3(wb), dim3(walk_threads), 0, stream, S, port_off, port_peer, n_ports, jur,
-                                        rule_off, rules, B.gcount, B.gofs, B.filt, ttl, live_cur, len_cur, level,
-                                        out, watch, K, visit, vsum, walk, B.cpos));
+                     hipLaunchKernelGGL(k_tr_walk, dim3(wb), dim3(walk_threads), 0, stream, S, B.sinfo, B.pinfo, jur,
+                                        rules, B.filt, ttl, live_cur, len_cur, level, out, watch, K, visit, vsum,
+                                        walk));
             PC_LAUNCH_CHECK(ctx);
             break;
         }
@@ -1460,14 +1529,14 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         PC_TIMED(ctx, "k_tr_scatter", stream,
                  hipLaunchKernelGGL(k_tr_scatter, dim3(grid_for(nlive, 256)), dim3(256), 0, stream, live_cur, len_cur,
                                     T, S, B.boff, B.bucket, B.ioff, B.imap, icap));
-        const Level lv{S,        T,     port_off, port_peer, B.pinfo, n_ports, jur,   ttl,  level,
-                       live_nxt, n_nxt, cnt_nxt,  out,       watch,   K,       visit, vsum, walk};
+        const Level lv{S,        T,     port_peer, B.pinfo, jur,   ttl, level, live_nxt, n_nxt,
+                       cnt_nxt, out,   watch,     K,       visit, vsum, walk};
         // at most nlive / kItemCap + S items: a switch of n lookups takes ceil(n / cap) items with cap >= kItemCap
         const int64_t max_items = std::min<int64_t>(static_cast<int64_t>(nlive) / kItemCap + S, nlive);
         PC_TIMED(ctx, "k_tr_match", stream,
                  hipLaunchKernelGGL(k_tr_match, dim3(static_cast<unsigned>(8 * ((max_items + 7) / 8))),
-                                    dim3(kMatchThreads), 0, stream, S, rule_off, rules, B.gcount, B.gofs, B.filt,
-                                    B.boff, B.ioff, B.imap, B.bucket, B.cpos, lv));
+                                    dim3(kMatchThreads), 0, stream, S, B.sinfo, rules, B.filt, B.boff, B.ioff,
+                                    B.imap, B.bucket, lv));
         PC_LAUNCH_CHECK(ctx);
         // the count leaving this level
         const int slot = (level + 1) & 1;
@@ -1581,7 +1650,8 @@ int run_trace_delta(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32
         if (rc) return rc;
         if (T == 0) return PC_OK;
         const TcMeta m = tc_meta(ctx, S);
-        const TracePrep pre{reinterpret_cast<const uint32_t *>(ctx->tc_filt), m.gcount, m.gofs, m.cpos};
+        const TracePrep pre{reinterpret_cast<const uint32_t *>(ctx->tc_filt), m.gcount, m.gofs, m.cpos,
+                            ctx->tc_groups};
         return run_trace(ctx, S, port_off, port_peer, n_ports, jur, rule_off, rules, n_rules, hdr, ingress, T, ttl,
                          nullptr, 0, out, nullptr, vsum, walk, stream, &pre);
     }
@@ -1668,7 +1738,8 @@ int run_trace_delta(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32
                                     ingress, hdr_c, ing_c));
         PC_LAUNCH_CHECK(ctx);
         const TcMeta m = tc_meta(ctx, S);
-        const TracePrep pre{reinterpret_cast<const uint32_t *>(ctx->tc_filt), m.gcount, m.gofs, m.cpos};
+        const TracePrep pre{reinterpret_cast<const uint32_t *>(ctx->tc_filt), m.gcount, m.gofs, m.cpos,
+                            ctx->tc_groups};
         rc = run_trace(ctx, S, port_off, port_peer, n_ports, jur, rule_off, rules, n_rules, hdr_c, ing_c, n, ttl,
                        nullptr, 0, out_c, nullptr, vsum_c, walk ? walk_c : nullptr, stream, &pre);
         if (rc) return rc;

@@ -266,3 +266,49 @@ def test_reach_via_leg_direction(g, orc, kind):
     do, _ = orc.reach_via(wl["V"], adj_off, adj, wl["region"], wl["src"], wl["allowed"], wl["target"], via, forbid)
     _same(dg, do, "reach_via")
     assert (do >= 0).sum() > 5
+
+
+@pytest.mark.parametrize("ttl", [0, 1, 2, 7, 8, 9, 31, 64, 254, 255])
+def test_trace_loops_of_every_length(g, orc, ttl):
+    """Rings of 1 to 13 switches (a switch may forward to itself), entered through lines of 0 to 6 switches:
+    records, visit words, visited-switch summaries and walk records of traces that loop until their TTL."""
+    import torch
+    import paper_2602_16100_amd as pc
+    peer, start = [], []
+    for ring in range(1, 14):
+        for line in range(7):
+            first = len(peer)
+            start.append(first)
+            peer += [first + i + 1 for i in range(line)]
+            peer += [first + line + (i + 1) % ring for i in range(ring)]
+    S = len(peer)
+    port_off = np.arange(S + 1, dtype=np.int32)
+    jur = (np.arange(S) % 31).astype(np.uint8)
+    rules = np.zeros(S, synth.RULE_DT)  # one rule a switch: every header, out of its only port
+    T = 3 * len(start)
+    ingress = np.repeat(start, 3).astype(np.int32) + np.tile([0, 1, 2], len(start)).astype(np.int32)
+    ingress = np.minimum(ingress, S - 1)
+    hdr = synth.random_keys(np.random.default_rng(1), T)
+    watch = (ingress[:, None] + np.arange(8)[None, :] * 2 - 2).astype(np.int32)
+    watch[(watch < 0) | (watch >= S)] = -1
+    args = (S, port_off, np.array(peer, np.int32), jur, port_off, rules, hdr, ingress, ttl)
+    to, vo, so, wo, _ = orc.trace(*args, watch=watch, summary=True)
+    tg, vg = g.trace_watch(*args, watch)
+    assert np.array_equal(tg, to) and np.array_equal(vg, vo)
+    d = lambda a: pc.to_device(a, "cuda")  # noqa: E731
+    out = torch.zeros((T, 12), dtype=torch.uint8, device="cuda")
+    vsum = torch.zeros(T, dtype=torch.int64, device="cuda")
+    walk = torch.full((T, 8), -5, dtype=torch.int32, device="cuda")
+    pc.pc_trace_flows_delta(S, d(port_off), d(args[2]), d(jur), d(port_off), d(rules), d(hdr), d(ingress), ttl, out,
+                            vsum, walk=walk, ctx=pc.Context(0))
+    torch.cuda.synchronize()
+    assert np.array_equal(pc.records(out, pc.TRACE_OUT_DT), to)
+    assert np.array_equal(vsum.cpu().numpy().view(np.uint64), so) and np.array_equal(walk.cpu().numpy(), wo)
+
+
+def test_walks_from_a_long_list(g, orc, monkeypatch):
+    """The walk takes over after a level whose list is many times longer than its grid, most of its slots ended."""
+    monkeypatch.setenv("PC_TRACE_WALK_MAX", "70000")
+    wl = synth.trace_workload(7, 8, 4, 256, 600_000, 16, 20_000)
+    a = (wl["S"], wl["port_off"], wl["port_peer"], wl["jur"], wl["rule_off"], wl["rules"], wl["hdr"], wl["ingress"], 16)
+    assert np.array_equal(g.trace(*a), orc.trace(*a)[0])
