@@ -64,6 +64,9 @@ static_assert(kItemCap % 4 == 0 && kItemCap <= kChunk, "an item holds >= kItemCa
 static_assert(kChunk % 4 == 0 && kMaxChunk % kChunk == 0 && kMaxChunk <= kMatchThreads,
               "one epilogue thread per lookup");
 constexpr int kCountPad = 32;  // live-trace counters are 128 bytes apart: contended atomics on one line serialise
+constexpr int32_t kDirectRules = 1024;               // mean rules per switch that a walk may match one by one,
+constexpr int64_t kDirectWork = 5000000;             // traces times mean rules
+constexpr int64_t kDirectWorst = int64_t(1) << 26;   // and traces times all rules
 constexpr int kPortSlots = 64;  // forwarding ports whose moves a match workgroup counts in LDS
 
 // 16 chunk-value sets of one 4-bit chunk, kept in VGPRs; indexed with a
@@ -121,69 +124,88 @@ __global__ void k_tr_switch_info(int32_t S, const int32_t *__restrict__ port_off
     if (errs) atomicOr(d_err, errs);
 }
 
-__global__ void k_tr_port_check(int64_t n_ports, const int32_t *__restrict__ port_peer, int32_t S,
-                                uint32_t *__restrict__ d_err)
-{
-    bool bad = false;
-    for (int64_t p = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; p < n_ports;
-         p += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        const int32_t v = port_peer[p];
-        bad |= (v < -1 || v >= S);
-    }
-    if (bad) atomicOr(d_err, PC_DERR_SWITCH);
-}
-
 // What a lookup at a switch starts from, in one 32-byte record.
 struct __align__(32) SwInfo {
-    int32_t G;      // 32-rule groups
-    int32_t gofs;   // the first one's place in the chunk sets
-    uint32_t cpos;  // filter chunks
-    int32_t rb;     // first rule
-    int32_t pb;     // first port
-    int32_t np;     // ports, -1 when the port range is invalid
-    int32_t pad[2];
+    int32_t G;        // 32-rule groups
+    int32_t gofs;     // the first one's place in the chunk sets
+    uint32_t cpos;    // filter chunks
+    int32_t rb;       // first rule
+    int32_t pb;       // first port
+    int32_t np;       // ports, -1 when the port range is invalid
+    int32_t R;        // rules
+    int32_t indexed;  // 0: the switch has no chunk sets, its rules are matched one by one
 };
 
-// Per port: its peer and the peer's jurisdiction bit (0 unless the peer is a
-// switch), read by the match and the walk with one load per port; per
-// switch: its record.
+__device__ __forceinline__ SwInfo make_info(int32_t s, const int32_t *__restrict__ port_off, int64_t n_ports,
+                                            const int32_t *__restrict__ rule_off, int64_t n_rules, int32_t gofs,
+                                            uint32_t cpos, bool indexed)
+{
+    const int64_t pb = port_off[s], pe = port_off[s + 1], rb = rule_off[s], re = rule_off[s + 1];
+    const bool rok = pc_range_ok(rb, re, n_rules);
+    SwInfo x;
+    x.R = rok ? static_cast<int32_t>(re - rb) : 0;
+    x.G = rok ? static_cast<int32_t>((re - rb + 31) / 32) : 0;
+    x.gofs = gofs;
+    x.cpos = cpos;
+    x.rb = rok ? static_cast<int32_t>(rb) : 0;
+    x.pb = static_cast<int32_t>(pb);
+    x.np = pc_range_ok(pb, pe, n_ports) ? static_cast<int32_t>(pe - pb) : -1;
+    x.indexed = indexed;
+    return x;
+}
+
+// A port's peer and the peer's jurisdiction bit (0 unless the peer is a switch).
+__device__ __forceinline__ int2 make_port(int32_t peer, int32_t S, const uint8_t *__restrict__ jur)
+{
+    const uint32_t j = peer >= 0 && peer < S ? jur[peer] : 32u;
+    return make_int2(peer, j < 32 ? static_cast<int32_t>(1u << j) : 0);
+}
+
+// Per port and per switch the records above, of tables prepared by an
+// earlier call.
 __global__ void k_tr_port_info(int64_t n_ports, const int32_t *__restrict__ port_off,
                                const int32_t *__restrict__ port_peer, int32_t S, const uint8_t *__restrict__ jur,
-                               const int32_t *__restrict__ rule_off, const int32_t *__restrict__ gcount,
+                               const int32_t *__restrict__ rule_off, int64_t n_rules,
                                const int32_t *__restrict__ gofs, const uint32_t *__restrict__ cpos,
                                int2 *__restrict__ pinfo, SwInfo *__restrict__ sinfo)
 {
     const int64_t tot = n_ports > S ? n_ports : S;
     for (int64_t p = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; p < tot;
          p += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        if (p < n_ports) {
-            const int32_t v = port_peer[p];
-            const uint32_t j = v >= 0 && v < S ? jur[v] : 32u;
-            pinfo[p] = make_int2(v, j < 32 ? static_cast<int32_t>(1u << j) : 0);
-        }
+        if (p < n_ports) pinfo[p] = make_port(port_peer[p], S, jur);
         if (p < S) {
-            const int64_t pb = port_off[p], pe = port_off[p + 1];
-            SwInfo x;
-            x.G = gcount[p];
-            x.gofs = gofs[p];
-            x.cpos = cpos[p];
-            x.rb = rule_off[p];
-            x.pb = static_cast<int32_t>(pb);
-            x.np = pc_range_ok(pb, pe, n_ports) ? static_cast<int32_t>(pe - pb) : -1;
-            x.pad[0] = x.pad[1] = 0;
-            sinfo[p] = x;
+            const int32_t s = static_cast<int32_t>(p);
+            sinfo[s] = make_info(s, port_off, n_ports, rule_off, n_rules, gofs[s], cpos[s], true);
         }
     }
+}
+
+// Input sweeps in one launch: ports (every peer -1 or a switch), watch
+// lists (n_watch ids) and, with hh, the header histogram below.
+__device__ __forceinline__ bool bad_ids(int64_t n, const int32_t *__restrict__ ids, int32_t S)
+{
+    bool bad = false;
+    for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
+         i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
+        const int32_t v = ids[i];
+        bad |= v < -1 || v >= S;
+    }
+    return bad;
 }
 
 // Histogram of the headers' nibble values over a strided sample of at most
 // kHeaderSample headers: hh[n][x] = sampled headers whose nibble n is x.
 // hh must be zero on entry.
 constexpr int kHeaderSample = 65536;
-__global__ __launch_bounds__(256) void k_tr_hdr_hist(const pc_key *__restrict__ hdr, int32_t T,
-                                                     uint32_t *__restrict__ hh)
+__global__ __launch_bounds__(256) void k_tr_sweep(int64_t n_ports, const int32_t *__restrict__ port_peer, int32_t S,
+                                                  int64_t n_watch, const int32_t *__restrict__ watch,
+                                                  const pc_key *__restrict__ hdr, int32_t T,
+                                                  uint32_t *__restrict__ hh, uint32_t *__restrict__ d_err)
 {
     __shared__ uint32_t loc[kKeyNibbles * 16];
+    const bool bad = bad_ids(n_ports, port_peer, S) | bad_ids(n_watch, watch, S);
+    if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(d_err, PC_DERR_SWITCH);
+    if (hh == nullptr) return;
     for (int i = threadIdx.x; i < kKeyNibbles * 16; i += 256) loc[i] = 0;
     __syncthreads();
     const int64_t stride = T > kHeaderSample ? (static_cast<int64_t>(T) + kHeaderSample - 1) / kHeaderSample : 1;
@@ -195,6 +217,142 @@ __global__ __launch_bounds__(256) void k_tr_hdr_hist(const pc_key *__restrict__ 
     __syncthreads();
     for (int i = threadIdx.x; i < kKeyNibbles * 16; i += 256)
         if (loc[i]) atomicAdd(hh + i, loc[i]);
+}
+
+// Per switch the group count and the exclusive scans of group counts
+// (gofs) and prep blocks (bofs), their totals at [S]; offsets and
+// jurisdictions validated; the header histogram cleared for k_tr_sweep.  One
+// workgroup: with the separate kernels, three launches and a clear.
+constexpr int32_t kLayoutS = 16384;  // switches at most
+__global__ __launch_bounds__(1024) void k_tr_layout(int32_t S, const int32_t *__restrict__ port_off, int64_t n_ports,
+                                                    const uint8_t *__restrict__ jur,
+                                                    const int32_t *__restrict__ rule_off, int64_t n_rules,
+                                                    int32_t *__restrict__ gcount, int32_t *__restrict__ gofs,
+                                                    int32_t *__restrict__ bofs, uint32_t *__restrict__ hh,
+                                                    uint32_t *__restrict__ d_err)
+{
+    constexpr int kPer = 4;  // consecutive switches per thread and pass
+    __shared__ int32_t wsum[2][16];
+    __shared__ int32_t carry_s[2];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    if (tid < 2) carry_s[tid] = 0;
+    for (int i = tid; i < kKeyNibbles * 16; i += 1024) hh[i] = 0;
+    __syncthreads();
+    uint32_t errs = 0;
+    for (int32_t base = 0; base < S; base += 1024 * kPer) {
+        const int32_t i0 = base + tid * kPer;
+        int32_t g[kPer], b[kPer];
+        int32_t s0 = 0, s1 = 0;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            g[k] = b[k] = 0;
+            const int32_t s = i0 + k;
+            if (s >= S) continue;
+            const int64_t rb = rule_off[s], re = rule_off[s + 1];
+            const bool rok = pc_range_ok(rb, re, n_rules);
+            if (jur[s] >= 32) errs |= PC_DERR_JUR;
+            if (!rok || !pc_range_ok(port_off[s], port_off[s + 1], n_ports)) errs |= PC_DERR_OFFSETS;
+            g[k] = rok ? static_cast<int32_t>((re - rb + 31) / 32) : 0;
+            b[k] = (g[k] + kPrepGroups - 1) / kPrepGroups;
+            gcount[s] = g[k];
+            s0 += g[k];
+            s1 += b[k];
+        }
+        int32_t x0 = s0, x1 = s1;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t y0 = __shfl_up(x0, off, 64), y1 = __shfl_up(x1, off, 64);
+            if (lane >= off) {
+                x0 += y0;
+                x1 += y1;
+            }
+        }
+        if (lane == 63) {
+            wsum[0][wid] = x0;
+            wsum[1][wid] = x1;
+        }
+        __syncthreads();
+        if (wid < 2) {
+            int32_t w = lane < 16 ? wsum[wid][lane] : 0;
+#pragma unroll
+            for (int off = 1; off < 16; off <<= 1) {
+                const int32_t y = __shfl_up(w, off, 64);
+                if (lane >= off) w += y;
+            }
+            if (lane < 16) wsum[wid][lane] = w;
+        }
+        __syncthreads();
+        int32_t e0 = carry_s[0] + (wid ? wsum[0][wid - 1] : 0) + x0 - s0;
+        int32_t e1 = carry_s[1] + (wid ? wsum[1][wid - 1] : 0) + x1 - s1;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k)
+            if (i0 + k < S) {
+                gofs[i0 + k] = e0;
+                bofs[i0 + k] = e1;
+                e0 += g[k];
+                e1 += b[k];
+            }
+        __syncthreads();
+        if (tid < 2) carry_s[tid] += wsum[tid][15];
+        __syncthreads();
+    }
+    if (tid == 0) {
+        gofs[S] = carry_s[0];
+        bofs[S] = carry_s[1];
+    }
+    if (errs) atomicOr(d_err, errs);
+}
+
+// What k_tr_choose needs to write the switches' and ports' records as well
+// (sinfo nullptr: it does not).
+struct Infos {
+    SwInfo *sinfo;
+    int2 *pinfo;
+    const int32_t *port_off, *port_peer;
+    int64_t n_ports;
+    const uint8_t *jur;
+    const int32_t *gofs;
+    uint32_t *d_err;
+
+    // a workgroup's share of switch s: its ports' records
+    __device__ __forceinline__ void ports(int32_t s, int32_t S) const
+    {
+        const int64_t pb = port_off[s], pe = port_off[s + 1];
+        if (pc_range_ok(pb, pe, n_ports))
+            for (int64_t p = pb + threadIdx.x; p < pe; p += blockDim.x) pinfo[p] = make_port(port_peer[p], S, jur);
+    }
+    // the action flag of a switch without chunk sets (else k_tr_prep raises it)
+    __device__ __forceinline__ void sweep_actions(int32_t s, const pc_rule *__restrict__ r, int64_t R) const
+    {
+        const int64_t pb = port_off[s], pe = port_off[s + 1];
+        const int64_t np = pc_range_ok(pb, pe, n_ports) ? pe - pb : 0;
+        bool bad = false;
+        for (int64_t i = threadIdx.x; i < R; i += blockDim.x) {
+            const uint32_t act = r[i].action;
+            bad |= act != PC_ACTION_DROP && static_cast<int64_t>(act) >= np;
+        }
+        if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(d_err, PC_DERR_ACTION);
+    }
+};
+
+// Small tables, whose rules a walk matches one by one: everything a trace
+// call prepares, in one launch (a workgroup per switch, the sweeps spread
+// over all of them).
+__global__ __launch_bounds__(64) void k_tr_direct(int32_t S, const int32_t *__restrict__ rule_off, int64_t n_rules,
+                                                  const pc_rule *__restrict__ rules, int64_t n_watch,
+                                                  const int32_t *__restrict__ watch, Infos inf)
+{
+    const int32_t s = blockIdx.x;
+    uint32_t errs = 0;
+    if (bad_ids(inf.n_ports, inf.port_peer, S) | bad_ids(n_watch, watch, S)) errs |= PC_DERR_SWITCH;
+    const int64_t rb = rule_off[s], re = rule_off[s + 1];
+    const bool rok = pc_range_ok(rb, re, n_rules);
+    if (inf.jur[s] >= 32) errs |= PC_DERR_JUR;
+    if (!rok || !pc_range_ok(inf.port_off[s], inf.port_off[s + 1], inf.n_ports)) errs |= PC_DERR_OFFSETS;
+    if (errs) atomicOr(inf.d_err, errs);
+    if (threadIdx.x == 0) inf.sinfo[s] = make_info(s, inf.port_off, inf.n_ports, rule_off, n_rules, 0, 0, false);
+    inf.ports(s, S);
+    if (rok) inf.sweep_actions(s, rules + rb, re - rb);
 }
 
 // The filter chunks of each switch (one workgroup per switch).  From a
@@ -210,7 +368,8 @@ __global__ __launch_bounds__(256) void k_tr_hdr_hist(const pc_key *__restrict__ 
 // decides how many rules reach the full 104-bit check.
 __global__ __launch_bounds__(256) void k_tr_choose(int32_t S, const int32_t *__restrict__ rule_off, int64_t n_rules,
                                                    const pc_rule *__restrict__ rules,
-                                                   const uint32_t *__restrict__ hh, uint32_t *__restrict__ cpos)
+                                                   const uint32_t *__restrict__ hh, uint32_t *__restrict__ cpos,
+                                                   Infos inf)
 {
     __shared__ uint32_t hist[kKeyNibbles][256];  // (value & mask, mask) patterns per nibble
     __shared__ unsigned long long score[kKeyNibbles];
@@ -251,7 +410,10 @@ __global__ __launch_bounds__(256) void k_tr_choose(int32_t S, const int32_t *__r
             cp |= static_cast<uint32_t>(best) << (5 * c);
         }
         cpos[s] = cp;
+        if (inf.sinfo != nullptr)
+            inf.sinfo[s] = make_info(s, inf.port_off, inf.n_ports, rule_off, n_rules, inf.gofs[s], cp, true);
     }
+    if (inf.sinfo != nullptr) inf.ports(s, S);
 }
 
 // Rows r of a 32-lane half hold 32-bit words x_r; afterwards lane i holds
@@ -1075,59 +1237,51 @@ __global__ __launch_bounds__(kMatchThreads, 4) void k_tr_match(
         *reinterpret_cast<int4 *>(lv.live_next + bb + threadIdx.x) = make_int4(-1, -1, 0, 0);
 }
 
-// Sparse tail: one workgroup per trace still in flight walks it to its end,
-// filtering each switch's rule groups with only the kChunks chunk-set words
-// its header selects (coalesced over groups) and reducing the first match in
-// LDS.  Bound by the latency of a hop: the switch's record, its ports
+// What every walk of a launch shares.
+struct WalkArgs {
+    int32_t S;
+    const SwInfo *sinfo;
+    const int2 *pinfo;
+    const pc_rule *rules;
+    const uint32_t *filt;
+    int32_t ttl;
+    pc_trace_out *out;
+    const int32_t *watch;
+    int32_t K;
+    uint32_t *visit;
+    uint64_t *vsum;
+    int32_t *walk;
+};
+
+// One workgroup walks trace t (header h) from switch s to its end, filtering
+// each switch's rule groups with only the kChunks chunk-set words its
+// header selects (coalesced over groups) and reducing the first match in
+// LDS; the rules of a switch without chunk sets are matched one per lane.
+// Bound by the latency of a hop: the switch's record, its ports
 // together with the chunk-set words of two groups per lane, the survivors'
 // rules.  Where 5,200 of 500,009 traces loop until a TTL of 32, 329 us with a hop
 // per link, now 46; 6,001 traces over 777 rules per switch 54 us, now 22.
-__global__ __launch_bounds__(256) void k_tr_walk(int32_t S, const SwInfo *__restrict__ sinfo,
-                                                 const int2 *__restrict__ pinfo, const uint8_t *__restrict__ jur,
-                                                 const pc_rule *__restrict__ rules, const uint32_t *__restrict__ filt,
-                                                 int32_t ttl,
-                                                 const LRec *__restrict__ live, const int32_t *__restrict__ len,
-                                                 int32_t hops0, pc_trace_out *__restrict__ out,
-                                                 const int32_t *__restrict__ watch, int32_t K,
-                                                 uint32_t *__restrict__ visit, uint64_t *__restrict__ vsum,
-                                                 int32_t *__restrict__ walk)
+__device__ __forceinline__ void walk_trace(const WalkArgs &w, unsigned long long *best, int32_t t, const pc_key &h,
+                                           int32_t s, uint32_t jm, uint32_t vis, uint64_t vs, int32_t hops)
 {
-    __shared__ unsigned long long best;
-    const int32_t n = *len;
     const int lane = threadIdx.x & 63;
-    // Every gridDim-th entry is this workgroup's, 64 of them looked at
-    // together (most are the slots of traces that have ended).
-    const int64_t grid = gridDim.x;
-    for (int64_t i0 = blockIdx.x; i0 < n; i0 += 64 * grid) {
-    const int64_t il = i0 + lane * grid;
-    const int32_t at = il < n ? live[il].next : -1;
-    uint64_t flying = __ballot(at >= 0 && at < S);
-    while (flying) {
-        const LRec e = live[i0 + __builtin_ctzll(flying) * grid];
-        flying &= flying - 1;
-        const int32_t t = e.t;
-        const pc_key h = e.key;
-        int32_t s = __builtin_amdgcn_readfirstlane(e.next);
-        uint32_t jm = e.jm;
-        uint32_t vis = visit ? visit[t] : 0u;
-        uint64_t vs = vsum ? vsum[t] : 0ull;
-        int32_t hops = hops0;
-        // A walk is a function of the switch (its header does not change): once
-        // a switch comes again, the walk repeats until its TTL, and whole
-        // turns of the cycle are skipped, their switches being in every mask
-        // already.  The switch two hops back finds the ping-pong of two
-        // switches at once, an anchor that moves on at doubled distances
-        // (Brent) any other cycle.
-        int32_t back1 = -1, back2 = -1, anchor = s, anchor_hops = hops, span = 1;
-        for (;;) {
-            if (threadIdx.x == 0) best = kNoMatch;
-            __syncthreads();
-            const SwInfo si = sinfo[s];
-            const int32_t G = si.G;
-            const uint32_t *fs = filt + static_cast<int64_t>(si.gofs) * kPlaneWords;
-            const pc_rule *rs = rules + si.rb;
-            // this lane's of the switch's first 64 ports
-            const int2 port_lane = lane < si.np ? pinfo[si.pb + lane] : make_int2(-2, 0);
+    // A walk is a function of the switch (its header does not change): once
+    // a switch comes again, the walk repeats until its TTL, and whole
+    // turns of the cycle are skipped, their switches being in every mask
+    // already.  The switch two hops back finds the ping-pong of two
+    // switches at once, an anchor that moves on at doubled distances
+    // (Brent) any other cycle.
+    int32_t back1 = -1, back2 = -1, anchor = s, anchor_hops = hops, span = 1;
+    for (;;) {
+        if (threadIdx.x == 0) *best = kNoMatch;
+        __syncthreads();
+        const SwInfo si = w.sinfo[s];
+        const int32_t G = si.G;
+        const pc_rule *rs = w.rules + si.rb;
+        // this lane's of the switch's first 64 ports
+        const int2 port_lane = lane < si.np ? w.pinfo[si.pb + lane] : make_int2(-2, 0);
+        if (si.indexed) {
+            const uint32_t *fs = w.filt + static_cast<int64_t>(si.gofs) * kPlaneWords;
             int64_t row[kChunks];
 #pragma unroll
             for (int c = 0; c < kChunks; ++c)
@@ -1140,52 +1294,102 @@ __global__ __launch_bounds__(256) void k_tr_walk(int32_t S, const SwInfo *__rest
                     surv &= fs[row[c] + g];
                     surv2 &= fs[row[c] + min(g2, G - 1)];
                 }
-                if (surv) verify_group(surv, rs + static_cast<int64_t>(g) * 32, static_cast<uint32_t>(g) * 32, h, &best);
+                if (surv) verify_group(surv, rs + static_cast<int64_t>(g) * 32, static_cast<uint32_t>(g) * 32, h, best);
                 if (surv2)
-                    verify_group(surv2, rs + static_cast<int64_t>(g2) * 32, static_cast<uint32_t>(g2) * 32, h, &best);
+                    verify_group(surv2, rs + static_cast<int64_t>(g2) * 32, static_cast<uint32_t>(g2) * 32, h, best);
             }
-            __syncthreads();
-            const uint64_t key = best;
-            int32_t next = -1;
-            uint32_t jb = 0;
-            uint16_t port = PC_NO_PORT;
-            const int state = apply_key(S, ttl, si.np, [&](uint32_t a) {
-                const uint32_t ua = __builtin_amdgcn_readfirstlane(a);
-                const int2 p = ua < 64 ? make_int2(__builtin_amdgcn_readlane(port_lane.x, static_cast<int>(ua)),
-                                                   __builtin_amdgcn_readlane(port_lane.y, static_cast<int>(ua)))
-                                       : pinfo[si.pb + static_cast<int64_t>(ua)];
-                jb = static_cast<uint32_t>(p.y);
-                return p.x;
-            }, key, hops, &next, &port);
-            __syncthreads();  // everyone has read `best` before it is reset
-            if (state >= 0) {
-                if (threadIdx.x == 0) {
-                    write_out(out, t, jm, s, port, hops, state);
-                    if (visit) visit[t] = vis;
-                    if (vsum) vsum[t] = vs;
-                }
-                break;
+        } else {
+            for (int32_t r = threadIdx.x; r < si.R; r += blockDim.x)
+                if (rule_matches(rs + r, h.w[0], h.w[1], h.w[2], h.w[3]))
+                    atomicMin(best, static_cast<unsigned long long>(rule_key(rs + r, static_cast<uint32_t>(r))));
+        }
+        __syncthreads();
+        const uint64_t key = *best;
+        int32_t next = -1;
+        uint32_t jb = 0;
+        uint16_t port = PC_NO_PORT;
+        const int state = apply_key(w.S, w.ttl, si.np, [&](uint32_t a) {
+            const uint32_t ua = __builtin_amdgcn_readfirstlane(a);
+            const int2 p = ua < 64 ? make_int2(__builtin_amdgcn_readlane(port_lane.x, static_cast<int>(ua)),
+                                               __builtin_amdgcn_readlane(port_lane.y, static_cast<int>(ua)))
+                                   : w.pinfo[si.pb + static_cast<int64_t>(ua)];
+            jb = static_cast<uint32_t>(p.y);
+            return p.x;
+        }, key, hops, &next, &port);
+        __syncthreads();  // everyone has read *best before it is reset
+        if (state >= 0) {
+            if (threadIdx.x == 0) {
+                write_out(w.out, t, jm, s, port, hops, state);
+                if (w.visit) w.visit[t] = vis;
+                if (w.vsum) w.vsum[t] = vs;
             }
-            back2 = back1;
-            back1 = s;
-            s = __builtin_amdgcn_readfirstlane(next);
-            hops += 1;
-            jm |= jb;
-            if (visit) vis |= watch_bits(watch, K, t, s);
-            if (vsum) vs |= sum_bit(s);
-            if (walk && hops < kWalkSlots && threadIdx.x == 0) walk[static_cast<int64_t>(t) * kWalkSlots + hops] = s;
-            const int32_t period = s == back2 ? 2 : s == anchor ? hops - anchor_hops : 0;
-            if (period > 0 && !(walk && hops < kWalkSlots)) {
-                hops += (ttl - hops) / period * period;  // (hops <= ttl: a forward at hops == ttl has ended the walk)
-                back2 = anchor = -1;                      // less than a turn is left
-                span = INT32_MAX;
-            } else if (hops - anchor_hops >= span) {
-                anchor = s;
-                anchor_hops = hops;
-                span = span < (1 << 20) ? 2 * span : span;
-            }
+            break;
+        }
+        back2 = back1;
+        back1 = s;
+        s = __builtin_amdgcn_readfirstlane(next);
+        hops += 1;
+        jm |= jb;
+        if (w.visit) vis |= watch_bits(w.watch, w.K, t, s);
+        if (w.vsum) vs |= sum_bit(s);
+        if (w.walk && hops < kWalkSlots && threadIdx.x == 0) w.walk[static_cast<int64_t>(t) * kWalkSlots + hops] = s;
+        const int32_t period = s == back2 ? 2 : s == anchor ? hops - anchor_hops : 0;
+        if (period > 0 && !(w.walk && hops < kWalkSlots)) {
+            hops += (w.ttl - hops) / period * period;  // (hops <= ttl: a forward at hops == ttl has ended the walk)
+            back2 = anchor = -1;                        // less than a turn is left
+            span = INT32_MAX;
+        } else if (hops - anchor_hops >= span) {
+            anchor = s;
+            anchor_hops = hops;
+            span = span < (1 << 20) ? 2 * span : span;
         }
     }
+}
+
+// Sparse tail: every trace of a level's list that is still in flight.
+__global__ __launch_bounds__(256) void k_tr_walk(WalkArgs w, const LRec *__restrict__ live,
+                                                 const int32_t *__restrict__ len, int32_t hops0)
+{
+    __shared__ unsigned long long best;
+    const int32_t n = *len;
+    const int lane = threadIdx.x & 63;
+    // Every gridDim-th entry is this workgroup's, 64 of them looked at
+    // together (most are the slots of traces that have ended).
+    const int64_t grid = gridDim.x;
+    for (int64_t i0 = blockIdx.x; i0 < n; i0 += 64 * grid) {
+        const int64_t il = i0 + lane * grid;
+        const int32_t at = il < n ? live[il].next : -1;
+        uint64_t flying = __ballot(at >= 0 && at < w.S);
+        while (flying) {
+            const LRec e = live[i0 + __builtin_ctzll(flying) * grid];
+            flying &= flying - 1;
+            walk_trace(w, &best, e.t, e.key, __builtin_amdgcn_readfirstlane(e.next), e.jm, w.visit ? w.visit[e.t] : 0u,
+                       w.vsum ? w.vsum[e.t] : 0ull, hops0);
+        }
+    }
+}
+
+// Few traces: every one from its ingress (an invalid ingress ends it at once
+// as MISS), without levels, lists or counts.
+__global__ __launch_bounds__(256) void k_tr_walk_all(WalkArgs w, int32_t T, const pc_key *__restrict__ hdr,
+                                                     const int32_t *__restrict__ ingress,
+                                                     const uint8_t *__restrict__ jur, uint32_t *__restrict__ d_err)
+{
+    __shared__ unsigned long long best;
+    for (int32_t t = blockIdx.x; t < T; t += gridDim.x) {
+        const int32_t s = __builtin_amdgcn_readfirstlane(ingress[t]);
+        const bool in = s >= 0 && s < w.S;
+        if (w.walk && threadIdx.x < kWalkSlots)
+            w.walk[static_cast<int64_t>(t) * kWalkSlots + threadIdx.x] = in && threadIdx.x == 0 ? s : -1;
+        if (in) {
+            walk_trace(w, &best, t, hdr[t], s, jur_bit(jur, s), w.visit ? watch_bits(w.watch, w.K, t, s) : 0u,
+                       sum_bit(s), 0);
+        } else if (threadIdx.x == 0) {
+            write_out(w.out, t, 0, s, PC_NO_PORT, 0, PC_MISS);
+            if (w.visit) w.visit[t] = 0;
+            if (w.vsum) w.vsum[t] = 0;
+            atomicOr(d_err, PC_DERR_SWITCH);
+        }
     }
 }
 
@@ -1339,17 +1543,42 @@ unsigned grid_for(int64_t n, int threads)
     return b > 0 ? static_cast<unsigned>(b) : 1u;
 }
 
-// Header histogram, then each switch's filter chunks.
-int choose_chunks(pc_ctx *ctx, int32_t S, const int32_t *rule_off, int64_t n_rules, const pc_rule *rules,
-                  const pc_key *hdr, int32_t T, uint32_t *hh, uint32_t *cpos, hipStream_t stream)
+// The input sweeps with the header histogram (hh zeroed), then each switch's
+// filter chunks and, when inf names them, the switches' and ports' records.
+int sweep_and_choose(pc_ctx *ctx, int32_t S, const int32_t *port_peer, int64_t n_ports, const int32_t *rule_off,
+                     int64_t n_rules, const pc_rule *rules, const pc_key *hdr, int32_t T, int64_t n_watch,
+                     const int32_t *watch, uint32_t *hh, uint32_t *cpos, const Infos &inf, hipStream_t stream)
 {
-    launch_fill_u32(hh, kKeyNibbles * 16, 0, stream);
-    if (T > 0)
-        PC_TIMED(ctx, "k_tr_hdr_hist", stream,
-                 hipLaunchKernelGGL(k_tr_hdr_hist, dim3(64), dim3(256), 0, stream, hdr, T, hh));
+    const int64_t n = std::max<int64_t>({n_ports, n_watch, std::min<int64_t>(T, kHeaderSample)});
+    const unsigned blocks = static_cast<unsigned>(std::min<int64_t>(std::max<int64_t>((n + 1023) / 1024, 1), 256));
+    PC_TIMED(ctx, "k_tr_sweep", stream,
+             hipLaunchKernelGGL(k_tr_sweep, dim3(blocks), dim3(256), 0, stream, n_ports, port_peer, S, n_watch, watch,
+                                hdr, T, hh, ctx->d_err));
     PC_TIMED(ctx, "k_tr_choose", stream,
              hipLaunchKernelGGL(k_tr_choose, dim3(static_cast<unsigned>(S)), dim3(256), 0, stream, S, rule_off,
-                                n_rules, rules, hh, cpos));
+                                n_rules, rules, hh, cpos, inf));
+    PC_LAUNCH_CHECK(ctx);
+    return PC_OK;
+}
+
+// Group counts and offsets, prep-block offsets (bcount: scratch of the form
+// for many switches) and the zeroed header histogram.
+int layout(pc_ctx *ctx, int32_t S, const int32_t *port_off, int64_t n_ports, const uint8_t *jur,
+           const int32_t *rule_off, int64_t n_rules, int32_t *gcount, int32_t *bcount, int32_t *gofs, int32_t *bofs,
+           uint32_t *hh, hipStream_t stream)
+{
+    if (S <= kLayoutS) {
+        PC_TIMED(ctx, "k_tr_layout", stream,
+                 hipLaunchKernelGGL(k_tr_layout, dim3(1), dim3(1024), 0, stream, S, port_off, n_ports, jur, rule_off,
+                                    n_rules, gcount, gofs, bofs, hh, ctx->d_err));
+    } else {
+        PC_TIMED(ctx, "k_tr_switch_info", stream,
+                 hipLaunchKernelGGL(k_tr_switch_info, dim3(grid_for(S, 256)), dim3(256), 0, stream, S, port_off,
+                                    n_ports, jur, rule_off, n_rules, gcount, bcount, ctx->d_err));
+        launch_scan_i32(gcount, S, gofs, nullptr, nullptr, stream);
+        launch_scan_i32(bcount, S, bofs, nullptr, nullptr, stream);
+        launch_fill_u32(hh, kKeyNibbles * 16, 0, stream);
+    }
     PC_LAUNCH_CHECK(ctx);
     return PC_OK;
 }
@@ -1370,24 +1599,51 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         SwInfo *sinfo;
         uint32_t *filt, *cpos, *hh;
     } B;
+    // the walks' workgroup: about two rule groups per lane of a mean table
+    const int64_t mean_groups = S > 0 ? (pre != nullptr ? pre->groups : (n_rules + 31) / 32) / S : 0;
+    const int walk_threads = mean_groups <= 128 ? 64 : mean_groups <= 256 ? 128 : 256;
+    // Levels with few traces in flight are cheaper as independent walks than as
+    // bucketed passes (tunable with PC_TRACE_WALK_MAX, 0 = never walk): a walk
+    // skips its loops, a level costs three launches and a pass over its
+    // tables.  Large tables make a walk's hop dearer (24 bytes per 32 rules).
+    // Calls that walk from the start / from 8,192 traces on: 60,000 traces over
+    // 512 rules per switch (k = 16) 231 / 258 us, over 2,048 (k = 32) 275 / 302,
+    // over 32,768 (k = 16) 908 / 835, 30,000 traces there 527 / 803; 4,194,304
+    // traces, of which 8,900 loop until their TTL, 2.4 / 3.2 ms.
+    int64_t walk_max = mean_groups <= 128 ? 65536 : 32768;
+    if (const char *env = getenv("PC_TRACE_WALK_MAX")) walk_max = atoll(env);
+    const bool levels = T > walk_max;
+    // Few enough traces over tables this small are matched rule by rule: no
+    // chunk sets, no wait for their count, two launches.  Chunk sets / rule by
+    // rule: 1,000 traces over 16 rules per switch 46 / 23 us (k = 16), 4,000
+    // over 1,024 rules 61 / 55, 60,000 over 64 rules 145 / 68, 16,000 over 256
+    // rules 89 / 54; past the limit 16,000 over 512 rules 93 / 100, over 1,024
+    // 96 / 189.  The host knows no single table's size: the third bound holds
+    // the cost down where one switch has all the rules (67 million matches,
+    // about 0.1 ms a hop).
+    const bool direct = pre == nullptr && !levels && S > 0 && n_rules <= static_cast<int64_t>(kDirectRules) * S &&
+                        static_cast<int64_t>(T) * (n_rules / S + 1) <= kDirectWork &&
+                        static_cast<int64_t>(T) * n_rules <= kDirectWorst;
     // work items of a level: at most T / kItemCap + S (see the match launch)
     const int32_t icap = static_cast<int32_t>(std::min<int64_t>(static_cast<int64_t>(T) / kItemCap + S + 1, INT32_MAX));
     auto carve = [&](Carver &c) {
+        B.pinfo = c.take<int2>(static_cast<size_t>(n_ports) + 1);
+        B.sinfo = c.take<SwInfo>(static_cast<size_t>(S) + 1);
+        if (direct) return;
         B.cpos = c.take<uint32_t>(S + 1);
         B.hh = c.take<uint32_t>(kKeyNibbles * 16);
         B.gcount = c.take<int32_t>(S + 1);
         B.bcount = c.take<int32_t>(S + 1);
         B.gofs = c.take<int32_t>(S + 1);
         B.bofs = c.take<int32_t>(S + 1);
-        B.counts0 = c.take<int32_t>(static_cast<size_t>(S + 1) * kCountPad);
-        B.counts1 = c.take<int32_t>(static_cast<size_t>(S + 1) * kCountPad);
+        if (!levels) return;
+        B.counts0 = c.take<int32_t>(2 * static_cast<size_t>(S + 1) * kCountPad);
+        B.counts1 = B.counts0 + static_cast<size_t>(S + 1) * kCountPad;
         B.boff = c.take<int32_t>(S + 1);
         B.ioff = c.take<int32_t>(S + 1);
         B.live0 = c.take<LRec>(T + 1);
         B.live1 = c.take<LRec>(T + 1);
         B.bucket = c.take<BRec>(T + 1);
-        B.pinfo = c.take<int2>(static_cast<size_t>(n_ports) + 1);
-        B.sinfo = c.take<SwInfo>(static_cast<size_t>(S) + 1);
         B.imap = c.take<int2>(static_cast<size_t>(icap));
     };
     Carver dry{nullptr, 0};
@@ -1396,44 +1652,54 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
     if (rc) return rc;
     Carver real{ctx->arena, 0};
     carve(real);
+    if (!visit) K = 0;
+    const int64_t n_watch = static_cast<int64_t>(T) * K;
+    Infos inf{B.sinfo, B.pinfo, port_off, port_peer, n_ports, jur, nullptr, ctx->d_err};
+    B.filt = nullptr;
 
     // ---- prep: per-switch sizes, offsets, chunk sets, data-error sweep
     // (done by the caller when it passes prepared tables)
     if (pre != nullptr) {
         B.filt = const_cast<uint32_t *>(pre->filt);
         B.gcount = const_cast<int32_t *>(pre->gcount);
-        B.gofs = const_cast<int32_t *>(pre->gofs);
-        B.cpos = const_cast<uint32_t *>(pre->cpos);
+        const int64_t n_info = std::max<int64_t>(n_ports, S);
+        if (n_info > 0)
+            PC_TIMED(ctx, "k_tr_port_info", stream,
+                     hipLaunchKernelGGL(k_tr_port_info, dim3(static_cast<unsigned>(std::min<int64_t>((n_info + 255) / 256, 4096))),
+                                        dim3(256), 0, stream, n_ports, port_off, port_peer, S, jur, rule_off, n_rules,
+                                        pre->gofs, pre->cpos, B.pinfo, B.sinfo));
+        if (n_watch > 0)
+            PC_TIMED(ctx, "k_tr_sweep", stream,
+                     hipLaunchKernelGGL(k_tr_sweep, dim3(256), dim3(256), 0, stream, int64_t(0), nullptr, S, n_watch,
+                                        watch, nullptr, 0, nullptr, ctx->d_err));
+        PC_LAUNCH_CHECK(ctx);
+    } else if (direct) {
+        PC_TIMED(ctx, "k_tr_direct", stream,
+                 hipLaunchKernelGGL(k_tr_direct, dim3(static_cast<unsigned>(S)), dim3(64), 0, stream, S, rule_off,
+                                    n_rules, rules, n_watch, watch, inf));
+        PC_LAUNCH_CHECK(ctx);
     } else if (S > 0) {
-        PC_TIMED(ctx, "k_tr_switch_info", stream, hipLaunchKernelGGL(k_tr_switch_info, dim3(grid_for(S, 256)), dim3(256), 0, stream, S, port_off, n_ports, jur,
-                           rule_off, n_rules, B.gcount, B.bcount, ctx->d_err));
-        PC_LAUNCH_CHECK(ctx);
-        launch_scan_i32(B.gcount, S, B.gofs, nullptr, nullptr, stream);
-        launch_scan_i32(B.bcount, S, B.bofs, nullptr, nullptr, stream);
-        PC_LAUNCH_CHECK(ctx);
+        rc = layout(ctx, S, port_off, n_ports, jur, rule_off, n_rules, B.gcount, B.bcount, B.gofs, B.bofs, B.hh, stream);
+        if (rc) return rc;
+        inf.gofs = B.gofs;
         // exact sizes of the chunk-set buffer and of the prep grid (switch
-        // ranges may overlap, so no host-side bound from n_rules holds); the
-        // host waits for these two counts only, while the port check and
+        // ranges may overlap, so no host-side bound from n_rules holds);
+        // the host waits for these two counts only, while the sweeps and
         // the chunk choice, queued behind them, keep the GPU busy
         PC_HIP(ctx, hipMemcpyAsync(ctx->h_small, B.gofs + S, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
         PC_HIP(ctx, hipMemcpyAsync(ctx->h_small + 1, B.bofs + S, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
         PC_HIP(ctx, hipEventRecord(ctx->lvl_ev[0], stream));
-        if (n_ports > 0) {
-            PC_TIMED(ctx, "k_tr_port_check", stream, hipLaunchKernelGGL(k_tr_port_check, dim3(grid_for(n_ports, 256)), dim3(256), 0, stream, n_ports,
-                               port_peer, S, ctx->d_err));
-            PC_LAUNCH_CHECK(ctx);
-        }
-        rc = choose_chunks(ctx, S, rule_off, n_rules, rules, hdr, T, B.hh, B.cpos, stream);
+        rc = sweep_and_choose(ctx, S, port_peer, n_ports, rule_off, n_rules, rules, hdr, T, n_watch, watch, B.hh,
+                              B.cpos, inf, stream);
         if (rc) return rc;
         PC_HIP(ctx, hipEventSynchronize(ctx->lvl_ev[0]));
-        const int64_t total_groups = ctx->h_small[0];
-        const int64_t prep_blocks = ctx->h_small[1];
-        if (total_groups < 0 || prep_blocks < 0)
+        const int64_t groups = ctx->h_small[0], prep_blocks = ctx->h_small[1];
+        if (groups < 0 || prep_blocks < 0)
             return pc_set_error(ctx, PC_EINVAL, "pc_trace_flows: more than 2^31 rule groups");
-        rc = pc_ensure_aux(ctx, static_cast<size_t>(total_groups + 1) * kPlaneWords * sizeof(uint32_t));
+        rc = pc_ensure_aux(ctx, static_cast<size_t>(groups + 1) * kPlaneWords * sizeof(uint32_t));
         if (rc) return rc;
         B.filt = reinterpret_cast<uint32_t *>(ctx->aux);
-        if (prep_blocks > 0) {
+        if (prep_blocks > 0 && n_rules > 0) {
             PC_TIMED(ctx, "k_tr_prep", stream, hipLaunchKernelGGL(k_tr_prep, dim3(static_cast<unsigned>(prep_blocks)), dim3(kPrepWaves * 64), 0, stream, S,
                                port_off, n_ports, rule_off, rules, B.gcount, B.gofs, B.bofs, B.filt, ctx->d_err,
                                nullptr, nullptr, B.cpos));
@@ -1441,32 +1707,20 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         }
     }
     if (T == 0) return PC_OK;
-    // the tail walk's workgroup: about two rule groups per lane of a mean table
-    const int64_t mean_groups = S > 0 ? (pre != nullptr ? pre->groups : ctx->h_small[0]) / S : 0;
-    const int walk_threads = mean_groups <= 128 ? 64 : mean_groups <= 256 ? 128 : 256;
-    if (visit && K > 0) {
-        PC_TIMED(ctx, "k_tr_watch_check", stream,
-                 hipLaunchKernelGGL(k_tr_port_check, dim3(grid_for(static_cast<int64_t>(T) * K, 256)), dim3(256), 0,
-                                    stream, static_cast<int64_t>(T) * K, watch, S, ctx->d_err));
+    const WalkArgs wa{S, B.sinfo, B.pinfo, rules, B.filt, ttl, out, watch, K, visit, vsum, walk};
+    if (!levels) {
+        PC_TIMED(ctx, "k_tr_walk", stream,
+                 hipLaunchKernelGGL(k_tr_walk_all, dim3(static_cast<unsigned>(std::min(T, 8192))),
+                                    dim3(direct ? 64 : walk_threads), 0, stream, wa, T, hdr, ingress, jur, ctx->d_err));
         PC_LAUNCH_CHECK(ctx);
-    }
-    if (!visit) K = 0;
-    if (std::max<int64_t>(n_ports, S) > 0) {
-        const int64_t n_info = std::max<int64_t>(n_ports, S);
-        PC_TIMED(ctx, "k_tr_port_info", stream,
-                 hipLaunchKernelGGL(k_tr_port_info, dim3(static_cast<unsigned>(std::min<int64_t>((n_info + 255) / 256, 4096))),
-                                    dim3(256), 0, stream, n_ports, port_off, port_peer, S, jur, rule_off, B.gcount,
-                                    B.gofs, B.cpos, B.pinfo, B.sinfo));
-        PC_LAUNCH_CHECK(ctx);
+        return PC_OK;
     }
 
     // ---- level-synchronous walk
     int32_t *d_n = ctx->d_small;  // [0], [1]: live counts of the two live lists ([4], [5]: the reach kernels')
     launch_fill_u32(reinterpret_cast<uint32_t *>(d_n), 2, 0, stream);
-    if (S > 0) {
-        launch_fill_u32(reinterpret_cast<uint32_t *>(B.counts0), static_cast<size_t>(S + 1) * kCountPad, 0, stream);
-        launch_fill_u32(reinterpret_cast<uint32_t *>(B.counts1), static_cast<size_t>(S + 1) * kCountPad, 0, stream);
-    }
+    if (S > 0)
+        launch_fill_u32(reinterpret_cast<uint32_t *>(B.counts0), 2 * static_cast<size_t>(S + 1) * kCountPad, 0, stream);
     {
         const dim3 ig(static_cast<unsigned>((static_cast<int64_t>(T) + kInitPer - 1) / kInitPer));
         if (S <= kInitLdsS)
@@ -1483,16 +1737,6 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
     LRec *live_cur = B.live0, *live_nxt = B.live1;
     int32_t *cnt_cur = B.counts0, *cnt_nxt = B.counts1;
     int32_t *n_cur = d_n, *n_nxt = d_n + 1;
-    // Levels with few traces in flight are cheaper as independent walks than as
-    // bucketed passes (tunable with PC_TRACE_WALK_MAX, 0 = never walk): a walk
-    // skips its loops, a level costs three launches and a pass over its
-    // tables.  Large tables make a walk's hop dearer (24 bytes per 32 rules).
-    // Calls that walk from the start / from 8,192 traces on: 60,000 traces over
-    // 512 rules per switch (k = 16) 231 / 258 us, over 2,048 (k = 32) 275 / 302,
-    // over 32,768 (k = 16) 908 / 835, 30,000 traces there 527 / 803; 4,194,304
-    // traces, of which 8,900 loop until their TTL, 2.4 / 3.2 ms.
-    int64_t walk_max = mean_groups <= 128 ? 65536 : 32768;
-    if (const char *env = getenv("PC_TRACE_WALK_MAX")) walk_max = atoll(env);
     // The host does not wait for a level before queueing the next one: live
     // counts only shrink, so level L is launched with the latest count the
     // host has (exact for level 0, else the count entering level L - 1) as
@@ -1516,9 +1760,8 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         if (known <= walk_max) {
             const unsigned wb = static_cast<unsigned>(known < 8192 ? known : 8192);
             PC_TIMED(ctx, "k_tr_walk", stream,
-                     hipLaunchKernelGGL(k_tr_walk, dim3(wb), dim3(walk_threads), 0, stream, S, B.sinfo, B.pinfo, jur,
-                                        rules, B.filt, ttl, live_cur, len_cur, level, out, watch, K, visit, vsum,
-                                        walk));
+                     hipLaunchKernelGGL(k_tr_walk, dim3(wb), dim3(walk_threads), 0, stream, wa, live_cur, len_cur,
+                                        level));
             PC_LAUNCH_CHECK(ctx);
             break;
         }
@@ -1594,13 +1837,8 @@ int tc_prepare_all(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_
     const TcMeta m = tc_meta(ctx, S);
     int64_t groups = 0, blocks = 0;
     if (S > 0) {
-        PC_TIMED(ctx, "k_tr_switch_info", stream,
-                 hipLaunchKernelGGL(k_tr_switch_info, dim3(grid_for(S, 256)), dim3(256), 0, stream, S, port_off,
-                                    n_ports, jur, rule_off, n_rules, m.gcount, m.bcount, ctx->d_err));
-        PC_LAUNCH_CHECK(ctx);
-        launch_scan_i32(m.gcount, S, m.gofs, nullptr, nullptr, stream);
-        launch_scan_i32(m.bcount, S, m.bofs, nullptr, nullptr, stream);
-        PC_LAUNCH_CHECK(ctx);
+        rc = layout(ctx, S, port_off, n_ports, jur, rule_off, n_rules, m.gcount, m.bcount, m.gofs, m.bofs, m.hh, stream);
+        if (rc) return rc;
         PC_HIP(ctx, hipMemcpyAsync(ctx->h_small, m.gofs + S, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
         PC_HIP(ctx, hipMemcpyAsync(ctx->h_small + 1, m.bofs + S, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
         PC_HIP(ctx, hipStreamSynchronize(stream));
@@ -1612,14 +1850,9 @@ int tc_prepare_all(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_
     rc = pc_ensure_tc_filt(ctx, static_cast<size_t>(groups + 1) * kPlaneWords * sizeof(uint32_t));
     if (rc) return rc;
     if (S > 0) {
-        if (n_ports > 0) {
-            PC_TIMED(ctx, "k_tr_port_check", stream,
-                     hipLaunchKernelGGL(k_tr_port_check, dim3(grid_for(n_ports, 256)), dim3(256), 0, stream, n_ports,
-                                        port_peer, S, ctx->d_err));
-            PC_LAUNCH_CHECK(ctx);
-        }
         launch_fill_u32(m.sw_bad, static_cast<size_t>(S), 0, stream);
-        rc = choose_chunks(ctx, S, rule_off, n_rules, rules, hdr, T, m.hh, m.cpos, stream);
+        rc = sweep_and_choose(ctx, S, port_peer, n_ports, rule_off, n_rules, rules, hdr, T, 0, nullptr, m.hh, m.cpos,
+                              Infos{}, stream);
         if (rc) return rc;
         if (blocks > 0) {
             PC_TIMED(ctx, "k_tr_prep", stream,
@@ -1707,9 +1940,10 @@ int run_trace_delta(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32
         // re-prepare only the changed switches, then the ACTION flag over all
         const TcMeta m = tc_meta(ctx, S);
         if (n_ports > 0) {
-            PC_TIMED(ctx, "k_tr_port_check", stream,
-                     hipLaunchKernelGGL(k_tr_port_check, dim3(grid_for(n_ports, 256)), dim3(256), 0, stream, n_ports,
-                                        port_peer, S, ctx->d_err));
+            PC_TIMED(ctx, "k_tr_sweep", stream,
+                     hipLaunchKernelGGL(k_tr_sweep, dim3(static_cast<unsigned>(std::min<int64_t>((n_ports + 1023) / 1024, 256))),
+                                        dim3(256), 0, stream, n_ports, port_peer, S, int64_t(0), nullptr, nullptr, 0,
+                                        nullptr, ctx->d_err));
         }
         if (C > 0) {
             PC_TIMED(ctx, "k_tc_clear", stream,

@@ -312,3 +312,52 @@ def test_walks_from_a_long_list(g, orc, monkeypatch):
     wl = synth.trace_workload(7, 8, 4, 256, 600_000, 16, 20_000)
     a = (wl["S"], wl["port_off"], wl["port_peer"], wl["jur"], wl["rule_off"], wl["rules"], wl["hdr"], wl["ingress"], 16)
     assert np.array_equal(g.trace(*a), orc.trace(*a)[0])
+
+
+@pytest.mark.parametrize("R,T", [(1, 1), (63, 500), (256, 3000), (1024, 3276), (1024, 3277), (1025, 300)])
+@pytest.mark.parametrize("bad", [False, True])
+def test_trace_small_tables(g, orc, R, T, bad):
+    """Tables matched rule by rule and, past 1,024 rules per switch or 2^26 matches, through chunk sets: skewed and
+    shared rule ranges, more than 64 ports on a switch, and malformed ingress, actions, peers, watch and offsets."""
+    import paper_2602_16100_amd as pc
+    rng = np.random.default_rng(R * 7 + T)
+    wl = synth.trace_workload(R + T, 4, 4, R, T, 16, max(T // 4, 1))
+    S, off, rules, peer = wl["S"], wl["rule_off"].copy(), wl["rules"].copy(), wl["port_peer"].copy()
+    port_off, ingress = wl["port_off"].copy(), wl["ingress"].copy()
+    assert S == 20
+    port_off[3:] += 70  # switch 2 takes 70 more ports, all to its neighbours
+    peer = np.insert(peer, wl["port_off"][3], rng.choice(peer[peer >= 0], 70))
+    lo, hi = off[2], off[3]
+    rules["action"][lo:hi][rng.random(hi - lo) < 0.5] = 68
+    off[10] = off[11] if R > 1 else off[10]  # one empty table, one of double length
+    watch = rng.integers(-1, S, size=(T, 5)).astype(np.int32)
+    if bad:
+        ingress[::7] = S
+        ingress[3::11] = -4
+        rules["action"][::5] = 3000
+        peer[5] = S + 9
+        watch[::9, 2] = S
+        off[15] = off[14] - 1 if R > 1 else -1
+    a = (S, port_off, peer, wl["jur"], off, rules, wl["hdr"], ingress, 16)
+    ctx = pc.context()
+    ctx.data_errors(clear=True)
+    tg, vg = g.trace_watch(*a, watch)
+    flags = ctx.data_errors(clear=True)
+    to, vo, err = orc.trace(*a, watch=watch)
+    _same_traces(tg, to)
+    _same(vg, vo, "visit")
+    assert flags == err
+
+
+@pytest.mark.parametrize("T", [4000, 4200])
+def test_trace_many_switches(g, orc, T):
+    """A ring of more switches than one workgroup lays out, rule by rule and through chunk sets (T above 2^26 / S)."""
+    S = 16390
+    off = np.arange(S + 1, dtype=np.int32)
+    peer = np.roll(np.arange(S, dtype=np.int32), -1)
+    peer[100::1000] = -1
+    rules = np.zeros(S, synth.RULE_DT)
+    rng = np.random.default_rng(T)
+    a = (S, off, peer, (np.arange(S) % 31).astype(np.uint8), off, rules, synth.random_keys(rng, T),
+         rng.integers(0, S, size=T).astype(np.int32), 200)
+    assert np.array_equal(g.trace(*a), orc.trace(*a)[0])
