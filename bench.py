@@ -696,8 +696,8 @@ def time_update(args, wl, pc, ctx, D, feasible, popcnt):
     """Incremental re-evaluation (pc_update_nodes) after relabelling M random
     nodes of the cluster, against the full pc_eval_selectors of the new
     labels.  The bitsets are brought to the old labels' state before each
-    timed call; the timed region is the call alone.  Above W / 32 nodes the
-    library itself takes the full evaluation."""
+    timed call; the timed region is the call alone.  Above 64 and W / 32
+    nodes the library itself takes the full evaluation."""
     import torch
     dev = feasible.device
     rng = np.random.default_rng([wl.seed, 15])
@@ -706,7 +706,7 @@ def time_update(args, wl, pc, ctx, D, feasible, popcnt):
     cards = wl.meta["cards"]
     labels = wl["labels"]
     base = pc.to_device(labels, dev)
-    out = {"rows": I, "nodes": N, "full_above": W // 32, "per_m": {}}
+    out = {"rows": I, "nodes": N, "full_above": max(64, W // 32), "per_m": {}}
     for M in (1, 16, 64, 1024):
         nodes = rng.choice(N, size=M, replace=False).astype(np.int32)
         new = labels.copy()

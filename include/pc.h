@@ -580,9 +580,9 @@ int pc_report_counts(pc_ctx *ctx, int32_t I, const pc_intent *intents, int32_t r
  * node outside [0, N) is skipped (PC_DERR_NODE); rows and predicates as in
  * pc_eval_selectors (PC_DERR_OFFSETS, PC_DERR_PRED).  The incremental cost
  * grows with the number of distinct bitset words the nodes touch per row;
- * above W / 32 listed nodes the call evaluates every row in full instead
- * (the same result; environment variable PC_UPDATE_FULL_ABOVE overrides the
- * threshold).
+ * lists above 64 nodes (32 KiB of label records where they take more) and
+ * above W / 32 are evaluated in full instead (the same result; environment
+ * variable PC_UPDATE_FULL_ABOVE overrides the threshold).
  */
 int pc_update_nodes(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, const int32_t *pred_off,
                     const pc_pred *preds, int64_t n_preds, int32_t I, const int32_t *nodes, int32_t M,

@@ -116,3 +116,28 @@ def test_update_full_size(g, orc, path):
     assert np.array_equal(pu, pf)
     assert np.array_equal(fu, ff)
     assert not np.array_equal(pu, p0)
+
+
+@pytest.mark.parametrize("L,cards", [(1, (5,)), (7, (2, 64, 254)), (256, (64,)), (257, (200,))])
+@pytest.mark.parametrize("M", [1, 7, 8, 9, 63, 64])
+def test_update_short_lists(g, orc, M, L, cards):
+    """Short lists: octet and word-batch remainders, nodes sharing a word and alone in theirs, repeats, invalid ids,
+    values on both sides of 64, label counts around the scratch limit, row counts around a workgroup."""
+    N = 64 * 19 + 1
+    rng = np.random.default_rng(M * 1000 + L)
+    for I in (1, 255, 257):
+        wl = synth.selector_workload(M + I, N, L, I, card_choices=cards, absent_p=0.1)
+        labels, off, preds = wl["labels"], wl["pred_off"].copy(), wl["preds"].copy()
+        if I > 1:
+            off[7] = off[8] + 1
+            preds["op"][off[20]] = 9
+        f0, p0 = _gpu_full(labels, off, preds)
+        spread = rng.permutation(20)[:min(M, 17)] * 64 % N
+        for nodes in (np.resize(spread, M), rng.integers(64, 128, M), rng.integers(-3, N + 3, M),
+                      np.full(M, N), np.full(M, N - 1)):
+            nodes = nodes.astype(np.int32)
+            new = _relabel(rng, labels, wl.meta["cards"], nodes)
+            fu, pu, eu = _gpu_update(new, off, preds, nodes, f0, p0)
+            fo, po, eo = orc.update_nodes(new, off, preds, nodes, f0, p0)
+            assert eu == eo
+            assert np.array_equal(fu, fo) and np.array_equal(pu, po)
