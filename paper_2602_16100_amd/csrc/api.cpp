@@ -169,6 +169,7 @@ int pc_create(pc_ctx **out, int device)
         hipMalloc(reinterpret_cast<void **>(&ctx->d_err), 256) != hipSuccess ||
         hipMemset(ctx->d_err, 0, 256) != hipSuccess ||
         hipMalloc(reinterpret_cast<void **>(&ctx->d_small), 256) != hipSuccess ||
+        hipMemset(ctx->d_small, 0, 256) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void **>(&ctx->h_small), 256, hipHostMallocDefault) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->lvl_ev[0], hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->lvl_ev[1], hipEventDisableTiming) != hipSuccess) {

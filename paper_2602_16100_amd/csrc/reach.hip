@@ -40,6 +40,7 @@ namespace {
 constexpr int kBitsetThreads = 1024;  // two workgroups per CU fill all 32 wave slots
 constexpr int kQueueThreads = 256;
 constexpr int kMaxBitsetV = 6016;  // 3 x 8 B + 1 B + 2 B per vertex, plus masks, within 160 KB of LDS
+constexpr int kBitsetStatic = 1024;  // LDS of the bitset search besides these, at most
 
 __device__ __forceinline__ bool allowed_v(const uint8_t *region, uint32_t A, int32_t v)
 {
@@ -55,75 +56,80 @@ __device__ __forceinline__ bool forbidden_v(const int32_t *__restrict__ fl, int3
     return false;
 }
 
-// Waypoint / forbidden lists: every entry must be -1 or a vertex.
-__global__ void k_rc_id_check(int64_t n, const int32_t *__restrict__ ids, int32_t V, uint32_t *__restrict__ d_err)
+// Everything a search checks about its inputs, in one launch (a small call is
+// its launches: with one kernel per check and a fill of the flag, 64 queries
+// on 20 vertices took 41 us, now 24).  The data errors: regions, offsets, adjacency
+// entries, sources, targets, waypoint and forbidden lists (every entry -1 or
+// a vertex).  And, for a gen other than 0, the graph's symmetry: *asym becomes gen
+// unless every adjacency list is sorted and every valid entry u -> v has its
+// reverse v -> u (a vertex whose offsets are invalid has no entries, so no
+// valid list may name it).  Then the search from v reaches u exactly when the
+// search from u reaches v, at the same distance.  One wavefront per vertex, its
+// lanes over the vertex's entries.  The caller numbers its calls, so that
+// the flag needs no clearing.
+struct Checks {
+    int32_t V;
+    const int32_t *adj_off, *adj;
+    int64_t n_adj;
+    const uint8_t *region;
+    int32_t Q;
+    const int32_t *src, *target;
+    int64_t nv, nf;
+    const int32_t *via, *forbid;
+    int32_t *asym;
+    int32_t gen;
+    uint32_t *d_err;
+};
+
+__device__ __forceinline__ bool bad_vertices(const int32_t *__restrict__ ids, int64_t n, int32_t lowest, int32_t V,
+                                             int64_t i0, int64_t stride)
 {
     bool bad = false;
-    for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
-         i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-        const int32_t v = ids[i];
-        bad |= (v < -1 || v >= V);
-    }
-    if (bad) atomicOr(d_err, PC_DERR_SWITCH);
+    for (int64_t i = i0; i < n; i += stride) bad |= ids[i] < lowest || ids[i] >= V;
+    return bad;
 }
 
-// *flag stays 1 only if every adjacency list is sorted and every valid
-// entry u -> v has its reverse v -> u (a vertex whose offsets are invalid has
-// no entries, so no valid list may name it): then the search from v reaches
-// u exactly when the search from u reaches v, at the same distance.  One
-// wavefront per vertex, its lanes over the vertex's entries.
-__global__ __launch_bounds__(256) void k_rc_symcheck(int32_t V, const int32_t *__restrict__ adj_off,
-                                                     const int32_t *__restrict__ adj, int64_t n_adj,
-                                                     int32_t *__restrict__ flag)
+__global__ __launch_bounds__(256) void k_rc_checks(Checks c)
 {
+    uint32_t errs = 0;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+    const int64_t i0 = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
+    for (int64_t v = i0; v < c.V; v += stride) {
+        if (c.region[v] >= 32) errs |= PC_DERR_JUR;
+        if (!pc_range_ok(c.adj_off[v], c.adj_off[v + 1], c.n_adj)) errs |= PC_DERR_OFFSETS;
+    }
+    if (bad_vertices(c.adj, c.n_adj, 0, c.V, i0, stride)) errs |= PC_DERR_GRAPH;
+    if (bad_vertices(c.src, c.Q, 0, c.V, i0, stride) ||
+        bad_vertices(c.target, c.target ? c.Q : 0, 0, c.V, i0, stride) ||
+        bad_vertices(c.via, c.nv, -1, c.V, i0, stride) || bad_vertices(c.forbid, c.nf, -1, c.V, i0, stride))
+        errs |= PC_DERR_SWITCH;
+    if (errs) atomicOr(c.d_err, errs);
+    if (c.gen == 0) return;
     const int lane = threadIdx.x & 63;
     const int32_t waves = gridDim.x * 4;
     bool bad = false;
-    for (int32_t u = blockIdx.x * 4 + (threadIdx.x >> 6); u < V; u += waves) {
-        const int64_t b = adj_off[u], e = adj_off[u + 1];
-        if (!pc_range_ok(b, e, n_adj)) continue;
+    for (int32_t u = blockIdx.x * 4 + (threadIdx.x >> 6); u < c.V; u += waves) {
+        const int64_t b = c.adj_off[u], e = c.adj_off[u + 1];
+        if (!pc_range_ok(b, e, c.n_adj)) continue;
         for (int64_t p = b + lane; p < e; p += 64) {
-            const int32_t v = adj[p];
-            if (p > b && adj[p - 1] > v) bad = true;
-            if (v < 0 || v >= V) continue;
-            int64_t lo = adj_off[v], hi = adj_off[v + 1];
-            if (!pc_range_ok(lo, hi, n_adj)) {
+            const int32_t v = c.adj[p];
+            if (p > b && c.adj[p - 1] > v) bad = true;
+            if (v < 0 || v >= c.V) continue;
+            int64_t lo = c.adj_off[v], hi = c.adj_off[v + 1];
+            if (!pc_range_ok(lo, hi, c.n_adj)) {
                 bad = true;
                 continue;
             }
             const int64_t end = hi;
             while (lo < hi) {  // first entry >= u
                 const int64_t mid = (lo + hi) >> 1;
-                if (adj[mid] < u) lo = mid + 1;
+                if (c.adj[mid] < u) lo = mid + 1;
                 else hi = mid;
             }
-            if (lo >= end || adj[lo] != u) bad = true;
+            if (lo >= end || c.adj[lo] != u) bad = true;
         }
     }
-    if (__ballot(bad) && lane == 0) atomicAnd(flag, 0);
-}
-
-__global__ void k_rc_validate(int32_t V, const int32_t *__restrict__ adj_off, const int32_t *__restrict__ adj,
-                              int64_t n_adj, const uint8_t *__restrict__ region, int32_t Q,
-                              const int32_t *__restrict__ src, const int32_t *__restrict__ target,
-                              uint32_t *__restrict__ d_err)
-{
-    uint32_t errs = 0;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    const int64_t i0 = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-    for (int64_t v = i0; v < V; v += stride) {
-        if (region[v] >= 32) errs |= PC_DERR_JUR;
-        if (!pc_range_ok(adj_off[v], adj_off[v + 1], n_adj)) errs |= PC_DERR_OFFSETS;
-    }
-    for (int64_t p = i0; p < n_adj; p += stride) {
-        const int32_t v = adj[p];
-        if (v < 0 || v >= V) errs |= PC_DERR_GRAPH;
-    }
-    for (int64_t q = i0; q < Q; q += stride) {
-        if (src[q] < 0 || src[q] >= V) errs |= PC_DERR_SWITCH;
-        if (target && (target[q] < 0 || target[q] >= V)) errs |= PC_DERR_SWITCH;
-    }
-    if (errs) atomicOr(d_err, errs);
+    if (__ballot(bad) && lane == 0) *c.asym = c.gen;
 }
 
 // Append v to an LDS list when `add`, one counter update per wavefront
@@ -189,13 +195,55 @@ __global__ void k_rc_src_place(int32_t Q, const int32_t *__restrict__ src, int32
     }
 }
 
+// Leg k of query q (k <= m, m = waypoints before the first -1) runs from the
+// previous waypoint (or src) to the next one (or target); legs past m are
+// inactive (-1 to -1).  On a symmetric graph (flip) legs 0, 2, 4, ... are
+// searched from their far end, so that legs 2j and 2j + 1 start at the same
+// waypoint and share their frontiers in the workgroup's bitsets.
+struct Leg {
+    int32_t from, to;
+    bool last;  // the walk ends with it
+};
+
+__device__ __forceinline__ Leg leg_of(const int32_t *__restrict__ src, const int32_t *__restrict__ target,
+                                      const int32_t *__restrict__ w, int32_t Kv, int32_t q, int32_t k, bool flip)
+{
+    int32_t from = src[q];
+    for (int32_t i = 0; i < k; ++i) {
+        from = w[i];
+        if (from == -1) return {-1, -1, true};
+    }
+    const int32_t nxt = k < Kv ? w[k] : -1;
+    const int32_t to = nxt == -1 ? target[q] : nxt;
+    return flip && (k & 1) == 0 ? Leg{to, from, nxt == -1} : Leg{from, to, nxt == -1};
+}
+
+// Sum of the distances of a walk's legs up to the last, -1 if any is
+// unreachable (saturating at INT32_MAX).
+struct WalkLength {
+    int64_t total = 0;
+    bool open = true;
+    __device__ __forceinline__ void add(int32_t d, bool last)
+    {
+        if (!open) return;
+        total = d < 0 ? -1 : total + d;
+        open = d >= 0 && !last;
+    }
+    __device__ __forceinline__ int32_t length() const
+    {
+        return static_cast<int32_t>(total > 0x7FFFFFFF ? 0x7FFFFFFF : total);
+    }
+};
+
 // 64 queries per workgroup; dist is [Q][V] (target == nullptr) or [Q].
 // Each level pushes the frontier along its edges: the frontier vertices are
 // kept as a list in LDS and GS lanes share one vertex's adjacency, so the
 // adjacency loads are coalesced and the vertex's frontier word is a
 // broadcast; the next frontier is built (and the list rewritten) in one
 // pass over the vertices.
-template <int GS>
+// kLegs: a query is Kv + 1 legs of one walk (leg_of), a workgroup takes as
+// many whole queries as fit 64 legs, and dist[q] is the walk's length.
+template <int GS, bool kLegs>
 __global__ __launch_bounds__(kBitsetThreads) void k_rc_bitset(int32_t V, const int32_t *__restrict__ adj_off,
                                                               const int32_t *__restrict__ adj, int64_t n_adj,
                                                               const uint8_t *__restrict__ region, int32_t Q,
@@ -204,8 +252,9 @@ __global__ __launch_bounds__(kBitsetThreads) void k_rc_bitset(int32_t V, const i
                                                               const int32_t *__restrict__ target,
                                                               int32_t *__restrict__ dist,
                                                               const int32_t *__restrict__ forbid, int32_t Kf,
-                                                              int32_t qdiv, const int32_t *__restrict__ sym,
-                                                              const int32_t *__restrict__ perm)
+                                                              int32_t qdiv, const int32_t *__restrict__ asym,
+                                                              int32_t gen, const int32_t *__restrict__ perm,
+                                                              const int32_t *__restrict__ via, int32_t Kv)
 {
     extern __shared__ uint64_t lds[];
     // visited / frontier / next words of vertex v sit in slot sl(v) =
@@ -231,9 +280,11 @@ __global__ __launch_bounds__(kBitsetThreads) void k_rc_bitset(int32_t V, const i
     // query of bit k: qid[k] (queries taken in perm order when given)
     __shared__ int32_t qid[64];
     const int tid = threadIdx.x, lane = tid & 63;
-    const int32_t q0 = blockIdx.x * 64;
-    const int32_t nq = min(64, Q - q0);
-    if (tid < 64) qid[lane] = lane < nq ? (perm ? perm[q0 + lane] : q0 + lane) : 0;
+    const int32_t legs = kLegs ? Kv + 1 : 1;
+    const int32_t per = 64 / legs;  // queries of this workgroup
+    const int32_t q0 = blockIdx.x * per;
+    const int32_t nq = min(per, Q - q0) * legs;
+    if (tid < 64) qid[lane] = lane < nq ? (perm ? perm[q0 + lane] : q0 + lane / legs) : 0;
     for (int32_t v = tid; v < Vp; v += kBitsetThreads) {
         vis[v] = 0;
         fr[v] = 0;
@@ -262,15 +313,23 @@ __global__ __launch_bounds__(kBitsetThreads) void k_rc_bitset(int32_t V, const i
     }
     // sources; per-query result state lives in wave 0, lane = query
     int32_t res = -1, tgt = -1;
-    bool done = true;
+    bool done = true, last = true;
     if (tid < 64 && lane < nq) {
         const int32_t q = qid[lane];
-        const int32_t s = src[q];
+        int32_t s;
+        if (kLegs) {
+            const Leg leg = leg_of(src, target, via + static_cast<int64_t>(q) * Kv, Kv, q, lane % legs, *asym != gen);
+            s = leg.from;
+            tgt = leg.to;
+            last = leg.last;
+        } else {
+            s = src[q];
+        }
         const bool s_ok = s >= 0 && s < V && allowed_v(reg, allowed[q / qdiv], s) && !((vis[sl(s)] >> lane) & 1);
         if (target) {
             // a target that is not allowed, or forbidden, is never reached:
             // the query is resolved (-1) without a search
-            tgt = target[q];
+            if (!kLegs) tgt = target[q];
             done = !(s_ok && tgt >= 0 && tgt < V && allowed_v(reg, allowed[q / qdiv], tgt) &&
                      !((vis[sl(tgt)] >> lane) & 1));
         }
@@ -291,11 +350,11 @@ __global__ __launch_bounds__(kBitsetThreads) void k_rc_bitset(int32_t V, const i
         // A query whose target is allowed and has a neighbour in its
         // frontier at distance d is resolved at d + 1 without expanding
         // that frontier: list each such target's adjacency once.  Only on
-        // a symmetric graph (*sym == 1), where the target's list names
+        // a symmetric graph (*asym != gen), where the target's list names
         // exactly the vertices whose lists name the target.
         int32_t deg = 0, b = 0;
         bool t_allowed = false;
-        if (target && !done && *sym == 1) {
+        if (target && !done && *asym != gen) {
             const int64_t b64 = adj_off[tgt], e64 = adj_off[tgt + 1];
             t_allowed = allowed_v(reg, allowed[qid[lane] / qdiv], tgt);
             if (t_allowed && pc_range_ok(b64, e64, n_adj)) {
@@ -415,7 +474,15 @@ __global__ __launch_bounds__(kBitsetThreads) void k_rc_bitset(int32_t V, const i
         // only after the next level's second barrier
         if (nfr[cur ^ 1] == 0 || flag_done) break;
     }
-    if (target && tid < 64 && lane < nq) dist[qid[lane]] = res;
+    if (kLegs) {
+        if (tid < 64) {
+            WalkLength w;
+            for (int32_t k = 0; k < legs; ++k) w.add(__shfl(res, (lane + k) & 63, 64), __shfl(last, (lane + k) & 63, 64));
+            if (lane < nq && lane % legs == 0) dist[qid[lane]] = w.length();
+        }
+    } else if (target && tid < 64 && lane < nq) {
+        dist[qid[lane]] = res;
+    }
 }
 
 // Neighbour records for the map search: word j of a vertex's 64 bytes is
@@ -763,69 +830,81 @@ __global__ __launch_bounds__(kQueueThreads) void k_rc_queue(int32_t V, const int
 
 namespace {
 
-void validate(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj, int64_t n_adj,
-              const uint8_t *region, int32_t Q, const int32_t *src, const int32_t *target, hipStream_t stream)
+// Data errors and, with sym, the graph's symmetry (see k_rc_checks): it is
+// symmetric unless *asym(ctx) holds the number returned.
+int32_t checks(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj, int64_t n_adj,
+               const uint8_t *region, int32_t Q, const int32_t *src, const int32_t *target, const int32_t *via,
+               int32_t Kv, const int32_t *forbid, int32_t Kf, bool sym, hipStream_t stream)
 {
-    const int64_t nval = (V > Q ? V : Q) > n_adj ? (V > Q ? V : Q) : n_adj;
-    if (nval > 0) {
-        int64_t blocks = (nval + 255) / 256;
-        if (blocks > 4096) blocks = 4096;
-        PC_TIMED(ctx, "k_rc_validate", stream, hipLaunchKernelGGL(k_rc_validate, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream, V, adj_off, adj,
-                           n_adj, region, Q, src, target, ctx->d_err));
-    }
+    if (sym) ctx->reach_gen = ctx->reach_gen == INT32_MAX ? 1 : ctx->reach_gen + 1;
+    const Checks c{V, adj_off, adj, n_adj, region, Q, src, target, static_cast<int64_t>(Q) * Kv,
+                   static_cast<int64_t>(Q) * Kf, via, forbid, ctx->d_small + 4, sym ? ctx->reach_gen : 0, ctx->d_err};
+    const int64_t n = std::max<int64_t>({V, Q, n_adj, c.nv, c.nf});
+    int64_t blocks = std::min<int64_t>((n + 255) / 256, 4096);
+    if (sym) blocks = std::max<int64_t>(blocks, std::min<int64_t>((V + 3) / 4, 8192));
+    if (blocks > 0)
+        PC_TIMED(ctx, "k_rc_checks", stream,
+                 hipLaunchKernelGGL(k_rc_checks, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, stream, c));
+    return c.gen;
 }
 
-// The symmetry flag of the graph, in ctx->d_small[4] (1 = symmetric,
-// sorted lists; see k_rc_symcheck).
-int32_t *symcheck(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj, int64_t n_adj,
-                  hipStream_t stream)
+// Does the bitset search take Q queries (legs)?  The graph has to fit its
+// LDS.  Few queries on a sparse graph would leave most of the
+// chip idle and pass over every vertex on each of many levels (bitset /
+// map, rows: 6,000 vertices of mean degree 4, 256 queries 272 / 80 us, 1,024
+// queries 280 / 145 us, 4,096 queries 309 / 424 us; 1,000 vertices, 64 queries
+// 46 / 33 us, 1,024 queries 75 / 77 us; 100 vertices, 64 queries 20 / 33 us).
+// Denser graphs have few levels (1,280 switches of degree 32, 64 queries
+// 41 / 36 us; 2,880 of degree 48 80 / 84 us): the bitset search keeps them.
+size_t bitset_lds(int32_t V)
 {
-    int32_t *sym = ctx->d_small + 4;
-    launch_fill_u32(reinterpret_cast<uint32_t *>(sym), 1, 1u, stream);
-    if (V > 0)
-        PC_TIMED(ctx, "k_rc_symcheck", stream,
-                 hipLaunchKernelGGL(k_rc_symcheck, dim3(static_cast<unsigned>(std::min<int64_t>((V + 3) / 4, 8192))),
-                                    dim3(256), 0, stream, V, adj_off, adj, n_adj, sym));
-    return sym;
+    // visited / frontier / next (8 B each), region (1 B) and list (2 B) per vertex
+    return ((static_cast<size_t>(V) + 15) & ~size_t(15)) * 3 * 8 + 32 * 8 + ((static_cast<size_t>(V) + 3) & ~size_t(3)) +
+           static_cast<size_t>(V) * 2;
+}
+
+bool takes_bitset(int32_t V, int64_t n_adj, int64_t Q)
+{
+    static_assert(kMaxBitsetV * 27 + 256 + kBitsetStatic <= 160 * 1024, "within a workgroup's LDS");
+    return V > 0 && V <= kMaxBitsetV && !(n_adj / V <= kEll / 2 && V >= 512 && Q <= 1024);
+}
+
+// Are the queries (legs) ordered by source?  Workgroups then share
+// frontiers and expand each for more of their queries, which pays for the
+// four launches of the sort only with enough workgroups and vertices.
+// Sorted / unsorted, targets: 20,000 queries on 1,280 vertices 40 / 31 us,
+// 266,666 on 80 143 / 114, 66,666 on 1,280 62 / 72, 20,000 on 2,880 49 / 55.
+// Legs (unsorted they are computed and summed in the search, and the two
+// legs of a waypoint share its workgroup): 6,000 walks of two legs on 1,280
+// vertices 56 / 43, 20,000 on 320 55 / 44, 66,666 on 320 90 / 103, 4,000 on
+// 2,880 82 / 90.  Rows: 20,000 queries on 320 vertices 53 / 38, 6,000 on
+// 2,880 103 / 96, 20,000 on 1,280 85 / 75.
+bool sorts(int32_t V, int64_t Q, bool legs)
+{
+    return Q > 64 && Q * V > (legs ? int64_t(1) << 24 : int64_t(1) << 25);
 }
 
 // BFS of Q queries; query j's allowed mask is allowed[j / qdiv] and its
-// forbidden list forbid[(j / qdiv) * Kf ...] (Kf = 0: none).  sym: the
-// graph's symmetry flag when the caller has it, else nullptr.  Takes the
-// context's arena when it needs scratch.
+// forbidden list forbid[(j / qdiv) * Kf ...] (Kf = 0: none).  gen: what
+// checks() returned.  via (bitset search, no sort): the queries are walks of
+// Kv + 1 legs.  Takes the context's arena when it needs scratch.
 int bfs(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj, int64_t n_adj, const uint8_t *region,
         int32_t Q, const int32_t *src, const uint32_t *allowed, const int32_t *target, int32_t *dist,
-        const int32_t *forbid, int32_t Kf, int32_t qdiv, const int32_t *sym, hipStream_t stream)
+        const int32_t *forbid, int32_t Kf, int32_t qdiv, int32_t gen, const int32_t *via, int32_t Kv,
+        hipStream_t stream)
 {
     if (V == 0) {
         if (target) launch_fill_u32(reinterpret_cast<uint32_t *>(dist), static_cast<size_t>(Q), 0xFFFFFFFFu, stream);
         PC_LAUNCH_CHECK(ctx);
         return PC_OK;
     }
-    int max_lds = 0;
-    PC_HIP(ctx, hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device));
-    // visited / frontier / next (8 B each), region (1 B) and list (2 B) per vertex
-    const size_t lds = ((static_cast<size_t>(V) + 15) & ~size_t(15)) * 3 * 8 + 32 * 8 +
-                       ((static_cast<size_t>(V) + 3) & ~size_t(3)) + static_cast<size_t>(V) * 2;
-    hipFuncAttributes fa{};
-    PC_HIP(ctx, hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(k_rc_bitset<16>)));  // static LDS
-    // Few queries on a sparse graph: the bitset search would leave most of the
-    // chip idle and pass over every vertex on each of many levels (bitset /
-    // map, rows: 6,000 vertices of mean degree 4, 256 queries 272 / 80 us, 1,024
-    // queries 280 / 145 us, 4,096 queries 309 / 424 us; 1,000 vertices, 64 queries
-    // 46 / 33 us, 1,024 queries 75 / 77 us; 100 vertices, 64 queries 20 / 33 us).
-    // Denser graphs have few levels (1,280 switches of degree 32, 64 queries
-    // 41 / 36 us; 2,880 of degree 48 80 / 84 us): the bitset search keeps them.
     const int64_t avg = n_adj / V;
-    const bool deep = avg <= kEll / 2 && V >= 512 && Q <= 1024;
-    if (V <= kMaxBitsetV && !deep && lds + fa.sharedSizeBytes <= static_cast<size_t>(max_lds)) {
-        if (!sym && target) sym = symcheck(ctx, V, adj_off, adj, n_adj, stream);
-        if (!sym) sym = ctx->d_small + 5;  // full rows: no look-ahead reads it
+    if (takes_bitset(V, n_adj, via ? static_cast<int64_t>(Q) * (Kv + 1) : Q)) {
+        const size_t lds = bitset_lds(V);
         if (!target) launch_fill_u32(reinterpret_cast<uint32_t *>(dist), static_cast<size_t>(Q) * V, 0xFFFFFFFFu, stream);
         PC_LAUNCH_CHECK(ctx);
-        // more than one workgroup: order the queries by source
         int32_t *perm = nullptr;
-        if (Q > 64) {
+        if (!via && sorts(V, Q, qdiv > 1)) {
             int32_t *cnt, *off, *pos;
             auto carve = [&](Carver &c) {
                 cnt = c.take<int32_t>(static_cast<size_t>(V) + 2);
@@ -852,21 +931,32 @@ int bfs(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj, int6
         }
         // lanes per vertex: a power of two near a third of the mean degree
         const int gs = avg <= 12 ? 4 : avg <= 24 ? 8 : avg <= 48 ? 16 : 32;
-        const dim3 grid_b(static_cast<unsigned>((Q + 63) / 64));
+        const int32_t per = via ? 64 / (Kv + 1) : 64;
+        const dim3 grid_b(static_cast<unsigned>((static_cast<int64_t>(Q) + per - 1) / per));
         auto launch = [&](auto kern) -> int {
-            PC_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
+            if (lds > 48 * 1024)
+                PC_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)));
             PC_TIMED(ctx, "k_rc_bitset", stream,
                      hipLaunchKernelGGL(kern, grid_b, dim3(kBitsetThreads), lds, stream, V, adj_off, adj, n_adj,
-                                        region, Q, src, allowed, target, dist, forbid, Kf, qdiv, sym, perm));
+                                        region, Q, src, allowed, target, dist, forbid, Kf, qdiv, ctx->d_small + 4, gen,
+                                        perm, via, Kv));
             PC_LAUNCH_CHECK(ctx);
             return PC_OK;
         };
-        if (gs == 4) return launch(k_rc_bitset<4>);
-        if (gs == 8) return launch(k_rc_bitset<8>);
-        if (gs == 16) return launch(k_rc_bitset<16>);
-        return launch(k_rc_bitset<32>);
+        if (via) {
+            if (gs == 4) return launch(k_rc_bitset<4, true>);
+            if (gs == 8) return launch(k_rc_bitset<8, true>);
+            if (gs == 16) return launch(k_rc_bitset<16, true>);
+            return launch(k_rc_bitset<32, true>);
+        }
+        if (gs == 4) return launch(k_rc_bitset<4, false>);
+        if (gs == 8) return launch(k_rc_bitset<8, false>);
+        if (gs == 16) return launch(k_rc_bitset<16, false>);
+        return launch(k_rc_bitset<32, false>);
     }
+    int max_lds = 0;
+    PC_HIP(ctx, hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device));
     const size_t lds_m = (static_cast<size_t>(V) + 127) / 128 * 16;
     hipFuncAttributes fm{};
     PC_HIP(ctx, hipFuncGetAttributes(&fm, reinterpret_cast<const void *>(k_rc_map<4, true>)));
@@ -924,59 +1014,29 @@ int bfs(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj, int6
     return PC_OK;
 }
 
-// Leg k of query q (k <= m, m = waypoints before the first -1) runs from the
-// previous waypoint (or src) to the next one (or target); legs past m are
-// inactive (src -1).  On a symmetric graph (*sym == 1) legs 0, 2, 4, ... are
-// searched from their far end, so that legs 2j and 2j + 1 start at the same
-// waypoint and share their frontiers in the workgroup's bitsets.
 __global__ void k_rc_legs(int32_t Q, const int32_t *__restrict__ src, const int32_t *__restrict__ target,
-                          const int32_t *__restrict__ via, int32_t Kv, const int32_t *__restrict__ sym,
+                          const int32_t *__restrict__ via, int32_t Kv, const int32_t *__restrict__ asym, int32_t gen,
                           int32_t *__restrict__ leg_src, int32_t *__restrict__ leg_tgt)
 {
-    const bool flip = *sym == 1;
     const int32_t q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= Q) return;
-    const int32_t *w = via + static_cast<int64_t>(q) * Kv;
-    int32_t *ls = leg_src + static_cast<int64_t>(q) * (Kv + 1);
-    int32_t *lt = leg_tgt + static_cast<int64_t>(q) * (Kv + 1);
-    int32_t from = src[q];
-    bool active = true;
+    const bool flip = *asym != gen;
     for (int32_t k = 0; k <= Kv; ++k) {
-        const int32_t nxt = k < Kv ? w[k] : -1;
-        if (!active) {
-            ls[k] = -1;
-            lt[k] = -1;
-        } else {
-            const int32_t to = nxt == -1 ? target[q] : nxt;  // the last leg ends at the target
-            const bool rev = flip && (k & 1) == 0;
-            ls[k] = rev ? to : from;
-            lt[k] = rev ? from : to;
-            from = to;
-            active = nxt != -1;
-        }
+        const Leg leg = leg_of(src, target, via + static_cast<int64_t>(q) * Kv, Kv, q, k, flip);
+        leg_src[static_cast<int64_t>(q) * (Kv + 1) + k] = leg.from;
+        leg_tgt[static_cast<int64_t>(q) * (Kv + 1) + k] = leg.to;
     }
 }
 
-// dist[q] = sum of the distances of q's active legs, -1 if any is -1
-// (saturating at INT32_MAX).
 __global__ void k_rc_via_sum(int32_t Q, const int32_t *__restrict__ via, int32_t Kv,
                              const int32_t *__restrict__ leg_dist, int32_t *__restrict__ dist)
 {
     const int32_t q = blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= Q) return;
-    const int32_t *w = via + static_cast<int64_t>(q) * Kv;
-    const int32_t *ld = leg_dist + static_cast<int64_t>(q) * (Kv + 1);
-    int64_t total = 0;
-    for (int32_t k = 0; k <= Kv; ++k) {
-        const int32_t d = ld[k];
-        if (d < 0) {
-            total = -1;
-            break;
-        }
-        total += d;
-        if (k == Kv || w[k] == -1) break;
-    }
-    dist[q] = static_cast<int32_t>(total > 0x7FFFFFFF ? 0x7FFFFFFF : total);
+    WalkLength w;
+    for (int32_t k = 0; k <= Kv && w.open; ++k)
+        w.add(leg_dist[static_cast<int64_t>(q) * (Kv + 1) + k], k == Kv || via[static_cast<int64_t>(q) * Kv + k] == -1);
+    dist[q] = w.length();
 }
 
 }  // namespace
@@ -985,9 +1045,11 @@ int run_reach(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj
               const uint8_t *region, int32_t Q, const int32_t *src, const uint32_t *allowed, const int32_t *target,
               int32_t *dist, hipStream_t stream)
 {
-    validate(ctx, V, adj_off, adj, n_adj, region, Q, src, target, stream);
+    const int32_t gen = checks(ctx, V, adj_off, adj, n_adj, region, Q, src, target, nullptr, 0, nullptr, 0,
+                               target && takes_bitset(V, n_adj, Q), stream);
     PC_LAUNCH_CHECK(ctx);
-    return bfs(ctx, V, adj_off, adj, n_adj, region, Q, src, allowed, target, dist, nullptr, 0, 1, nullptr, stream);
+    return bfs(ctx, V, adj_off, adj, n_adj, region, Q, src, allowed, target, dist, nullptr, 0, 1, gen, nullptr, 0,
+               stream);
 }
 
 int run_reach_via(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj, int64_t n_adj,
@@ -995,24 +1057,17 @@ int run_reach_via(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t 
                   const int32_t *target, const int32_t *via, int32_t Kv, const int32_t *forbid, int32_t Kf,
                   int32_t *dist, hipStream_t stream)
 {
-    validate(ctx, V, adj_off, adj, n_adj, region, Q, src, target, stream);
-    const int64_t nv = static_cast<int64_t>(Q) * Kv, nf = static_cast<int64_t>(Q) * Kf;
-    if (nv > 0)
-        PC_TIMED(ctx, "k_rc_id_check", stream,
-                 hipLaunchKernelGGL(k_rc_id_check, dim3(static_cast<unsigned>(std::min<int64_t>((nv + 255) / 256, 4096))),
-                                    dim3(256), 0, stream, nv, via, V, ctx->d_err));
-    if (nf > 0)
-        PC_TIMED(ctx, "k_rc_id_check", stream,
-                 hipLaunchKernelGGL(k_rc_id_check, dim3(static_cast<unsigned>(std::min<int64_t>((nf + 255) / 256, 4096))),
-                                    dim3(256), 0, stream, nf, forbid, V, ctx->d_err));
+    const int64_t nl = static_cast<int64_t>(Q) * (Kv + 1);
+    const bool bits = takes_bitset(V, n_adj, nl);
+    const int32_t gen = checks(ctx, V, adj_off, adj, n_adj, region, Q, src, target, via, Kv, forbid, Kf,
+                               Q > 0 && (Kv > 0 || bits), stream);
     PC_LAUNCH_CHECK(ctx);
     if (Q == 0) return PC_OK;
-    if (Kv == 0)
-        return bfs(ctx, V, adj_off, adj, n_adj, region, Q, src, allowed, target, dist, forbid, Kf, 1, nullptr,
-                   stream);
+    if (Kv == 0 || (bits && !sorts(V, nl, true)))
+        return bfs(ctx, V, adj_off, adj, n_adj, region, Q, src, allowed, target, dist, forbid, Kf, 1, gen,
+                   Kv == 0 ? nullptr : via, Kv, stream);
     // legs [Q][Kv + 1] (sources, targets, distances) in the auxiliary
     // buffer; leg j belongs to query j / (Kv + 1)
-    const int64_t nl = static_cast<int64_t>(Q) * (Kv + 1);
     if (nl > 0x7FFFFFFF) return pc_set_error(ctx, PC_EINVAL, "pc_masked_reach_via: Q*(Kv+1) over 2^31 legs");
     int32_t *leg_src, *leg_tgt, *leg_dist;
     auto carve = [&](Carver &c) {
@@ -1027,13 +1082,12 @@ int run_reach_via(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t 
     Carver real{ctx->aux, 0};
     carve(real);
     const unsigned qb = static_cast<unsigned>((Q + 255) / 256);
-    const int32_t *sym = symcheck(ctx, V, adj_off, adj, n_adj, stream);
     PC_TIMED(ctx, "k_rc_legs", stream,
-             hipLaunchKernelGGL(k_rc_legs, dim3(qb), dim3(256), 0, stream, Q, src, target, via, Kv, sym, leg_src,
-                                leg_tgt));
+             hipLaunchKernelGGL(k_rc_legs, dim3(qb), dim3(256), 0, stream, Q, src, target, via, Kv, ctx->d_small + 4,
+                                gen, leg_src, leg_tgt));
     PC_LAUNCH_CHECK(ctx);
     rc = bfs(ctx, V, adj_off, adj, n_adj, region, static_cast<int32_t>(nl), leg_src, allowed, leg_tgt, leg_dist,
-             forbid, Kf, Kv + 1, sym, stream);
+             forbid, Kf, Kv + 1, gen, nullptr, 0, stream);
     if (rc) return rc;
     PC_TIMED(ctx, "k_rc_via_sum", stream,
              hipLaunchKernelGGL(k_rc_via_sum, dim3(qb), dim3(256), 0, stream, Q, via, Kv, leg_dist, dist));

@@ -361,3 +361,39 @@ def test_trace_many_switches(g, orc, T):
     a = (S, off, peer, (np.arange(S) % 31).astype(np.uint8), off, rules, synth.random_keys(rng, T),
          rng.integers(0, S, size=T).astype(np.int32), 200)
     assert np.array_equal(g.trace(*a), orc.trace(*a)[0])
+
+
+@pytest.mark.parametrize("k,Q,Kv", [(6, 65, 0), (6, 33, 1), (6, 43, 2), (8, 200, 20), (8, 70, 31), (8, 61, 32),
+                                    (32, 6553, 1), (32, 6554, 1), (32, 4400, 2), (32, 26300, 0)])
+def test_reach_bitset_orders(g, orc, k, Q, Kv):
+    """Legs searched and summed by their workgroup, and in source order past 2^24 legs x vertices (2^25 targets without
+    legs): whole-query remainders, lists cut at every length, forbidden vertices, and on one context a graph that is
+    symmetric, one that is not, and the first again, with invalid lists in between."""
+    import paper_2602_16100_amd as pc
+    topo = synth.fat_tree(k, 4)
+    S, off, adj = topo["S"], topo["adj_off"], topo["adj"].copy()
+    rng = np.random.default_rng(k * Q + Kv)
+    src, target = (rng.integers(0, S, size=Q).astype(np.int32) for _ in range(2))
+    allowed = rng.integers(0, 16, size=Q).astype(np.uint32)
+    allowed[::2] = 15
+    via, forbid = _via_lists(rng, Q, S, Kv, 3, src, target)
+    oneway = adj.copy()
+    for u in (1, S // 2):  # this vertex's list names others that do not name it
+        oneway[off[u]:off[u + 1]] = np.sort(rng.integers(0, S, off[u + 1] - off[u]))
+    bad_via, bad_adj = via.copy(), adj.copy()
+    if Kv:
+        bad_via[Q // 2, 0] = S + 3
+    bad_adj[off[3]] = -7
+    ctx = pc.context()
+    some = 0
+    for a, v in ((adj, via), (oneway, via), (adj, via), (bad_adj, bad_via), (adj, via)):
+        ctx.data_errors(clear=True)
+        dg = g.reach_via(S, off, a, topo["jur"], src, allowed, target, v, forbid)
+        flags = ctx.data_errors(clear=True)
+        do, err = orc.reach_via(S, off, a, topo["jur"], src, allowed, target, v, forbid)
+        _same(dg, do, "reach_via")
+        assert flags == err
+        some += (do >= 0).sum()
+        if k == 32 and a is oneway:
+            break
+    assert some > 0
