@@ -8,14 +8,16 @@
 //
 // Design (gfx950):
 //   1. presence  : which values of each label occur at all.
-//   2. label scan: plane numbering -- one plane per present (label, value).
+//   2. label scan: plane numbering -- one plane per present (label, value);
+//                  on small inputs by the last presence workgroup.
 //   3. planes    : one 64-bit node set per (plane, 64-node word), built with
 //                  a ballot per present value; row-major, Wp words a plane.
-//   4. compile   : one thread per row turns its predicates into a clause
+//                  For the affinity paths also the prefix planes.
+//   4. compile   : eight lanes per row turn its predicates into a clause
 //                  program over plane ids (In S = OR of S's planes or NOT OR
 //                  of the rest, whichever is shorter; NotIn the reverse;
-//                  Exists = NOT the absent-value plane), validates it, and
-//                  writes a 64-byte row record holding programs of up to 15
+//                  Exists = NOT the absent-value plane), validate it, and
+//                  write a 64-byte row record holding programs of up to 15
 //                  entries inline.
 //   5. eval      : one row at a time per wavefront over a tile of 128 words
 //                  (two per lane, 16-byte loads and stores).  The row's
@@ -27,6 +29,7 @@
 //                  128-byte lines.  Per-lane popcounts are collected as
 //                  bytes in LDS and summed once per 64 rows; a last pass
 //                  sums the tiles.
+// Small clusters take none of these: k_sel_small.
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
@@ -51,15 +54,77 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t x)
     return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
+// What a call clears before it counts, merges or reads: its presence sets,
+// the all-zero plane, its counters.  One launch, or the validation's.
+struct Clears {
+    uint64_t *p[4];
+    int64_t n[4];
+    uint64_t v[4];
+    __device__ __forceinline__ void run() const
+    {
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n[k];
+                 i += static_cast<int64_t>(gridDim.x) * blockDim.x)
+                p[k][i] = v[k];
+    }
+};
+
+__global__ __launch_bounds__(256) void k_sel_clear(Clears c) { c.run(); }
+
+// A call's counters (64-bit words, cleared): workgroups done with the
+// presence sets, the entries of prog used, the class lists' lengths.
+constexpr int kCtlDone = 0, kCtlProg = 1, kCtlLists = 2, kCtlWords = 4;
+
+// Exclusive scan of per-label plane counts -> wbase[l][k] = id of the first
+// plane of label l whose value lies in 64-value word k.  One workgroup of kT threads.
+template <int kT, class Load>
+__device__ __forceinline__ void scan_labels(int32_t L, uint32_t *__restrict__ wbase, Load &&present)
+{
+    constexpr int kW = kT / 64;
+    __shared__ uint32_t wsum[kW];
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    uint32_t carry = 0;
+    for (int32_t base = 0; base < L; base += kT) {
+        const int32_t l = base + tid;
+        uint32_t c[4] = {0, 0, 0, 0};
+        if (l < L)
+            for (int k = 0; k < 4; ++k) c[k] = __popcll(present(static_cast<int64_t>(l) * 4 + k));
+        const uint32_t v = c[0] + c[1] + c[2] + c[3];
+        uint32_t x = v;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            uint32_t y = __shfl_up(x, off, 64);
+            if (lane >= off) x += y;
+        }
+        if (lane == 63) wsum[wid] = x;
+        __syncthreads();
+        uint32_t excl = carry + x - v;
+        for (int w = 0; w < kW; ++w) {
+            if (w < wid) excl += wsum[w];
+            carry += wsum[w];
+        }
+        if (l < L) {
+            for (int k = 0; k < 4; ++k) {
+                wbase[static_cast<int64_t>(l) * 4 + k] = excl;
+                excl += c[k];
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // Which values each label has: labels is read as one flat array in 16-byte
 // pieces (from the first 16-byte boundary on; the bytes before it and after
 // the last piece one by one), a byte at a time tested against, and if new
 // OR-ed into, the workgroup's LDS table (L x 256 bits), which is OR-ed into
 // present32 at the end.  After the first nodes nearly every byte is only an
 // LDS read.  100,000 nodes x 64 labels (6.4 MB): 38 us by single bytes, now 16.
+// With done, the last workgroup to finish (no workgroup waits) numbers the planes.
 constexpr int32_t kPresenceLdsL = 1024;  // labels whose table fits 32 KB
 __global__ __launch_bounds__(256) void k_sel_presence_flat(const uint8_t *__restrict__ labels, int64_t n_bytes,
-                                                           int32_t L, uint32_t *present32)
+                                                           int32_t L, uint32_t *present32,
+                                                           uint32_t *__restrict__ wbase, uint64_t *done)
 {
     extern __shared__ uint32_t ptab[];  // [L][8]
     for (int32_t i = threadIdx.x; i < L * 8; i += 256) ptab[i] = 0;
@@ -97,8 +162,27 @@ __global__ __launch_bounds__(256) void k_sel_presence_flat(const uint8_t *__rest
         for (int64_t o = tail + threadIdx.x; o < n_bytes; o += 256) put(static_cast<uint32_t>(o % L), labels[o]);
     }
     __syncthreads();
+    if (done == nullptr) {
+        for (int32_t i = threadIdx.x; i < L * 8; i += 256)
+            if (ptab[i] & ~present32[i]) atomicOr(&present32[i], ptab[i]);  // (mostly known by then: no contended atomics)
+        return;
+    }
+    // An atomic that has returned its old value has been performed, so the
+    // count below comes after this workgroup's sets without a fence (an
+    // agent-wide release writes the L2 back: 100,000 nodes 89 us with one).
+    uint32_t seen = 0;
     for (int32_t i = threadIdx.x; i < L * 8; i += 256)
-        if (ptab[i] & ~present32[i]) atomicOr(&present32[i], ptab[i]);  // (mostly known by then: no contended atomics)
+        if (ptab[i] & ~present32[i]) seen |= atomicOr(&present32[i], ptab[i]);
+    asm volatile("" ::"v"(seen) : "memory");
+    __shared__ bool last;
+    __syncthreads();
+    if (threadIdx.x == 0) last = atomicAdd(reinterpret_cast<unsigned long long *>(done), 1ull) + 1 == gridDim.x;
+    __syncthreads();
+    if (!last) return;
+    const uint64_t *present = reinterpret_cast<const uint64_t *>(present32);
+    scan_labels<256>(L, wbase, [&](int64_t i) {
+        return __hip_atomic_load(present + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    });
 }
 
 // The same for more labels than the table holds: a tile of 64 labels per workgroup column.
@@ -132,53 +216,10 @@ __global__ __launch_bounds__(256) void k_sel_presence(const uint8_t *__restrict_
     }
 }
 
-// Exclusive scan of per-label plane counts -> wbase[l][k] = id of the first
-// plane of label l whose value lies in 64-value word k.
 __global__ __launch_bounds__(1024) void k_sel_label_scan(const uint64_t *__restrict__ present, int32_t L,
-                                                         uint32_t *__restrict__ wbase, int32_t *__restrict__ d_P)
+                                                         uint32_t *__restrict__ wbase)
 {
-    __shared__ uint32_t wsum[16];
-    __shared__ uint32_t carry_s;
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-    if (tid == 0) carry_s = 0;
-    __syncthreads();
-    for (int32_t base = 0; base < L; base += 1024) {
-        const int32_t l = base + tid;
-        uint32_t c[4] = {0, 0, 0, 0};
-        if (l < L)
-            for (int k = 0; k < 4; ++k) c[k] = __popcll(present[static_cast<int64_t>(l) * 4 + k]);
-        const uint32_t v = c[0] + c[1] + c[2] + c[3];
-        uint32_t x = v;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            uint32_t y = __shfl_up(x, off, 64);
-            if (lane >= off) x += y;
-        }
-        if (lane == 63) wsum[wid] = x;
-        __syncthreads();
-        if (wid == 0) {
-            uint32_t w = lane < 16 ? wsum[lane] : 0;
-#pragma unroll
-            for (int off = 1; off < 16; off <<= 1) {
-                uint32_t y = __shfl_up(w, off, 64);
-                if (lane >= off) w += y;
-            }
-            if (lane < 16) wsum[lane] = w;
-        }
-        __syncthreads();
-        const uint32_t carry = carry_s;
-        uint32_t excl = carry + (wid ? wsum[wid - 1] : 0) + x - v;
-        if (l < L) {
-            for (int k = 0; k < 4; ++k) {
-                wbase[static_cast<int64_t>(l) * 4 + k] = excl;
-                excl += c[k];
-            }
-        }
-        __syncthreads();
-        if (tid == 0) carry_s = carry + wsum[15];
-        __syncthreads();
-    }
-    if (tid == 0) *d_P = static_cast<int32_t>(carry_s);
+    scan_labels<1024>(L, wbase, [&](int64_t i) { return present[i]; });
 }
 
 // A wavefront builds kPlaneWords words (1,024 nodes) of one label's planes, so
@@ -192,13 +233,18 @@ __global__ __launch_bounds__(1024) void k_sel_label_scan(const uint64_t *__restr
 // Word w of plane p lives at planes[p * Wp + kPad + w].
 // 100,000 nodes x 64 labels: 78 us with a word per wavefront (8 bytes of a line
 // written at a time), now 25; 50,000 nodes 44 us, now 16.
+// kPrefix (the affinity paths): also plane pfx0 + p for each plane p of value v
+// (not the absent value's) = OR of the label's planes of present values <= v, so that
+// Gt / Lt take at most two entries (cmp_clause): an OR scan over the four values of
+// a store, carried from store to store.  64 labels over 5,037 nodes: planes 11 us
+// and, reading them again, prefix planes 11 in a launch of its own, now 13 together.
 constexpr int kPlaneWords = 16;
 constexpr int kBallots = 8;
-template <bool kWide>
+template <bool kWide, bool kPrefix>
 __global__ __launch_bounds__(256) void k_sel_planes(const uint8_t *__restrict__ labels, int32_t N, int32_t L,
                                                     const uint64_t *__restrict__ present,
                                                     const uint32_t *__restrict__ wbase, uint64_t *__restrict__ planes,
-                                                    int64_t Wp)
+                                                    int64_t Wp, uint32_t pfx0)
 {
     constexpr int kRow = 2 * kPlaneWords + 2;  // dwords per value of the tile: neighbouring values in other banks
     __shared__ __align__(8) uint32_t tiles[4][64 * kRow];
@@ -223,9 +269,25 @@ __global__ __launch_bounds__(256) void k_sel_planes(const uint8_t *__restrict__ 
     }
     const int col = lane & (kPlaneWords - 1), slot = lane / kPlaneWords;
     const bool store = w0 + col < W;
+    uint64_t acc = 0;  // column col of the label's last prefix plane
+    // words col of values v0 + slot of k4 (word 0 past the last) to their planes
+    auto put = [&](uint64_t *out, int v0, int n, bool absent_last, uint64_t word) {
+        const bool here = store && v0 + slot < n;
+        if (here) out[static_cast<int64_t>(v0 + slot) * Wp + col] = word;
+        if constexpr (kPrefix) {
+            const uint64_t one = __shfl_up(word, kPlaneWords, 64);
+            uint64_t x = word | (slot >= 1 ? one : 0);
+            const uint64_t two = __shfl_up(x, 2 * kPlaneWords, 64);
+            x |= (slot >= 2 ? two : 0) | acc;
+            if (here && !(absent_last && v0 + slot == n - 1))
+                out[(static_cast<int64_t>(pfx0) + v0 + slot) * Wp + col] = x;
+            acc = __shfl(x, 3 * kPlaneWords + col, 64);
+        }
+    };
     for (int k4 = 0; k4 < 4; ++k4) {
         const uint64_t here = uniform_u64(present[static_cast<int64_t>(l) * 4 + k4]);
         const int n = __popcll(here);
+        const bool absent_last = k4 == 3 && here >> 63;
         uint64_t *out = planes + static_cast<int64_t>(__builtin_amdgcn_readfirstlane(wbase[static_cast<int64_t>(l) * 4 + k4])) * Wp +
                         kPad + w0;
         if (n > kBallots) {
@@ -241,10 +303,9 @@ __global__ __launch_bounds__(256) void k_sel_planes(const uint8_t *__restrict__ 
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            for (int v = slot; v < n; v += 4)
-                if (store)
-                    out[static_cast<int64_t>(v) * Wp + col] =
-                        *reinterpret_cast<const uint64_t *>(tile + v * kRow + 2 * col);
+            for (int v0 = 0; v0 < n; v0 += 4)
+                put(out, v0, n, absent_last,
+                    v0 + slot < n ? *reinterpret_cast<const uint64_t *>(tile + (v0 + slot) * kRow + 2 * col) : 0);
             __builtin_amdgcn_wave_barrier();
             continue;
         }
@@ -262,8 +323,7 @@ __global__ __launch_bounds__(256) void k_sel_planes(const uint8_t *__restrict__ 
                     word = lane == j * kPlaneWords + k ? b : word;
                 }
             }
-            if (store && v0 + slot < n)
-                out[static_cast<int64_t>(v0 + slot) * Wp + col] = word;
+            put(out, v0, n, absent_last, word);
         }
     }
 }
@@ -273,6 +333,128 @@ __device__ __forceinline__ bool pred_valid(uint32_t label, uint32_t op, uint32_t
 {
     return static_cast<int32_t>(label) < L && op <= 2 && rsv0 == 0 && rsv1 == 0 &&
            (op == PC_OP_EXISTS || (v3 >> 63) == 0);
+}
+
+// Small clusters: every row evaluated from the labels themselves in one
+// launch, without planes or programs.  A workgroup holds the cluster's
+// labels in LDS and takes a row per wavefront; lane j of a wavefront has node j of
+// each 64-node word, so that a predicate test ends in a ballot, and a row's
+// predicates come by scalar loads.  Labels are kept per label in quads of words:
+// dword (w / 4) * 64 + j of a label's row holds node j of words w..w+3, a byte each.
+// Bound by launch and latency: 64 rows over 16 nodes 35 us in seven launches, now
+// 15 (most of it the caller's); later ones by the scalar loads and 64-bit shifts
+// of a test, about 120 clocks per predicate and word.
+constexpr int kSmallThreads = 1024;
+constexpr size_t kSmallLds = 64 * 1024;      // labels of the cluster, at most: two workgroups per CU
+constexpr int64_t kSmallW = 8;               // words of a row, at most
+constexpr int64_t kSmallWork = 400000;       // predicates x (words + 2), at most
+
+// bytes of a label's row: whole pairs of quads, and a dword against bank conflicts
+__host__ __device__ inline int64_t small_pitch(int64_t W) { return (W + 7) / 8 * 8 * 64 + 4; }
+
+template <int kWords>  // words tested together: 1, 4 or 8
+__global__ __launch_bounds__(kSmallThreads) void k_sel_small(const uint8_t *__restrict__ labels, int32_t N, int32_t L,
+                                                             const int32_t *__restrict__ pred_off,
+                                                             const pc_pred *__restrict__ preds, int64_t n_preds,
+                                                             int32_t I, int32_t W, uint64_t *__restrict__ feasible,
+                                                             uint32_t *__restrict__ popcnt,
+                                                             uint32_t *__restrict__ d_err)
+{
+    extern __shared__ uint32_t small_lab[];
+    uint8_t *lab8 = reinterpret_cast<uint8_t *>(small_lab);
+    const int32_t pitch = static_cast<int32_t>(small_pitch(W));
+    auto put = [&](int32_t n, int32_t l, uint32_t x) {
+        lab8[l * pitch + (n >> 8) * 256 + (n & 63) * 4 + ((n >> 6) & 3)] = static_cast<uint8_t>(x);
+    };
+    const int32_t n_bytes = N * L;
+    const int32_t n_dwords = (reinterpret_cast<uintptr_t>(labels) & 3) == 0 ? n_bytes / 4 : 0;
+    constexpr int kAhead = 8;  // loads in flight
+    for (int32_t i0 = threadIdx.x; i0 < n_dwords; i0 += kAhead * kSmallThreads) {
+        uint32_t x[kAhead];
+#pragma unroll
+        for (int c = 0; c < kAhead; ++c)
+            x[c] = reinterpret_cast<const uint32_t *>(labels)[min(i0 + c * kSmallThreads, n_dwords - 1)];
+#pragma unroll
+        for (int c = 0; c < kAhead; ++c) {
+            const int32_t i = i0 + c * kSmallThreads;
+            if (i >= n_dwords) break;
+            int32_t n = 4 * i / L, l = 4 * i - n * L;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                put(n, l, (x[c] >> (8 * k)) & 255);
+                if (++l == L) {
+                    l = 0;
+                    ++n;
+                }
+            }
+        }
+    }
+    for (int32_t i = 4 * n_dwords + threadIdx.x; i < n_bytes; i += kSmallThreads) put(i / L, i % L, labels[i]);
+    __syncthreads();
+
+    const int lane = threadIdx.x & 63;
+    constexpr int kWaves = kSmallThreads / 64;
+    uint32_t errs = 0;
+    for (int32_t r = blockIdx.x * kWaves + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); r < I;
+         r += gridDim.x * kWaves) {
+        const int64_t b = pred_off[r], e = pred_off[r + 1];
+        bool good = pc_range_ok(b, e, n_preds);
+        if (!good) errs |= PC_DERR_OFFSETS;
+        uint32_t cnt = 0;
+        uint64_t mine = 0;  // lane j: word j of the current 64
+        for (int32_t w0 = 0; w0 < W; w0 += kWords) {
+            uint64_t hold[kWords];
+#pragma unroll
+            for (int k = 0; k < kWords; ++k) {
+                const int32_t left = N - (w0 + k) * 64;
+                hold[k] = left >= 64 ? ~0ull : left > 0 ? (1ull << left) - 1 : 0ull;
+            }
+            pc_pred ahead;
+            if (good && b < e) ahead = preds[b];
+            for (int64_t p = b; good && p < e;) {
+                const pc_pred q = ahead;
+                if (++p < e) ahead = preds[p];
+                if (!pred_valid(q.label, q.op, q.rsv0, q.rsv1, q.vals[3], L)) {
+                    errs |= PC_DERR_PRED;
+                    good = false;
+                    break;
+                }
+                const uint32_t *at = small_lab + (q.label * pitch >> 2) + (w0 >> 2) * 64 + lane;
+                uint32_t x4[(kWords + 3) / 4];
+#pragma unroll
+                for (int k = 0; k < (kWords + 3) / 4; ++k) x4[k] = at[64 * k];
+                auto test = [&](auto admits) {
+#pragma unroll
+                    for (int k = 0; k < kWords; ++k) {
+                        const uint32_t x = (x4[k / 4] >> (8 * (k & 3))) & 255;
+                        hold[k] &= admits(x);
+                    }
+                };
+                const uint64_t flip = q.op == PC_OP_NOTIN ? ~0ull : 0ull;
+                if (q.op == PC_OP_EXISTS) {
+                    test([&](uint32_t x) { return __ballot(x != PC_LABEL_ABSENT); });
+                } else if ((q.vals[1] | q.vals[2] | q.vals[3]) == 0) {
+                    test([&](uint32_t x) { return __ballot(x < 64 && ((q.vals[0] >> (x & 63)) & 1)) ^ flip; });
+                } else {
+                    test([&](uint32_t x) {
+                        const uint64_t lo = x & 64 ? q.vals[1] : q.vals[0], hi = x & 64 ? q.vals[3] : q.vals[2];
+                        return __ballot(((x & 128 ? hi : lo) >> (x & 63)) & 1) ^ flip;
+                    });
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < kWords; ++k) {
+                const uint64_t h = good ? hold[k] : 0;
+                cnt += __popcll(h);
+                mine = lane == ((w0 + k) & 63) ? h : mine;
+            }
+            const int32_t base = w0 & ~63;
+            if (feasible != nullptr && ((w0 & 63) == 64 - kWords || w0 + kWords >= W) && base + lane < W)
+                feasible[static_cast<int64_t>(r) * W + base + lane] = mine;
+        }
+        if (lane == 0) popcnt[r] = cnt;
+    }
+    if (errs && lane == 0) atomicOr(d_err, errs);
 }
 
 // Program entries: plane id, plus flags on the last entry of a clause
@@ -582,8 +764,9 @@ __global__ __launch_bounds__(kCompThreads) void k_sel_compile(const int32_t *__r
 __global__ __launch_bounds__(256) void k_aff_validate(const int32_t *__restrict__ row_off, int32_t I,
                                                       const int32_t *__restrict__ term_off, int32_t n_terms,
                                                       const pc_pred *__restrict__ preds, int64_t n_preds, int32_t L,
-                                                      uint32_t *__restrict__ d_err)
+                                                      uint32_t *__restrict__ d_err, Clears clears)
 {
+    clears.run();
     uint32_t errs = 0;
     const int64_t tot = I > n_terms ? I : n_terms;
     for (int64_t x = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; x < tot;
@@ -1326,8 +1509,9 @@ __global__ __launch_bounds__(256) void k_pref_validate(const int32_t *__restrict
                                                        const int32_t *__restrict__ term_off, int32_t n_terms,
                                                        const uint32_t *__restrict__ weight,
                                                        const pc_pred *__restrict__ preds, int64_t n_preds, int32_t L,
-                                                       uint32_t *__restrict__ d_err)
+                                                       uint32_t *__restrict__ d_err, Clears clears)
 {
+    clears.run();
     uint32_t errs = 0;
     const int64_t tot = I > n_terms ? I : n_terms;
     for (int64_t x = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; x < tot;
@@ -2026,59 +2210,32 @@ EvalGeom eval_geom(int32_t N)
     return g;
 }
 
-// Prefix planes of the affinity paths: plane pfx0 + plane_id(v) = OR of the
-// planes of the label's present values <= v (v in 0..254), so that Gt / Lt
-// take at most two entries (cmp_clause).  One thread per (label, plane
-// word), over the label's present values in increasing order.
-__global__ __launch_bounds__(256) void k_aff_prefix(const uint64_t *__restrict__ present,
-                                                    const uint32_t *__restrict__ wbase, int32_t L,
-                                                    uint64_t *__restrict__ planes, int64_t Wp, uint32_t pfx0)
+Clears clears(uint64_t *present, int32_t L, uint64_t *planes, int64_t pzero, int64_t Wp, uint64_t *ctl,
+              uint64_t *ones = nullptr, int64_t n_ones = 0)
 {
-    const int64_t idx = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (idx >= static_cast<int64_t>(L) * Wp) return;
-    const int32_t l = static_cast<int32_t>(idx / Wp);
-    const int64_t w = idx % Wp;
-    const uint64_t *pres = present + static_cast<int64_t>(l) * 4;
-    const uint32_t *wb = wbase + static_cast<int64_t>(l) * 4;
-    uint64_t acc = 0;
-    for (int k = 0; k < 4; ++k) {
-        uint64_t m = pres[k];
-        if (k == 3) m &= ~(1ull << 63);  // the absent value has no prefix plane
-        // the present values of one 64-value word have consecutive planes:
-        // eight loads in flight (one at a time: 31 us for 64 labels over 5,037
-        // nodes, now 10)
-        const int n = __popcll(m);
-        const uint64_t *in = planes + static_cast<int64_t>(wb[k]) * Wp + w;
-        uint64_t *out = planes + static_cast<int64_t>(pfx0 + wb[k]) * Wp + w;
-        for (int j0 = 0; j0 < n; j0 += 8) {
-            uint64_t x[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) x[j] = j0 + j < n ? in[(j0 + j) * Wp] : 0ull;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                acc |= x[j];
-                if (j0 + j < n) out[(j0 + j) * Wp] = acc;
-            }
-        }
-    }
+    return Clears{{present, planes + pzero * Wp, ctl, ones},
+                  {static_cast<int64_t>(L) * 4, Wp, kCtlWords, n_ones},
+                  {0, 0, 0, ~0ull}};
 }
 
-// Value planes of the node labels: presence, plane numbering (d_P = P),
-// the planes themselves, and the all-zero plane pmax.
-int build_planes(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, int64_t W, int64_t Wp, int64_t pmax,
-                 uint64_t *present, uint32_t *wbase, uint64_t *planes, int32_t *d_P, hipStream_t stream)
+// Value planes of the node labels: presence, plane numbering, the planes
+// themselves and, for a pfx0 other than 0, the prefix planes (present, the all-zero
+// plane and ctl are cleared).
+int build_planes(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, int64_t W, int64_t Wp, uint32_t pfx0,
+                 uint64_t *present, uint32_t *wbase, uint64_t *planes, uint64_t *ctl, hipStream_t stream)
 {
-    launch_fill_u64(present, static_cast<size_t>(L) * 4, 0, stream);
-    if (Wp > 0) launch_fill_u64(planes + static_cast<size_t>(pmax) * Wp, static_cast<size_t>(Wp), 0, stream);
-    if (L == 0) launch_fill_u32(reinterpret_cast<uint32_t *>(d_P), 1, 0, stream);
-    PC_LAUNCH_CHECK(ctx);
+    bool numbered = false;
     if (N > 0 && L > 0) {
         if (L <= kPresenceLdsL) {
             const int64_t n_bytes = static_cast<int64_t>(N) * L;
             const unsigned blocks = static_cast<unsigned>(std::min<int64_t>((n_bytes + (4 << 10) - 1) / (4 << 10), 1024));
+            // Few workgroups: the last one numbers the planes (one launch less, 3 us).
+            // Many queue up for the count (1,024: 26 us, against 17 and 6 apart).
+            numbered = blocks <= 256;
             PC_TIMED(ctx, "k_sel_presence", stream,
                      hipLaunchKernelGGL(k_sel_presence_flat, dim3(blocks), dim3(256), static_cast<size_t>(L) * 32,
-                                        stream, labels, n_bytes, L, reinterpret_cast<uint32_t *>(present)));
+                                        stream, labels, n_bytes, L, reinterpret_cast<uint32_t *>(present), wbase,
+                                        numbered ? ctl + kCtlDone : nullptr));
             PC_LAUNCH_CHECK(ctx);
         } else {
             // about 2048 workgroups: a few hundred nodes each
@@ -2093,33 +2250,20 @@ int build_planes(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, int64
             PC_LAUNCH_CHECK(ctx);
         }
     }
-    if (L > 0) {
+    if (L > 0 && !numbered) {
         PC_TIMED(ctx, "k_sel_label_scan", stream,
-                 hipLaunchKernelGGL(k_sel_label_scan, dim3(1), dim3(1024), 0, stream, present, L, wbase, d_P));
+                 hipLaunchKernelGGL(k_sel_label_scan, dim3(1), dim3(1024), 0, stream, present, L, wbase));
         PC_LAUNCH_CHECK(ctx);
     }
     if (N > 0 && L > 0) {
         dim3 gb(static_cast<unsigned>((W + kPlaneWords - 1) / kPlaneWords), static_cast<unsigned>((L + 3) / 4));
         const bool wide = L % 4 == 0 && (reinterpret_cast<uintptr_t>(labels) & 3) == 0;
-        const auto kern = wide ? k_sel_planes<true> : k_sel_planes<false>;
+        const auto kern = pfx0 ? (wide ? k_sel_planes<true, true> : k_sel_planes<false, true>)
+                               : (wide ? k_sel_planes<true, false> : k_sel_planes<false, false>);
         PC_TIMED(ctx, "k_sel_planes", stream,
-                 hipLaunchKernelGGL(kern, gb, dim3(256), 0, stream, labels, N, L, present, wbase, planes, Wp));
+                 hipLaunchKernelGGL(kern, gb, dim3(256), 0, stream, labels, N, L, present, wbase, planes, Wp, pfx0));
         PC_LAUNCH_CHECK(ctx);
     }
-    return PC_OK;
-}
-
-// The prefix planes pmax + 1 + [0, pmax) of the affinity paths (after
-// build_planes).
-int build_prefix(pc_ctx *ctx, int32_t L, int64_t Wp, int64_t pmax, const uint64_t *present, const uint32_t *wbase,
-                 uint64_t *planes, hipStream_t stream)
-{
-    const int64_t n = static_cast<int64_t>(L) * Wp;
-    if (n == 0) return PC_OK;
-    PC_TIMED(ctx, "k_aff_prefix", stream,
-             hipLaunchKernelGGL(k_aff_prefix, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, stream,
-                                present, wbase, L, planes, Wp, static_cast<uint32_t>(pmax + 1)));
-    PC_LAUNCH_CHECK(ctx);
     return PC_OK;
 }
 
@@ -2200,9 +2344,8 @@ int run_selectors(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, cons
     if (plane_bytes > (size_t(64) << 30))
         return pc_set_error(ctx, PC_ENOMEM, "pc_eval_selectors: value planes need %zu bytes (L=%d N=%d)", plane_bytes,
                             L, N);
-    uint64_t *present, *planes;
+    uint64_t *present, *planes, *ctl;
     uint32_t *wbase, *prog, *rec, *part;
-    int32_t *d_P;
     auto carve = [&](Carver &cv) {
         present = cv.take<uint64_t>(static_cast<size_t>(L) * 4 + 1);
         wbase = cv.take<uint32_t>(static_cast<size_t>(L) * 4 + 1);
@@ -2210,7 +2353,26 @@ int run_selectors(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, cons
         prog = cv.take<uint32_t>(static_cast<size_t>(n_preds) * 4 + 4);
         rec = cv.take<uint32_t>(static_cast<size_t>(I) * kRecWords + kRecWords);
         part = ntiles > 1 ? cv.take<uint32_t>(static_cast<size_t>(ntiles) * I + 1) : nullptr;
-        d_P = cv.take<int32_t>(1);
+        ctl = cv.take<uint64_t>(kCtlWords);
+    };
+    // Few words and predicates: the labels themselves, in one launch.  Planes
+    // and programs / labels: 43 to 6,000 rows over 16 nodes 35 / 15 us, 20,000 rows
+    // over 64 34 / 20, 6,000 over 300 34 / 18, 20,000 over 300 36 / 35; past the
+    // limits 60,000 rows over 64 nodes 48 / 50, 6,000 over 1,500 35 / 50.
+    const size_t small_lds = static_cast<size_t>(L) * static_cast<size_t>(small_pitch(W));
+    const bool small = W > 0 && W <= kSmallW && small_lds <= kSmallLds && n_preds <= kSmallWork / (W + 2);
+    auto launch_small = [&]() -> int {
+        const unsigned blocks = static_cast<unsigned>(std::min(I / (kSmallThreads / 64) + 1, 512));
+        const auto kern = W == 1 ? k_sel_small<1> : W <= 4 ? k_sel_small<4> : k_sel_small<8>;
+        if (small_lds > 48 * 1024)
+            PC_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(small_lds)));
+        PC_TIMED(ctx, "k_sel_small", stream,
+                 hipLaunchKernelGGL(kern, dim3(blocks), dim3(kSmallThreads), small_lds, stream, labels, N, L,
+                                    pred_off, preds, n_preds, I, static_cast<int32_t>(W), feasible, popcnt,
+                                    ctx->d_err));
+        PC_LAUNCH_CHECK(ctx);
+        return PC_OK;
     };
     Carver dry{nullptr, 0};
     carve(dry);
@@ -2228,10 +2390,14 @@ int run_selectors(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, cons
     }
     Carver real{base, 0};
     carve(real);
+    if (small) return launch_small();
     int rc = PC_OK;
 
     if (W == 0) launch_fill_u32(popcnt, static_cast<size_t>(I), 0, stream);
-    rc = build_planes(ctx, labels, N, L, W, Wp, pmax, present, wbase, planes, d_P, stream);
+    PC_TIMED(ctx, "k_sel_clear", stream,
+             hipLaunchKernelGGL(k_sel_clear, dim3(static_cast<unsigned>(std::max<int64_t>(int64_t(4) * L, Wp) / 1024 + 1)),
+                                dim3(256), 0, stream, clears(present, L, planes, pmax, Wp, ctl)));
+    rc = build_planes(ctx, labels, N, L, W, Wp, 0, present, wbase, planes, ctl, stream);
     if (rc) return rc;
     constexpr int kRows = kCompThreads / kSelLanes;  // rows per workgroup
     const unsigned rgrid = static_cast<unsigned>(std::min<int64_t>((I + kRows - 1) / kRows, 65536));
@@ -2260,10 +2426,8 @@ int run_affinity(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, const
     // indirect programs take slices of prog: room for 4 entries per
     // expression on average, rounded per row; the rest decode on the fly
     const int64_t prog_cap = 4 * n_preds + 4 * static_cast<int64_t>(I) + 64;
-    uint64_t *present, *planes;
+    uint64_t *present, *planes, *ctl;
     uint32_t *wbase, *prog, *rec, *part;
-    int32_t *d_P;
-    unsigned long long *prog_used;
     auto carve = [&](Carver &cv) {
         present = cv.take<uint64_t>(static_cast<size_t>(L) * 4 + 1);
         wbase = cv.take<uint32_t>(static_cast<size_t>(L) * 4 + 1);
@@ -2271,8 +2435,7 @@ int run_affinity(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, const
         prog = cv.take<uint32_t>(static_cast<size_t>(prog_cap));
         rec = cv.take<uint32_t>(static_cast<size_t>(I) * kRecWords + kRecWords);
         part = ntiles > 1 ? cv.take<uint32_t>(static_cast<size_t>(ntiles) * I + 1) : nullptr;
-        d_P = cv.take<int32_t>(1);
-        prog_used = cv.take<unsigned long long>(1);
+        ctl = cv.take<uint64_t>(kCtlWords);
     };
     Carver dry{nullptr, 0};
     carve(dry);
@@ -2286,15 +2449,12 @@ int run_affinity(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, const
         const unsigned vgrid = static_cast<unsigned>(std::min<int64_t>((nval + 255) / 256, 8192));
         PC_TIMED(ctx, "k_aff_validate", stream,
                  hipLaunchKernelGGL(k_aff_validate, dim3(vgrid), dim3(256), 0, stream, row_off, I, term_off, n_terms,
-                                    preds, n_preds, L, ctx->d_err));
+                                    preds, n_preds, L, ctx->d_err, clears(present, L, planes, pmax, Wp, ctl)));
         PC_LAUNCH_CHECK(ctx);
     }
     if (I == 0) return PC_OK;
     if (W == 0) launch_fill_u32(popcnt, static_cast<size_t>(I), 0, stream);
-    launch_fill_u64(reinterpret_cast<uint64_t *>(prog_used), 1, 0, stream);
-    rc = build_planes(ctx, labels, N, L, W, Wp, pmax, present, wbase, planes, d_P, stream);
-    if (rc) return rc;
-    rc = build_prefix(ctx, L, Wp, pmax, present, wbase, planes, stream);
+    rc = build_planes(ctx, labels, N, L, W, Wp, static_cast<uint32_t>(pmax + 1), present, wbase, planes, ctl, stream);
     if (rc) return rc;
     const bool groups = I < kAffGroupRows;
     const int64_t rows = groups ? 256 / kAffLanes : 256;  // per workgroup
@@ -2303,7 +2463,7 @@ int run_affinity(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, const
     PC_TIMED(ctx, "k_aff_compile", stream,
              hipLaunchKernelGGL(kern, dim3(rgrid), dim3(256), 0, stream, row_off, I, term_off, n_terms,
                                 preds, n_preds, L, present, wbase, prog, prog_cap,
-                                prog_used, rec, unknown, static_cast<uint32_t>(pmax + 1)));
+                                reinterpret_cast<unsigned long long *>(ctl + kCtlProg), rec, unknown, static_cast<uint32_t>(pmax + 1)));
     PC_LAUNCH_CHECK(ctx);
     if (W == 0) return PC_OK;
     return launch_eval<true>(ctx, rec, prog, row_off, preds, present, wbase, planes, ptop, Wp, I, W, N, feasible,
@@ -2326,10 +2486,9 @@ int run_preferred(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, cons
                             plane_bytes, L, N);
     // room for a header per term and 4 entries per expression; rows beyond it decode on the fly
     const int64_t prog_cap = std::min<int64_t>(static_cast<int64_t>(n_terms) + 4 * n_preds + 64, int64_t(1) << 31);
-    uint64_t *present, *planes, *part_key, *ones;
-    uint32_t *wbase, *prog, *rec, *part_cnt, *list_len;
-    int32_t *d_P, *list;
-    unsigned long long *prog_used;
+    uint64_t *present, *planes, *part_key, *ones, *ctl;
+    uint32_t *wbase, *prog, *rec, *part_cnt;
+    int32_t *list;
     auto carve = [&](Carver &cv) {
         present = cv.take<uint64_t>(static_cast<size_t>(L) * 4 + 1);
         wbase = cv.take<uint32_t>(static_cast<size_t>(L) * 4 + 1);
@@ -2337,12 +2496,10 @@ int run_preferred(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, cons
         prog = cv.take<uint32_t>(static_cast<size_t>(prog_cap));
         rec = cv.take<uint32_t>(static_cast<size_t>(I) * kPrefRec + kPrefRec);
         list = cv.take<int32_t>(static_cast<size_t>(I) * kPrefClasses + 1);
-        list_len = cv.take<uint32_t>(kPrefClasses);
         ones = cv.take<uint64_t>(feasible ? 1 : static_cast<size_t>(W) + 1);
         part_key = cv.take<uint64_t>(static_cast<size_t>(ntiles) * I + 1);
         part_cnt = cv.take<uint32_t>(static_cast<size_t>(ntiles) * I + 1);
-        d_P = cv.take<int32_t>(1);
-        prog_used = cv.take<unsigned long long>(1);
+        ctl = cv.take<uint64_t>(kCtlWords);
     };
     Carver dry{nullptr, 0};
     carve(dry);
@@ -2356,17 +2513,16 @@ int run_preferred(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, cons
         const unsigned vgrid = static_cast<unsigned>(std::min<int64_t>((nval + 255) / 256, 8192));
         PC_TIMED(ctx, "k_pref_validate", stream,
                  hipLaunchKernelGGL(k_pref_validate, dim3(vgrid), dim3(256), 0, stream, row_off, I, term_off, n_terms,
-                                    weight, preds, n_preds, L, ctx->d_err));
+                                    weight, preds, n_preds, L, ctx->d_err,
+                                    clears(present, L, planes, pmax, Wp, ctl, ones, feasible ? 0 : W)));
         PC_LAUNCH_CHECK(ctx);
     }
     if (I == 0) return PC_OK;
-    launch_fill_u64(reinterpret_cast<uint64_t *>(prog_used), 1, 0, stream);
-    launch_fill_u32(list_len, kPrefClasses, 0, stream);
-    if (!feasible && W > 0) launch_fill_u64(ones, static_cast<size_t>(W), ~0ull, stream);
-    rc = build_planes(ctx, labels, N, L, W, Wp, pmax, present, wbase, planes, d_P, stream);
+    rc = build_planes(ctx, labels, N, L, W, Wp, static_cast<uint32_t>(pmax + 1), present, wbase, planes, ctl, stream);
     if (rc) return rc;
-    rc = build_prefix(ctx, L, Wp, pmax, present, wbase, planes, stream);
-    if (rc) return rc;
+    static_assert(kPrefClasses <= 2 * (kCtlWords - kCtlLists), "a length per class list");
+    uint32_t *list_len = reinterpret_cast<uint32_t *>(ctl + kCtlLists);
+    auto *prog_used = reinterpret_cast<unsigned long long *>(ctl + kCtlProg);
     // rows per workgroup: all 256 threads', or 16 at a time (up to 256, so that
     // the class lists' counters are not updated too often)
     const bool groups = I < kPrefGroupRows;

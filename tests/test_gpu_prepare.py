@@ -98,3 +98,54 @@ def test_row_counts_at_the_compile_rules(g, orc, I):
     bg, sg, cg, eg = g.preferred(labels, row_off, term_off, weight, preds)
     bo, so, co, eo = orc.preferred(labels, row_off, term_off, weight, preds)
     assert np.array_equal(bg, bo) and np.array_equal(sg, so) and np.array_equal(cg, co) and eg == eo
+
+
+@pytest.mark.parametrize("N,L,I,shift", [(1, 1, 1, 1), (63, 8, 15, 3), (64, 200, 17, 0), (65, 9, 300, 2), (255, 32, 1500, 0),
+                                         (257, 5, 40, 1), (512, 64, 700, 0), (512, 127, 33, 0), (512, 128, 33, 0),
+                                         (513, 8, 50, 0), (64, 4, 20000, 0), (64, 4, 70000, 0)])
+def test_small_clusters(g, orc, N, L, I, shift):
+    """Rows evaluated from the labels themselves, and the sizes past its limits (words, labels in LDS, predicates):
+    sets of values on both sides of 64, rows without predicates, malformed rows, every alignment of the labels; also
+    the counting and the allocation-free entry point."""
+    import torch
+    import paper_2602_16100_amd as pc
+    rng = np.random.default_rng(N * L + I)
+    cards = rng.choice([1, 2, 16, 64, 65, 200, 255], size=L)
+    labels = synth.gen_labels(rng, N, cards, 0.1)
+    off, preds = synth.gen_preds(rng, I, cards, 0, 7, mmax=4)
+    if I > 30:
+        off[11] = off[12] + 1
+        preds["op"][off[20]:off[21]] = 3
+        preds["label"][off[25]:off[26]] = L
+    flat = torch.zeros(N * L + shift, dtype=torch.uint8, device="cuda")
+    flat[shift:] = torch.from_numpy(labels.reshape(-1)).cuda()
+    lab, o, p = flat[shift:].view(N, L), g.dev(off), g.dev(preds)
+    fo, po, err = orc.selectors(labels, off, preds)
+    ctx = pc.context()
+    for call in ("full", "noalloc", "count"):
+        ctx.data_errors(clear=True)
+        f = torch.full((I, (N + 63) // 64), -1, dtype=torch.int64, device="cuda")
+        c = torch.full((I,), -1, dtype=torch.int32, device="cuda")
+        if call == "full":
+            pc.pc_eval_selectors(lab, o, p, feasible=f, popcnt=c)
+        elif call == "noalloc":
+            pc.pc_eval_selectors_noalloc(lab, o, p, f, c)
+        else:
+            c = pc.pc_eval_selectors_count(lab, o, p)
+        assert ctx.data_errors(clear=True) == err
+        assert np.array_equal(c.cpu().numpy().view(np.uint32), po)
+        if call != "count":
+            assert np.array_equal(f.cpu().numpy().view(np.uint64), fo)
+
+
+@pytest.mark.parametrize("N", [16384, 16385])
+def test_presence_workgroups(g, orc, N):
+    """Planes numbered by the last of 256 workgroups, and by a launch of their own from 257 on; several passes."""
+    rng = np.random.default_rng(N)
+    cards = rng.choice([2, 64, 255], size=64)
+    off, preds = synth.gen_preds(rng, 200, cards, 1, 6, mmax=4)
+    for _ in range(3):
+        labels = synth.gen_labels(rng, N, cards, 0.05)
+        f, p = g.selectors(labels, off, preds)
+        fo, po, _ = orc.selectors(labels, off, preds)
+        assert np.array_equal(f, fo) and np.array_equal(p, po)
