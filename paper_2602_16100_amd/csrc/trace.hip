@@ -163,11 +163,12 @@ __device__ __forceinline__ int2 make_port(int32_t peer, int32_t S, const uint8_t
 
 // Per port and per switch the records above, of tables prepared by an
 // earlier call.
-__global__ void k_tr_port_info(int64_t n_ports, const int32_t *__restrict__ port_off,
-                               const int32_t *__restrict__ port_peer, int32_t S, const uint8_t *__restrict__ jur,
-                               const int32_t *__restrict__ rule_off, int64_t n_rules,
-                               const int32_t *__restrict__ gofs, const uint32_t *__restrict__ cpos,
-                               int2 *__restrict__ pinfo, SwInfo *__restrict__ sinfo)
+__device__ __forceinline__ void port_infos(int64_t n_ports, const int32_t *__restrict__ port_off,
+                                           const int32_t *__restrict__ port_peer, int32_t S,
+                                           const uint8_t *__restrict__ jur, const int32_t *__restrict__ rule_off,
+                                           int64_t n_rules, const int32_t *__restrict__ gofs,
+                                           const uint32_t *__restrict__ cpos, int2 *__restrict__ pinfo,
+                                           SwInfo *__restrict__ sinfo)
 {
     const int64_t tot = n_ports > S ? n_ports : S;
     for (int64_t p = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; p < tot;
@@ -178,6 +179,15 @@ __global__ void k_tr_port_info(int64_t n_ports, const int32_t *__restrict__ port
             sinfo[s] = make_info(s, port_off, n_ports, rule_off, n_rules, gofs[s], cpos[s], true);
         }
     }
+}
+
+__global__ void k_tr_port_info(int64_t n_ports, const int32_t *__restrict__ port_off,
+                               const int32_t *__restrict__ port_peer, int32_t S, const uint8_t *__restrict__ jur,
+                               const int32_t *__restrict__ rule_off, int64_t n_rules,
+                               const int32_t *__restrict__ gofs, const uint32_t *__restrict__ cpos,
+                               int2 *__restrict__ pinfo, SwInfo *__restrict__ sinfo)
+{
+    port_infos(n_ports, port_off, port_peer, S, jur, rule_off, n_rules, gofs, cpos, pinfo, sinfo);
 }
 
 // Input sweeps in one launch: ports (every peer -1 or a switch), watch
@@ -221,15 +231,16 @@ __global__ __launch_bounds__(256) void k_tr_sweep(int64_t n_ports, const int32_t
 
 // Per switch the group count and the exclusive scans of group counts
 // (gofs) and prep blocks (bofs), their totals at [S]; offsets and
-// jurisdictions validated; the header histogram cleared for k_tr_sweep.  One
-// workgroup: with the separate kernels, three launches and a clear.
+// jurisdictions validated; the header histogram cleared for k_tr_sweep; the
+// totals also to host memory.  One workgroup: with the separate kernels, three
+// launches, a clear and two copies.
 constexpr int32_t kLayoutS = 16384;  // switches at most
 __global__ __launch_bounds__(1024) void k_tr_layout(int32_t S, const int32_t *__restrict__ port_off, int64_t n_ports,
                                                     const uint8_t *__restrict__ jur,
                                                     const int32_t *__restrict__ rule_off, int64_t n_rules,
                                                     int32_t *__restrict__ gcount, int32_t *__restrict__ gofs,
                                                     int32_t *__restrict__ bofs, uint32_t *__restrict__ hh,
-                                                    uint32_t *__restrict__ d_err)
+                                                    int32_t *__restrict__ host, uint32_t *__restrict__ d_err)
 {
     constexpr int kPer = 4;  // consecutive switches per thread and pass
     __shared__ int32_t wsum[2][16];
@@ -299,6 +310,9 @@ __global__ __launch_bounds__(1024) void k_tr_layout(int32_t S, const int32_t *__
     if (tid == 0) {
         gofs[S] = carry_s[0];
         bofs[S] = carry_s[1];
+        host[0] = carry_s[0];
+        host[1] = carry_s[1];
+        __threadfence_system();
     }
     if (errs) atomicOr(d_err, errs);
 }
@@ -459,37 +473,22 @@ constexpr int kPrepRounds = 4;                          // 64-rule rounds per wa
 constexpr int kTileStride = kPrepGroups + 2;            // LDS row pitch (spreads a half-wave's rows over banks)
 static_assert(kPrepGroups == 2 * kPrepWaves * kPrepRounds, "two groups per wavefront round");
 
-// Build the chunk sets of kPrepGroups groups of one switch; validate actions.
+// Build the chunk sets of kPrepGroups groups (block b) of switch s; validate actions.
 // Lane r of a half-wave holds rule r of a group and looks up, for each chunk,
 // the 16-bit set of chunk values its value/mask admit (a 256-entry LDS table
 // indexed by the chunk's value & mask and mask).  Two chunks share a word;
 // a 32 x 32 bit transpose over the half-wave turns the rules' admit sets
 // into the group's per-value rule sets: word (chunk c, value x) lands in lane
 // (c % 2) * 16 + x of the transpose of word c / 2.
-__global__ __launch_bounds__(1024) void k_tr_prep(int32_t S, const int32_t *__restrict__ port_off, int64_t n_ports,
-                                                  const int32_t *__restrict__ rule_off,
-                                                  const pc_rule *__restrict__ rules,
-                                                  const int32_t *__restrict__ gcount,
-                                                  const int32_t *__restrict__ gofs, const int32_t *__restrict__ bofs,
-                                                  uint32_t *__restrict__ filt, uint32_t *__restrict__ d_err,
-                                                  const uint32_t *__restrict__ only, uint32_t *__restrict__ sw_bad,
-                                                  const uint32_t *__restrict__ cpos)
+__device__ __forceinline__ void prep_block(int32_t s, int32_t b, uint32_t *tile, uint16_t *admit,
+                                           const int32_t *__restrict__ port_off, int64_t n_ports,
+                                           const int32_t *__restrict__ rule_off, const pc_rule *__restrict__ rules,
+                                           const int32_t *__restrict__ gcount, const int32_t *__restrict__ gofs,
+                                           uint32_t *__restrict__ filt, uint32_t *__restrict__ d_err,
+                                           uint32_t *__restrict__ sw_bad, const uint32_t *__restrict__ cpos)
 {
-    __shared__ uint32_t tile[kPlaneWords * kTileStride];
-    __shared__ uint16_t admit[256];
-    const int32_t b = blockIdx.x;
-    if (b >= bofs[S]) return;
-    // switch owning this block: largest s with bofs[s] <= b
-    int32_t lo = 0, hi = S;  // invariant: bofs[lo] <= b < bofs[hi]
-    while (hi - lo > 1) {
-        const int32_t mid = (lo + hi) >> 1;
-        if (bofs[mid] <= b) lo = mid;
-        else hi = mid;
-    }
-    const int32_t s = lo;
-    if (only != nullptr && !((only[s >> 5] >> (s & 31)) & 1u)) return;  // only the listed switches (whole block)
     const int32_t G = gcount[s];
-    const int32_t g0 = (b - bofs[s]) * kPrepGroups;
+    const int32_t g0 = b * kPrepGroups;
     const int64_t rb = rule_off[s];
     const int64_t R = rule_off[s + 1] - rb;
     const bool pok = pc_range_ok(port_off[s], port_off[s + 1], n_ports);
@@ -563,6 +562,52 @@ __global__ __launch_bounds__(1024) void k_tr_prep(int32_t S, const int32_t *__re
         const int32_t g = g0 + gl;
         if (g < G) dst[static_cast<int64_t>(row) * G + g] = tile[row * kTileStride + gl];
     }
+}
+
+__global__ __launch_bounds__(1024) void k_tr_prep(int32_t S, const int32_t *__restrict__ port_off, int64_t n_ports,
+                                                  const int32_t *__restrict__ rule_off,
+                                                  const pc_rule *__restrict__ rules,
+                                                  const int32_t *__restrict__ gcount,
+                                                  const int32_t *__restrict__ gofs, const int32_t *__restrict__ bofs,
+                                                  uint32_t *__restrict__ filt, uint32_t *__restrict__ d_err,
+                                                  uint32_t *__restrict__ sw_bad, const uint32_t *__restrict__ cpos)
+{
+    __shared__ uint32_t tile[kPlaneWords * kTileStride];
+    __shared__ uint16_t admit[256];
+    const int32_t b = blockIdx.x;
+    if (b >= bofs[S]) return;
+    // switch owning this block: largest s with bofs[s] <= b
+    int32_t lo = 0, hi = S;  // invariant: bofs[lo] <= b < bofs[hi]
+    while (hi - lo > 1) {
+        const int32_t mid = (lo + hi) >> 1;
+        if (bofs[mid] <= b) lo = mid;
+        else hi = mid;
+    }
+    prep_block(lo, b - bofs[lo], tile, admit, port_off, n_ports, rule_off, rules, gcount, gofs, filt, d_err, sw_bad,
+               cpos);
+}
+
+// The same for listed switches, unless *skip: list entry blockIdx.x, its
+// blocks in turn (a repeated switch is done twice, alike).
+__global__ __launch_bounds__(1024) void k_tr_prep_listed(int32_t S, const int32_t *__restrict__ port_off,
+                                                         int64_t n_ports, const int32_t *__restrict__ rule_off,
+                                                         const pc_rule *__restrict__ rules,
+                                                         const int32_t *__restrict__ gcount,
+                                                         const int32_t *__restrict__ gofs,
+                                                         const int32_t *__restrict__ bofs,
+                                                         uint32_t *__restrict__ filt, uint32_t *__restrict__ d_err,
+                                                         uint32_t *__restrict__ sw_bad,
+                                                         const uint32_t *__restrict__ cpos,
+                                                         const int32_t *__restrict__ listed,
+                                                         const uint32_t *__restrict__ skip)
+{
+    __shared__ uint32_t tile[kPlaneWords * kTileStride];
+    __shared__ uint16_t admit[256];
+    if (*skip) return;
+    const int32_t s = listed[blockIdx.x];
+    if (s < 0 || s >= S) return;
+    for (int32_t b = blockIdx.y; b < bofs[s + 1] - bofs[s]; b += gridDim.y)
+        prep_block(s, b, tile, admit, port_off, n_ports, rule_off, rules, gcount, gofs, filt, d_err, sw_bad, cpos);
 }
 
 // Level 0: every trace starts at its ingress switch (an invalid ingress
@@ -819,14 +864,15 @@ __device__ __forceinline__ int32_t item_lookups(int32_t G, int32_t n)
 // Per level: bucket offsets boff = exclusive scan of counts (which are
 // cleared for reuse), work-item offsets ioff = exclusive scan of
 // ceil(counts / item_lookups(G, counts)), *total = the level's lookups (the
-// length of the live list its match writes), and *nlive_next = 0 for the
-// match to count the traces that move on.  One workgroup of 1024 threads;
+// length of the live list its match writes) and *host, and *nlive_next = 0 for
+// the match to count the traces that move on.  One workgroup of 1024 threads;
 // each thread takes kPlanPer consecutive switches per pass, so a pass
 // covers 4,096 switches with all of its loads in flight together.
 constexpr int kPlanPer = 4;
 __global__ __launch_bounds__(1024) void k_tr_plan(int32_t *__restrict__ counts, int32_t S, int32_t *__restrict__ boff,
                                                   int32_t *__restrict__ ioff, const int32_t *__restrict__ gcount,
-                                                  int32_t *__restrict__ total, int32_t *__restrict__ nlive_next)
+                                                  int32_t *__restrict__ total, int32_t *__restrict__ nlive_next,
+                                                  int32_t *__restrict__ host)
 {
     __shared__ int32_t wsum[2][16];
     __shared__ int32_t carry_s[2];
@@ -897,6 +943,8 @@ __global__ __launch_bounds__(1024) void k_tr_plan(int32_t *__restrict__ counts, 
         boff[S] = carry_s[0];
         ioff[S] = carry_s[1];
         *total = carry_s[0];
+        *host = carry_s[0];
+        __threadfence_system();
     }
 }
 
@@ -1369,14 +1417,16 @@ __global__ __launch_bounds__(256) void k_tr_walk(WalkArgs w, const LRec *__restr
     }
 }
 
-// Few traces: every one from its ingress (an invalid ingress ends it at once
-// as MISS), without levels, lists or counts.
+// Few traces: every one (or those of a list) from its ingress (an invalid
+// ingress ends it at once as MISS), without levels or counts.
 __global__ __launch_bounds__(256) void k_tr_walk_all(WalkArgs w, int32_t T, const pc_key *__restrict__ hdr,
                                                      const int32_t *__restrict__ ingress,
-                                                     const uint8_t *__restrict__ jur, uint32_t *__restrict__ d_err)
+                                                     const uint8_t *__restrict__ jur, uint32_t *__restrict__ d_err,
+                                                     const int32_t *__restrict__ list)
 {
     __shared__ unsigned long long best;
-    for (int32_t t = blockIdx.x; t < T; t += gridDim.x) {
+    for (int32_t i = blockIdx.x; i < T; i += gridDim.x) {
+        const int32_t t = list != nullptr ? list[i] : i;
         const int32_t s = __builtin_amdgcn_readfirstlane(ingress[t]);
         const bool in = s >= 0 && s < w.S;
         if (w.walk && threadIdx.x < kWalkSlots)
@@ -1394,30 +1444,102 @@ __global__ __launch_bounds__(256) void k_tr_walk_all(WalkArgs w, int32_t T, cons
 }
 
 // ---------------------------------------------------------------- deltas
+// The state of a delta call on the device: cleared words, then the bitmap of
+// the changed switches.
+struct DeltaState {
+    unsigned long long mask;  // summary bits of the changed switches
+    uint32_t n;               // traces to trace again
+    uint32_t differs;         // the kept tables have another switch's group count
+};
+
 // Summary bits and the bitmap of the changed switches (ids outside [0, S)
-// are ignored and raise SWITCH); one workgroup.
-__global__ __launch_bounds__(256) void k_delta_mask(const int32_t *__restrict__ changed, int32_t C, int32_t S,
-                                                    unsigned long long *__restrict__ mask,
-                                                    uint32_t *__restrict__ bitmap, uint32_t *__restrict__ d_err)
+// are ignored and raise SWITCH).  With kept tables (gold, sw_bad): offsets and
+// jurisdictions validated, the group counts compared with the kept ones
+// (then no chunk set moves), the changed switches' action flags cleared.  A
+// single workgroup (up to kLayoutS switches) clears the state itself;
+// the bitmap's clearing has returned before its setting starts.
+__global__ __launch_bounds__(1024) void k_delta_plan(const int32_t *__restrict__ changed, int32_t C, int32_t S,
+                                                     DeltaState *__restrict__ state, uint32_t *__restrict__ bitmap,
+                                                     int32_t words, const int32_t *__restrict__ port_off,
+                                                     int64_t n_ports, const uint8_t *__restrict__ jur,
+                                                     const int32_t *__restrict__ rule_off, int64_t n_rules,
+                                                     const int32_t *__restrict__ gold, uint32_t *__restrict__ sw_bad,
+                                                     uint32_t *__restrict__ d_err)
 {
     __shared__ unsigned long long m;
-    if (threadIdx.x == 0) m = 0;
+    __shared__ uint32_t differs;
+    const int32_t i0 = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
+    if (threadIdx.x == 0) {
+        m = 0;
+        differs = 0;
+    }
+    uint32_t seen = 0;
+    if (gridDim.x == 1)
+        for (int32_t i = threadIdx.x; i < words; i += blockDim.x) seen |= atomicExch(bitmap + i, 0u);
+    asm volatile("" ::"v"(seen) : "memory");
     __syncthreads();
     uint64_t mine = 0;
-    bool bad = false;
-    for (int32_t i = threadIdx.x; i < C; i += blockDim.x) {
+    uint32_t errs = 0;
+    for (int32_t i = i0; i < C; i += stride) {
         const int32_t s = changed[i];
         if (s < 0 || s >= S) {
-            bad = true;
+            errs |= PC_DERR_SWITCH;
         } else {
             mine |= sum_bit(s);
             atomicOr(bitmap + (s >> 5), 1u << (s & 31));
+            if (sw_bad != nullptr) sw_bad[s] = 0;
         }
     }
     if (mine) atomicOr(&m, static_cast<unsigned long long>(mine));
-    if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(d_err, PC_DERR_SWITCH);
+    bool d = false;
+    if (gold != nullptr)
+        for (int32_t s = i0; s < S; s += stride) {
+            const int64_t rb = rule_off[s], re = rule_off[s + 1];
+            const bool rok = pc_range_ok(rb, re, n_rules);
+            if (jur[s] >= 32) errs |= PC_DERR_JUR;
+            if (!rok || !pc_range_ok(port_off[s], port_off[s + 1], n_ports)) errs |= PC_DERR_OFFSETS;
+            d |= (rok ? static_cast<int32_t>((re - rb + 31) / 32) : 0) != gold[s];
+        }
+    if (d) differs = 1;
+    if (errs) atomicOr(d_err, errs);
     __syncthreads();
-    if (threadIdx.x == 0) *mask = m;
+    if (threadIdx.x != 0) return;
+    if (gridDim.x == 1) {
+        *state = DeltaState{m, 0u, differs};
+    } else {
+        if (m) atomicOr(&state->mask, m);
+        if (differs) atomicOr(&state->differs, 1u);
+    }
+}
+
+// What follows the selection: the counts to the host and the caller, the
+// ports' sweep and, where the kept tables serve, their switch and port
+// records and the ACTION flag of the unchanged switches (k_tr_prep raises it
+// for the others).
+__global__ __launch_bounds__(256) void k_delta_post(const DeltaState *__restrict__ state, int32_t *__restrict__ host,
+                                                    int32_t *__restrict__ n_out, bool kept, int64_t n_ports,
+                                                    const int32_t *__restrict__ port_off,
+                                                    const int32_t *__restrict__ port_peer, int32_t S,
+                                                    const uint8_t *__restrict__ jur,
+                                                    const int32_t *__restrict__ rule_off, int64_t n_rules,
+                                                    const int32_t *__restrict__ gofs,
+                                                    const uint32_t *__restrict__ cpos, int2 *__restrict__ pinfo,
+                                                    SwInfo *__restrict__ sinfo, const uint32_t *__restrict__ sw_bad,
+                                                    uint32_t *__restrict__ d_err)
+{
+    const DeltaState d = *state;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *n_out = static_cast<int32_t>(d.n);
+        host[0] = static_cast<int32_t>(d.n);
+        host[1] = static_cast<int32_t>(d.differs);
+        __threadfence_system();
+    }
+    if (!kept || d.differs) return;
+    uint32_t errs = bad_ids(n_ports, port_peer, S) ? PC_DERR_SWITCH : 0;
+    port_infos(n_ports, port_off, port_peer, S, jur, rule_off, n_rules, gofs, cpos, pinfo, sinfo);
+    for (int32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < S; s += gridDim.x * blockDim.x)
+        if (sw_bad[s]) errs |= PC_DERR_ACTION;
+    if (errs) atomicOr(d_err, errs);
 }
 
 // The traces to trace again, in a list (one counter update per workgroup
@@ -1430,12 +1552,11 @@ __global__ __launch_bounds__(1024) void k_delta_select(const uint64_t *__restric
                                                        const pc_trace_out *__restrict__ out,
                                                        const uint32_t *__restrict__ bitmap,
                                                        const int32_t *__restrict__ ingress, int32_t T, int32_t S,
-                                                       const unsigned long long *__restrict__ mask,
-                                                       int32_t *__restrict__ list, uint32_t *__restrict__ count,
+                                                       DeltaState *__restrict__ state, int32_t *__restrict__ list,
                                                        uint32_t *__restrict__ d_err)
 {
     __shared__ uint32_t wcount[16], wbase[16];
-    const uint64_t m = *mask;
+    const uint64_t m = state->mask;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int64_t base = static_cast<int64_t>(blockIdx.x) * blockDim.x; base < T;
          base += static_cast<int64_t>(gridDim.x) * blockDim.x) {
@@ -1465,7 +1586,7 @@ __global__ __launch_bounds__(1024) void k_delta_select(const uint64_t *__restric
                 wbase[w] = tot;
                 tot += wcount[w];
             }
-            const uint32_t off = tot ? atomicAdd(count, tot) : 0u;
+            const uint32_t off = tot ? atomicAdd(&state->n, tot) : 0u;
             for (int w = 0; w < 16; ++w) wbase[w] += off;
         }
         __syncthreads();
@@ -1493,8 +1614,7 @@ __global__ __launch_bounds__(256) void k_delta_scatter(const int32_t *__restrict
                                                        const uint64_t *__restrict__ vsum_c,
                                                        const int32_t *__restrict__ walk_c,
                                                        pc_trace_out *__restrict__ out, uint64_t *__restrict__ vsum,
-                                                       int32_t *__restrict__ walk,
-                                                       const uint32_t *__restrict__ count, int32_t *__restrict__ n_out)
+                                                       int32_t *__restrict__ walk)
 {
     for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         const int32_t t = list[i];
@@ -1504,36 +1624,26 @@ __global__ __launch_bounds__(256) void k_delta_scatter(const int32_t *__restrict
             for (int j = 0; j < kWalkSlots; ++j)
                 walk[static_cast<int64_t>(t) * kWalkSlots + j] = walk_c[static_cast<int64_t>(i) * kWalkSlots + j];
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *n_out = static_cast<int32_t>(*count);
 }
 
-// Cached prepared tables: 1 in *diff when some switch's group count differs
-// from the cached one.
-__global__ __launch_bounds__(256) void k_tc_compare(const int32_t *__restrict__ gnew, const int32_t *__restrict__ gold,
-                                                    int32_t S, uint32_t *__restrict__ diff)
-{
-    bool d = false;
-    for (int32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < S; s += gridDim.x * blockDim.x) d |= gnew[s] != gold[s];
-    if (__ballot(d) && (threadIdx.x & 63) == 0) atomicOr(diff, 1u);
-}
+// Levels with few traces in flight are cheaper as independent walks than as
+// bucketed passes (tunable with PC_TRACE_WALK_MAX, 0 = never walk): a walk
+// skips its loops, a level costs three launches and a pass over its
+// tables.  Large tables make a walk's hop dearer (24 bytes per 32 rules).
+// Calls that walk from the start / from 8,192 traces on: 60,000 traces over
+// 512 rules per switch (k = 16) 231 / 258 us, over 2,048 (k = 32) 275 / 302,
+// over 32,768 (k = 16) 908 / 835, 30,000 traces there 527 / 803; 4,194,304
+// traces, of which 8,900 loop until their TTL, 2.4 / 3.2 ms.
+struct WalkRule {
+    int64_t most;  // traces at most
+    int threads;   // the walks' workgroup: about two rule groups per lane of a mean table
+};
 
-// Clear the action-error flags of the listed switches (ids outside [0, S) skipped).
-__global__ __launch_bounds__(256) void k_tc_clear(const int32_t *__restrict__ changed, int32_t C, int32_t S,
-                                                  uint32_t *__restrict__ sw_bad)
+WalkRule walk_rule(int64_t mean_groups)
 {
-    for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < C; i += gridDim.x * blockDim.x) {
-        const int32_t s = changed[i];
-        if (s >= 0 && s < S) sw_bad[s] = 0;
-    }
-}
-
-// ACTION when any switch's flag is set.
-__global__ __launch_bounds__(256) void k_tc_badsum(const uint32_t *__restrict__ sw_bad, int32_t S,
-                                                   uint32_t *__restrict__ d_err)
-{
-    bool any = false;
-    for (int32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < S; s += gridDim.x * blockDim.x) any |= sw_bad[s] != 0;
-    if (__ballot(any) && (threadIdx.x & 63) == 0) atomicOr(d_err, PC_DERR_ACTION);
+    WalkRule r{mean_groups <= 128 ? 65536 : 32768, mean_groups <= 128 ? 64 : mean_groups <= 256 ? 128 : 256};
+    if (const char *env = getenv("PC_TRACE_WALK_MAX")) r.most = atoll(env);
+    return r;
 }
 
 unsigned grid_for(int64_t n, int threads)
@@ -1562,7 +1672,8 @@ int sweep_and_choose(pc_ctx *ctx, int32_t S, const int32_t *port_peer, int64_t n
 }
 
 // Group counts and offsets, prep-block offsets (bcount: scratch of the form
-// for many switches) and the zeroed header histogram.
+// for many switches) and the zeroed header histogram; the two totals in
+// ctx->h_small[0], [1] once the stream has come so far.
 int layout(pc_ctx *ctx, int32_t S, const int32_t *port_off, int64_t n_ports, const uint8_t *jur,
            const int32_t *rule_off, int64_t n_rules, int32_t *gcount, int32_t *bcount, int32_t *gofs, int32_t *bofs,
            uint32_t *hh, hipStream_t stream)
@@ -1570,7 +1681,7 @@ int layout(pc_ctx *ctx, int32_t S, const int32_t *port_off, int64_t n_ports, con
     if (S <= kLayoutS) {
         PC_TIMED(ctx, "k_tr_layout", stream,
                  hipLaunchKernelGGL(k_tr_layout, dim3(1), dim3(1024), 0, stream, S, port_off, n_ports, jur, rule_off,
-                                    n_rules, gcount, gofs, bofs, hh, ctx->d_err));
+                                    n_rules, gcount, gofs, bofs, hh, ctx->h_small, ctx->d_err));
     } else {
         PC_TIMED(ctx, "k_tr_switch_info", stream,
                  hipLaunchKernelGGL(k_tr_switch_info, dim3(grid_for(S, 256)), dim3(256), 0, stream, S, port_off,
@@ -1578,6 +1689,8 @@ int layout(pc_ctx *ctx, int32_t S, const int32_t *port_off, int64_t n_ports, con
         launch_scan_i32(gcount, S, gofs, nullptr, nullptr, stream);
         launch_scan_i32(bcount, S, bofs, nullptr, nullptr, stream);
         launch_fill_u32(hh, kKeyNibbles * 16, 0, stream);
+        PC_HIP(ctx, hipMemcpyAsync(ctx->h_small, gofs + S, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
+        PC_HIP(ctx, hipMemcpyAsync(ctx->h_small + 1, bofs + S, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
     }
     PC_LAUNCH_CHECK(ctx);
     return PC_OK;
@@ -1599,19 +1712,9 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         SwInfo *sinfo;
         uint32_t *filt, *cpos, *hh;
     } B;
-    // the walks' workgroup: about two rule groups per lane of a mean table
-    const int64_t mean_groups = S > 0 ? (pre != nullptr ? pre->groups : (n_rules + 31) / 32) / S : 0;
-    const int walk_threads = mean_groups <= 128 ? 64 : mean_groups <= 256 ? 128 : 256;
-    // Levels with few traces in flight are cheaper as independent walks than as
-    // bucketed passes (tunable with PC_TRACE_WALK_MAX, 0 = never walk): a walk
-    // skips its loops, a level costs three launches and a pass over its
-    // tables.  Large tables make a walk's hop dearer (24 bytes per 32 rules).
-    // Calls that walk from the start / from 8,192 traces on: 60,000 traces over
-    // 512 rules per switch (k = 16) 231 / 258 us, over 2,048 (k = 32) 275 / 302,
-    // over 32,768 (k = 16) 908 / 835, 30,000 traces there 527 / 803; 4,194,304
-    // traces, of which 8,900 loop until their TTL, 2.4 / 3.2 ms.
-    int64_t walk_max = mean_groups <= 128 ? 65536 : 32768;
-    if (const char *env = getenv("PC_TRACE_WALK_MAX")) walk_max = atoll(env);
+    const WalkRule rule = walk_rule(S > 0 ? (pre != nullptr ? pre->groups : (n_rules + 31) / 32) / S : 0);
+    const int walk_threads = rule.threads;
+    const int64_t walk_max = rule.most;
     const bool levels = T > walk_max;
     // Few enough traces over tables this small are matched rule by rule: no
     // chunk sets, no wait for their count, two launches.  Chunk sets / rule by
@@ -1686,8 +1789,6 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         // ranges may overlap, so no host-side bound from n_rules holds);
         // the host waits for these two counts only, while the sweeps and
         // the chunk choice, queued behind them, keep the GPU busy
-        PC_HIP(ctx, hipMemcpyAsync(ctx->h_small, B.gofs + S, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
-        PC_HIP(ctx, hipMemcpyAsync(ctx->h_small + 1, B.bofs + S, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
         PC_HIP(ctx, hipEventRecord(ctx->lvl_ev[0], stream));
         rc = sweep_and_choose(ctx, S, port_peer, n_ports, rule_off, n_rules, rules, hdr, T, n_watch, watch, B.hh,
                               B.cpos, inf, stream);
@@ -1702,7 +1803,7 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         if (prep_blocks > 0 && n_rules > 0) {
             PC_TIMED(ctx, "k_tr_prep", stream, hipLaunchKernelGGL(k_tr_prep, dim3(static_cast<unsigned>(prep_blocks)), dim3(kPrepWaves * 64), 0, stream, S,
                                port_off, n_ports, rule_off, rules, B.gcount, B.gofs, B.bofs, B.filt, ctx->d_err,
-                               nullptr, nullptr, B.cpos));
+                               nullptr, B.cpos));
             PC_LAUNCH_CHECK(ctx);
         }
     }
@@ -1711,7 +1812,8 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
     if (!levels) {
         PC_TIMED(ctx, "k_tr_walk", stream,
                  hipLaunchKernelGGL(k_tr_walk_all, dim3(static_cast<unsigned>(std::min(T, 8192))),
-                                    dim3(direct ? 64 : walk_threads), 0, stream, wa, T, hdr, ingress, jur, ctx->d_err));
+                                    dim3(direct ? 64 : walk_threads), 0, stream, wa, T, hdr, ingress, jur, ctx->d_err,
+                                    nullptr));
         PC_LAUNCH_CHECK(ctx);
         return PC_OK;
     }
@@ -1741,8 +1843,8 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
     // counts only shrink, so level L is launched with the latest count the
     // host has (exact for level 0, else the count entering level L - 1) as
     // the bound for its grids, and the kernels read the exact count on the
-    // device.  The count entering level L is copied back after level L - 1
-    // and waited for (an event one level behind) while level L runs.
+    // device.  Level L's plan writes the count entering it to host memory,
+    // and the host waits for that plan while level L runs.
     int32_t *h_cnt = ctx->h_small + 8;  // two pinned slots, by level parity
     int32_t *d_len = ctx->d_small + 6;  // two slots, by level parity: each level's lookups (its live list's length)
     // An upper bound on the count entering the next level (T for level 0:
@@ -1768,7 +1870,8 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         const int32_t nlive = static_cast<int32_t>(known);
         PC_TIMED(ctx, "k_tr_plan", stream,
                  hipLaunchKernelGGL(k_tr_plan, dim3(1), dim3(1024), 0, stream, cnt_cur, S, B.boff, B.ioff,
-                                    B.gcount, d_len + (level & 1), n_nxt));
+                                    B.gcount, d_len + (level & 1), n_nxt, h_cnt + (level & 1)));
+        PC_HIP(ctx, hipEventRecord(ctx->lvl_ev[level & 1], stream));
         PC_TIMED(ctx, "k_tr_scatter", stream,
                  hipLaunchKernelGGL(k_tr_scatter, dim3(grid_for(nlive, 256)), dim3(256), 0, stream, live_cur, len_cur,
                                     T, S, B.boff, B.bucket, B.ioff, B.imap, icap));
@@ -1781,15 +1884,10 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
                                     dim3(kMatchThreads), 0, stream, S, B.sinfo, rules, B.filt, B.boff, B.ioff,
                                     B.imap, B.bucket, lv));
         PC_LAUNCH_CHECK(ctx);
-        // the count leaving this level
-        const int slot = (level + 1) & 1;
-        PC_HIP(ctx, hipMemcpyAsync(h_cnt + slot, n_nxt, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
-        PC_HIP(ctx, hipEventRecord(ctx->lvl_ev[slot], stream));
         if (level == 0) {
             known = nlive;  // the bound for level 1; its exact count is learned after level 0 completes
         } else {
-            // the count entering this level (left by the previous level): its
-            // copy completed before this level started
+            // the count entering this level, written by its plan
             PC_HIP(ctx, hipEventSynchronize(ctx->lvl_ev[level & 1]));
             known = h_cnt[level & 1];
         }
@@ -1839,9 +1937,13 @@ int tc_prepare_all(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_
     if (S > 0) {
         rc = layout(ctx, S, port_off, n_ports, jur, rule_off, n_rules, m.gcount, m.bcount, m.gofs, m.bofs, m.hh, stream);
         if (rc) return rc;
-        PC_HIP(ctx, hipMemcpyAsync(ctx->h_small, m.gofs + S, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
-        PC_HIP(ctx, hipMemcpyAsync(ctx->h_small + 1, m.bofs + S, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
-        PC_HIP(ctx, hipStreamSynchronize(stream));
+        PC_HIP(ctx, hipEventRecord(ctx->lvl_ev[0], stream));
+        // queued while the host waits for the two counts
+        launch_fill_u32(m.sw_bad, static_cast<size_t>(S), 0, stream);
+        rc = sweep_and_choose(ctx, S, port_peer, n_ports, rule_off, n_rules, rules, hdr, T, 0, nullptr, m.hh, m.cpos,
+                              Infos{}, stream);
+        if (rc) return rc;
+        PC_HIP(ctx, hipEventSynchronize(ctx->lvl_ev[0]));
         groups = ctx->h_small[0];
         blocks = ctx->h_small[1];
         if (groups < 0 || blocks < 0)
@@ -1850,16 +1952,11 @@ int tc_prepare_all(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_
     rc = pc_ensure_tc_filt(ctx, static_cast<size_t>(groups + 1) * kPlaneWords * sizeof(uint32_t));
     if (rc) return rc;
     if (S > 0) {
-        launch_fill_u32(m.sw_bad, static_cast<size_t>(S), 0, stream);
-        rc = sweep_and_choose(ctx, S, port_peer, n_ports, rule_off, n_rules, rules, hdr, T, 0, nullptr, m.hh, m.cpos,
-                              Infos{}, stream);
-        if (rc) return rc;
         if (blocks > 0) {
             PC_TIMED(ctx, "k_tr_prep", stream,
                      hipLaunchKernelGGL(k_tr_prep, dim3(static_cast<unsigned>(blocks)), dim3(kPrepWaves * 64), 0,
                                         stream, S, port_off, n_ports, rule_off, rules, m.gcount, m.gofs, m.bofs,
-                                        reinterpret_cast<uint32_t *>(ctx->tc_filt), ctx->d_err, nullptr, m.sw_bad,
-                                        m.cpos));
+                                        reinterpret_cast<uint32_t *>(ctx->tc_filt), ctx->d_err, m.sw_bad, m.cpos));
             PC_LAUNCH_CHECK(ctx);
         }
     }
@@ -1896,91 +1993,101 @@ int run_trace_delta(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32
     int rc = pc_ensure_delta(ctx, need);
     if (rc) return rc;
     Carver cv{ctx->delta, 0};
-    unsigned long long *mask = cv.take<unsigned long long>(1);
-    uint32_t *count = cv.take<uint32_t>(2);  // [0] selected traces, [1] a group count differs from the cache
+    DeltaState *state = cv.take<DeltaState>(1);
+    uint32_t *bitmap = cv.take<uint32_t>(words);
     int32_t *list = cv.take<int32_t>(Tn);
     pc_key *hdr_c = cv.take<pc_key>(Tn);
     int32_t *ing_c = cv.take<int32_t>(Tn);
     pc_trace_out *out_c = cv.take<pc_trace_out>(Tn);
     uint64_t *vsum_c = cv.take<uint64_t>(Tn);
     int32_t *walk_c = cv.take<int32_t>(Tn * kWalkSlots);
-    uint32_t *bitmap = cv.take<uint32_t>(words);
-    int32_t *gnew = cv.take<int32_t>(static_cast<size_t>(S) + 1);
-    int32_t *bnew = cv.take<int32_t>(static_cast<size_t>(S) + 1);
-    launch_fill_u32(count, 2, 0, stream);
-    launch_fill_u32(bitmap, words, 0, stream);
-    PC_TIMED(ctx, "k_delta_mask", stream,
-             hipLaunchKernelGGL(k_delta_mask, dim3(1), dim3(256), 0, stream, changed, C, S, mask, bitmap,
-                                ctx->d_err));
-    PC_LAUNCH_CHECK(ctx);
-    if (T > 0) {
-        PC_TIMED(ctx, "k_delta_select", stream,
-                 hipLaunchKernelGGL(k_delta_select, dim3(grid_for(T, 1024)), dim3(1024), 0, stream, vsum, walk, out,
-                                    bitmap, ingress, T, S, mask, list, count, ctx->d_err));
-        PC_LAUNCH_CHECK(ctx);
-    }
+    int2 *pinfo;
+    SwInfo *sinfo;
+    auto carve = [&](Carver &c) {
+        pinfo = c.take<int2>(static_cast<size_t>(n_ports) + 1);
+        sinfo = c.take<SwInfo>(static_cast<size_t>(S) + 1);
+    };
+    Carver dry{nullptr, 0};
+    carve(dry);
+    rc = pc_ensure_arena(ctx, dry.off);
+    if (rc) return rc;
+    Carver real{ctx->arena, 0};
+    carve(real);
+
     // with reuse declared (pc_trace_keep_tables) the cache holds the previous
     // tables when its switch count matches; it serves the new ones when no
     // switch's group count changed.  Without it every call prepares anew.
     const bool cached = ctx->tc_keep && ctx->tc_S == S && S > 0;
-    if (cached) {
-        const TcMeta m = tc_meta(ctx, S);
-        PC_TIMED(ctx, "k_tr_switch_info", stream,
-                 hipLaunchKernelGGL(k_tr_switch_info, dim3(grid_for(S, 256)), dim3(256), 0, stream, S, port_off,
-                                    n_ports, jur, rule_off, n_rules, gnew, bnew, ctx->d_err));
-        PC_TIMED(ctx, "k_tc_compare", stream,
-                 hipLaunchKernelGGL(k_tc_compare, dim3(grid_for(S, 256)), dim3(256), 0, stream, gnew, m.gcount, S,
-                                    count + 1));
+    const TcMeta kept = cached ? tc_meta(ctx, S) : TcMeta{};
+    const bool one = S <= kLayoutS && C <= kLayoutS;
+    if (!one) {
+        launch_fill_u32(reinterpret_cast<uint32_t *>(state), sizeof(DeltaState) / 4, 0, stream);
+        launch_fill_u32(bitmap, words, 0, stream);
+    }
+    PC_TIMED(ctx, "k_delta_plan", stream,
+             hipLaunchKernelGGL(k_delta_plan, dim3(one ? 1 : grid_for(std::max(S, C), 1024)), dim3(1024), 0, stream,
+                                changed, C, S, state, bitmap, static_cast<int32_t>(words), port_off, n_ports, jur,
+                                rule_off, n_rules, kept.gcount, kept.sw_bad, ctx->d_err));
+    if (T > 0)
+        PC_TIMED(ctx, "k_delta_select", stream,
+                 hipLaunchKernelGGL(k_delta_select, dim3(grid_for(T, 1024)), dim3(1024), 0, stream, vsum, walk, out,
+                                    bitmap, ingress, T, S, state, list, ctx->d_err));
+    PC_TIMED(ctx, "k_delta_post", stream,
+             hipLaunchKernelGGL(k_delta_post,
+                                dim3(cached ? grid_for(std::min<int64_t>(std::max<int64_t>(n_ports, S), 1 << 20), 256) : 1),
+                                dim3(256), 0, stream, state, ctx->h_small, n_retraced, cached, n_ports, port_off,
+                                port_peer, S, jur, rule_off, n_rules, kept.gofs, kept.cpos, pinfo, sinfo, kept.sw_bad,
+                                ctx->d_err));
+    PC_LAUNCH_CHECK(ctx);
+    PC_HIP(ctx, hipEventRecord(ctx->lvl_ev[0], stream));
+    // while the host waits for the counts: the changed switches are prepared
+    // again if the kept tables serve (they keep their filter chunks: any choice is exact)
+    if (cached && ctx->tc_blocks > 0 && C > 0) {
+        // workgroups per listed switch: the mean table's blocks
+        const unsigned per = static_cast<unsigned>(std::min<int64_t>((ctx->tc_blocks + S - 1) / S, 1024));
+        PC_TIMED(ctx, "k_tr_prep_listed", stream,
+                 hipLaunchKernelGGL(k_tr_prep_listed, dim3(static_cast<unsigned>(C), per), dim3(kPrepWaves * 64), 0, stream,
+                                    S, port_off, n_ports, rule_off, rules, kept.gcount, kept.gofs, kept.bofs,
+                                    reinterpret_cast<uint32_t *>(ctx->tc_filt), ctx->d_err, kept.sw_bad,
+                                    kept.cpos, changed, &state->differs));
         PC_LAUNCH_CHECK(ctx);
     }
-    PC_HIP(ctx, hipMemcpyAsync(ctx->h_small, count, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, stream));
-    PC_HIP(ctx, hipStreamSynchronize(stream));
+    PC_HIP(ctx, hipEventSynchronize(ctx->lvl_ev[0]));
     const int32_t n = ctx->h_small[0];
-    if (cached && ctx->h_small[1] == 0) {
-        // re-prepare only the changed switches, then the ACTION flag over all
-        const TcMeta m = tc_meta(ctx, S);
-        if (n_ports > 0) {
-            PC_TIMED(ctx, "k_tr_sweep", stream,
-                     hipLaunchKernelGGL(k_tr_sweep, dim3(static_cast<unsigned>(std::min<int64_t>((n_ports + 1023) / 1024, 256))),
-                                        dim3(256), 0, stream, n_ports, port_peer, S, int64_t(0), nullptr, nullptr, 0,
-                                        nullptr, ctx->d_err));
-        }
-        if (C > 0) {
-            PC_TIMED(ctx, "k_tc_clear", stream,
-                     hipLaunchKernelGGL(k_tc_clear, dim3(grid_for(C, 256)), dim3(256), 0, stream, changed, C, S,
-                                        m.sw_bad));
-        }
-        if (ctx->tc_blocks > 0 && C > 0) {
-            // the changed switches keep their filter chunks (any choice is exact)
-            PC_TIMED(ctx, "k_tr_prep", stream,
-                     hipLaunchKernelGGL(k_tr_prep, dim3(static_cast<unsigned>(ctx->tc_blocks)), dim3(kPrepWaves * 64),
-                                        0, stream, S, port_off, n_ports, rule_off, rules, m.gcount, m.gofs, m.bofs,
-                                        reinterpret_cast<uint32_t *>(ctx->tc_filt), ctx->d_err, bitmap, m.sw_bad,
-                                        m.cpos));
-        }
-        PC_TIMED(ctx, "k_tc_badsum", stream,
-                 hipLaunchKernelGGL(k_tc_badsum, dim3(grid_for(S, 256)), dim3(256), 0, stream, m.sw_bad, S,
-                                    ctx->d_err));
-        PC_LAUNCH_CHECK(ctx);
-    } else {
+    const bool serves = cached && ctx->h_small[1] == 0;
+    if (!serves) {
         rc = tc_prepare_all(ctx, S, port_off, port_peer, n_ports, jur, rule_off, rules, n_rules, hdr, T, stream);
         if (rc) return rc;
     }
-    if (n > 0) {
-        PC_TIMED(ctx, "k_delta_gather", stream,
-                 hipLaunchKernelGGL(k_delta_gather, dim3(grid_for(n, 256)), dim3(256), 0, stream, list, n, hdr,
-                                    ingress, hdr_c, ing_c));
+    if (n == 0) return PC_OK;
+    const TcMeta m = tc_meta(ctx, S);
+    const WalkRule rule = walk_rule(S > 0 ? ctx->tc_groups / S : 0);
+    if (n <= rule.most) {  // walked in place
+        const int64_t n_info = std::max<int64_t>(n_ports, S);
+        if (!serves && n_info > 0)
+            PC_TIMED(ctx, "k_tr_port_info", stream,
+                     hipLaunchKernelGGL(k_tr_port_info, dim3(static_cast<unsigned>(std::min<int64_t>((n_info + 255) / 256, 4096))),
+                                        dim3(256), 0, stream, n_ports, port_off, port_peer, S, jur, rule_off, n_rules,
+                                        m.gofs, m.cpos, pinfo, sinfo));
+        const WalkArgs wa{S, sinfo, pinfo, rules, reinterpret_cast<const uint32_t *>(ctx->tc_filt), ttl, out, nullptr,
+                          0, nullptr, vsum, walk};
+        PC_TIMED(ctx, "k_tr_walk", stream,
+                 hipLaunchKernelGGL(k_tr_walk_all, dim3(static_cast<unsigned>(std::min(n, 8192))), dim3(rule.threads),
+                                    0, stream, wa, n, hdr, ingress, jur, ctx->d_err, list));
         PC_LAUNCH_CHECK(ctx);
-        const TcMeta m = tc_meta(ctx, S);
-        const TracePrep pre{reinterpret_cast<const uint32_t *>(ctx->tc_filt), m.gcount, m.gofs, m.cpos,
-                            ctx->tc_groups};
-        rc = run_trace(ctx, S, port_off, port_peer, n_ports, jur, rule_off, rules, n_rules, hdr_c, ing_c, n, ttl,
-                       nullptr, 0, out_c, nullptr, vsum_c, walk ? walk_c : nullptr, stream, &pre);
-        if (rc) return rc;
+        return PC_OK;
     }
+    PC_TIMED(ctx, "k_delta_gather", stream,
+             hipLaunchKernelGGL(k_delta_gather, dim3(grid_for(n, 256)), dim3(256), 0, stream, list, n, hdr, ingress,
+                                hdr_c, ing_c));
+    PC_LAUNCH_CHECK(ctx);
+    const TracePrep pre{reinterpret_cast<const uint32_t *>(ctx->tc_filt), m.gcount, m.gofs, m.cpos, ctx->tc_groups};
+    rc = run_trace(ctx, S, port_off, port_peer, n_ports, jur, rule_off, rules, n_rules, hdr_c, ing_c, n, ttl, nullptr,
+                   0, out_c, nullptr, vsum_c, walk ? walk_c : nullptr, stream, &pre);
+    if (rc) return rc;
     PC_TIMED(ctx, "k_delta_scatter", stream,
-             hipLaunchKernelGGL(k_delta_scatter, dim3(grid_for(n > 0 ? n : 1, 256)), dim3(256), 0, stream, list, n,
-                                out_c, vsum_c, walk_c, out, vsum, walk, count, n_retraced));
+             hipLaunchKernelGGL(k_delta_scatter, dim3(grid_for(n, 256)), dim3(256), 0, stream, list, n, out_c, vsum_c,
+                                walk_c, out, vsum, walk));
     PC_LAUNCH_CHECK(ctx);
     return PC_OK;
 }

@@ -272,3 +272,48 @@ def test_default_context_prepares_every_call(g, orc):
     # the selected walks meet the switches that changed between A and B as well
     both = np.isin(wb_, [20, 21]).any(axis=1) & np.isin(wb_, [3, 17, 40]).any(axis=1)
     assert both.sum() > 0
+
+
+@pytest.mark.parametrize("walk_max", [None, "0", "50"])
+@pytest.mark.parametrize("ring", [False, True])
+def test_delta_forms(g, orc, monkeypatch, walk_max, ring):
+    """The traces to trace again walked in place, or gathered for a pass by levels; kept tables that serve, that do not
+    (a table resized past a group boundary) and none; a ring of more switches than one workgroup plans; repeated and
+    invalid ids in the list, actions that become invalid and valid again."""
+    import paper_2602_16100_amd as pc
+    if walk_max is not None:
+        monkeypatch.setenv("PC_TRACE_WALK_MAX", walk_max)
+    rng = np.random.default_rng(12)
+    if ring:
+        S = 16390
+        off = np.arange(S + 1, dtype=np.int32)
+        peer = np.roll(np.arange(S, dtype=np.int32), -1)
+        peer[100::1000] = -1
+        wl = dict(S=S, port_off=off, port_peer=peer, jur=(np.arange(S) % 31).astype(np.uint8), rule_off=off,
+                  rules=np.zeros(S, synth.RULE_DT), hdr=synth.random_keys(rng, 3000),
+                  ingress=rng.integers(0, S, 3000).astype(np.int32), ttl=40)
+    else:
+        wl = synth.trace_workload(7, 8, 4, 4200, 2500, 12, 300, variant="dense")
+        S = wl["S"]
+    for keep in (True, False):
+        ctx = pc.Context(0)
+        ctx.keep_tables(keep)
+        rule_off, rules = wl["rule_off"], wl["rules"]
+        rec, vs, wk, _, _ = _run(wl, rule_off, rules, None, None, None, ctx=ctx)
+        for step in range(4):
+            sw = rng.choice(S, size=200 if ring else 5, replace=False).astype(np.int32)
+            resize = step == 2 and not ring
+            rule_off, rules = synth.mutate_tables(60 + step, wl["port_off"], rule_off, rules, sw, resize=resize)
+            if step == 1:  # an action beyond the switch's ports, put right by the next step
+                bad = sw[0]
+                rules = rules.copy()
+                rules["action"][rule_off[bad]:rule_off[bad + 1]] = 5000
+            if step == 2:
+                sw = np.append(sw, bad).astype(np.int32)
+                rules["action"][rule_off[bad]:rule_off[bad + 1]] = 0
+            listed = np.concatenate([sw, sw[:3], [-1, S]]).astype(np.int32)
+            rec, vs, wk, n, flags = _run(wl, rule_off, rules, rec, vs, listed, walk=wk, ctx=ctx)
+            ro, vo, wo, err = _oracle(orc, wl, rule_off, rules)
+            _same_records(rec, ro)
+            assert np.array_equal(vs, vo) and np.array_equal(wk, wo) and flags == err | F_SWITCH
+            assert n > 0
