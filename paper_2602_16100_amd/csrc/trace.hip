@@ -49,7 +49,7 @@ namespace {
 
 constexpr int kChunks = 6;                 // 4-bit chunks of the key used by the filter (chosen per switch)
 constexpr int kKeyNibbles = 26;            // the 104-bit key: 8 nibbles in each of w0..w2, 2 in w3's low byte
-constexpr int kChooseSample = 512;         // rules per switch sampled to choose its filter chunks
+constexpr int kChooseSample = 256;         // rules per switch sampled to choose its filter chunks
 constexpr int kPlaneWords = kChunks * 16;  // words per 32-rule group
 constexpr int kMatchWaves = 4;
 constexpr int kMatchThreads = kMatchWaves * 64;
@@ -402,7 +402,10 @@ __global__ __launch_bounds__(256) void k_tr_choose(int32_t S, const int32_t *__r
         for (uint32_t n = 0; n < kKeyNibbles; ++n) {
             const uint32_t m = key_nibble(m0, m1, m2, m3, n);
             const uint32_t v = key_nibble(v0, v1, v2, v3, n) & m;
-            atomicAdd(&hist[n][m << 4 | v], 1u);
+            // rules that wildcard the nibble share one count: added by one lane
+            const uint64_t any = __ballot(m == 0);
+            if (m != 0) atomicAdd(&hist[n][m << 4 | v], 1u);
+            else if (static_cast<int>(threadIdx.x & 63) == __builtin_ctzll(any)) atomicAdd(&hist[n][0], static_cast<uint32_t>(__popcll(any)));
         }
     }
     __syncthreads();
