@@ -25,12 +25,12 @@
 //            scatter pass writes each trace's 32-byte bucket record (trace,
 //            jurisdiction mask, header) at its switch's offset plus its
 //            rank.  One workgroup per work item (a switch and a balanced
-//            share of its bucket) keeps the switch's chunk sets in VGPRs
-//            (8,192 rules per 4-wave slice) and filters every lookup with
-//            kChunks uniform-index register reads and ANDs; the rare
-//            survivors are verified against the full 104-bit rule and the
-//            first match is the minimum of (0xFFFF - priority, index) over
-//            the workgroup (LDS 64-bit atomic min).  The same workgroup then
+//            share of its bucket) keeps the switch's chunk sets in LDS
+//            (4,096 rules a slice) or, few lookups per table, in VGPRs,
+//            and filters every lookup with kChunks reads and ANDs; the
+//            survivors of the highest priorities are verified against the full
+//            104-bit rule and the first match is the minimum of (0xFFFF -
+//            priority, index) (LDS 64-bit atomic min).  The same workgroup then
 //            applies the match with the switch's ports staged in LDS, counts
 //            the moving traces per forwarding port (one count update per
 //            port and workgroup, which also gives each trace its rank in its
@@ -51,27 +51,29 @@ constexpr int kChunks = 6;                 // 4-bit chunks of the key used by th
 constexpr int kKeyNibbles = 26;            // the 104-bit key: 8 nibbles in each of w0..w2, 2 in w3's low byte
 constexpr int kChooseSample = 256;         // rules per switch sampled to choose its filter chunks
 constexpr int kPlaneWords = kChunks * 16;  // words per 32-rule group
-constexpr int kMatchWaves = 4;
+constexpr int kMatchWaves = 8;
 constexpr int kMatchThreads = kMatchWaves * 64;
-constexpr int kSliceGroups = kMatchThreads;  // one group (32 rules) per lane
-constexpr int kChunk = 256;                  // lookups per lookup stream of a small table's work item (a multiple of 4)
-constexpr int kMaxChunk = 256;               // lookups per work item at most (<= kMatchThreads)
-constexpr int kItemCap = 192;                // lookups per work item of a table of kSliceGroups groups or more
-constexpr int kQueue = 512;                  // queued filter survivors per wavefront (>= 4 x 64)
+constexpr int kSliceGroups = 128;            // groups whose chunk sets a match workgroup holds in LDS (48 KB)
+constexpr int kChunk = kMatchThreads;        // lookups matched together at most (one epilogue thread each)
+constexpr int kItemMax = kChunk;             // lookups per work item at most
+constexpr int kItemLeast = 384;              // the same of a small level
+constexpr int64_t kItemsWanted = 4096;       // work items of a large level
+constexpr int kQueue = 128;                  // queued filter survivors per wavefront (>= 64)
+constexpr int kWideWaves = 4;                // k_tr_match_wide: a group (32 rules) per lane, its sets in registers
+constexpr int kWideThreads = kWideWaves * 64;
+constexpr int kWideItem = 192;               // lookups per work item
+constexpr int kWideChunk = 256;              // the same, padded, at most
+constexpr int kWideQueue = 512;              // queued filter survivors per wavefront (>= 4 x 64)
+constexpr int kItemMin = kWideItem;          // lookups per work item, of either form, unless it is its switch's only one
 constexpr int kPrepGroups = 128;             // groups per prep workgroup (16 wavefronts x 4 rounds x 2 groups)
 constexpr uint64_t kNoMatch = ~0ull;
-static_assert(kItemCap % 4 == 0 && kItemCap <= kChunk, "an item holds >= kItemCap lookups unless it is its switch's only one");
-static_assert(kChunk % 4 == 0 && kMaxChunk % kChunk == 0 && kMaxChunk <= kMatchThreads,
-              "one epilogue thread per lookup");
+static_assert(kItemMin <= kChunk && kChunk <= kMatchWaves * 64, "a wavefront's lookups fit its lanes");
+static_assert((kWideItem + 3) / 4 * 4 <= kWideChunk && kWideChunk <= kWideThreads, "one epilogue thread per lookup");
 constexpr int kCountPad = 32;  // live-trace counters are 128 bytes apart: contended atomics on one line serialise
 constexpr int32_t kDirectRules = 1024;               // mean rules per switch that a walk may match one by one,
 constexpr int64_t kDirectWork = 5000000;             // traces times mean rules
 constexpr int64_t kDirectWorst = int64_t(1) << 26;   // and traces times all rules
 constexpr int kPortSlots = 64;  // forwarding ports whose moves a match workgroup counts in LDS
-
-// 16 chunk-value sets of one 4-bit chunk, kept in VGPRs; indexed with a
-// wave-uniform value this lowers to register-indexed moves (s_set_gpr_idx).
-typedef uint32_t v16u __attribute__((ext_vector_type(16)));
 
 // Bit k set iff slot k of trace t's watch list names switch s (K = 0: none).
 __device__ __forceinline__ uint32_t watch_bits(const int32_t *__restrict__ watch, int32_t K, int32_t t, int32_t s)
@@ -213,7 +215,8 @@ __global__ __launch_bounds__(256) void k_tr_sweep(int64_t n_ports, const int32_t
                                                   uint32_t *__restrict__ hh, uint32_t *__restrict__ d_err)
 {
     __shared__ uint32_t loc[kKeyNibbles * 16];
-    const bool bad = bad_ids(n_ports, port_peer, S) | bad_ids(n_watch, watch, S);
+    const bool bad_port = bad_ids(n_ports, port_peer, S), bad_watch = bad_ids(n_watch, watch, S);
+    const bool bad = bad_port || bad_watch;
     if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(d_err, PC_DERR_SWITCH);
     if (hh == nullptr) return;
     for (int i = threadIdx.x; i < kKeyNibbles * 16; i += 256) loc[i] = 0;
@@ -358,7 +361,7 @@ __global__ __launch_bounds__(64) void k_tr_direct(int32_t S, const int32_t *__re
 {
     const int32_t s = blockIdx.x;
     uint32_t errs = 0;
-    if (bad_ids(inf.n_ports, inf.port_peer, S) | bad_ids(n_watch, watch, S)) errs |= PC_DERR_SWITCH;
+    if (bad_ids(inf.n_ports, inf.port_peer, S) || bad_ids(n_watch, watch, S)) errs |= PC_DERR_SWITCH;
     const int64_t rb = rule_off[s], re = rule_off[s + 1];
     const bool rok = pc_range_ok(rb, re, n_rules);
     if (inf.jur[s] >= 32) errs |= PC_DERR_JUR;
@@ -476,7 +479,8 @@ constexpr int kPrepRounds = 4;                          // 64-rule rounds per wa
 constexpr int kTileStride = kPrepGroups + 2;            // LDS row pitch (spreads a half-wave's rows over banks)
 static_assert(kPrepGroups == 2 * kPrepWaves * kPrepRounds, "two groups per wavefront round");
 
-// Build the chunk sets of kPrepGroups groups (block b) of switch s; validate actions.
+// Build the chunk sets of kPrepGroups groups (block b) of switch s, and with
+// prio the rules' priorities (0xFFFF - priority, 32 a group); validate actions.
 // Lane r of a half-wave holds rule r of a group and looks up, for each chunk,
 // the 16-bit set of chunk values its value/mask admit (a 256-entry LDS table
 // indexed by the chunk's value & mask and mask).  Two chunks share a word;
@@ -487,8 +491,9 @@ __device__ __forceinline__ void prep_block(int32_t s, int32_t b, uint32_t *tile,
                                            const int32_t *__restrict__ port_off, int64_t n_ports,
                                            const int32_t *__restrict__ rule_off, const pc_rule *__restrict__ rules,
                                            const int32_t *__restrict__ gcount, const int32_t *__restrict__ gofs,
-                                           uint32_t *__restrict__ filt, uint32_t *__restrict__ d_err,
-                                           uint32_t *__restrict__ sw_bad, const uint32_t *__restrict__ cpos)
+                                           uint32_t *__restrict__ filt, uint16_t *__restrict__ prio,
+                                           uint32_t *__restrict__ d_err, uint32_t *__restrict__ sw_bad,
+                                           const uint32_t *__restrict__ cpos)
 {
     const int32_t G = gcount[s];
     const int32_t g0 = b * kPrepGroups;
@@ -514,6 +519,7 @@ __device__ __forceinline__ void prep_block(int32_t s, int32_t b, uint32_t *tile,
             vv[k] = make_uint4(r->value.w[0], r->value.w[1], r->value.w[2], r->value.w[3]);
             mm[k] = make_uint4(r->mask.w[0], r->mask.w[1], r->mask.w[2], r->mask.w[3]);
             act[k] = r->action;
+            if (prio != nullptr) prio[static_cast<int64_t>(gofs[s]) * 32 + local] = static_cast<uint16_t>(0xFFFFu - r->priority);
         }
     }
     // admit[(v & m) | m << 4] = set of 4-bit values y with (y & m) == (v & m)
@@ -572,8 +578,9 @@ __global__ __launch_bounds__(1024) void k_tr_prep(int32_t S, const int32_t *__re
                                                   const pc_rule *__restrict__ rules,
                                                   const int32_t *__restrict__ gcount,
                                                   const int32_t *__restrict__ gofs, const int32_t *__restrict__ bofs,
-                                                  uint32_t *__restrict__ filt, uint32_t *__restrict__ d_err,
-                                                  uint32_t *__restrict__ sw_bad, const uint32_t *__restrict__ cpos)
+                                                  uint32_t *__restrict__ filt, uint16_t *__restrict__ prio,
+                                                  uint32_t *__restrict__ d_err, uint32_t *__restrict__ sw_bad,
+                                                  const uint32_t *__restrict__ cpos)
 {
     __shared__ uint32_t tile[kPlaneWords * kTileStride];
     __shared__ uint16_t admit[256];
@@ -586,8 +593,8 @@ __global__ __launch_bounds__(1024) void k_tr_prep(int32_t S, const int32_t *__re
         if (bofs[mid] <= b) lo = mid;
         else hi = mid;
     }
-    prep_block(lo, b - bofs[lo], tile, admit, port_off, n_ports, rule_off, rules, gcount, gofs, filt, d_err, sw_bad,
-               cpos);
+    prep_block(lo, b - bofs[lo], tile, admit, port_off, n_ports, rule_off, rules, gcount, gofs, filt, prio, d_err,
+               sw_bad, cpos);
 }
 
 // The same for listed switches, unless *skip: list entry blockIdx.x, its
@@ -598,8 +605,8 @@ __global__ __launch_bounds__(1024) void k_tr_prep_listed(int32_t S, const int32_
                                                          const int32_t *__restrict__ gcount,
                                                          const int32_t *__restrict__ gofs,
                                                          const int32_t *__restrict__ bofs,
-                                                         uint32_t *__restrict__ filt, uint32_t *__restrict__ d_err,
-                                                         uint32_t *__restrict__ sw_bad,
+                                                         uint32_t *__restrict__ filt, uint16_t *__restrict__ prio,
+                                                         uint32_t *__restrict__ d_err, uint32_t *__restrict__ sw_bad,
                                                          const uint32_t *__restrict__ cpos,
                                                          const int32_t *__restrict__ listed,
                                                          const uint32_t *__restrict__ skip)
@@ -610,7 +617,8 @@ __global__ __launch_bounds__(1024) void k_tr_prep_listed(int32_t S, const int32_
     const int32_t s = listed[blockIdx.x];
     if (s < 0 || s >= S) return;
     for (int32_t b = blockIdx.y; b < bofs[s + 1] - bofs[s]; b += gridDim.y)
-        prep_block(s, b, tile, admit, port_off, n_ports, rule_off, rules, gcount, gofs, filt, d_err, sw_bad, cpos);
+        prep_block(s, b, tile, admit, port_off, n_ports, rule_off, rules, gcount, gofs, filt, prio, d_err, sw_bad,
+                   cpos);
 }
 
 // Level 0: every trace starts at its ingress switch (an invalid ingress
@@ -839,6 +847,7 @@ struct Level {
     const int2 *pinfo;      // per port: (peer, the peer's jurisdiction bit)
     const uint8_t *jur;
     int32_t ttl;
+    int32_t cap;            // lookups per work item at most
     int32_t hops;           // hops every trace of this level has made (the level's index)
     LRec *live_next;        // one entry per lookup of this level, at its bucket slot (switch -1: the trace ended)
     int32_t *nlive_next;    // traces in flight after this level
@@ -851,29 +860,25 @@ struct Level {
     int32_t *walk;          // [T][kWalkSlots] walk records or nullptr
 };
 
-// Lookups per match work item of a switch of G groups with n lookups in
-// this level: the switch's lookups split evenly (in multiples of 4) over as
-// few items as hold at most kItemCap each, where a table of fewer than
-// kSliceGroups groups, which leaves wavefronts free for further lookup
-// streams, takes kChunk per stream (at most kMaxChunk).
-__device__ __forceinline__ int32_t item_lookups(int32_t G, int32_t n)
+// Lookups per match work item of a switch with n lookups in this level: the
+// switch's lookups split evenly over as few items as hold at most cap each;
+// and of the parts an item of n lookups is matched in.
+__device__ __forceinline__ int32_t even_parts(int32_t n, int32_t cap)
 {
-    const int32_t gws = G >= kSliceGroups ? kMatchWaves : max(1, (G + 63) / 64);
-    const int32_t cap = gws == kMatchWaves ? kItemCap : min(kMaxChunk, kChunk * (kMatchWaves / gws));
-    const int32_t items = max(1, (n + cap - 1) / cap);
-    return max(4, ((n + items - 1) / items + 3) & ~3);
+    const int32_t parts = max(1, (n + cap - 1) / cap);
+    return max(1, (n + parts - 1) / parts);
 }
 
 // Per level: bucket offsets boff = exclusive scan of counts (which are
 // cleared for reuse), work-item offsets ioff = exclusive scan of
-// ceil(counts / item_lookups(G, counts)), *total = the level's lookups (the
+// ceil(counts / even_parts(counts, cap)), *total = the level's lookups (the
 // length of the live list its match writes) and *host, and *nlive_next = 0 for
 // the match to count the traces that move on.  One workgroup of 1024 threads;
 // each thread takes kPlanPer consecutive switches per pass, so a pass
 // covers 4,096 switches with all of its loads in flight together.
 constexpr int kPlanPer = 4;
 __global__ __launch_bounds__(1024) void k_tr_plan(int32_t *__restrict__ counts, int32_t S, int32_t *__restrict__ boff,
-                                                  int32_t *__restrict__ ioff, const int32_t *__restrict__ gcount,
+                                                  int32_t *__restrict__ ioff, int32_t cap,
                                                   int32_t *__restrict__ total, int32_t *__restrict__ nlive_next,
                                                   int32_t *__restrict__ host)
 {
@@ -885,16 +890,13 @@ __global__ __launch_bounds__(1024) void k_tr_plan(int32_t *__restrict__ counts, 
     __syncthreads();
     for (int32_t base = 0; base < S; base += 1024 * kPlanPer) {
         const int32_t i0 = base + tid * kPlanPer;
-        int32_t v0[kPlanPer], g[kPlanPer], v1[kPlanPer];
+        int32_t v0[kPlanPer], v1[kPlanPer];
 #pragma unroll
-        for (int k = 0; k < kPlanPer; ++k) {
-            v0[k] = i0 + k < S ? counts[static_cast<int64_t>(i0 + k) * kCountPad] : 0;
-            g[k] = i0 + k < S ? gcount[i0 + k] : 0;
-        }
+        for (int k = 0; k < kPlanPer; ++k) v0[k] = i0 + k < S ? counts[static_cast<int64_t>(i0 + k) * kCountPad] : 0;
         int32_t s0 = 0, s1 = 0;
 #pragma unroll
         for (int k = 0; k < kPlanPer; ++k) {
-            const int32_t ch = item_lookups(g[k], v0[k]);
+            const int32_t ch = even_parts(v0[k], cap);
             v1[k] = (v0[k] + ch - 1) / ch;
             s0 += v0[k];
             s1 += v1[k];
@@ -950,6 +952,386 @@ __global__ __launch_bounds__(1024) void k_tr_plan(int32_t *__restrict__ counts, 
         __threadfence_system();
     }
 }
+
+// The survivors of a lookup in four groups: bit r of s[k] is rule r of group
+// k.  at: the groups' chunk sets of value 0 of chunk 0, rows of 16 << kLg bytes
+// (row c * 16 + x: chunk c, value x); nib: the lookup's values, four bits each.
+template <int kLg>
+__device__ __forceinline__ void load_sets(const char *at, uint32_t nib, uint4 (&v)[kChunks])
+{
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c)
+        v[c] = *reinterpret_cast<const uint4 *>(at + (c * 16 << (kLg + 4)) + (((nib >> (4 * c)) & 15) << (kLg + 4)));
+}
+
+__device__ __forceinline__ void and_sets(const uint4 (&v)[kChunks], uint32_t (&s)[4])
+{
+    s[0] = v[0].x & v[1].x & v[2].x & v[3].x & v[4].x & v[5].x;
+    s[1] = v[0].y & v[1].y & v[2].y & v[3].y & v[4].y & v[5].y;
+    s[2] = v[0].z & v[1].z & v[2].z & v[3].z & v[4].z & v[5].z;
+    s[3] = v[0].w & v[1].w & v[2].w & v[3].w & v[4].w & v[5].w;
+    static_assert(kChunks == 6, "every chunk's set");
+}
+
+// One wavefront matches its nw <= 64 lookups (lane j's packed: lookup j's values
+// of the chunks) against the slice whose chunk sets and priorities (0xFFFF -
+// priority) are in LDS.  1 << kLg lanes take a lookup, four groups a lane, so
+// that a read is 16 bytes a lane; two passes' reads go out together.  A pass only
+// asks which lanes have survivors and queues these; 64 queued at a time, their sets are
+// formed again and cand[j], cand2[j] become lookup j's first two survivors by (priority,
+// index).  Only these rules are checked in full (lane j: verify(lookup, rule)): where
+// many rules admit a header, as with prefixes, nearly every survivor matches.
+// A lookup whose candidates both fail checks all its survivors.
+template <int kLg, class Verify>
+__device__ __forceinline__ void filter_slice(const uint4 *sets, const uint16_t *prio, uint32_t packed, int32_t nw,
+                                             uint16_t *q, uint32_t *cand, uint32_t *cand2,
+                                             Verify &&verify)
+{
+    constexpr int kPer = 64 >> kLg;  // lookups per pass
+    const int lane = threadIdx.x & 63, sub = lane >> kLg, l = lane & ((1 << kLg) - 1);
+    const char *base = reinterpret_cast<const char *>(sets);
+    auto of_lane = [&](int32_t j, uint32_t x) {
+        return static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(4 * j, static_cast<int>(x)));
+    };
+    auto settle = [&]() {  // what other lanes of this wavefront wrote to LDS
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    int32_t qn = 0;
+    auto push = [&](bool any, uint32_t entry, auto &&drain) {
+        const uint64_t m = __ballot(any);
+        const int n = __popcll(m);
+        if (qn + n > kQueue) drain();
+        const uint32_t below = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
+        if (any) q[qn + below] = static_cast<uint16_t>(entry);
+        qn += n;
+    };
+    // queued: lookup << 5 | lane of its groups
+    auto rank = [&]() {
+        settle();
+        for (int32_t e0 = 0; e0 < qn; e0 += 64) {
+            const uint32_t en = q[min(e0 + lane, qn - 1)];
+            const int32_t j = static_cast<int32_t>(en >> 5), ql = static_cast<int32_t>(en & 31);
+            uint4 v[kChunks];
+            uint32_t s[4], first = ~0u, second = ~0u;
+            load_sets<kLg>(base + 16 * ql, of_lane(j, packed), v);
+            and_sets(v, s);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                for (uint32_t m = s[k]; m; m &= m - 1) {
+                    const uint32_t at = 128 * ql + 32 * k + __builtin_ctz(m);
+                    const uint32_t key = static_cast<uint32_t>(prio[at]) << 12 | at;
+                    second = min(second, max(first, key));
+                    first = min(first, key);
+                }
+            // what does not stay the first competes for the second place
+            if (e0 + lane < qn) second = min(second, max(first, atomicMin(cand + j, first)));
+            if (e0 + lane < qn && second != ~0u) atomicMin(cand2 + j, second);
+        }
+        settle();
+        qn = 0;
+    };
+    if (lane < nw) cand[lane] = cand2[lane] = ~0u;
+    for (int32_t j0 = 0; j0 < nw; j0 += 2 * kPer) {
+        uint4 a[kChunks], b[kChunks];
+        uint32_t s[4];
+        load_sets<kLg>(base + 16 * l, of_lane(min(j0 + sub, nw - 1), packed), a);
+        load_sets<kLg>(base + 16 * l, of_lane(min(j0 + kPer + sub, nw - 1), packed), b);
+        and_sets(a, s);
+        push((s[0] | s[1] | s[2] | s[3]) != 0 && j0 + sub < nw, (j0 + sub) << 5 | l, rank);
+        and_sets(b, s);
+        push((s[0] | s[1] | s[2] | s[3]) != 0 && j0 + kPer + sub < nw, (j0 + kPer + sub) << 5 | l, rank);
+    }
+    rank();
+    const uint32_t first = lane < nw ? cand[lane] : ~0u, second = lane < nw ? cand2[lane] : ~0u;
+    const bool one = first != ~0u && verify(lane, static_cast<int32_t>(first & 4095));
+    const bool two = second != ~0u && verify(lane, static_cast<int32_t>(second & 4095));
+    const bool failed = second != ~0u && !one && !two;
+    const uint64_t fm = __ballot(failed);
+    if (fm == 0) return;
+    // the failed lookups again, compacted; queued: place << 7 | lane << 2 | word
+    const int32_t nf = __popcll(fm);
+    if (failed) q[__popcll(fm & ((1ull << lane) - 1))] = static_cast<uint16_t>(lane);
+    settle();
+    const uint32_t which = q[min(lane, nf - 1)];
+    const uint32_t again = of_lane(static_cast<int32_t>(which), packed);
+    settle();
+    auto check = [&]() {
+        settle();
+        for (int32_t e0 = 0; e0 < qn; e0 += 64) {
+            const uint32_t en = q[min(e0 + lane, qn - 1)];
+            const int32_t j = static_cast<int32_t>(en >> 7), ql = static_cast<int32_t>((en >> 2) & 31);
+            uint4 v[kChunks];
+            uint32_t s[4];
+            load_sets<kLg>(base + 16 * ql, of_lane(j, again), v);
+            and_sets(v, s);
+            const uint32_t k = en & 3, to = of_lane(j, which);
+            if (e0 + lane < qn)
+                for (uint32_t m = k == 0 ? s[0] : k == 1 ? s[1] : k == 2 ? s[2] : s[3]; m; m &= m - 1)
+                    (void)verify(static_cast<int32_t>(to), static_cast<int32_t>(128 * ql + 32 * k + __builtin_ctz(m)));
+        }
+        settle();
+        qn = 0;
+    };
+    for (int32_t j0 = 0; j0 < nf; j0 += kPer) {
+        uint4 a[kChunks];
+        uint32_t s[4];
+        load_sets<kLg>(base + 16 * l, of_lane(min(j0 + sub, nf - 1), again), a);
+        and_sets(a, s);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            push(s[k] != 0 && j0 + sub < nf, (j0 + sub) << 7 | l << 2 | k, check);
+    }
+    check();
+}
+
+// What a match workgroup keeps of its switch's first kPortSlots ports: peer,
+// the peer's jurisdiction bit, and the item's traces that leave through the port
+// (count, then the base of their ranks in the peer's bucket).  The item's live
+// entries are ordered by forwarding port: port p's run starts at run[p], the run
+// of the other ports at run[kPortSlots].
+struct PortMoves {
+    int32_t peer[kPortSlots], count[kPortSlots], base[kPortSlots];
+    uint32_t jbit[kPortSlots];
+    int32_t run[kPortSlots + 1];
+    int32_t nother, nmove;  // traces leaving through the other ports; all that move on
+};
+
+// The end of a match workgroup: every lookup's first match is in best (all in
+// LDS; behind a barrier); at most a lookup per thread.
+__device__ __forceinline__ void apply_matches(const Level &lv, int32_t s, int64_t pb, int64_t np, int32_t bb,
+                                              int32_t tn, const int32_t *tids, const uint32_t *tjm,
+                                              const uint64_t *best, const pc_key *keys, PortMoves &ports)
+{
+    const int lane = threadIdx.x & 63;
+    // apply the first match.  A trace that moves on is counted in its next
+    // switch's bucket (one count update per forwarding port and workgroup;
+    // its rank there is the port's base plus its rank in the item) and gets
+    // an entry in the item's share of the live list, grouped by port so that
+    // the bucketing pass writes runs; the slots after the item's moving
+    // traces are marked as ended (switch -1).
+    const int32_t h = lv.hops;
+    int32_t t = -1, lrank = -1, orank = -1, next = -1, rk = 0;
+    uint32_t jm_next = 0;
+    uint16_t port = PC_NO_PORT;
+    if (threadIdx.x < tn) {  // (at most a lookup per thread)
+        t = tids[threadIdx.x];
+        if (t >= 0) {
+            const uint32_t jmv = tjm[threadIdx.x];
+            const int state = apply_key(
+                lv.S, lv.ttl, np,
+                [&](uint32_t a) { return a < kPortSlots ? ports.peer[a] : lv.port_peer[pb + a]; },
+                best[threadIdx.x], h, &next, &port);
+            if (state >= 0) {
+                write_out(lv.out, t, jmv, s, port, h, state);
+                t = -1;
+            } else {
+                jm_next = jmv | (port < kPortSlots ? ports.jbit[port] : jur_bit(lv.jur, next));
+                if (lv.visit) lv.visit[t] |= watch_bits(lv.watch, lv.K, t, next);
+                if (lv.vsum) lv.vsum[t] |= sum_bit(next);
+                if (lv.walk && h + 1 < kWalkSlots) lv.walk[static_cast<int64_t>(t) * kWalkSlots + h + 1] = next;
+                if (port < kPortSlots) {
+                    lrank = atomicAdd(&ports.count[port], 1);
+                } else {
+                    rk = atomicAdd(&lv.counts_next[static_cast<int64_t>(next) * kCountPad], 1);
+                    orank = atomicAdd(&ports.nother, 1);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    static_assert(kPortSlots == 64, "one wavefront scans the port counts");
+    if (threadIdx.x < kPortSlots) {
+        const int32_t c = ports.count[threadIdx.x];
+        // a port some trace forwarded through: its peer is a valid switch
+        if (c > 0) ports.base[threadIdx.x] = atomicAdd(&lv.counts_next[static_cast<int64_t>(ports.peer[threadIdx.x]) * kCountPad], c);
+        int32_t x = c;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t y = __shfl_up(x, off, 64);
+            if (lane >= off) x += y;
+        }
+        ports.run[threadIdx.x] = x - c;
+        if (threadIdx.x == kPortSlots - 1) {
+            ports.run[kPortSlots] = x;
+            const int32_t m = x + ports.nother;
+            ports.nmove = m;
+            if (m) atomicAdd(lv.nlive_next, m);  // the traces in flight after this level
+        }
+    }
+    __syncthreads();
+    int32_t slot = -1;
+    if (lrank >= 0) {
+        rk = ports.base[port] + lrank;
+        slot = ports.run[port] + lrank;
+    } else if (orank >= 0) {
+        slot = ports.run[kPortSlots] + orank;
+    }
+    if (slot >= 0) {
+        LRec e;
+        e.t = t;
+        e.next = next;
+        e.rk = rk;
+        e.jm = jm_next;
+        e.key = keys[threadIdx.x];
+        lv.live_next[bb + slot] = e;
+    }
+    if (threadIdx.x >= ports.nmove && threadIdx.x < tn)
+        *reinterpret_cast<int4 *>(lv.live_next + bb + threadIdx.x) = make_int4(-1, -1, 0, 0);
+}
+
+// One workgroup per work item = (switch, an even share of at most lv.cap
+// lookups of its bucket).  Items are dealt to XCDs in contiguous ranges, so
+// the shares of one switch share an L2.  The switch's chunk sets are read from
+// LDS, a slice of 4,096 rules at a time, which takes half the instructions of
+// k_tr_match_wide's register indexing (a level of 4.2 million lookups in 1,280
+// tables of 4,096 rules: 42 vector and 35 scalar instructions per lookup there,
+// 31 and 15 here).  Bound by staging and moving the lookups, 155 of such a level's 340
+// us, then by the vector instructions of the filter, 130.  4,194,304 traces
+// over these tables 1,757 us in k_tr_match_wide, now 1,417; 500,009 over
+// 720 routing tables of 2,048 prefixes, where a lookup has dozens of matching
+// rules, 935 and 470 (842 with every survivor checked).
+__global__ __launch_bounds__(kMatchThreads, 4) void k_tr_match(
+    int32_t S, const SwInfo *__restrict__ sinfo, const pc_rule *__restrict__ rules, const uint32_t *__restrict__ filt,
+    const uint16_t *__restrict__ prios, const int32_t *__restrict__ boff, const int32_t *__restrict__ ioff,
+    const int2 *__restrict__ imap, const BRec *__restrict__ bucket, Level lv)
+{
+    __shared__ uint4 sets[kPlaneWords * kSliceGroups / 4];
+    __shared__ uint64_t best[kChunk];
+    __shared__ __align__(16) pc_key keys[kChunk];
+    __shared__ uint32_t cidx[kChunk];  // each lookup's values of the switch's filter chunks, four bits each; then its
+                                       // candidate (a wavefront's own lookups only)
+    __shared__ uint32_t cand2[kChunk];
+    __shared__ int32_t tids[kChunk];
+    __shared__ uint32_t tjm[kChunk];   // each lookup's trace: jurisdiction mask so far
+    __shared__ uint16_t prio[kSliceGroups * 32] __attribute__((aligned(16)));
+    __shared__ uint16_t queue[kMatchWaves][kQueue];  // per wavefront (see filter_slice)
+    __shared__ PortMoves ports;
+    // the grid was sized from an upper bound on the item count: blocks past
+    // the real count's per-XCD share return at once
+    const int32_t n_items = ioff[S];
+    const int32_t per = (n_items + 7) / 8;
+    const int32_t kx = static_cast<int32_t>(blockIdx.x >> 3);
+    if (kx >= per) return;
+    const int32_t item = static_cast<int32_t>(blockIdx.x & 7) * per + kx;
+    if (item >= n_items) return;
+    // the item's switch and its index among the switch's items
+    const int2 im = imap[item];
+    const int32_t s = im.x;
+    if (static_cast<uint32_t>(s) >= static_cast<uint32_t>(S)) return;
+    const SwInfo si = sinfo[s];
+    const int32_t b0 = boff[s], b1 = boff[s + 1];
+    const int32_t share = even_parts(b1 - b0, lv.cap);
+    const int32_t bb = b0 + im.y * share;
+    const int32_t tn = min(share, min(b1, lv.T) - bb);  // bucket holds at most T entries
+    if (tn <= 0) return;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t G = si.G;
+    const int64_t rb = si.rb;
+    const uint32_t *fs = filt + static_cast<int64_t>(si.gofs) * kPlaneWords;
+    const uint32_t cp = si.cpos;
+    // the switch's ports (np < 0: its port range is invalid)
+    const int64_t pb = si.pb, np = si.np;
+    // lanes that take a lookup: a slice's groups, four a lane
+    const int32_t quads = (min(G, kSliceGroups) + 3) / 4;
+    const int lpl_bits = quads <= 1 ? 0 : 32 - __builtin_clz(static_cast<uint32_t>(quads - 1)), lpl = 1 << lpl_bits;
+    // a slice's chunk sets into LDS (no survivors past the last group)
+    auto fill = [&](int32_t g0) {
+        const int32_t ng = min(G - g0, kSliceGroups);
+        constexpr int kFills = kPlaneWords * kSliceGroups / 4 / kMatchThreads;
+        static_assert(kSliceGroups * 4 == kMatchThreads, "16 bytes of priorities per thread");
+        uint4 v[kFills], pr = make_uint4(0, 0, 0, 0);
+        if (static_cast<int32_t>(threadIdx.x) < ng * 4)
+            pr = reinterpret_cast<const uint4 *>(prios + (static_cast<int64_t>(si.gofs) + g0) * 32)[threadIdx.x];
+#pragma unroll
+        for (int k = 0; k < kFills; ++k) {
+            const int x = static_cast<int>(threadIdx.x) + k * kMatchThreads;
+            const int32_t row = x >> lpl_bits, g = 4 * (x & (lpl - 1));
+            v[k] = make_uint4(0, 0, 0, 0);
+            if (row < kPlaneWords) {
+                const uint32_t *src = fs + static_cast<int64_t>(row) * G + g0 + g;
+                if (g + 4 <= ng) {
+                    __builtin_memcpy(&v[k], src, 16);
+                } else {
+                    if (g < ng) v[k].x = src[0];
+                    if (g + 1 < ng) v[k].y = src[1];
+                    if (g + 2 < ng) v[k].z = src[2];
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kFills; ++k) {
+            const int x = static_cast<int>(threadIdx.x) + k * kMatchThreads;
+            if (x < kPlaneWords * lpl) sets[x] = v[k];
+        }
+        reinterpret_cast<uint4 *>(prio)[threadIdx.x] = pr;
+    };
+    // stage the lookups (one per thread) and the first slice's sets
+    const int i = static_cast<int>(threadIdx.x);
+    BRec r{};
+    if (i < tn) r = bucket[bb + i];
+    fill(0);
+    if (threadIdx.x < kPortSlots) {
+        const int2 pi = static_cast<int64_t>(threadIdx.x) < np ? lv.pinfo[pb + threadIdx.x] : make_int2(-2, 0);
+        ports.peer[threadIdx.x] = pi.x;
+        ports.jbit[threadIdx.x] = static_cast<uint32_t>(pi.y);
+        ports.count[threadIdx.x] = 0;
+        if (threadIdx.x == 0) ports.nother = 0;
+    }
+    if (i < tn) {
+        int32_t t = r.t;
+        pc_key h = r.key;
+        uint32_t jmv = r.jm;
+        if (static_cast<uint32_t>(t) >= static_cast<uint32_t>(lv.T)) {  // not a trace id: skipped
+            t = -1;
+            h = pc_key{};
+            jmv = 0;
+        }
+        tids[i] = t;
+        keys[i] = h;
+        tjm[i] = jmv;
+        best[i] = kNoMatch;
+        uint32_t x = 0;
+#pragma unroll
+        for (int c = 0; c < kChunks; ++c) x |= key_nibble(h.w[0], h.w[1], h.w[2], h.w[3], chunk_pos(cp, c)) << (4 * c);
+        cidx[i] = x;
+    }
+    __syncthreads();
+    const int32_t per_wave = (tn + kMatchWaves - 1) / kMatchWaves;  // the wavefront's lookups
+    const int32_t jw = wave * per_wave, nw = min(per_wave, tn - jw);
+    const uint32_t packed = nw > 0 ? cidx[jw + min(lane, nw - 1)] : 0u;
+    for (int32_t g0 = 0; g0 < G; g0 += kSliceGroups) {
+        if (g0 > 0) {
+            __syncthreads();  // the slice before is no longer read
+            fill(g0);
+            __syncthreads();
+        }
+        auto verify = [&](int32_t j, int32_t at) {
+            const uint32_t local = static_cast<uint32_t>(g0) * 32 + static_cast<uint32_t>(at);
+            const pc_rule x = rules[rb + local];
+            const pc_key &h = keys[jw + j];
+            const bool ok = rule_matches(&x, h.w[0], h.w[1], h.w[2], h.w[3]);
+            if (ok)
+                atomicMin(reinterpret_cast<unsigned long long *>(&best[jw + j]),
+                          static_cast<unsigned long long>(rule_key(&x, local)));
+            return ok;
+        };
+        if (lpl_bits == 5) filter_slice<5>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
+        else if (lpl_bits == 4) filter_slice<4>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
+        else if (lpl_bits == 3) filter_slice<3>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
+        else if (lpl_bits == 2) filter_slice<2>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
+        else if (lpl_bits == 1) filter_slice<1>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
+        else filter_slice<0>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
+    }
+    // every wavefront's matches are in best[]
+    __syncthreads();
+    apply_matches(lv, s, pb, np, bb, tn, tids, tjm, best, keys, ports);
+}
+
+typedef uint32_t v16u __attribute__((ext_vector_type(16)));
 
 // Filter four lookups: sv[k] = AND over the six chunks c of F[c][x[c][k]].
 // GPR index mode stays on while only its index changes, and every indexed
@@ -1013,29 +1395,21 @@ __device__ __forceinline__ void filter_quad(const uint32_t (&x)[kChunks][4], con
 }
 #undef PC_IDX
 
-// One workgroup per work item = (switch, chunk of at most item_lookups(G, n)
-// lookups of its bucket).  Items are dealt to XCDs in contiguous ranges, so
-// the chunks of one switch share an L2.
-__global__ __launch_bounds__(kMatchThreads, 4) void k_tr_match(
+// The same with the chunk sets in registers, a group per lane and 256 groups
+// per workgroup, for levels of few lookups per table (see wide_level): no barrier
+// between the parts of a table, and smaller items.
+__global__ __launch_bounds__(kWideThreads, 4) void k_tr_match_wide(
     int32_t S, const SwInfo *__restrict__ sinfo, const pc_rule *__restrict__ rules, const uint32_t *__restrict__ filt,
     const int32_t *__restrict__ boff, const int32_t *__restrict__ ioff, const int2 *__restrict__ imap,
     const BRec *__restrict__ bucket, Level lv)
 {
-    __shared__ uint64_t best[kMaxChunk];
-    __shared__ __align__(16) uint32_t cidx[kChunks][kMaxChunk];  // each lookup's values of the switch's filter chunks
-    __shared__ __align__(16) pc_key keys[kMaxChunk];
-    __shared__ int32_t tids[kMaxChunk];
-    __shared__ uint32_t tjm[kMaxChunk];  // each lookup's trace: jurisdiction mask so far
-    __shared__ uint2 queue[kMatchWaves][kQueue];  // per wavefront: (survivor set, lookup << 6 | lane)
-    // the switch's first kPortSlots ports: peer, the peer's jurisdiction
-    // bit, and the item's traces that leave through the port (count, then
-    // the base of their ranks in the peer's bucket)
-    __shared__ int32_t ppeer[kPortSlots], pcnt[kPortSlots], pbase[kPortSlots];
-    __shared__ uint32_t pjb[kPortSlots];
-    // the item's live entries are ordered by forwarding port: port p's run
-    // starts at prun[p], the run of the other ports at prun[kPortSlots]
-    __shared__ int32_t prun[kPortSlots + 1];
-    __shared__ int32_t nother, nmove;  // traces leaving through the other ports; all that move on
+    __shared__ uint64_t best[kWideChunk];
+    __shared__ __align__(16) uint32_t cidx[kChunks][kWideChunk];  // each lookup's values of the switch's filter chunks
+    __shared__ __align__(16) pc_key keys[kWideChunk];
+    __shared__ int32_t tids[kWideChunk];
+    __shared__ uint32_t tjm[kWideChunk];  // each lookup's trace: jurisdiction mask so far
+    __shared__ uint2 queue[kWideWaves][kWideQueue];  // per wavefront: (survivor set, lookup << 6 | lane)
+    __shared__ PortMoves ports;
     // the grid was sized from an upper bound on the item count: blocks past
     // the real count's per-XCD share return at once
     const int32_t n_items = ioff[S];
@@ -1050,7 +1424,7 @@ __global__ __launch_bounds__(kMatchThreads, 4) void k_tr_match(
     if (static_cast<uint32_t>(s) >= static_cast<uint32_t>(S)) return;
     const SwInfo si = sinfo[s];
     const int32_t b0 = boff[s], b1 = boff[s + 1];
-    const int32_t chunk = item_lookups(si.G, b1 - b0);
+    const int32_t chunk = even_parts(b1 - b0, lv.cap);
     const int32_t bb = b0 + im.y * chunk;
     const int32_t tn = min(chunk, min(b1, lv.T) - bb);  // bucket holds at most T entries
     if (tn <= 0) return;
@@ -1060,15 +1434,15 @@ __global__ __launch_bounds__(kMatchThreads, 4) void k_tr_match(
     const int32_t G = si.G;
     const int64_t rb = si.rb;
     const uint32_t *fs = filt + static_cast<int64_t>(si.gofs) * kPlaneWords;
-    const int32_t nslices = max(1, (G + kSliceGroups - 1) / kSliceGroups);
+    const int32_t nslices = max(1, (G + kWideThreads - 1) / kWideThreads);
     const uint32_t cp = si.cpos;
     uint2 *q = queue[wave];
-    // A table of fewer than kSliceGroups groups fills gws wavefronts; the
+    // A table of fewer than kWideThreads groups fills gws wavefronts; the
     // workgroup's other wavefronts take further shares of the lookups: wave
     // = stream * gws + gwi holds groups gwi * 64 .. and filters the lookups
     // of its stream (contiguous quads).  Waves past the last stream idle.
-    const int32_t gws = G >= kSliceGroups ? kMatchWaves : max(1, (G + 63) / 64);
-    const int32_t streams = kMatchWaves / gws;
+    const int32_t gws = G >= kWideThreads ? kWideWaves : max(1, (G + 63) / 64);
+    const int32_t streams = kWideWaves / gws;
     const int32_t gwi = wave % gws, st = wave / gws;
     const int32_t nquads = tn4 / 4;
     const int32_t per_stream = (nquads + streams - 1) / streams;
@@ -1099,8 +1473,8 @@ __global__ __launch_bounds__(kMatchThreads, 4) void k_tr_match(
             for (int x = 0; x < 16; ++x) F[0][x] = 0u;
         }
     };
-    // stage the chunk (at most one lookup per thread: tn4 <= kMaxChunk <=
-    // kMatchThreads); pad to a multiple of 4 lookups with copies of the last
+    // stage the chunk (at most one lookup per thread: tn4 <= kWideChunk <=
+    // kWideThreads); pad to a multiple of 4 lookups with copies of the last
     const int i = static_cast<int>(threadIdx.x);
     BRec r{};
     if (i < tn4) r = bucket[bb + min(i, tn - 1)];
@@ -1127,10 +1501,10 @@ __global__ __launch_bounds__(kMatchThreads, 4) void k_tr_match(
     }
     if (threadIdx.x < kPortSlots) {
         const int2 pi = static_cast<int64_t>(threadIdx.x) < np ? lv.pinfo[pb + threadIdx.x] : make_int2(-2, 0);
-        ppeer[threadIdx.x] = pi.x;
-        pjb[threadIdx.x] = static_cast<uint32_t>(pi.y);
-        pcnt[threadIdx.x] = 0;
-        if (threadIdx.x == 0) nother = 0;
+        ports.peer[threadIdx.x] = pi.x;
+        ports.jbit[threadIdx.x] = static_cast<uint32_t>(pi.y);
+        ports.count[threadIdx.x] = 0;
+        if (threadIdx.x == 0) ports.nother = 0;
     }
     __syncthreads();
     // Filter phase: survivors of the chunk filter are queued (per wavefront)
@@ -1164,7 +1538,7 @@ __global__ __launch_bounds__(kMatchThreads, 4) void k_tr_match(
                     m[k] = __ballot(sv[k] != 0);
                     n += __popcll(m[k]);
                 }
-                if (qn + n > kQueue) break;  // resume at this quad after verifying
+                if (qn + n > kWideQueue) break;  // resume at this quad after verifying
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     if (sv[k]) {
@@ -1191,7 +1565,7 @@ __global__ __launch_bounds__(kMatchThreads, 4) void k_tr_match(
         }
         __builtin_amdgcn_wave_barrier();
     };
-    // one slice of kSliceGroups groups at a time, one group per lane, its
+    // one slice of kWideThreads groups at a time, one group per lane, its
     // chunk sets held in VGPRs while the chunk's lookups stream past.  The
     // first round of the first slice uses the sets loaded with the staging;
     // it runs outside the slice loop, so those sets are dead after it and
@@ -1200,8 +1574,8 @@ __global__ __launch_bounds__(kMatchThreads, 4) void k_tr_match(
     int32_t jr0 = jb;
     if (jb < je) round(gwi * 64, jr0, F0);
     for (int32_t sl = 0; sl < nslices; ++sl) {
-        const int32_t g = sl * kSliceGroups + gwi * 64 + lane;
-        const int32_t gw = sl * kSliceGroups + gwi * 64;
+        const int32_t g = sl * kWideThreads + gwi * 64 + lane;
+        const int32_t gw = sl * kWideThreads + gwi * 64;
         int32_t jr = sl == 0 ? jr0 : jb;
         while (jr < je) {
             v16u F[kChunks];
@@ -1212,80 +1586,7 @@ __global__ __launch_bounds__(kMatchThreads, 4) void k_tr_match(
     // every wavefront's matches are in best[] (a lookup's matches come from
     // the wavefronts that hold its groups, its epilogue thread may be another)
     __syncthreads();
-    // apply the first match.  A trace that moves on is counted in its next
-    // switch's bucket (one count update per forwarding port and workgroup;
-    // its rank there is the port's base plus its rank in the item) and gets
-    // an entry in the item's share of the live list, grouped by port so that
-    // the bucketing pass writes runs; the slots after the item's moving
-    // traces are marked as ended (switch -1).
-    const int32_t h = lv.hops;
-    int32_t t = -1, lrank = -1, orank = -1, next = -1, rk = 0;
-    uint32_t jm_next = 0;
-    uint16_t port = PC_NO_PORT;
-    if (threadIdx.x < tn) {  // tn <= kMaxChunk <= kMatchThreads
-        t = tids[threadIdx.x];
-        if (t >= 0) {
-            const uint32_t jmv = tjm[threadIdx.x];
-            const int state = apply_key(
-                lv.S, lv.ttl, np,
-                [&](uint32_t a) { return a < kPortSlots ? ppeer[a] : lv.port_peer[pb + a]; },
-                best[threadIdx.x], h, &next, &port);
-            if (state >= 0) {
-                write_out(lv.out, t, jmv, s, port, h, state);
-                t = -1;
-            } else {
-                jm_next = jmv | (port < kPortSlots ? pjb[port] : jur_bit(lv.jur, next));
-                if (lv.visit) lv.visit[t] |= watch_bits(lv.watch, lv.K, t, next);
-                if (lv.vsum) lv.vsum[t] |= sum_bit(next);
-                if (lv.walk && h + 1 < kWalkSlots) lv.walk[static_cast<int64_t>(t) * kWalkSlots + h + 1] = next;
-                if (port < kPortSlots) {
-                    lrank = atomicAdd(&pcnt[port], 1);
-                } else {
-                    rk = atomicAdd(&lv.counts_next[static_cast<int64_t>(next) * kCountPad], 1);
-                    orank = atomicAdd(&nother, 1);
-                }
-            }
-        }
-    }
-    __syncthreads();
-    static_assert(kPortSlots == 64, "one wavefront scans the port counts");
-    if (threadIdx.x < kPortSlots) {
-        const int32_t c = pcnt[threadIdx.x];
-        // a port some trace forwarded through: its peer is a valid switch
-        if (c > 0) pbase[threadIdx.x] = atomicAdd(&lv.counts_next[static_cast<int64_t>(ppeer[threadIdx.x]) * kCountPad], c);
-        int32_t x = c;
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int32_t y = __shfl_up(x, off, 64);
-            if (lane >= off) x += y;
-        }
-        prun[threadIdx.x] = x - c;
-        if (threadIdx.x == kPortSlots - 1) {
-            prun[kPortSlots] = x;
-            const int32_t m = x + nother;
-            nmove = m;
-            if (m) atomicAdd(lv.nlive_next, m);  // the traces in flight after this level
-        }
-    }
-    __syncthreads();
-    int32_t slot = -1;
-    if (lrank >= 0) {
-        rk = pbase[port] + lrank;
-        slot = prun[port] + lrank;
-    } else if (orank >= 0) {
-        slot = prun[kPortSlots] + orank;
-    }
-    if (slot >= 0) {
-        LRec e;
-        e.t = t;
-        e.next = next;
-        e.rk = rk;
-        e.jm = jm_next;
-        e.key = keys[threadIdx.x];
-        lv.live_next[bb + slot] = e;
-    }
-    if (threadIdx.x >= nmove && threadIdx.x < tn)
-        *reinterpret_cast<int4 *>(lv.live_next + bb + threadIdx.x) = make_int4(-1, -1, 0, 0);
+    apply_matches(lv, s, pb, np, bb, tn, tids, tjm, best, keys, ports);
 }
 
 // What every walk of a launch shares.
@@ -1649,6 +1950,31 @@ WalkRule walk_rule(int64_t mean_groups)
     return r;
 }
 
+// The chunk sets' buffer: the sets of every group, then (for levels matched
+// by candidate) the rules' priorities.
+size_t chunk_set_bytes(int64_t groups, bool prio)
+{
+    return static_cast<size_t>(groups + 1) * (kPlaneWords * sizeof(uint32_t) + (prio ? 32 * sizeof(uint16_t) : 0));
+}
+
+uint16_t *priorities(void *filt, int64_t groups)
+{
+    return reinterpret_cast<uint16_t *>(static_cast<uint32_t *>(filt) + groups * kPlaneWords);
+}
+
+// Is a level of n lookups matched by k_tr_match_wide?  It spreads a large table
+// over the registers of its wavefronts; k_tr_match reads the table's sets into LDS
+// slice by slice, which pays with enough lookups per table.  Wide / not, us of
+// all levels (rpath unless noted): tables of one slice, 78 lookups a table 156 / 191,
+// 234 238 / 226, 3,276 1,882 / 1,412, prefixes 694 896 / 458; two slices, 277
+// 288 / 327, 1,388 776 / 697; four slices, 347 1,530 / 1,958, 781 1,463 / 1,796,
+// 1,250 652 / 650, 1,388 1,323 / 1,263.
+bool wide_level(int64_t n, int32_t S, int64_t mean_groups)
+{
+    const int64_t slices = std::max<int64_t>((mean_groups + kSliceGroups - 1) / kSliceGroups, 1);
+    return n < S * (slices == 1 ? 128 : 320 * slices);
+}
+
 unsigned grid_for(int64_t n, int threads)
 {
     int64_t b = (n + threads - 1) / threads;
@@ -1714,11 +2040,14 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         int2 *pinfo, *imap;
         SwInfo *sinfo;
         uint32_t *filt, *cpos, *hh;
+        uint16_t *prio;
     } B;
-    const WalkRule rule = walk_rule(S > 0 ? (pre != nullptr ? pre->groups : (n_rules + 31) / 32) / S : 0);
+    const int64_t mean_groups = S > 0 ? (pre != nullptr ? pre->groups : (n_rules + 31) / 32) / S : 0;
+    const WalkRule rule = walk_rule(mean_groups);
     const int walk_threads = rule.threads;
     const int64_t walk_max = rule.most;
     const bool levels = T > walk_max;
+    const bool ranked = levels && !wide_level(T, S, mean_groups);  // (levels only shrink)
     // Few enough traces over tables this small are matched rule by rule: no
     // chunk sets, no wait for their count, two launches.  Chunk sets / rule by
     // rule: 1,000 traces over 16 rules per switch 46 / 23 us (k = 16), 4,000
@@ -1730,8 +2059,8 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
     const bool direct = pre == nullptr && !levels && S > 0 && n_rules <= static_cast<int64_t>(kDirectRules) * S &&
                         static_cast<int64_t>(T) * (n_rules / S + 1) <= kDirectWork &&
                         static_cast<int64_t>(T) * n_rules <= kDirectWorst;
-    // work items of a level: at most T / kItemCap + S (see the match launch)
-    const int32_t icap = static_cast<int32_t>(std::min<int64_t>(static_cast<int64_t>(T) / kItemCap + S + 1, INT32_MAX));
+    // work items of a level: at most T / kItemMin + S (see the match launch)
+    const int32_t icap = static_cast<int32_t>(std::min<int64_t>(static_cast<int64_t>(T) / kItemMin + S + 1, INT32_MAX));
     auto carve = [&](Carver &c) {
         B.pinfo = c.take<int2>(static_cast<size_t>(n_ports) + 1);
         B.sinfo = c.take<SwInfo>(static_cast<size_t>(S) + 1);
@@ -1767,6 +2096,7 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
     // (done by the caller when it passes prepared tables)
     if (pre != nullptr) {
         B.filt = const_cast<uint32_t *>(pre->filt);
+        B.prio = priorities(B.filt, pre->groups);
         B.gcount = const_cast<int32_t *>(pre->gcount);
         const int64_t n_info = std::max<int64_t>(n_ports, S);
         if (n_info > 0)
@@ -1800,13 +2130,14 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         const int64_t groups = ctx->h_small[0], prep_blocks = ctx->h_small[1];
         if (groups < 0 || prep_blocks < 0)
             return pc_set_error(ctx, PC_EINVAL, "pc_trace_flows: more than 2^31 rule groups");
-        rc = pc_ensure_aux(ctx, static_cast<size_t>(groups + 1) * kPlaneWords * sizeof(uint32_t));
+        rc = pc_ensure_aux(ctx, chunk_set_bytes(groups, ranked));
         if (rc) return rc;
         B.filt = reinterpret_cast<uint32_t *>(ctx->aux);
+        B.prio = priorities(ctx->aux, groups);
         if (prep_blocks > 0 && n_rules > 0) {
             PC_TIMED(ctx, "k_tr_prep", stream, hipLaunchKernelGGL(k_tr_prep, dim3(static_cast<unsigned>(prep_blocks)), dim3(kPrepWaves * 64), 0, stream, S,
-                               port_off, n_ports, rule_off, rules, B.gcount, B.gofs, B.bofs, B.filt, ctx->d_err,
-                               nullptr, B.cpos));
+                               port_off, n_ports, rule_off, rules, B.gcount, B.gofs, B.bofs, B.filt,
+                               ranked ? B.prio : nullptr, ctx->d_err, nullptr, B.cpos));
             PC_LAUNCH_CHECK(ctx);
         }
     }
@@ -1871,21 +2202,31 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
             break;
         }
         const int32_t nlive = static_cast<int32_t>(known);
+        const bool wide = wide_level(known, S, mean_groups);
+        // Larger items read a table's sets less often, as long as there are enough
+        // of them (192 / 256 / 384 lookups: a million over 320 tables of 1,024
+        // rules 254 / 232 / 199 us, over 720 of 8,192 816 / 772 / 697).
+        const int32_t cap = wide ? kWideItem
+                                 : static_cast<int32_t>(std::min<int64_t>(std::max<int64_t>(known / kItemsWanted, kItemLeast), kItemMax));
         PC_TIMED(ctx, "k_tr_plan", stream,
-                 hipLaunchKernelGGL(k_tr_plan, dim3(1), dim3(1024), 0, stream, cnt_cur, S, B.boff, B.ioff,
-                                    B.gcount, d_len + (level & 1), n_nxt, h_cnt + (level & 1)));
+                 hipLaunchKernelGGL(k_tr_plan, dim3(1), dim3(1024), 0, stream, cnt_cur, S, B.boff, B.ioff, cap, d_len + (level & 1), n_nxt, h_cnt + (level & 1)));
         PC_HIP(ctx, hipEventRecord(ctx->lvl_ev[level & 1], stream));
         PC_TIMED(ctx, "k_tr_scatter", stream,
                  hipLaunchKernelGGL(k_tr_scatter, dim3(grid_for(nlive, 256)), dim3(256), 0, stream, live_cur, len_cur,
                                     T, S, B.boff, B.bucket, B.ioff, B.imap, icap));
-        const Level lv{S,        T,     port_peer, B.pinfo, jur,   ttl, level, live_nxt, n_nxt,
+        const Level lv{S,        T,     port_peer, B.pinfo, jur,   ttl, cap, level, live_nxt, n_nxt,
                        cnt_nxt, out,   watch,     K,       visit, vsum, walk};
-        // at most nlive / kItemCap + S items: a switch of n lookups takes ceil(n / cap) items with cap >= kItemCap
-        const int64_t max_items = std::min<int64_t>(static_cast<int64_t>(nlive) / kItemCap + S, nlive);
-        PC_TIMED(ctx, "k_tr_match", stream,
-                 hipLaunchKernelGGL(k_tr_match, dim3(static_cast<unsigned>(8 * ((max_items + 7) / 8))),
-                                    dim3(kMatchThreads), 0, stream, S, B.sinfo, rules, B.filt, B.boff, B.ioff,
-                                    B.imap, B.bucket, lv));
+        // at most nlive / kItemMin + S items: a switch of n lookups takes ceil(n / cap) items with cap >= kItemMin
+        const int64_t max_items = std::min<int64_t>(static_cast<int64_t>(nlive) / kItemMin + S, nlive);
+        const dim3 mgrid(static_cast<unsigned>(8 * ((max_items + 7) / 8)));
+        if (wide)
+            PC_TIMED(ctx, "k_tr_match_wide", stream,
+                     hipLaunchKernelGGL(k_tr_match_wide, mgrid, dim3(kWideThreads), 0, stream, S, B.sinfo, rules,
+                                        B.filt, B.boff, B.ioff, B.imap, B.bucket, lv));
+        else
+            PC_TIMED(ctx, "k_tr_match", stream,
+                     hipLaunchKernelGGL(k_tr_match, mgrid, dim3(kMatchThreads), 0, stream, S, B.sinfo, rules, B.filt,
+                                        B.prio, B.boff, B.ioff, B.imap, B.bucket, lv));
         PC_LAUNCH_CHECK(ctx);
         if (level == 0) {
             known = nlive;  // the bound for level 1; its exact count is learned after level 0 completes
@@ -1952,14 +2293,15 @@ int tc_prepare_all(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_
         if (groups < 0 || blocks < 0)
             return pc_set_error(ctx, PC_EINVAL, "pc_trace_flows_delta: more than 2^31 rule groups");
     }
-    rc = pc_ensure_tc_filt(ctx, static_cast<size_t>(groups + 1) * kPlaneWords * sizeof(uint32_t));
+    rc = pc_ensure_tc_filt(ctx, chunk_set_bytes(groups, true));
     if (rc) return rc;
     if (S > 0) {
         if (blocks > 0) {
             PC_TIMED(ctx, "k_tr_prep", stream,
                      hipLaunchKernelGGL(k_tr_prep, dim3(static_cast<unsigned>(blocks)), dim3(kPrepWaves * 64), 0,
                                         stream, S, port_off, n_ports, rule_off, rules, m.gcount, m.gofs, m.bofs,
-                                        reinterpret_cast<uint32_t *>(ctx->tc_filt), ctx->d_err, m.sw_bad, m.cpos));
+                                        reinterpret_cast<uint32_t *>(ctx->tc_filt), priorities(ctx->tc_filt, groups),
+                                        ctx->d_err, m.sw_bad, m.cpos));
             PC_LAUNCH_CHECK(ctx);
         }
     }
@@ -2051,7 +2393,8 @@ int run_trace_delta(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32
         PC_TIMED(ctx, "k_tr_prep_listed", stream,
                  hipLaunchKernelGGL(k_tr_prep_listed, dim3(static_cast<unsigned>(C), per), dim3(kPrepWaves * 64), 0, stream,
                                     S, port_off, n_ports, rule_off, rules, kept.gcount, kept.gofs, kept.bofs,
-                                    reinterpret_cast<uint32_t *>(ctx->tc_filt), ctx->d_err, kept.sw_bad,
+                                    reinterpret_cast<uint32_t *>(ctx->tc_filt), priorities(ctx->tc_filt, ctx->tc_groups),
+                                    ctx->d_err, kept.sw_bad,
                                     kept.cpos, changed, &state->differs));
         PC_LAUNCH_CHECK(ctx);
     }

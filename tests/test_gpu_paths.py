@@ -397,3 +397,39 @@ def test_reach_bitset_orders(g, orc, k, Q, Kv):
         if k == 32 and a is oneway:
             break
     assert some > 0
+
+
+@pytest.mark.parametrize("variant", ["rpath", "prefix", "dense"])
+@pytest.mark.parametrize("R,T", [(1, 4100), (33, 2559), (33, 2560), (128, 9000), (257, 4100), (1500, 5000), (4096, 4100),
+                                 (4097, 12900), (8300, 19300)])
+def test_match_forms(g, orc, monkeypatch, variant, R, T):
+    """Levels matched with the table's sets in LDS (one to three slices, one to thirty-two lanes a lookup) and, as they
+    shrink or for few lookups a table, in registers: one and many matching rules per header, ties of priority."""
+    monkeypatch.setenv("PC_TRACE_WALK_MAX", "0")
+    wl = synth.trace_workload(R + T, 4, 4, R, T, 16, 40, variant=variant)
+    a = (wl["S"], wl["port_off"], wl["port_peer"], wl["jur"], wl["rule_off"], wl["rules"], wl["hdr"], wl["ingress"], 16)
+    _same_traces(g.trace(*a), orc.trace(*a)[0])
+
+
+def test_match_failing_candidates(g, orc, monkeypatch):
+    """Rules of the highest priorities that pass the chunk filter and fail in full: the first two survivors of every
+    lookup fail, up to twenty more do before the one that matches, which some switches lack; two match at a tie."""
+    monkeypatch.setenv("PC_TRACE_WALK_MAX", "0")
+    rng = np.random.default_rng(5)
+    wl = synth.trace_workload(9, 4, 4, 200, 6000, 16, 40)
+    S, off, rules = wl["S"], wl["rule_off"], wl["rules"].copy()
+    key = synth.random_keys(rng, 1)[0]
+    hdr = np.repeat(key[None], 6000, 0).astype(np.uint32)
+    for s in range(S):
+        n = off[s + 1] - off[s]
+        r = rules[off[s]:off[s + 1]]
+        r["value"], r["mask"] = key[None], np.array([~np.uint32(0)] * 3 + [np.uint32(255)], np.uint32)
+        at = rng.integers(0, 26, n)
+        r["value"][np.arange(n), at // 8] ^= (np.uint32(5) << (4 * (at % 8)).astype(np.uint32))
+        r["priority"] = rng.integers(100, 65536, n)
+        r["action"] = rng.integers(0, 4, n)
+        if s % 5:
+            for x in rng.integers(0, n, 2):
+                r["mask"][x], r["priority"][x] = 0, 50
+    a = (S, wl["port_off"], wl["port_peer"], wl["jur"], off, rules, hdr, wl["ingress"], 16)
+    _same_traces(g.trace(*a), orc.trace(*a)[0])
