@@ -17,7 +17,10 @@ namespace {
 
 constexpr int kThreads = 256;
 
-__global__ __launch_bounds__(kThreads) void k_report(int32_t I, const pc_intent *__restrict__ intents, int32_t rows,
+// kT threads a workgroup, an intent each.  A single workgroup writes the
+// summary, several add to it (cleared by a launch before).
+template <int kT>
+__global__ __launch_bounds__(kT) void k_report(int32_t I, const pc_intent *__restrict__ intents, int32_t rows,
                                                      const uint64_t *__restrict__ feasible, int32_t W,
                                                      const uint8_t *__restrict__ ends,
                                                      const uint32_t *__restrict__ popcnt, int32_t N,
@@ -35,7 +38,7 @@ __global__ __launch_bounds__(kThreads) void k_report(int32_t I, const pc_intent 
     const int tid = threadIdx.x, lane = tid & 63;
     if (tid < kHist) hist[tid] = 0;
     __syncthreads();
-    const int32_t i = blockIdx.x * kThreads + tid;
+    const int32_t i = blockIdx.x * kT + tid;
     bool ok = false, bad = false;
     if (i < I) {
         const pc_intent it = intents[i];
@@ -104,7 +107,9 @@ __global__ __launch_bounds__(kThreads) void k_report(int32_t I, const pc_intent 
     if (lane == 0 && i0 < I) pass[i0 >> 6] = word;
     if (__ballot(bad) && lane == 0) atomicOr(d_err, PC_DERR_INTENT);
     __syncthreads();
-    if (tid < kHist && hist[tid]) atomicAdd(&summary[tid], static_cast<unsigned long long>(hist[tid]));
+    if (tid >= kHist) return;
+    if (gridDim.x == 1) summary[tid] = hist[tid];
+    else if (hist[tid]) atomicAdd(&summary[tid], static_cast<unsigned long long>(hist[tid]));
 }
 
 }  // namespace
@@ -115,12 +120,17 @@ int run_report(pc_ctx *ctx, int32_t I, const pc_intent *intents, int32_t rows, c
                const pc_path_expect *pexp, uint64_t *pass, uint8_t *reason, pc_summary *summary, hipStream_t stream)
 {
     static_assert(sizeof(pc_summary) == 68 * 8, "summary layout");
-    launch_fill_u64(reinterpret_cast<uint64_t *>(summary), 68, 0, stream);
+    // up to 1,024 intents in one workgroup, without the clear
+    const bool one = I > 0 && I <= 1024;
+    if (!one) launch_fill_u64(reinterpret_cast<uint64_t *>(summary), 68, 0, stream);
     PC_LAUNCH_CHECK(ctx);
     if (I == 0) return PC_OK;
-    PC_TIMED(ctx, "k_report", stream, hipLaunchKernelGGL(k_report, dim3(static_cast<unsigned>((I + kThreads - 1) / kThreads)), dim3(kThreads), 0,
-                       stream, I, intents, rows, feasible, W, ends, popcnt, N, traces, T, expect, reach, Q, visit, pexp, pass, reason,
-                       reinterpret_cast<unsigned long long *>(summary), ctx->d_err));
+    const int threads = one && I > kThreads ? 1024 : kThreads;
+    PC_TIMED(ctx, "k_report", stream,
+             hipLaunchKernelGGL(threads == kThreads ? k_report<kThreads> : k_report<1024>,
+                                dim3(static_cast<unsigned>((I + threads - 1) / threads)), dim3(threads), 0, stream, I,
+                                intents, rows, feasible, W, ends, popcnt, N, traces, T, expect, reach, Q, visit, pexp,
+                                pass, reason, reinterpret_cast<unsigned long long *>(summary), ctx->d_err));
     PC_LAUNCH_CHECK(ctx);
     return PC_OK;
 }

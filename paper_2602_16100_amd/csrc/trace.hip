@@ -331,12 +331,12 @@ struct Infos {
     const int32_t *gofs;
     uint32_t *d_err;
 
-    // a workgroup's share of switch s: its ports' records
-    __device__ __forceinline__ void ports(int32_t s, int32_t S) const
+    // the ports' records of switch s, by n threads
+    __device__ __forceinline__ void ports(int32_t s, int32_t S, int32_t thread, int32_t n) const
     {
         const int64_t pb = port_off[s], pe = port_off[s + 1];
         if (pc_range_ok(pb, pe, n_ports))
-            for (int64_t p = pb + threadIdx.x; p < pe; p += blockDim.x) pinfo[p] = make_port(port_peer[p], S, jur);
+            for (int64_t p = pb + thread; p < pe; p += n) pinfo[p] = make_port(port_peer[p], S, jur);
     }
     // the action flag of a switch without chunk sets (else k_tr_prep raises it)
     __device__ __forceinline__ void sweep_actions(int32_t s, const pc_rule *__restrict__ r, int64_t R) const
@@ -368,7 +368,7 @@ __global__ __launch_bounds__(64) void k_tr_direct(int32_t S, const int32_t *__re
     if (!rok || !pc_range_ok(inf.port_off[s], inf.port_off[s + 1], inf.n_ports)) errs |= PC_DERR_OFFSETS;
     if (errs) atomicOr(inf.d_err, errs);
     if (threadIdx.x == 0) inf.sinfo[s] = make_info(s, inf.port_off, inf.n_ports, rule_off, n_rules, 0, 0, false);
-    inf.ports(s, S);
+    inf.ports(s, S, threadIdx.x, blockDim.x);
     if (rok) inf.sweep_actions(s, rules + rb, re - rb);
 }
 
@@ -420,20 +420,27 @@ __global__ __launch_bounds__(256) void k_tr_choose(int32_t S, const int32_t *__r
         atomicAdd(&score[n], static_cast<unsigned long long>(a * (static_cast<uint64_t>(hh[n * 16 + x]) + 1)));
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t taken = 0, cp = 0;
-        for (int c = 0; c < kChunks; ++c) {
-            int best = -1;
-            for (int n = 0; n < kKeyNibbles; ++n)
-                if (!((taken >> n) & 1u) && (best < 0 || score[n] < score[best])) best = n;
-            taken |= 1u << best;
-            cp |= static_cast<uint32_t>(best) << (5 * c);
-        }
+    // the first wavefront ranks the scores, a nibble per lane (a thread that
+    // picked them one after the other read 156 in a chain); the others write
+    // the ports' records
+    if (threadIdx.x >= 64) {
+        if (inf.sinfo != nullptr) inf.ports(s, S, threadIdx.x - 64, 192);
+        return;
+    }
+    const int n = threadIdx.x;
+    int rank = kChunks;
+    if (n < kKeyNibbles) {
+        rank = 0;
+        for (int k = 0; k < kKeyNibbles; ++k) rank += score[k] < score[n] || (score[k] == score[n] && k < n);
+    }
+    uint32_t cp = rank < kChunks ? static_cast<uint32_t>(n) << (5 * rank) : 0u;
+#pragma unroll
+    for (int off = 16; off > 0; off >>= 1) cp |= __shfl_xor(cp, off, 64);
+    if (n == 0) {
         cpos[s] = cp;
         if (inf.sinfo != nullptr)
             inf.sinfo[s] = make_info(s, inf.port_off, inf.n_ports, rule_off, n_rules, inf.gofs[s], cp, true);
     }
-    if (inf.sinfo != nullptr) inf.ports(s, S);
 }
 
 // Rows r of a 32-lane half hold 32-bit words x_r; afterwards lane i holds
@@ -1989,7 +1996,7 @@ int sweep_and_choose(pc_ctx *ctx, int32_t S, const int32_t *port_peer, int64_t n
                      const int32_t *watch, uint32_t *hh, uint32_t *cpos, const Infos &inf, hipStream_t stream)
 {
     const int64_t n = std::max<int64_t>({n_ports, n_watch, std::min<int64_t>(T, kHeaderSample)});
-    const unsigned blocks = static_cast<unsigned>(std::min<int64_t>(std::max<int64_t>((n + 1023) / 1024, 1), 256));
+    const unsigned blocks = static_cast<unsigned>(std::min<int64_t>(std::max<int64_t>((n + 255) / 256, 1), 256));
     PC_TIMED(ctx, "k_tr_sweep", stream,
              hipLaunchKernelGGL(k_tr_sweep, dim3(blocks), dim3(256), 0, stream, n_ports, port_peer, S, n_watch, watch,
                                 hdr, T, hh, ctx->d_err));

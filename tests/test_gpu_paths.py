@@ -433,3 +433,27 @@ def test_match_failing_candidates(g, orc, monkeypatch):
                 r["mask"][x], r["priority"][x] = 0, 50
     a = (S, wl["port_off"], wl["port_peer"], wl["jur"], off, rules, hdr, wl["ingress"], 16)
     _same_traces(g.trace(*a), orc.trace(*a)[0])
+
+
+@pytest.mark.parametrize("I", [1, 63, 256, 257, 1024, 1025, 2500])
+def test_report_sizes(g, orc, I):
+    """One workgroup that writes the summary (up to 1,024 intents) and several that add to it."""
+    wl = synth.cfg1(0, "rpath")
+    oo = orc.run_workload(wl)
+    rng = np.random.default_rng(I)
+    pick = rng.integers(0, wl["intents"].shape[0], I)
+    intents, expect = wl["intents"][pick].copy(), wl["expect"][pick].copy()
+    intents["trace_end"][::17] = 1 << 30
+    T = wl["hdr"].shape[0]
+    visit = rng.integers(0, 8, size=T).astype(np.uint32)
+    pexp = np.zeros(I, synth.PATH_EXPECT_DT)
+    pexp["must"] = rng.integers(0, 2, size=I)
+    for _ in range(2):
+        pg, rg, sg = g.report_paths(intents, oo["feasible"], oo["popcnt"], wl["N"], oo["traces"], expect, oo["reach"],
+                                    visit, pexp)
+        po, ro, so, _ = orc.report(intents, oo["feasible"], oo["popcnt"], wl["N"], oo["traces"], expect, oo["reach"],
+                                   visit, pexp)
+        _same(rg, ro, "reason")
+        _same(pg, po, "pass")
+        _same(sg["counts"], so["counts"], "counts")
+        _same(sg["no_path"], so["no_path"], "no_path")
