@@ -457,3 +457,30 @@ def test_report_sizes(g, orc, I):
         _same(pg, po, "pass")
         _same(sg["counts"], so["counts"], "counts")
         _same(sg["no_path"], so["no_path"], "no_path")
+
+
+@pytest.mark.parametrize("deg", [1, 15, 16, 17, 31, 32, 33, 80])
+def test_reach_target_degrees(g, orc, deg):
+    """Targets of every number of neighbours around the look-ahead's two registers per lane, some reached through one
+    of them only, most of them forbidden on the way."""
+    rng = np.random.default_rng(deg)
+    hubs, ring = 40, 300  # hub h: deg neighbours on a ring
+    pairs = [(v, hubs + (v - hubs + 1) % ring) for v in range(hubs, hubs + ring)]
+    pairs += [(h, hubs + int(x)) for h in range(hubs) for x in rng.choice(ring, deg, replace=False)]
+    pairs = np.array(pairs, np.int32)
+    pairs = np.unique(np.concatenate([pairs, pairs[:, ::-1]]), axis=0)
+    V = hubs + ring
+    off = np.zeros(V + 1, np.int32)
+    off[1:] = np.cumsum(np.bincount(pairs[:, 0], minlength=V))
+    adj = pairs[:, 1].astype(np.int32)
+    Q = 130
+    target = rng.integers(0, hubs, Q).astype(np.int32)
+    src = rng.integers(hubs, V, Q).astype(np.int32)
+    region = (rng.random(V) < 0.2).astype(np.uint8)
+    region[:hubs] = 0
+    allowed = rng.integers(0, 2, Q).astype(np.uint32) * 2 + 1
+    forbid = np.stack([adj[off[target] + np.minimum(k, off[target + 1] - off[target] - 1)] for k in range(6)], 1).astype(np.int32)
+    none = np.full((Q, 0), -1, np.int32)
+    dg = g.reach_via(V, off, adj, region, src, allowed, target, none, forbid)
+    do, _ = orc.reach_via(V, off, adj, region, src, allowed, target, none, forbid)
+    _same(dg, do, "reach_via")
