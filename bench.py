@@ -365,18 +365,21 @@ def cpu_baseline(wl, pairs_total, target_s, gpu=None):
     return out
 
 
-HOP_KERNELS = ("k_tr_init", "k_tr_plan", "k_tr_scatter", "k_tr_match", "k_tr_walk")  # A3 after preparation
+HOP_KERNELS = ("k_tr_init", "k_tr_plan", "k_tr_scatter", "k_tr_match", "k_tr_match_wide", "k_tr_walk")  # A3 after preparation
 
 
-WALK_MAX = 8192  # the library's default switch-over to per-trace walks (PC_TRACE_WALK_MAX)
+def walk_max(wl):
+    """The library's default switch-over to per-trace walks (PC_TRACE_WALK_MAX overrides it)."""
+    R = int(np.asarray(wl["rule_off"], np.int64)[-1])
+    return 65536 if wl["S"] == 0 or (R + 31) // 32 // wl["S"] <= 128 else 32768
 
 
 def trace_levels(wl, pc, ctx, D, full):
     """The hop levels the bucketed match kernel runs, with the switches each
     touches, from the library's own walk records (the first 8 switches of
     every walk; for later levels, a run with TTL l stops every trace that is
-    still going at its level-l switch).  The library buckets level 0 when more than WALK_MAX traces
-    start, and level l >= 1 when more than WALK_MAX traces entered level
+    still going at its level-l switch).  The library buckets level 0 when more than walk_max traces
+    start, and level l >= 1 when more than walk_max traces entered level
     l - 1; later levels are walked per trace.  Returns the per-level
     (lookups, touched switches, rules of those switches) of the bucketed
     levels and the lookups of the walked ones."""
@@ -389,8 +392,9 @@ def trace_levels(wl, pc, ctx, D, full):
     live = [int((started & (hops >= lv)).sum()) for lv in range(int(hops[started].max()) + 1)] if started.any() \
         else []
     bucketed = []
+    most = walk_max(wl)
     for lv in range(len(live)):
-        if (live[0] if lv == 0 else live[lv - 1]) > WALK_MAX:
+        if (live[0] if lv == 0 else live[lv - 1]) > most:
             bucketed.append(lv)
         else:
             break
@@ -415,7 +419,8 @@ def trace_levels(wl, pc, ctx, D, full):
 
 
 def trace_roofline(wl, pc, ctx, D, full, prof, steps, workload):
-    """k_tr_match, the hop loop's dominant kernel, against the HBM roofline
+    """The match kernel (k_tr_match, or k_tr_match_wide where it took most of
+    the levels), the hop loop's dominant kernel, against the HBM roofline
     with its algorithmic bytes: 30 B per rule of every switch a
     bucketed level touches, plus 32 B per trace (header, ingress, record).
     `layout_bytes` is what this library's layout needs for the same levels
@@ -426,12 +431,13 @@ def trace_roofline(wl, pc, ctx, D, full, prof, steps, workload):
     R = np.diff(np.asarray(wl["rule_off"], np.int64))
     rules = sum(r for _, _, r in lv["levels"])
     alg = rules * 30 + T * 32
-    n, ms_tot = prof.get("k_tr_match", (0, 0.0))
+    kernel = max(("k_tr_match", "k_tr_match_wide"), key=lambda k: prof.get(k, (0, 0.0))[1])
+    n, ms_tot = prof.get(kernel, (0, 0.0))
     ms = ms_tot / steps
     gbs = alg / (ms * 1e-3) / 1e9 if ms > 0 else 0.0
     hop_ms = {k: prof[k][1] / steps for k in HOP_KERNELS if k in prof}
-    out = {"kernel": "k_tr_match", "bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-           "frac": gbs / HBM_PEAK_GBS, "traffic": measured_traffic(workload, "k_tr_match"),
+    out = {"kernel": kernel, "bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+           "frac": gbs / HBM_PEAK_GBS, "traffic": measured_traffic(workload, kernel),
            "alg_bytes_per_step": alg, "launches_per_step": n / steps, "ms_per_step": ms,
            "bucketed_levels": [{"lookups": a, "switches": b, "rules": c} for a, b, c in lv["levels"]],
            "walked_lookups": lv["walked_lookups"],
@@ -729,7 +735,7 @@ def time_update(args, wl, pc, ctx, D, feasible, popcnt):
                 t_full.append(t2 - t1)
         u, f = float(np.median(t_upd)), float(np.median(t_full))
         out["per_m"][str(M)] = {"ms_per_update": 1e3 * u, "ms_full_evaluation": 1e3 * f, "speedup": f / u,
-                                "path": "incremental" if M <= W // 32 else "full re-evaluation"}
+                                "path": "incremental" if M <= out["full_above"] else "full re-evaluation"}
     if not args.no_cpu_baseline:
         import oracle
         threads = len(os.sched_getaffinity(0))
@@ -880,8 +886,8 @@ def time_synthesis(args, wl, pc, ctx):
         "data_error_flags": flags,
         # the search is instruction and latency bound (no HBM stream to
         # price): its issue rate, when counters are recorded for its source
-        "roofline": alu_view("k_ps_search", prof["k_ps_search"][1] / max(prof["k_ps_search"][0], 1)
-                             if "k_ps_search" in prof else None),
+        "roofline": alu_view("k_ps_goal", prof["k_ps_goal"][1] / max(prof["k_ps_goal"][0], 1)
+                             if "k_ps_goal" in prof else None),
     }
     if not args.no_cpu_baseline:
         import oracle
@@ -1061,8 +1067,8 @@ def bench_cfg3(args, pc, ctx):
     started = (ing >= 0) & (ing < wl["S"])
     lookups = int((tr["hops"][started].astype(np.int64) + 1).sum())
     roof = trace_roofline(wl, pc, ctx, D, tr, prof, args.steps, f"cfg3-{args.variant}")
-    prep_ms = sum(ms for k, (n, ms) in prof.items() if k in ("k_tr_prep", "k_tr_choose", "k_tr_switch_info",
-                                                             "k_tr_port_check")) / args.steps
+    prep_ms = sum(ms for k, (n, ms) in prof.items() if k in ("k_tr_prep", "k_tr_choose", "k_tr_layout",
+                                                             "k_tr_sweep")) / args.steps
     extra = {"per_kernel": per_kernel_table(prof, args.steps), "flow_lookups_per_step": lookups,
              "mean_lookups_per_trace": lookups / max(int(started.sum()), 1),
              "terminal_states": {k: int((tr["state"] == v).sum()) for k, v in

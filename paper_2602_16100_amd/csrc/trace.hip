@@ -960,140 +960,6 @@ __global__ __launch_bounds__(1024) void k_tr_plan(int32_t *__restrict__ counts, 
     }
 }
 
-// The survivors of a lookup in four groups: bit r of s[k] is rule r of group
-// k.  at: the groups' chunk sets of value 0 of chunk 0, rows of 16 << kLg bytes
-// (row c * 16 + x: chunk c, value x); nib: the lookup's values, four bits each.
-template <int kLg>
-__device__ __forceinline__ void load_sets(const char *at, uint32_t nib, uint4 (&v)[kChunks])
-{
-#pragma unroll
-    for (int c = 0; c < kChunks; ++c)
-        v[c] = *reinterpret_cast<const uint4 *>(at + (c * 16 << (kLg + 4)) + (((nib >> (4 * c)) & 15) << (kLg + 4)));
-}
-
-__device__ __forceinline__ void and_sets(const uint4 (&v)[kChunks], uint32_t (&s)[4])
-{
-    s[0] = v[0].x & v[1].x & v[2].x & v[3].x & v[4].x & v[5].x;
-    s[1] = v[0].y & v[1].y & v[2].y & v[3].y & v[4].y & v[5].y;
-    s[2] = v[0].z & v[1].z & v[2].z & v[3].z & v[4].z & v[5].z;
-    s[3] = v[0].w & v[1].w & v[2].w & v[3].w & v[4].w & v[5].w;
-    static_assert(kChunks == 6, "every chunk's set");
-}
-
-// One wavefront matches its nw <= 64 lookups (lane j's packed: lookup j's values
-// of the chunks) against the slice whose chunk sets and priorities (0xFFFF -
-// priority) are in LDS.  1 << kLg lanes take a lookup, four groups a lane, so
-// that a read is 16 bytes a lane; two passes' reads go out together.  A pass only
-// asks which lanes have survivors and queues these; 64 queued at a time, their sets are
-// formed again and cand[j], cand2[j] become lookup j's first two survivors by (priority,
-// index).  Only these rules are checked in full (lane j: verify(lookup, rule)): where
-// many rules admit a header, as with prefixes, nearly every survivor matches.
-// A lookup whose candidates both fail checks all its survivors.
-template <int kLg, class Verify>
-__device__ __forceinline__ void filter_slice(const uint4 *sets, const uint16_t *prio, uint32_t packed, int32_t nw,
-                                             uint16_t *q, uint32_t *cand, uint32_t *cand2,
-                                             Verify &&verify)
-{
-    constexpr int kPer = 64 >> kLg;  // lookups per pass
-    const int lane = threadIdx.x & 63, sub = lane >> kLg, l = lane & ((1 << kLg) - 1);
-    const char *base = reinterpret_cast<const char *>(sets);
-    auto of_lane = [&](int32_t j, uint32_t x) {
-        return static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(4 * j, static_cast<int>(x)));
-    };
-    auto settle = [&]() {  // what other lanes of this wavefront wrote to LDS
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    };
-    int32_t qn = 0;
-    auto push = [&](bool any, uint32_t entry, auto &&drain) {
-        const uint64_t m = __ballot(any);
-        const int n = __popcll(m);
-        if (qn + n > kQueue) drain();
-        const uint32_t below = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
-                                                         __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
-        if (any) q[qn + below] = static_cast<uint16_t>(entry);
-        qn += n;
-    };
-    // queued: lookup << 5 | lane of its groups
-    auto rank = [&]() {
-        settle();
-        for (int32_t e0 = 0; e0 < qn; e0 += 64) {
-            const uint32_t en = q[min(e0 + lane, qn - 1)];
-            const int32_t j = static_cast<int32_t>(en >> 5), ql = static_cast<int32_t>(en & 31);
-            uint4 v[kChunks];
-            uint32_t s[4], first = ~0u, second = ~0u;
-            load_sets<kLg>(base + 16 * ql, of_lane(j, packed), v);
-            and_sets(v, s);
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                for (uint32_t m = s[k]; m; m &= m - 1) {
-                    const uint32_t at = 128 * ql + 32 * k + __builtin_ctz(m);
-                    const uint32_t key = static_cast<uint32_t>(prio[at]) << 12 | at;
-                    second = min(second, max(first, key));
-                    first = min(first, key);
-                }
-            // what does not stay the first competes for the second place
-            if (e0 + lane < qn) second = min(second, max(first, atomicMin(cand + j, first)));
-            if (e0 + lane < qn && second != ~0u) atomicMin(cand2 + j, second);
-        }
-        settle();
-        qn = 0;
-    };
-    if (lane < nw) cand[lane] = cand2[lane] = ~0u;
-    for (int32_t j0 = 0; j0 < nw; j0 += 2 * kPer) {
-        uint4 a[kChunks], b[kChunks];
-        uint32_t s[4];
-        load_sets<kLg>(base + 16 * l, of_lane(min(j0 + sub, nw - 1), packed), a);
-        load_sets<kLg>(base + 16 * l, of_lane(min(j0 + kPer + sub, nw - 1), packed), b);
-        and_sets(a, s);
-        push((s[0] | s[1] | s[2] | s[3]) != 0 && j0 + sub < nw, (j0 + sub) << 5 | l, rank);
-        and_sets(b, s);
-        push((s[0] | s[1] | s[2] | s[3]) != 0 && j0 + kPer + sub < nw, (j0 + kPer + sub) << 5 | l, rank);
-    }
-    rank();
-    const uint32_t first = lane < nw ? cand[lane] : ~0u, second = lane < nw ? cand2[lane] : ~0u;
-    const bool one = first != ~0u && verify(lane, static_cast<int32_t>(first & 4095));
-    const bool two = second != ~0u && verify(lane, static_cast<int32_t>(second & 4095));
-    const bool failed = second != ~0u && !one && !two;
-    const uint64_t fm = __ballot(failed);
-    if (fm == 0) return;
-    // the failed lookups again, compacted; queued: place << 7 | lane << 2 | word
-    const int32_t nf = __popcll(fm);
-    if (failed) q[__popcll(fm & ((1ull << lane) - 1))] = static_cast<uint16_t>(lane);
-    settle();
-    const uint32_t which = q[min(lane, nf - 1)];
-    const uint32_t again = of_lane(static_cast<int32_t>(which), packed);
-    settle();
-    auto check = [&]() {
-        settle();
-        for (int32_t e0 = 0; e0 < qn; e0 += 64) {
-            const uint32_t en = q[min(e0 + lane, qn - 1)];
-            const int32_t j = static_cast<int32_t>(en >> 7), ql = static_cast<int32_t>((en >> 2) & 31);
-            uint4 v[kChunks];
-            uint32_t s[4];
-            load_sets<kLg>(base + 16 * ql, of_lane(j, again), v);
-            and_sets(v, s);
-            const uint32_t k = en & 3, to = of_lane(j, which);
-            if (e0 + lane < qn)
-                for (uint32_t m = k == 0 ? s[0] : k == 1 ? s[1] : k == 2 ? s[2] : s[3]; m; m &= m - 1)
-                    (void)verify(static_cast<int32_t>(to), static_cast<int32_t>(128 * ql + 32 * k + __builtin_ctz(m)));
-        }
-        settle();
-        qn = 0;
-    };
-    for (int32_t j0 = 0; j0 < nf; j0 += kPer) {
-        uint4 a[kChunks];
-        uint32_t s[4];
-        load_sets<kLg>(base + 16 * l, of_lane(min(j0 + sub, nf - 1), again), a);
-        and_sets(a, s);
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            push(s[k] != 0 && j0 + sub < nf, (j0 + sub) << 7 | l << 2 | k, check);
-    }
-    check();
-}
-
 // What a match workgroup keeps of its switch's first kPortSlots ports: peer,
 // the peer's jurisdiction bit, and the item's traces that leave through the port
 // (count, then the base of their ranks in the peer's bucket).  The item's live
@@ -1189,155 +1055,6 @@ __device__ __forceinline__ void apply_matches(const Level &lv, int32_t s, int64_
         *reinterpret_cast<int4 *>(lv.live_next + bb + threadIdx.x) = make_int4(-1, -1, 0, 0);
 }
 
-// One workgroup per work item = (switch, an even share of at most lv.cap
-// lookups of its bucket).  Items are dealt to XCDs in contiguous ranges, so
-// the shares of one switch share an L2.  The switch's chunk sets are read from
-// LDS, a slice of 4,096 rules at a time, which takes half the instructions of
-// k_tr_match_wide's register indexing (a level of 4.2 million lookups in 1,280
-// tables of 4,096 rules: 42 vector and 35 scalar instructions per lookup there,
-// 31 and 15 here).  Bound by staging and moving the lookups, 155 of such a level's 340
-// us, then by the vector instructions of the filter, 130.  4,194,304 traces
-// over these tables 1,757 us in k_tr_match_wide, now 1,417; 500,009 over
-// 720 routing tables of 2,048 prefixes, where a lookup has dozens of matching
-// rules, 935 and 470 (842 with every survivor checked).
-__global__ __launch_bounds__(kMatchThreads, 4) void k_tr_match(
-    int32_t S, const SwInfo *__restrict__ sinfo, const pc_rule *__restrict__ rules, const uint32_t *__restrict__ filt,
-    const uint16_t *__restrict__ prios, const int32_t *__restrict__ boff, const int32_t *__restrict__ ioff,
-    const int2 *__restrict__ imap, const BRec *__restrict__ bucket, Level lv)
-{
-    __shared__ uint4 sets[kPlaneWords * kSliceGroups / 4];
-    __shared__ uint64_t best[kChunk];
-    __shared__ __align__(16) pc_key keys[kChunk];
-    __shared__ uint32_t cidx[kChunk];  // each lookup's values of the switch's filter chunks, four bits each; then its
-                                       // candidate (a wavefront's own lookups only)
-    __shared__ uint32_t cand2[kChunk];
-    __shared__ int32_t tids[kChunk];
-    __shared__ uint32_t tjm[kChunk];   // each lookup's trace: jurisdiction mask so far
-    __shared__ uint16_t prio[kSliceGroups * 32] __attribute__((aligned(16)));
-    __shared__ uint16_t queue[kMatchWaves][kQueue];  // per wavefront (see filter_slice)
-    __shared__ PortMoves ports;
-    // the grid was sized from an upper bound on the item count: blocks past
-    // the real count's per-XCD share return at once
-    const int32_t n_items = ioff[S];
-    const int32_t per = (n_items + 7) / 8;
-    const int32_t kx = static_cast<int32_t>(blockIdx.x >> 3);
-    if (kx >= per) return;
-    const int32_t item = static_cast<int32_t>(blockIdx.x & 7) * per + kx;
-    if (item >= n_items) return;
-    // the item's switch and its index among the switch's items
-    const int2 im = imap[item];
-    const int32_t s = im.x;
-    if (static_cast<uint32_t>(s) >= static_cast<uint32_t>(S)) return;
-    const SwInfo si = sinfo[s];
-    const int32_t b0 = boff[s], b1 = boff[s + 1];
-    const int32_t share = even_parts(b1 - b0, lv.cap);
-    const int32_t bb = b0 + im.y * share;
-    const int32_t tn = min(share, min(b1, lv.T) - bb);  // bucket holds at most T entries
-    if (tn <= 0) return;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int32_t G = si.G;
-    const int64_t rb = si.rb;
-    const uint32_t *fs = filt + static_cast<int64_t>(si.gofs) * kPlaneWords;
-    const uint32_t cp = si.cpos;
-    // the switch's ports (np < 0: its port range is invalid)
-    const int64_t pb = si.pb, np = si.np;
-    // lanes that take a lookup: a slice's groups, four a lane
-    const int32_t quads = (min(G, kSliceGroups) + 3) / 4;
-    const int lpl_bits = quads <= 1 ? 0 : 32 - __builtin_clz(static_cast<uint32_t>(quads - 1)), lpl = 1 << lpl_bits;
-    // a slice's chunk sets into LDS (no survivors past the last group)
-    auto fill = [&](int32_t g0) {
-        const int32_t ng = min(G - g0, kSliceGroups);
-        constexpr int kFills = kPlaneWords * kSliceGroups / 4 / kMatchThreads;
-        static_assert(kSliceGroups * 4 == kMatchThreads, "16 bytes of priorities per thread");
-        uint4 v[kFills], pr = make_uint4(0, 0, 0, 0);
-        if (static_cast<int32_t>(threadIdx.x) < ng * 4)
-            pr = reinterpret_cast<const uint4 *>(prios + (static_cast<int64_t>(si.gofs) + g0) * 32)[threadIdx.x];
-#pragma unroll
-        for (int k = 0; k < kFills; ++k) {
-            const int x = static_cast<int>(threadIdx.x) + k * kMatchThreads;
-            const int32_t row = x >> lpl_bits, g = 4 * (x & (lpl - 1));
-            v[k] = make_uint4(0, 0, 0, 0);
-            if (row < kPlaneWords) {
-                const uint32_t *src = fs + static_cast<int64_t>(row) * G + g0 + g;
-                if (g + 4 <= ng) {
-                    __builtin_memcpy(&v[k], src, 16);
-                } else {
-                    if (g < ng) v[k].x = src[0];
-                    if (g + 1 < ng) v[k].y = src[1];
-                    if (g + 2 < ng) v[k].z = src[2];
-                }
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kFills; ++k) {
-            const int x = static_cast<int>(threadIdx.x) + k * kMatchThreads;
-            if (x < kPlaneWords * lpl) sets[x] = v[k];
-        }
-        reinterpret_cast<uint4 *>(prio)[threadIdx.x] = pr;
-    };
-    // stage the lookups (one per thread) and the first slice's sets
-    const int i = static_cast<int>(threadIdx.x);
-    BRec r{};
-    if (i < tn) r = bucket[bb + i];
-    fill(0);
-    if (threadIdx.x < kPortSlots) {
-        const int2 pi = static_cast<int64_t>(threadIdx.x) < np ? lv.pinfo[pb + threadIdx.x] : make_int2(-2, 0);
-        ports.peer[threadIdx.x] = pi.x;
-        ports.jbit[threadIdx.x] = static_cast<uint32_t>(pi.y);
-        ports.count[threadIdx.x] = 0;
-        if (threadIdx.x == 0) ports.nother = 0;
-    }
-    if (i < tn) {
-        int32_t t = r.t;
-        pc_key h = r.key;
-        uint32_t jmv = r.jm;
-        if (static_cast<uint32_t>(t) >= static_cast<uint32_t>(lv.T)) {  // not a trace id: skipped
-            t = -1;
-            h = pc_key{};
-            jmv = 0;
-        }
-        tids[i] = t;
-        keys[i] = h;
-        tjm[i] = jmv;
-        best[i] = kNoMatch;
-        uint32_t x = 0;
-#pragma unroll
-        for (int c = 0; c < kChunks; ++c) x |= key_nibble(h.w[0], h.w[1], h.w[2], h.w[3], chunk_pos(cp, c)) << (4 * c);
-        cidx[i] = x;
-    }
-    __syncthreads();
-    const int32_t per_wave = (tn + kMatchWaves - 1) / kMatchWaves;  // the wavefront's lookups
-    const int32_t jw = wave * per_wave, nw = min(per_wave, tn - jw);
-    const uint32_t packed = nw > 0 ? cidx[jw + min(lane, nw - 1)] : 0u;
-    for (int32_t g0 = 0; g0 < G; g0 += kSliceGroups) {
-        if (g0 > 0) {
-            __syncthreads();  // the slice before is no longer read
-            fill(g0);
-            __syncthreads();
-        }
-        auto verify = [&](int32_t j, int32_t at) {
-            const uint32_t local = static_cast<uint32_t>(g0) * 32 + static_cast<uint32_t>(at);
-            const pc_rule x = rules[rb + local];
-            const pc_key &h = keys[jw + j];
-            const bool ok = rule_matches(&x, h.w[0], h.w[1], h.w[2], h.w[3]);
-            if (ok)
-                atomicMin(reinterpret_cast<unsigned long long *>(&best[jw + j]),
-                          static_cast<unsigned long long>(rule_key(&x, local)));
-            return ok;
-        };
-        if (lpl_bits == 5) filter_slice<5>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
-        else if (lpl_bits == 4) filter_slice<4>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
-        else if (lpl_bits == 3) filter_slice<3>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
-        else if (lpl_bits == 2) filter_slice<2>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
-        else if (lpl_bits == 1) filter_slice<1>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
-        else filter_slice<0>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
-    }
-    // every wavefront's matches are in best[]
-    __syncthreads();
-    apply_matches(lv, s, pb, np, bb, tn, tids, tjm, best, keys, ports);
-}
-
 typedef uint32_t v16u __attribute__((ext_vector_type(16)));
 
 // Filter four lookups: sv[k] = AND over the six chunks c of F[c][x[c][k]].
@@ -1402,9 +1119,12 @@ __device__ __forceinline__ void filter_quad(const uint32_t (&x)[kChunks][4], con
 }
 #undef PC_IDX
 
-// The same with the chunk sets in registers, a group per lane and 256 groups
-// per workgroup, for levels of few lookups per table (see wide_level): no barrier
-// between the parts of a table, and smaller items.
+// One workgroup per work item = (switch, an even share of at most lv.cap
+// lookups of its bucket).  Items are dealt to XCDs in contiguous ranges, so
+// the shares of one switch share an L2.  The chunk sets are in registers, a
+// group per lane and 256 groups per workgroup: for levels of few lookups per
+// table (see wide_level), where no barrier between the parts of a table and smaller
+// items count for more than k_tr_match's cheaper filter.
 __global__ __launch_bounds__(kWideThreads, 4) void k_tr_match_wide(
     int32_t S, const SwInfo *__restrict__ sinfo, const pc_rule *__restrict__ rules, const uint32_t *__restrict__ filt,
     const int32_t *__restrict__ boff, const int32_t *__restrict__ ioff, const int2 *__restrict__ imap,
@@ -1592,6 +1312,286 @@ __global__ __launch_bounds__(kWideThreads, 4) void k_tr_match_wide(
     }
     // every wavefront's matches are in best[] (a lookup's matches come from
     // the wavefronts that hold its groups, its epilogue thread may be another)
+    __syncthreads();
+    apply_matches(lv, s, pb, np, bb, tn, tids, tjm, best, keys, ports);
+}
+
+// The survivors of a lookup in four groups: bit r of s[k] is rule r of group
+// k.  at: the groups' chunk sets of value 0 of chunk 0, rows of 16 << kLg bytes
+// (row c * 16 + x: chunk c, value x); nib: the lookup's values, four bits each.
+template <int kLg>
+__device__ __forceinline__ void load_sets(const char *at, uint32_t nib, uint4 (&v)[kChunks])
+{
+#pragma unroll
+    for (int c = 0; c < kChunks; ++c)
+        v[c] = *reinterpret_cast<const uint4 *>(at + (c * 16 << (kLg + 4)) + (((nib >> (4 * c)) & 15) << (kLg + 4)));
+}
+
+__device__ __forceinline__ void and_sets(const uint4 (&v)[kChunks], uint32_t (&s)[4])
+{
+    s[0] = v[0].x & v[1].x & v[2].x & v[3].x & v[4].x & v[5].x;
+    s[1] = v[0].y & v[1].y & v[2].y & v[3].y & v[4].y & v[5].y;
+    s[2] = v[0].z & v[1].z & v[2].z & v[3].z & v[4].z & v[5].z;
+    s[3] = v[0].w & v[1].w & v[2].w & v[3].w & v[4].w & v[5].w;
+    static_assert(kChunks == 6, "every chunk's set");
+}
+
+// One wavefront matches its nw <= 64 lookups (lane j's packed: lookup j's values
+// of the chunks) against the slice whose chunk sets and priorities (0xFFFF -
+// priority) are in LDS.  1 << kLg lanes take a lookup, four groups a lane, so
+// that a read is 16 bytes a lane; two passes' reads go out together.  A pass only
+// asks which lanes have survivors and queues these; 64 queued at a time, their sets are
+// formed again and cand[j], cand2[j] become lookup j's first two survivors by (priority,
+// index).  Only these rules are checked in full (lane j: verify(lookup, rule)): where
+// many rules admit a header, as with prefixes, nearly every survivor matches.
+// A lookup whose candidates both fail checks all its survivors.
+template <int kLg, class Verify>
+__device__ __forceinline__ void filter_slice(const uint4 *sets, const uint16_t *prio, uint32_t packed, int32_t nw,
+                                             uint16_t *q, uint32_t *cand, uint32_t *cand2,
+                                             Verify &&verify)
+{
+    constexpr int kPer = 64 >> kLg;  // lookups per pass
+    const int lane = threadIdx.x & 63, sub = lane >> kLg, l = lane & ((1 << kLg) - 1);
+    const char *base = reinterpret_cast<const char *>(sets);
+    auto of_lane = [&](int32_t j, uint32_t x) {
+        return static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute(4 * j, static_cast<int>(x)));
+    };
+    auto settle = [&]() {  // what other lanes of this wavefront wrote to LDS
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+    int32_t qn = 0;
+    auto push = [&](bool any, uint32_t entry, auto &&drain) {
+        const uint64_t m = __ballot(any);
+        const int n = __popcll(m);
+        if (qn + n > kQueue) drain();
+        const uint32_t below = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
+        if (any) q[qn + below] = static_cast<uint16_t>(entry);
+        qn += n;
+    };
+    // queued: lookup << 5 | lane of its groups
+    auto rank = [&]() {
+        settle();
+        for (int32_t e0 = 0; e0 < qn; e0 += 64) {
+            const uint32_t en = q[min(e0 + lane, qn - 1)];
+            const int32_t j = static_cast<int32_t>(en >> 5), ql = static_cast<int32_t>(en & 31);
+            uint4 v[kChunks];
+            uint32_t s[4], first = ~0u, second = ~0u;
+            load_sets<kLg>(base + 16 * ql, of_lane(j, packed), v);
+            and_sets(v, s);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                for (uint32_t m = s[k]; m; m &= m - 1) {
+                    const uint32_t at = 128 * ql + 32 * k + __builtin_ctz(m);
+                    const uint32_t key = static_cast<uint32_t>(prio[at]) << 12 | at;
+                    second = min(second, max(first, key));
+                    first = min(first, key);
+                }
+            // what does not stay the first competes for the second place
+            if (e0 + lane < qn) second = min(second, max(first, atomicMin(cand + j, first)));
+            if (e0 + lane < qn && second != ~0u) atomicMin(cand2 + j, second);
+        }
+        settle();
+        qn = 0;
+    };
+    if (lane < nw) cand[lane] = cand2[lane] = ~0u;
+    for (int32_t j0 = 0; j0 < nw; j0 += 2 * kPer) {
+        uint4 a[kChunks], b[kChunks];
+        uint32_t s[4];
+        load_sets<kLg>(base + 16 * l, of_lane(min(j0 + sub, nw - 1), packed), a);
+        load_sets<kLg>(base + 16 * l, of_lane(min(j0 + kPer + sub, nw - 1), packed), b);
+        and_sets(a, s);
+        push((s[0] | s[1] | s[2] | s[3]) != 0 && j0 + sub < nw, (j0 + sub) << 5 | l, rank);
+        and_sets(b, s);
+        push((s[0] | s[1] | s[2] | s[3]) != 0 && j0 + kPer + sub < nw, (j0 + kPer + sub) << 5 | l, rank);
+    }
+    rank();
+    const uint32_t first = lane < nw ? cand[lane] : ~0u, second = lane < nw ? cand2[lane] : ~0u;
+    const bool one = first != ~0u && verify(lane, static_cast<int32_t>(first & 4095));
+    const bool two = second != ~0u && verify(lane, static_cast<int32_t>(second & 4095));
+    const bool failed = second != ~0u && !one && !two;
+    const uint64_t fm = __ballot(failed);
+    if (fm == 0) return;
+    // the failed lookups again, compacted; queued: place << 7 | lane << 2 | word
+    const int32_t nf = __popcll(fm);
+    if (failed) q[__popcll(fm & ((1ull << lane) - 1))] = static_cast<uint16_t>(lane);
+    settle();
+    const uint32_t which = q[min(lane, nf - 1)];
+    const uint32_t again = of_lane(static_cast<int32_t>(which), packed);
+    settle();
+    auto check = [&]() {
+        settle();
+        for (int32_t e0 = 0; e0 < qn; e0 += 64) {
+            const uint32_t en = q[min(e0 + lane, qn - 1)];
+            const int32_t j = static_cast<int32_t>(en >> 7), ql = static_cast<int32_t>((en >> 2) & 31);
+            uint4 v[kChunks];
+            uint32_t s[4];
+            load_sets<kLg>(base + 16 * ql, of_lane(j, again), v);
+            and_sets(v, s);
+            const uint32_t k = en & 3, to = of_lane(j, which);
+            if (e0 + lane < qn)
+                for (uint32_t m = k == 0 ? s[0] : k == 1 ? s[1] : k == 2 ? s[2] : s[3]; m; m &= m - 1)
+                    (void)verify(static_cast<int32_t>(to), static_cast<int32_t>(128 * ql + 32 * k + __builtin_ctz(m)));
+        }
+        settle();
+        qn = 0;
+    };
+    for (int32_t j0 = 0; j0 < nf; j0 += kPer) {
+        uint4 a[kChunks];
+        uint32_t s[4];
+        load_sets<kLg>(base + 16 * l, of_lane(min(j0 + sub, nf - 1), again), a);
+        and_sets(a, s);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            push(s[k] != 0 && j0 + sub < nf, (j0 + sub) << 7 | l << 2 | k, check);
+    }
+    check();
+}
+
+// The same with the chunk sets read from LDS, a slice of 4,096 rules at a time, which takes half the instructions of
+// k_tr_match_wide's register indexing (a level of 4.2 million lookups in 1,280
+// tables of 4,096 rules: 42 vector and 35 scalar instructions per lookup there,
+// 31 and 15 here).  Bound by staging and moving the lookups, 155 of such a level's 340
+// us, then by the vector instructions of the filter, 130.  4,194,304 traces
+// over these tables 1,757 us in k_tr_match_wide, now 1,417; 500,009 over
+// 720 routing tables of 2,048 prefixes, where a lookup has dozens of matching
+// rules, 935 and 470 (842 with every survivor checked).
+__global__ __launch_bounds__(kMatchThreads, 4) void k_tr_match(
+    int32_t S, const SwInfo *__restrict__ sinfo, const pc_rule *__restrict__ rules, const uint32_t *__restrict__ filt,
+    const uint16_t *__restrict__ prios, const int32_t *__restrict__ boff, const int32_t *__restrict__ ioff,
+    const int2 *__restrict__ imap, const BRec *__restrict__ bucket, Level lv)
+{
+    __shared__ uint4 sets[kPlaneWords * kSliceGroups / 4];
+    __shared__ uint64_t best[kChunk];
+    __shared__ __align__(16) pc_key keys[kChunk];
+    __shared__ uint32_t cidx[kChunk];  // each lookup's values of the switch's filter chunks, four bits each; then its
+                                       // candidate (a wavefront's own lookups only)
+    __shared__ uint32_t cand2[kChunk];
+    __shared__ int32_t tids[kChunk];
+    __shared__ uint32_t tjm[kChunk];   // each lookup's trace: jurisdiction mask so far
+    __shared__ uint16_t prio[kSliceGroups * 32] __attribute__((aligned(16)));
+    __shared__ uint16_t queue[kMatchWaves][kQueue];  // per wavefront (see filter_slice)
+    __shared__ PortMoves ports;
+    // the grid was sized from an upper bound on the item count: blocks past
+    // the real count's per-XCD share return at once
+    const int32_t n_items = ioff[S];
+    const int32_t per = (n_items + 7) / 8;
+    const int32_t kx = static_cast<int32_t>(blockIdx.x >> 3);
+    if (kx >= per) return;
+    const int32_t item = static_cast<int32_t>(blockIdx.x & 7) * per + kx;
+    if (item >= n_items) return;
+    // the item's switch and its index among the switch's items
+    const int2 im = imap[item];
+    const int32_t s = im.x;
+    if (static_cast<uint32_t>(s) >= static_cast<uint32_t>(S)) return;
+    const SwInfo si = sinfo[s];
+    const int32_t b0 = boff[s], b1 = boff[s + 1];
+    const int32_t share = even_parts(b1 - b0, lv.cap);
+    const int32_t bb = b0 + im.y * share;
+    const int32_t tn = min(share, min(b1, lv.T) - bb);  // bucket holds at most T entries
+    if (tn <= 0) return;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t G = si.G;
+    const int64_t rb = si.rb;
+    const uint32_t *fs = filt + static_cast<int64_t>(si.gofs) * kPlaneWords;
+    const uint32_t cp = si.cpos;
+    // the switch's ports (np < 0: its port range is invalid)
+    const int64_t pb = si.pb, np = si.np;
+    // lanes that take a lookup: a slice's groups, four a lane
+    const int32_t quads = (min(G, kSliceGroups) + 3) / 4;
+    const int lpl_bits = quads <= 1 ? 0 : 32 - __builtin_clz(static_cast<uint32_t>(quads - 1)), lpl = 1 << lpl_bits;
+    // a slice's chunk sets into LDS (no survivors past the last group)
+    auto fill = [&](int32_t g0) {
+        const int32_t ng = min(G - g0, kSliceGroups);
+        constexpr int kFills = kPlaneWords * kSliceGroups / 4 / kMatchThreads;
+        static_assert(kSliceGroups * 4 == kMatchThreads, "16 bytes of priorities per thread");
+        uint4 v[kFills], pr = make_uint4(0, 0, 0, 0);
+        if (static_cast<int32_t>(threadIdx.x) < ng * 4)
+            pr = reinterpret_cast<const uint4 *>(prios + (static_cast<int64_t>(si.gofs) + g0) * 32)[threadIdx.x];
+#pragma unroll
+        for (int k = 0; k < kFills; ++k) {
+            const int x = static_cast<int>(threadIdx.x) + k * kMatchThreads;
+            const int32_t row = x >> lpl_bits, g = 4 * (x & (lpl - 1));
+            v[k] = make_uint4(0, 0, 0, 0);
+            if (row < kPlaneWords) {
+                const uint32_t *src = fs + static_cast<int64_t>(row) * G + g0 + g;
+                if (g + 4 <= ng) {
+                    __builtin_memcpy(&v[k], src, 16);
+                } else {
+                    if (g < ng) v[k].x = src[0];
+                    if (g + 1 < ng) v[k].y = src[1];
+                    if (g + 2 < ng) v[k].z = src[2];
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kFills; ++k) {
+            const int x = static_cast<int>(threadIdx.x) + k * kMatchThreads;
+            if (x < kPlaneWords * lpl) sets[x] = v[k];
+        }
+        reinterpret_cast<uint4 *>(prio)[threadIdx.x] = pr;
+    };
+    // stage the lookups (one per thread) and the first slice's sets
+    const int i = static_cast<int>(threadIdx.x);
+    BRec r{};
+    if (i < tn) r = bucket[bb + i];
+    fill(0);
+    if (threadIdx.x < kPortSlots) {
+        const int2 pi = static_cast<int64_t>(threadIdx.x) < np ? lv.pinfo[pb + threadIdx.x] : make_int2(-2, 0);
+        ports.peer[threadIdx.x] = pi.x;
+        ports.jbit[threadIdx.x] = static_cast<uint32_t>(pi.y);
+        ports.count[threadIdx.x] = 0;
+        if (threadIdx.x == 0) ports.nother = 0;
+    }
+    if (i < tn) {
+        int32_t t = r.t;
+        pc_key h = r.key;
+        uint32_t jmv = r.jm;
+        if (static_cast<uint32_t>(t) >= static_cast<uint32_t>(lv.T)) {  // not a trace id: skipped
+            t = -1;
+            h = pc_key{};
+            jmv = 0;
+        }
+        tids[i] = t;
+        keys[i] = h;
+        tjm[i] = jmv;
+        best[i] = kNoMatch;
+        uint32_t x = 0;
+#pragma unroll
+        for (int c = 0; c < kChunks; ++c) x |= key_nibble(h.w[0], h.w[1], h.w[2], h.w[3], chunk_pos(cp, c)) << (4 * c);
+        cidx[i] = x;
+    }
+    __syncthreads();
+    const int32_t per_wave = (tn + kMatchWaves - 1) / kMatchWaves;  // the wavefront's lookups
+    const int32_t jw = wave * per_wave, nw = min(per_wave, tn - jw);
+    const uint32_t packed = nw > 0 ? cidx[jw + min(lane, nw - 1)] : 0u;
+    for (int32_t g0 = 0; g0 < G; g0 += kSliceGroups) {
+        if (g0 > 0) {
+            __syncthreads();  // the slice before is no longer read
+            fill(g0);
+            __syncthreads();
+        }
+        auto verify = [&](int32_t j, int32_t at) {
+            const uint32_t local = static_cast<uint32_t>(g0) * 32 + static_cast<uint32_t>(at);
+            const pc_rule x = rules[rb + local];
+            const pc_key &h = keys[jw + j];
+            const bool ok = rule_matches(&x, h.w[0], h.w[1], h.w[2], h.w[3]);
+            if (ok)
+                atomicMin(reinterpret_cast<unsigned long long *>(&best[jw + j]),
+                          static_cast<unsigned long long>(rule_key(&x, local)));
+            return ok;
+        };
+        if (lpl_bits == 5) filter_slice<5>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
+        else if (lpl_bits == 4) filter_slice<4>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
+        else if (lpl_bits == 3) filter_slice<3>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
+        else if (lpl_bits == 2) filter_slice<2>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
+        else if (lpl_bits == 1) filter_slice<1>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
+        else filter_slice<0>(sets, prio, packed, nw, queue[wave], cidx + jw, cand2 + jw, verify);
+    }
+    // every wavefront's matches are in best[]
     __syncthreads();
     apply_matches(lv, s, pb, np, bb, tn, tids, tjm, best, keys, ports);
 }
