@@ -550,7 +550,7 @@ __device__ __forceinline__ int32_t pres_max_le(const uint64_t *pres, int64_t x)
 
 // Gt / Lt over the label's prefix planes (plane pfx0 + plane_id(v) is the
 // OR of the planes of the label's present values <= v, built by
-// k_aff_prefix): Lt t is the prefix of the largest present value below t,
+// k_sel_planes): Lt t is the prefix of the largest present value below t,
 // one entry; Gt t is NOT (the prefix of the largest present value <= t OR
 // the absent-value plane), at most two entries.  The node sets are those
 // expr_clause selects value by value.  Returns the entry count (ids in e)
