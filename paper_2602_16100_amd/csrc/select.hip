@@ -758,6 +758,23 @@ __global__ __launch_bounds__(kCompThreads) void k_sel_compile(const int32_t *__r
     if (errs) atomicOr(d_err, errs);
 }
 
+// Is every expression of [b, e) well-formed?  Bound by the latency of scattered
+// 40-byte expressions, so four are requested together (233,017 affinity rows 31
+// -> 16 us, 3.4 TB/s with the offsets; as many preferred ones 21 -> 15).
+constexpr int kSweep = 4;
+__device__ __forceinline__ bool exprs_valid(const pc_pred *__restrict__ preds, int64_t b, int64_t e, int32_t L)
+{
+    bool ok = true;
+    for (int64_t p = b; p < e && ok; p += kSweep) {
+        pc_pred q[kSweep];
+#pragma unroll
+        for (int k = 0; k < kSweep; ++k) q[k] = preds[min(p + k, e - 1)];
+#pragma unroll
+        for (int k = 0; k < kSweep; ++k) ok &= aff_valid(q[k], L);
+    }
+    return ok;
+}
+
 // Affinity input sweep: the data-error flags are properties of the whole
 // input.  OFFSETS for any bad term or row offset pair, PRED for any
 // malformed expression inside a term with a valid offset pair.
@@ -776,11 +793,7 @@ __global__ __launch_bounds__(256) void k_aff_validate(const int32_t *__restrict_
             if (!pc_range_ok(b, e, n_preds)) {
                 errs |= PC_DERR_OFFSETS;
             } else {
-                for (int64_t p = b; p < e; ++p)
-                    if (!aff_valid(preds[p], L)) {
-                        errs |= PC_DERR_PRED;
-                        break;
-                    }
+                if (!exprs_valid(preds, b, e, L)) errs |= PC_DERR_PRED;
             }
         }
         if (x < I && !pc_range_ok(row_off[x], row_off[x + 1], n_terms)) errs |= PC_DERR_OFFSETS;
@@ -827,8 +840,56 @@ __device__ __forceinline__ bool aff_term(const pc_pred *__restrict__ preds, int6
     return ok;
 }
 
+// Entries that a lane which compiles a row holds in LDS: programs past the inline
+// words are copied from there, and only still longer ones, one row in hundreds
+// of the generated ones, are formed again, which the whole wavefront waits for
+// (233,017 affinity rows 55 -> 42 us).
+constexpr int kHeldWords = 32;
+
+// A row's expressions on one lane, each requested while the one before is looked at
+// (adjacent terms' too) with kAhead (233,017 affinity rows 61 -> 55 us; not for a
+// group's odd row, where the registers cost a wavefront per SIMD).
+template <bool kAhead>
+struct NextExpr {
+    pc_pred q;
+    int64_t at = -1;
+    __device__ __forceinline__ pc_pred take(const pc_pred *__restrict__ preds, int64_t p, int64_t n_preds)
+    {
+        if constexpr (!kAhead) return preds[p];
+        if (at != p) q = preds[p];
+        const pc_pred now = q;
+        at = p + 1;
+        q = preds[min(at, n_preds - 1)];
+        return now;
+    }
+};
+
+// The label tables that a row's expressions look up.
+struct LabelTables {
+    const uint64_t *present;  // [L][4]
+    const uint32_t *wbase;    // [L][4]
+};
+
+// Up to this many labels the compiles hold them in LDS: a lane looks up each
+// expression's presence words and then the base of each entry's plane, a chain of
+// gathers from memory otherwise (233,017 rows of 64 labels: affinity 75 -> 61 us,
+// preferred 89 -> 77).
+constexpr int32_t kLdsLabels = 64;
+__device__ __forceinline__ LabelTables stage_labels(const uint64_t *__restrict__ present,
+                                                    const uint32_t *__restrict__ wbase, int32_t L, uint64_t *sp,
+                                                    uint32_t *sw)
+{
+    for (int32_t x = threadIdx.x; x < L * 4; x += blockDim.x) {
+        sp[x] = present[x];
+        sw[x] = wbase[x];
+    }
+    __syncthreads();
+    return {sp, sw};
+}
+
 // One affinity row, on one lane (rows that k_aff_compile's groups do not
 // take): the record in rr, the inventory flags in unknown[i].
+template <bool kAhead, int kHeld>
 __device__ __forceinline__ void aff_compile_row(const int32_t *__restrict__ row_off, int32_t i, const int32_t *__restrict__ term_off,
                                 int32_t n_terms, const pc_pred *__restrict__ preds, int64_t n_preds, int32_t L,
                                 const uint64_t *__restrict__ present, const uint32_t *__restrict__ wbase,
@@ -853,6 +914,7 @@ __device__ __forceinline__ void aff_compile_row(const int32_t *__restrict__ row_
     bool all = tb == te;
     int64_t n = 0, live = 0, k_out = 0;
     uint32_t *in_out = rr + 1;
+    NextExpr<kAhead> ahead;
     for (int64_t t = tb; t < te; ++t) {
         const int64_t b = term_off[t], e = term_off[t + 1];
         if (!pc_range_ok(b, e, n_preds)) continue;
@@ -860,7 +922,7 @@ __device__ __forceinline__ void aff_compile_row(const int32_t *__restrict__ row_
         const int64_t start = k_out;
         int64_t len = 0;
         for (int64_t p = b; p < e; ++p) {
-            const pc_pred q = preds[p];
+            const pc_pred q = ahead.take(preds, p, n_preds);
             if (!aff_valid(q, L)) {
                 ok = false;
                 continue;
@@ -871,7 +933,7 @@ __device__ __forceinline__ void aff_compile_row(const int32_t *__restrict__ row_
             bool neg;
             const uint32_t cnt = aff_entries(q, pres, wbase + static_cast<int64_t>(q.label) * 4, pfx0, neg,
                                              [&](uint32_t ent) {
-                                                 if (k_out < kInline) in_out[k_out] = ent;
+                                                 if (k_out < kHeld) in_out[k_out] = ent;
                                                  ++k_out;
                                              });
             if (cnt == 0 && !neg) ok = false;
@@ -886,7 +948,7 @@ __device__ __forceinline__ void aff_compile_row(const int32_t *__restrict__ row_
             all = true;
             continue;
         }
-        if (k_out <= kInline) in_out[k_out - 1] |= kTermEnd;
+        if (k_out <= kHeld) in_out[k_out - 1] |= kTermEnd;
         n += len;
         ++live;
     }
@@ -903,18 +965,21 @@ __device__ __forceinline__ void aff_compile_row(const int32_t *__restrict__ row_
         rr[0] = static_cast<uint32_t>(n);
         return;
     }
-    // longer than the inline area: a slice of prog, written by a
-    // second pass (slices are whole multiples of 4 entries: the
-    // record stores off / 4)
+    // longer than the inline area: a slice of prog, copied from the entries
+    // held or written by a second pass (slices are whole multiples of 4
+    // entries: the record stores off / 4)
     const unsigned long long off = atomicAdd(prog_used, static_cast<unsigned long long>((n + 3) & ~int64_t(3)));
     if (static_cast<int64_t>(off) + n > prog_cap) {
         rr[0] = static_cast<uint32_t>(kRowLong);
         return;
     }
     uint32_t *out = prog + off;
+    if (n <= kHeld)
+        for (int32_t k = 0; k < static_cast<int32_t>(n); ++k) out[k] = in_out[k];
     rr[0] = static_cast<uint32_t>(kRowIndirect);
     rr[1] = static_cast<uint32_t>(off / 4);
     rr[2] = static_cast<uint32_t>(n);
+    if (n <= kHeld) return;
     int64_t k2 = 0;
     for (int64_t t = tb; t < te; ++t) {
         const int64_t b = term_off[t], e = term_off[t + 1];
@@ -997,28 +1062,39 @@ __device__ __forceinline__ int group_term_of(const GroupTerms &g)
 // that group_terms does not take are compiled by one lane.
 // Bound by the chain offsets -> expression -> presence words, which a thread
 // per row walked once per expression (3,001 rows 67 us, now 9); of many rows a
-// thread each (G = 1) has the better throughput.
+// thread each (G = 1) has the better throughput: bound there by the chains of its
+// three or four wavefronts per SIMD (233,017 rows 75 us before the look-ahead, the tables in LDS
+// and the held entries, now 42; expressions staged in LDS lost, 85).
 constexpr int kAffLanes = 16;
 // rows below which the groups win (a thread per row / groups, at 64 labels:
-// affinity 80,000 rows 56 / 37 us, 160,000 rows 69 / 67, 699,051 rows 147 / 266;
-// preferred 40,000 rows 46 / 40 us, 80,000 rows 52 / 54, 699,051 rows 195 / 343)
-constexpr int32_t kAffGroupRows = 131072, kPrefGroupRows = 65536;
-template <int G>
+// affinity 45,000 rows 28 / 22 us, 60,000 rows 28 / 27, 100,000 rows 31 / 40;
+// preferred 24,000 rows 26 / 22 us, 30,000 rows 26 / 24, 36,000 rows 26 / 28)
+constexpr int32_t kAffGroupRows = 65536, kPrefGroupRows = 32768;
+template <int G, bool kLds>
 __global__ __launch_bounds__(256) void k_aff_compile(const int32_t *__restrict__ row_off, int32_t I,
                                                      const int32_t *__restrict__ term_off, int32_t n_terms,
                                                      const pc_pred *__restrict__ preds, int64_t n_preds, int32_t L,
-                                                     const uint64_t *__restrict__ present,
-                                                     const uint32_t *__restrict__ wbase,
+                                                     const uint64_t *__restrict__ present_all,
+                                                     const uint32_t *__restrict__ wbase_all,
                                                      uint32_t *__restrict__ prog, int64_t prog_cap,
                                                      unsigned long long *__restrict__ prog_used,
                                                      uint32_t *__restrict__ rec, uint8_t *__restrict__ unknown,
                                                      uint32_t pfx0)
 {
-    __shared__ uint32_t srec[256 / G][kRecWords + 1];
+    const uint64_t *present = kLds ? nullptr : present_all;
+    const uint32_t *wbase = kLds ? nullptr : wbase_all;
+    __shared__ uint32_t srec[256 / G][G == 1 ? kHeldWords + 1 : kRecWords + 1];
     uint32_t *rr = srec[threadIdx.x / G];
+    __shared__ uint64_t sp[kLds ? kLdsLabels * 4 : 1];
+    __shared__ uint32_t sw[kLds ? kLdsLabels * 4 : 1];
+    if constexpr (kLds) {
+        const LabelTables tab = stage_labels(present_all, wbase_all, L, sp, sw);
+        present = tab.present;
+        wbase = tab.wbase;
+    }
     if constexpr (G == 1) {
         for (int32_t i = blockIdx.x * 256 + threadIdx.x; i < I; i += gridDim.x * 256) {
-            aff_compile_row(row_off, i, term_off, n_terms, preds, n_preds, L, present, wbase, prog, prog_cap,
+            aff_compile_row<true, kHeldWords>(row_off, i, term_off, n_terms, preds, n_preds, L, present, wbase, prog, prog_cap,
                             prog_used, rr, unknown, pfx0);
             uint4 *dst = reinterpret_cast<uint4 *>(rec + static_cast<int64_t>(i) * kRecWords);
 #pragma unroll
@@ -1044,7 +1120,7 @@ __global__ __launch_bounds__(256) void k_aff_compile(const int32_t *__restrict__
         }
         const GroupTerms g = group_terms<G>(tb, te, term_off, n_preds, good);
         if (good && !g.fits && gl == 0)
-            aff_compile_row(row_off, static_cast<int32_t>(i), term_off, n_terms, preds, n_preds, L, present, wbase,
+            aff_compile_row<false, kInline>(row_off, static_cast<int32_t>(i), term_off, n_terms, preds, n_preds, L, present, wbase,
                             prog, prog_cap, prog_used, rr, unknown, pfx0);
         // this lane's expression
         pc_pred q{};
@@ -1522,11 +1598,7 @@ __global__ __launch_bounds__(256) void k_pref_validate(const int32_t *__restrict
             if (!pc_range_ok(b, e, n_preds)) {
                 errs |= PC_DERR_OFFSETS;
             } else {
-                for (int64_t p = b; p < e; ++p)
-                    if (!aff_valid(preds[p], L)) {
-                        errs |= PC_DERR_PRED;
-                        break;
-                    }
+                if (!exprs_valid(preds, b, e, L)) errs |= PC_DERR_PRED;
             }
         }
         if (x < I && !pref_row_ok(row_off, x, n_terms)) errs |= PC_DERR_OFFSETS;
@@ -1537,6 +1609,7 @@ __global__ __launch_bounds__(256) void k_pref_validate(const int32_t *__restrict
 // One row of k_pref_compile: its record, and its class (3: at most three
 // live terms, including none; 0: scores fit 8 bits, 1: 16 bits; 2: decoded
 // on the fly).
+template <bool kAhead, int kHeld>
 __device__ __forceinline__ uint32_t pref_compile_row(const int32_t *__restrict__ row_off, int32_t i,
                                      const int32_t *__restrict__ term_off, int32_t n_terms,
                                      const uint32_t *__restrict__ weight, const pc_pred *__restrict__ preds,
@@ -1546,7 +1619,8 @@ __device__ __forceinline__ uint32_t pref_compile_row(const int32_t *__restrict__
 {
     rr[0] = kPrefNone << 24;
     if (!pref_row_ok(row_off, i, n_terms)) return 3;
-    const int64_t tb = row_off[i], te = row_off[i + 1];
+    int64_t tb = row_off[i];
+    const int64_t te = row_off[i + 1];
     // One pass: each live term's header and entries go into the record's
     // inline words as they come (counted past their end); a term that turns
     // out dead (weight out of range, a malformed expression, an empty
@@ -1556,8 +1630,9 @@ __device__ __forceinline__ uint32_t pref_compile_row(const int32_t *__restrict__
     uint32_t live = 0, sum = 0;
     bool decode = false;
     uint32_t *in_out = rr + 2;
+    NextExpr<kAhead> ahead;
     auto put = [&](uint32_t word) {
-        if (k_out < kPrefInlineWords) in_out[k_out] = word;
+        if (k_out < kHeld) in_out[k_out] = word;
         ++k_out;
     };
     for (int64_t t = tb; t < te; ++t) {
@@ -1569,7 +1644,7 @@ __device__ __forceinline__ uint32_t pref_compile_row(const int32_t *__restrict__
         bool ok = true;
         int64_t len = 0;
         for (int64_t p = b; p < e && ok; ++p) {
-            const pc_pred q = preds[p];
+            const pc_pred q = ahead.take(preds, p, n_preds);
             if (!aff_valid(q, L)) {
                 ok = false;
                 break;
@@ -1585,7 +1660,7 @@ __device__ __forceinline__ uint32_t pref_compile_row(const int32_t *__restrict__
             continue;
         }
         if (len >= (int64_t(1) << kPrefLenBits)) decode = true;
-        if (start < kPrefInlineWords) in_out[start] = w << kPrefLenBits | static_cast<uint32_t>(len);
+        if (start < kHeld) in_out[start] = w << kPrefLenBits | static_cast<uint32_t>(len);
         n += 1 + len;
         sum += w;
         ++live;
@@ -1601,6 +1676,10 @@ __device__ __forceinline__ uint32_t pref_compile_row(const int32_t *__restrict__
             rr[1] = static_cast<uint32_t>(off);
             kind = kPrefIndirect;
             int64_t k2 = 0;
+            if (n <= kHeld) {
+                for (; k2 < n; ++k2) out[k2] = in_out[k2];
+                tb = te;
+            }
             for (int64_t t = tb; t < te; ++t) {
                 const int64_t b = term_off[t], e = term_off[t + 1];
                 int64_t len;
@@ -1634,29 +1713,38 @@ __device__ __forceinline__ uint32_t pref_compile_row(const int32_t *__restrict__
 // entries, the row is decoded at evaluation time.
 // Each row is appended to the list of its class.
 // Bound as k_aff_compile (3,001 rows 57 us, now 11).
-template <int G>
+template <int G, bool kLds>
 __global__ __launch_bounds__(256) void k_pref_compile(const int32_t *__restrict__ row_off, int32_t I,
                                                       const int32_t *__restrict__ term_off, int32_t n_terms,
                                                       const uint32_t *__restrict__ weight,
                                                       const pc_pred *__restrict__ preds, int64_t n_preds, int32_t L,
-                                                      const uint64_t *__restrict__ present,
-                                                      const uint32_t *__restrict__ wbase, uint32_t *__restrict__ prog,
+                                                      const uint64_t *__restrict__ present_all,
+                                                      const uint32_t *__restrict__ wbase_all, uint32_t *__restrict__ prog,
                                                       int64_t prog_cap, unsigned long long *__restrict__ prog_used,
                                                       uint32_t *__restrict__ rec, int32_t *__restrict__ list,
                                                       uint32_t *__restrict__ list_len, uint32_t pfx0, int32_t rpb)
 {
     static_assert(G == 1 || G == kPrefRec, "a lane per record word");
-    __shared__ uint32_t srec[256 / G][kPrefRec + 1];
+    __shared__ uint32_t srec[256 / G][G == 1 ? kHeldWords + 1 : kPrefRec + 1];
     __shared__ uint8_t scls[256];  // the classes of the workgroup's rows
     uint32_t *rr = srec[threadIdx.x / G];
     const int gl = threadIdx.x % G;
     const int lane = threadIdx.x & 63;
     const int64_t block0 = static_cast<int64_t>(blockIdx.x) * rpb;
+    const uint64_t *present = kLds ? nullptr : present_all;
+    const uint32_t *wbase = kLds ? nullptr : wbase_all;
+    __shared__ uint64_t sp[kLds ? kLdsLabels * 4 : 1];
+    __shared__ uint32_t sw[kLds ? kLdsLabels * 4 : 1];
+    if constexpr (kLds) {
+        const LabelTables tab = stage_labels(present_all, wbase_all, L, sp, sw);
+        present = tab.present;
+        wbase = tab.wbase;
+    }
     if constexpr (G == 1) {
         const int64_t i = block0 + threadIdx.x;
         if (i < I) {
             scls[threadIdx.x] = static_cast<uint8_t>(
-                pref_compile_row(row_off, static_cast<int32_t>(i), term_off, n_terms, weight, preds, n_preds, L,
+                pref_compile_row<true, kHeldWords - 1>(row_off, static_cast<int32_t>(i), term_off, n_terms, weight, preds, n_preds, L,
                                  present, wbase, prog, prog_cap, prog_used, rr, pfx0));
             uint4 *dst = reinterpret_cast<uint4 *>(rec + i * kPrefRec);
 #pragma unroll
@@ -1678,7 +1766,7 @@ __global__ __launch_bounds__(256) void k_pref_compile(const int32_t *__restrict_
         uint32_t cls = i < I ? 3u : kPrefClasses;  // (a bad row has no terms)
         const GroupTerms g = group_terms<G>(tb, te, term_off, n_preds, good);
         if (good && !g.fits && gl == 0)
-            cls = pref_compile_row(row_off, static_cast<int32_t>(i), term_off, n_terms, weight, preds, n_preds, L,
+            cls = pref_compile_row<false, kPrefInlineWords>(row_off, static_cast<int32_t>(i), term_off, n_terms, weight, preds, n_preds, L,
                                    present, wbase, prog, prog_cap, prog_used, rr, pfx0);
         // this lane's expression
         pc_pred q{};
@@ -1752,20 +1840,34 @@ __global__ __launch_bounds__(256) void k_pref_compile(const int32_t *__restrict_
         if (gl == 0) scls[at] = static_cast<uint8_t>(cls);
     }
     __syncthreads();
-    // append the rows to their class lists: one counter update per class and
-    // wavefront (one per four rows would keep the counters busy for 11 ns each)
+    // append the rows to their class lists, one counter update per class and
+    // workgroup: the counters share a line, and one per class and wavefront was
+    // what bounded the launch (233,017 rows 71 -> 42 us)
     const uint32_t cls = static_cast<int>(threadIdx.x) < rpb ? scls[threadIdx.x] : kPrefClasses;
+    const int wave = threadIdx.x >> 6;
+    __shared__ uint32_t places[4][kPrefClasses];  // per wavefront and class: rows, then the first one's place
+    uint32_t below = 0;
     for (uint32_t c = 0; c < kPrefClasses; ++c) {
         const uint64_t mask = __ballot(cls == c);
-        if (mask == 0) continue;
-        const int leader = __builtin_ctzll(mask);
-        uint32_t off = 0;
-        if (lane == leader) off = atomicAdd(list_len + c, static_cast<uint32_t>(__popcll(mask)));
-        off = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(off), leader));
-        const uint32_t below = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
-                                                         __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
-        if (cls == c) list[static_cast<int64_t>(c) * I + off + below] = static_cast<int32_t>(block0 + threadIdx.x);
+        if (lane == 0) places[wave][c] = static_cast<uint32_t>(__popcll(mask));
+        if (cls == c)
+            below = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                              __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
     }
+    __syncthreads();
+    if (threadIdx.x < kPrefClasses) {
+        uint32_t n = 0;
+        for (int w = 0; w < 4; ++w) n += places[w][threadIdx.x];
+        uint32_t at = n ? atomicAdd(list_len + threadIdx.x, n) : 0u;
+        for (int w = 0; w < 4; ++w) {
+            const uint32_t x = places[w][threadIdx.x];
+            places[w][threadIdx.x] = at;
+            at += x;
+        }
+    }
+    __syncthreads();
+    if (cls < kPrefClasses)
+        list[static_cast<int64_t>(cls) * I + places[wave][cls] + below] = static_cast<int32_t>(block0 + threadIdx.x);
 }
 
 
@@ -2459,7 +2561,9 @@ int run_affinity(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, const
     const bool groups = I < kAffGroupRows;
     const int64_t rows = groups ? 256 / kAffLanes : 256;  // per workgroup
     const unsigned rgrid = static_cast<unsigned>(std::min<int64_t>((I + rows - 1) / rows, 8192));
-    const auto kern = groups ? k_aff_compile<kAffLanes> : k_aff_compile<1>;
+    const bool lds = L <= kLdsLabels;
+    const auto kern = groups ? (lds ? k_aff_compile<kAffLanes, true> : k_aff_compile<kAffLanes, false>)
+                             : (lds ? k_aff_compile<1, true> : k_aff_compile<1, false>);
     PC_TIMED(ctx, "k_aff_compile", stream,
              hipLaunchKernelGGL(kern, dim3(rgrid), dim3(256), 0, stream, row_off, I, term_off, n_terms,
                                 preds, n_preds, L, present, wbase, prog, prog_cap,
@@ -2527,9 +2631,11 @@ int run_preferred(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, cons
     // the class lists' counters are not updated too often)
     const bool groups = I < kPrefGroupRows;
     const int32_t rpb =
-        groups ? static_cast<int32_t>(std::min<int64_t>(256, std::max<int64_t>(16, I / 2048 / 16 * 16))) : 256;
+        groups ? static_cast<int32_t>(std::min<int64_t>(256, std::max<int64_t>(16, I / 512 / 16 * 16))) : 256;
     const unsigned rgrid = static_cast<unsigned>((static_cast<int64_t>(I) + rpb - 1) / rpb);
-    const auto kern = groups ? k_pref_compile<kAffLanes> : k_pref_compile<1>;
+    const bool lds = L <= kLdsLabels;
+    const auto kern = groups ? (lds ? k_pref_compile<kAffLanes, true> : k_pref_compile<kAffLanes, false>)
+                             : (lds ? k_pref_compile<1, true> : k_pref_compile<1, false>);
     PC_TIMED(ctx, "k_pref_compile", stream,
              hipLaunchKernelGGL(kern, dim3(rgrid), dim3(256), 0, stream, row_off, I, term_off, n_terms,
                                 weight, preds, n_preds, L, present, wbase, prog, prog_cap, prog_used, rec, list,

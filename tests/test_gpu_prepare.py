@@ -100,6 +100,30 @@ def test_row_counts_at_the_compile_rules(g, orc, I):
     assert np.array_equal(bg, bo) and np.array_equal(sg, so) and np.array_equal(cg, co) and eg == eo
 
 
+@pytest.mark.parametrize("I,L,t,k", [(32767, 64, 3, 6), (32768, 64, 3, 6), (33100, 65, 20, 1), (65536, 64, 3, 5), (65800, 65, 3, 5),
+                                     (65999, 3, 3, 8)])
+def test_many_rows(g, orc, I, L, t, k):
+    """Rows compiled a thread each: label tables that fit LDS and one label more, programs around and past the words a
+    thread holds, terms that are not adjacent, malformed expressions and offsets, all classes of preferred rows."""
+    rng = np.random.default_rng(I + L)
+    cards = rng.choice([2, 16, 64], size=L)
+    labels = synth.gen_labels(rng, 100, cards, 0.1)
+    row_off, term_off, preds = synth.gen_affinity(rng, I, cards, 0, t, 1, k)
+    weight = rng.integers(1, 101, term_off.shape[0] - 1).astype(np.uint32)
+    at = rng.integers(0, preds.shape[0], 600)
+    preds["op"][at[:200]], preds["label"][at[200:400]], preds["rsv0"][at[400:]] = 9, L, 1
+    weight[rng.integers(0, weight.shape[0], 100)] = [0, 101] * 50
+    x = rng.integers(1, term_off.shape[0] - 1, 300)
+    term_off[x] += rng.integers(-9, 10, 300).astype(np.int32)  # terms that share expressions, run backwards, are negative
+    row_off[rng.integers(1, row_off.shape[0] - 1, 60)] += 5
+    fg, pg, ug, eg = g.affinity(labels, row_off, term_off, preds)
+    fo, po, uo, eo = orc.affinity(labels, row_off, term_off, preds)
+    assert np.array_equal(fg, fo) and np.array_equal(pg, po) and np.array_equal(ug, uo) and eg == eo
+    bg, sg, cg, eg = g.preferred(labels, row_off, term_off, weight, preds)
+    bo, so, co, eo = orc.preferred(labels, row_off, term_off, weight, preds)
+    assert np.array_equal(bg, bo) and np.array_equal(sg, so) and np.array_equal(cg, co) and eg == eo
+
+
 @pytest.mark.parametrize("N,L,I,shift", [(1, 1, 1, 1), (63, 8, 15, 3), (64, 200, 17, 0), (65, 9, 300, 2), (255, 32, 1500, 0),
                                          (257, 5, 40, 1), (512, 64, 700, 0), (512, 127, 33, 0), (512, 128, 33, 0),
                                          (513, 8, 50, 0), (64, 4, 20000, 0), (64, 4, 70000, 0)])
