@@ -653,6 +653,29 @@ __device__ __forceinline__ uint32_t group_scan(uint32_t x, uint32_t &total)
     return s - x;
 }
 
+// The label tables that a row's expressions look up.
+struct LabelTables {
+    const uint64_t *present;  // [L][4]
+    const uint32_t *wbase;    // [L][4]
+};
+
+// Up to this many labels the compiles hold them in LDS: a lane looks up each
+// expression's presence words and then the base of each entry's plane, a chain of
+// gathers from memory otherwise (233,017 rows of 64 labels: affinity 75 -> 61 us,
+// preferred 89 -> 77).
+constexpr int32_t kLdsLabels = 64;
+__device__ __forceinline__ LabelTables stage_labels(const uint64_t *__restrict__ present,
+                                                    const uint32_t *__restrict__ wbase, int32_t L, uint64_t *sp,
+                                                    uint32_t *sw)
+{
+    for (int32_t x = threadIdx.x; x < L * 4; x += blockDim.x) {
+        sp[x] = present[x];
+        sw[x] = wbase[x];
+    }
+    __syncthreads();
+    return {sp, sw};
+}
+
 // kSelLanes lanes per row, one predicate each: validate and size the
 // predicates, then emit the program -- inline in the row record when it has
 // at most 15 entries, else at prog[4 * pred_off[i] ...] (at most 4 entries
@@ -660,14 +683,16 @@ __device__ __forceinline__ uint32_t group_scan(uint32_t x, uint32_t &total)
 // is built in LDS and written by the group.
 // Bound by the chain offsets -> predicate -> presence words of a row, which
 // the lanes walk together (a thread per row walked it once per predicate:
-// 16,384 rows 22 us, now 7.5; 699,051 rows 113 us, now 81).
+// 16,384 rows 22 us, now 7.5; 699,051 rows 113 us, 81 with the groups, now 57 with
+// the label tables in LDS).
 constexpr int kCompThreads = 256;
 constexpr int kSelLanes = 8;
+template <bool kLds>
 __global__ __launch_bounds__(kCompThreads) void k_sel_compile(const int32_t *__restrict__ pred_off,
                                                               const pc_pred *__restrict__ preds, int64_t n_preds,
                                                               int32_t I, int32_t L,
-                                                              const uint64_t *__restrict__ present,
-                                                              const uint32_t *__restrict__ wbase,
+                                                              const uint64_t *__restrict__ present_all,
+                                                              const uint32_t *__restrict__ wbase_all,
                                                               uint32_t *__restrict__ prog, uint32_t *__restrict__ rec,
                                                               uint32_t *__restrict__ d_err)
 {
@@ -676,6 +701,15 @@ __global__ __launch_bounds__(kCompThreads) void k_sel_compile(const int32_t *__r
     uint32_t *R = srec[threadIdx.x / G];
     const int gl = threadIdx.x % G;
     uint32_t errs = 0;
+    const uint64_t *present = kLds ? nullptr : present_all;
+    const uint32_t *wbase = kLds ? nullptr : wbase_all;
+    __shared__ uint64_t sp[kLds ? kLdsLabels * 4 : 1];
+    __shared__ uint32_t sw[kLds ? kLdsLabels * 4 : 1];
+    if constexpr (kLds) {
+        const LabelTables tab = stage_labels(present_all, wbase_all, L, sp, sw);
+        present = tab.present;
+        wbase = tab.wbase;
+    }
     for (int64_t i0 = static_cast<int64_t>(blockIdx.x) * (kCompThreads / G); i0 < I;
          i0 += static_cast<int64_t>(gridDim.x) * (kCompThreads / G)) {
         const int64_t i = i0 + threadIdx.x / G;
@@ -863,29 +897,6 @@ struct NextExpr {
         return now;
     }
 };
-
-// The label tables that a row's expressions look up.
-struct LabelTables {
-    const uint64_t *present;  // [L][4]
-    const uint32_t *wbase;    // [L][4]
-};
-
-// Up to this many labels the compiles hold them in LDS: a lane looks up each
-// expression's presence words and then the base of each entry's plane, a chain of
-// gathers from memory otherwise (233,017 rows of 64 labels: affinity 75 -> 61 us,
-// preferred 89 -> 77).
-constexpr int32_t kLdsLabels = 64;
-__device__ __forceinline__ LabelTables stage_labels(const uint64_t *__restrict__ present,
-                                                    const uint32_t *__restrict__ wbase, int32_t L, uint64_t *sp,
-                                                    uint32_t *sw)
-{
-    for (int32_t x = threadIdx.x; x < L * 4; x += blockDim.x) {
-        sp[x] = present[x];
-        sw[x] = wbase[x];
-    }
-    __syncthreads();
-    return {sp, sw};
-}
 
 // One affinity row, on one lane (rows that k_aff_compile's groups do not
 // take): the record in rr, the inventory flags in unknown[i].
@@ -2502,9 +2513,11 @@ int run_selectors(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, cons
     rc = build_planes(ctx, labels, N, L, W, Wp, 0, present, wbase, planes, ctl, stream);
     if (rc) return rc;
     constexpr int kRows = kCompThreads / kSelLanes;  // rows per workgroup
-    const unsigned rgrid = static_cast<unsigned>(std::min<int64_t>((I + kRows - 1) / kRows, 65536));
+    // (a workgroup fills its label tables once: of 699,051 rows, 21,846 workgroups
+    // 63.5 us, 8,192 56.7, 4,096 58.5, 2,048 62.6)
+    const unsigned rgrid = static_cast<unsigned>(std::min<int64_t>((I + kRows - 1) / kRows, 8192));
     PC_TIMED(ctx, "k_sel_compile", stream,
-             hipLaunchKernelGGL(k_sel_compile, dim3(rgrid), dim3(256), 0, stream, pred_off, preds, n_preds, I, L,
+             hipLaunchKernelGGL(L <= kLdsLabels ? k_sel_compile<true> : k_sel_compile<false>, dim3(rgrid), dim3(256), 0, stream, pred_off, preds, n_preds, I, L,
                                 present, wbase, prog, rec, ctx->d_err));
     PC_LAUNCH_CHECK(ctx);
     if (W == 0) return PC_OK;

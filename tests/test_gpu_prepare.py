@@ -173,3 +173,16 @@ def test_presence_workgroups(g, orc, N):
         f, p = g.selectors(labels, off, preds)
         fo, po, _ = orc.selectors(labels, off, preds)
         assert np.array_equal(f, fo) and np.array_equal(p, po)
+
+
+@pytest.mark.parametrize("L", [64, 65])
+def test_many_selectors(g, orc, L):
+    """More rows than the compile's workgroups take at once; label tables that fit LDS and one label more."""
+    rng = np.random.default_rng(L)
+    cards = rng.choice([2, 16, 64], size=L)
+    labels = synth.gen_labels(rng, 70, cards, 0.1)
+    off, preds = synth.gen_preds(rng, 8192 * 32 + 33, cards, 0, 6, mmax=4)
+    preds["op"][rng.integers(0, preds.shape[0], 100)] = 9
+    fo, po, _ = orc.selectors(labels, off, preds)
+    fg, pg = g.selectors(labels, off, preds)[:2]
+    assert np.array_equal(fg, fo) and np.array_equal(pg, po)
