@@ -159,16 +159,85 @@ __global__ __launch_bounds__(256) void k_ps_in_fill(int32_t V, const int32_t *__
 constexpr uint32_t kNoLink = 0xFFFF0000u;  // bounds' links: slot 0 at the weight that saturates every sum
 constexpr uint32_t kNoPeer = 0xFFFFu;  // packed links: the port is no link (switch ids stay below 12,288)
 
+// How the bounds are kept, from a sorted sample of n link weights: in 16 bits
+// and units of 2^shift, where nineteen links in twenty have at most twelve
+// bits left (sixteen such links before a bound saturates), and the heavier
+// ones count no more than a saturated bound.  Weights are rounded down and
+// clamped, so the sums stay lower bounds.  Where a unit would be coarse for the
+// lighter links (less than sixteen of them in the lowest quarter's weight),
+// which the search would then wander along at no cost: kWideBounds, 32 bits and the
+// weights as they are.
+// (32,768 requests over 2,880 switches.  One drained link of 65,535 among
+// weights 1-10: 6.8 ms with the largest weight's scale, whose bounds are all 0,
+// 5.3 by the workgroup search alone, 0.68 so, as without that link; a fifth of
+// the links drained 7.4 / 5.7 / 1.6; weights up to 2^20, their logarithms
+// uniform, 10.9 / 9.4 / 2.5.)
+constexpr uint32_t kWideBounds = 256;
+__device__ __forceinline__ uint32_t bound_form(const uint32_t *sorted, int n)
+{
+    if (n == 0) return kWideBounds;
+    const uint32_t heavy = sorted[(n - 1) * 19 / 20], light = sorted[n / 4];
+    const int bits = 32 - __builtin_clz(heavy | 1u);
+    const uint32_t shift = bits > 12 ? static_cast<uint32_t>(bits - 12) : 0u;
+    return shift == 0 || (light >> shift) >= 16 ? shift : kWideBounds;
+}
+
+// A sample of the links' weights, a port from every stretch of n_ports /
+// kSample, sorted (bitonic, two values a thread; non-links last); returns the
+// number of links.  A step within 128 values is one wavefront's and needs no
+// barrier.
+constexpr int kSample = 512;
+__device__ __forceinline__ int sample_weights(int32_t V, const int32_t *__restrict__ port_peer, int64_t n_ports,
+                                              const uint32_t *__restrict__ weight, uint32_t *sorted)
+{
+    __shared__ int n;
+    const int tid = threadIdx.x;
+    if (tid == 0) n = 0;
+    __syncthreads();
+    const int64_t per = (n_ports + kSample - 1) / kSample;
+    for (int i = tid; i < kSample; i += kSample / 2) {
+        const int64_t p = i * per + (static_cast<uint32_t>(i) * 2654435761u >> 8) % per;
+        const uint32_t w = p < n_ports ? link_weight(port_peer, weight, V, p) : 0u;
+        sorted[i] = w ? w : ~0u;
+        if (w) atomicAdd(&n, 1);
+    }
+    __syncthreads();
+    for (int k = 2; k <= kSample; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            const int a = (tid & ~(j - 1)) << 1 | (tid & (j - 1)), b = a + j;
+            const uint32_t x = sorted[a], y = sorted[b];
+            if ((x > y) == ((a & k) == 0)) {
+                sorted[a] = y;
+                sorted[b] = x;
+            }
+            if (j > 64 || (j == 1 && k >= 128)) {  // the step is, or the next one will be, across wavefronts
+                __syncthreads();
+            } else {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+        }
+    return n;
+}
+
 // The links' largest weight and the complement of their smallest
 // (wspan[0], wspan[1], both maxima), and the switches that some leg ends at
-// (every target and waypoint that is a switch).
+// (every target and waypoint that is a switch).  Meanwhile the last workgroup
+// chooses the bounds' form (wspan[2]) from a sample.
 __global__ __launch_bounds__(256) void k_ps_survey(int32_t V, const int32_t *__restrict__ port_peer, int64_t n_ports,
                                                    const uint32_t *__restrict__ weight, int32_t Q,
                                                    const int32_t *__restrict__ target, const int32_t *__restrict__ via,
                                                    int32_t Kv, int32_t *__restrict__ need,
                                                    uint32_t *__restrict__ wspan)
 {
-    __shared__ uint32_t top[2];
+    __shared__ uint32_t top[2], sorted[kSample];
+    const unsigned blocks = gridDim.x - 1;
+    if (blockIdx.x == blocks) {
+        const int n = sample_weights(V, port_peer, n_ports, weight, sorted);
+        if (threadIdx.x == 0) wspan[2] = bound_form(sorted, n);
+        return;
+    }
     if (threadIdx.x < 2) top[threadIdx.x] = 0;
     __syncthreads();
     const int64_t nv = static_cast<int64_t>(Q) * Kv;
@@ -176,7 +245,7 @@ __global__ __launch_bounds__(256) void k_ps_survey(int32_t V, const int32_t *__r
     if (Q > tot) tot = Q;
     uint32_t mine = 0, least = ~0u;
     for (int64_t x = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; x < tot;
-         x += static_cast<int64_t>(gridDim.x) * blockDim.x) {
+         x += static_cast<int64_t>(blocks) * blockDim.x) {
         if (x < n_ports) {
             const uint32_t w = link_weight(port_peer, weight, V, x);
             mine = mine > w ? mine : w;
@@ -200,21 +269,15 @@ __global__ __launch_bounds__(256) void k_ps_survey(int32_t V, const int32_t *__r
 // directed 3.1 ms; weights 1-2: 2.5 ms, directed 0.8 ms).
 __device__ __forceinline__ bool one_weight(const uint32_t *wspan) { return wspan[0] == ~wspan[1] || wspan[0] == 0; }
 
-// Bounds are kept in 16 bits, in units of 2^shift: a largest weight of up
-// to 12 bits leaves room for sixteen such links before a bound saturates.
-// Weights are rounded down, so the sums stay lower bounds.
-__device__ __forceinline__ uint32_t bound_shift(const uint32_t *wspan)
-{
-    const int bits = 32 - __builtin_clz(wspan[0] | 1u);
-    return bits > 12 ? static_cast<uint32_t>(bits - 12) : 0u;
-}
+__device__ __forceinline__ bool wide_bounds(const uint32_t *wspan) { return wspan[2] == kWideBounds; }
+__device__ __forceinline__ uint32_t bound_shift(const uint32_t *wspan) { return wspan[2] & 31u; }
 
 // The LDS slot of switch v in the bounds kernel: switches 16 apart fall in
 // different banks (the peers of a fat-tree's core are a pod apart).
 __device__ __forceinline__ int32_t bslot(int32_t v) { return v ^ ((v >> 4) & 15); }
 
 // Packed forms of the port graph: per port (peer | region << 16, weight)
-// and (peer's slot | scaled weight << 16), per switch its port range (empty when
+// and (peer's slot | scaled weight << 16, for 16-bit bounds), per switch its port range (empty when
 // its offsets are bad), and the list of the switches that legs end at.
 __global__ __launch_bounds__(256) void k_ps_links(int32_t V, const int32_t *__restrict__ port_off,
                                                   const int32_t *__restrict__ port_peer, int64_t n_ports,
@@ -246,62 +309,82 @@ __global__ __launch_bounds__(256) void k_ps_links(int32_t V, const int32_t *__re
 }
 
 // Distances of the whole port graph to 2 * kW of the listed switches per
-// workgroup, two 16-bit values a word: every switch takes the minimum over
-// its links of weight + the peer's values until nothing changes.  A quad of
+// workgroup, two 16-bit values a word, or to kW of them in 32 bits: every
+// switch takes the minimum over its links of weight + the peer's values until
+// nothing changes.  A quad of
 // lanes shares a switch's links, kBv switches and kBu links of each in flight
 // at once, the next switches' ranges read ahead (wider groups spend more
 // instructions on the minimum over the group than on the links: 0.63 ms with
 // 16 lanes instead of 0.34 ms).  Values only fall, and each entry is written by one
-// lane, so sweeps read whatever is newest.  Saturated sums (0xFFFF) are lower
+// lane, so sweeps read whatever is newest.  Saturated sums are lower
 // bounds like the rest.  A graph that needs more than kSweeps sweeps is too
 // long for this: its rows are marked as missing.
 // Bound by vector instructions (two packed adds and minima per link, word and
 // sweep): 2,880 rows over 138,240 links, 7-8 sweeps, in 0.31 ms with eight
-// rows per workgroup, 0.33 ms with four.
+// rows per workgroup, 0.33 ms with four; in 32 bits, over weights of a range
+// that needs them, 0.53-1.2 ms.
 constexpr int kSweeps = 40;
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ u16x2 pk_min(u16x2 a, u16x2 b) { return __builtin_elementwise_min(a, b); }
+template <class T>
+__device__ __forceinline__ T pk_min(T a, T b)
+{
+    return __builtin_elementwise_min(a, b);
+}
 
 // Minimum over a quad of lanes, in each of them.
-__device__ __forceinline__ u16x2 quad_pk_min(u16x2 x)
+template <class T>
+__device__ __forceinline__ T quad_pk_min(T x)
 {
-    const auto dpp = [](u16x2 a, auto ctrl) {
+    const auto dpp = [](T a, auto ctrl) {
         const int v = __builtin_bit_cast(int, a);
-        return __builtin_bit_cast(
-            u16x2, __builtin_amdgcn_update_dpp(v, v, decltype(ctrl)::value, 0xF, 0xF, false));
+        return __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(v, v, decltype(ctrl)::value, 0xF, 0xF, false));
     };
     x = pk_min(x, dpp(x, std::integral_constant<int, 0xB1>{}));     // quad_perm 1,0,3,2
     return pk_min(x, dpp(x, std::integral_constant<int, 0x4E>{}));  // quad_perm 2,3,0,1
 }
 
-template <int kW>
+template <class T, int kW>
 struct __align__(4 * kW) BoundWords {
-    u16x2 w[kW];
+    T w[kW];
 };
 
-template <int kBv, int kBu, int kW>
-__global__ __launch_bounds__(256 * kW) void k_ps_bound(int32_t V, const int2 *__restrict__ range,
-                                                            const uint32_t *__restrict__ blink,
-                                                            const int32_t *__restrict__ ends,
-                                                            const int32_t *__restrict__ n_ends,
-                                                            const uint32_t *__restrict__ wspan,
-                                                            uint16_t *__restrict__ bound, int32_t *__restrict__ row_ok)
+// A link as a sweep reads it: the peer's slot and the weight (no link: slot 0 at
+// the weight that saturates every sum).
+__device__ __forceinline__ uint32_t bound_link(const uint32_t *__restrict__ links, int32_t p, bool in)
 {
-    using Words = BoundWords<kW>;
-    constexpr int kRows = 2 * kW, kBoundThreads = 256 * kW;
-    extern __shared__ uint4 ps_bound_lds[];
-    Words *dd = reinterpret_cast<Words *>(ps_bound_lds);  // [V rounded up to 16], at bslot(v)
-    const int32_t n = *n_ends;
-    const int32_t r0 = blockIdx.x * kRows;
-    if (r0 >= n || one_weight(wspan)) return;
+    return in ? links[p] : kNoLink;
+}
+__device__ __forceinline__ int2 bound_link(const int2 *__restrict__ links, int32_t p, bool in)
+{
+    const int2 x = in ? links[p] : make_int2(static_cast<int>(kNoPeer), 0);
+    const int32_t u = x.x & 0xFFFF;
+    return u == static_cast<int32_t>(kNoPeer) ? make_int2(0, -1) : make_int2(bslot(u), x.y);
+}
+__device__ __forceinline__ uint32_t link_slot(uint32_t link) { return link & 0xFFFFu; }
+__device__ __forceinline__ uint32_t link_slot(int2 link) { return static_cast<uint32_t>(link.x); }
+__device__ __forceinline__ u16x2 link_cost(uint32_t link)
+{
+    const uint16_t w = static_cast<uint16_t>(link >> 16);
+    return u16x2{w, w};
+}
+__device__ __forceinline__ uint32_t link_cost(int2 link) { return static_cast<uint32_t>(link.y); }
+
+// The rows from r0 on.  T: a word of values (u16x2 or uint32_t), Out: a value.
+template <int kBv, int kBu, int kW, class T, class Out, class Link>
+__device__ __forceinline__ void bound_rows(int32_t V, const int2 *__restrict__ range, const Link *__restrict__ links,
+                                           const int32_t *__restrict__ ends, int32_t n, int32_t r0, uint4 *lds,
+                                           Out *__restrict__ bound, int32_t *__restrict__ row_ok)
+{
+    using Words = BoundWords<T, kW>;
+    constexpr int kRows = static_cast<int>(sizeof(Words) / sizeof(Out)), kBoundThreads = 256 * kW;
+    Words *dd = reinterpret_cast<Words *>(lds);  // [V rounded up to 16], at bslot(v)
     const int tid = threadIdx.x;
-    const u16x2 far = {0xFFFF, 0xFFFF};
     Words none;
 #pragma unroll
-    for (int k = 0; k < kW; ++k) none.w[k] = far;
+    for (int k = 0; k < kW; ++k) none.w[k] = __builtin_bit_cast(T, ~0u);
     for (int32_t v = tid; v < ((V + 15) & ~15); v += kBoundThreads) dd[v] = none;
     __syncthreads();
-    if (tid < kRows && r0 + tid < n) reinterpret_cast<uint16_t *>(&dd[bslot(ends[r0 + tid])])[tid] = 0;
+    if (tid < kRows && r0 + tid < n) reinterpret_cast<Out *>(&dd[bslot(ends[r0 + tid])])[tid] = 0;
     __syncthreads();
     constexpr int GS = 4, kStep = kBoundThreads / GS * kBv;
     const int grp = tid / GS, gl = tid % GS;
@@ -318,30 +401,28 @@ __global__ __launch_bounds__(256 * kW) void k_ps_bound(int32_t V, const int2 *__
             int2 r[kBv];
 #pragma unroll
             for (int k = 0; k < kBv; ++k) r[k] = rn[k];
-            uint32_t L[kBv][kBu];
+            Link L[kBv][kBu];
 #pragma unroll
             for (int k = 0; k < kBv; ++k)
 #pragma unroll
                 for (int j = 0; j < kBu; ++j) {
                     const int32_t p = r[k].x + j * GS + gl;
-                    L[k][j] = p < r[k].y ? blink[p] : kNoLink;
+                    L[k][j] = bound_link(links, p, p < r[k].y);
                 }
             ranges(v0 + kStep, rn);
 #pragma unroll
             for (int k = 0; k < kBv; ++k) {
                 if (v0 + k >= V) break;
                 Words acc = none;
-                auto take = [&](uint32_t link) {  // (no link: weight 0xFFFF, which saturates)
-                    const Words x = dd[link & 0xFFFFu];
-                    const uint16_t w = static_cast<uint16_t>(link >> 16);
-                    const u16x2 ww = {w, w};
+                auto take = [&](Link link) {
+                    const Words x = dd[link_slot(link)];
+                    const T w = link_cost(link);
 #pragma unroll
-                    for (int i = 0; i < kW; ++i) acc.w[i] = pk_min(acc.w[i], __builtin_elementwise_add_sat(x.w[i], ww));
+                    for (int i = 0; i < kW; ++i) acc.w[i] = pk_min(acc.w[i], __builtin_elementwise_add_sat(x.w[i], w));
                 };
 #pragma unroll
                 for (int j = 0; j < kBu; ++j) take(L[k][j]);
-                for (int32_t p = r[k].x + kBu * GS; p < r[k].y; p += GS)
-                    take(p + gl < r[k].y ? blink[p + gl] : kNoLink);
+                for (int32_t p = r[k].x + kBu * GS; p < r[k].y; p += GS) take(bound_link(links, p + gl, p + gl < r[k].y));
 #pragma unroll
                 for (int i = 0; i < kW; ++i) acc.w[i] = quad_pk_min(acc.w[i]);
                 if (gl == 0) {
@@ -363,10 +444,34 @@ __global__ __launch_bounds__(256 * kW) void k_ps_bound(int32_t V, const int2 *__
     }
     for (int k = 0; k < kRows; ++k) {
         if (r0 + k >= n) break;
-        uint16_t *row = bound + static_cast<int64_t>(r0 + k) * V;
-        for (int32_t v = tid; v < V; v += kBoundThreads) row[v] = reinterpret_cast<const uint16_t *>(&dd[bslot(v)])[k];
+        Out *row = bound + static_cast<int64_t>(r0 + k) * V;
+        for (int32_t v = tid; v < V; v += kBoundThreads) row[v] = reinterpret_cast<const Out *>(&dd[bslot(v)])[k];
         if (tid == 0) row_ok[r0 + k] = done;
     }
+}
+
+// (A grid of V / kW workgroups: half of them end at once with 16-bit values.  The
+// 32-bit form has half as many switches in flight where that is several: its
+// links take twice the registers, and a second workgroup has to fit a CU.)
+template <int kBv, int kBu, int kW>
+__global__ __launch_bounds__(256 * kW) void k_ps_bound(int32_t V, const int2 *__restrict__ range,
+                                                            const uint32_t *__restrict__ blink,
+                                                            const int2 *__restrict__ link,
+                                                            const int32_t *__restrict__ ends,
+                                                            const int32_t *__restrict__ n_ends,
+                                                            const uint32_t *__restrict__ wspan,
+                                                            uint32_t *__restrict__ bound, int32_t *__restrict__ row_ok)
+{
+    extern __shared__ uint4 ps_bound_lds[];
+    const int32_t n = *n_ends;
+    const bool wide = wide_bounds(wspan);
+    const int32_t r0 = blockIdx.x * (wide ? kW : 2 * kW);
+    if (r0 >= n || one_weight(wspan)) return;
+    if (wide)
+        bound_rows<(kBv + 1) / 2, kBu, kW, uint32_t, uint32_t>(V, range, link, ends, n, r0, ps_bound_lds, bound, row_ok);
+    else
+        bound_rows<kBv, kBu, kW, u16x2, uint16_t>(V, range, blink, ends, n, r0, ps_bound_lds,
+                                                  reinterpret_cast<uint16_t *>(bound), row_ok);
 }
 
 // One wavefront per request, directed by the bounds.  A switch u relaxed to
@@ -401,7 +506,7 @@ template <int GS>
 __global__ __launch_bounds__(64) void k_ps_goal(
     int32_t V, int64_t n_ports, const int2 *__restrict__ range, const int2 *__restrict__ link, const uint8_t *__restrict__ region,
     const int32_t *__restrict__ rin_off, const int2 *__restrict__ rin, const int32_t *__restrict__ row,
-    const int32_t *__restrict__ row_ok, const uint16_t *__restrict__ bound, const uint32_t *__restrict__ wspan,
+    const int32_t *__restrict__ row_ok, const uint32_t *__restrict__ bound, const uint32_t *__restrict__ wspan,
     const int32_t *__restrict__ src, const int32_t *__restrict__ target, const uint32_t *__restrict__ allowed,
     const int32_t *__restrict__ via, int32_t Kv, const int32_t *__restrict__ forbid, int32_t Kf,
     const pc_key *__restrict__ key, const int32_t *__restrict__ out_port, int32_t prio, int32_t max_hops,
@@ -442,6 +547,7 @@ __global__ __launch_bounds__(64) void k_ps_goal(
     };
     int32_t m = 0;  // waypoints: the list ends at its first -1
     while (m < Kv && vl[m] != -1) ++m;
+    const bool wide = wide_bounds(wspan);
     const uint32_t shift = bound_shift(wspan);
     // every stop is a usable switch, or the request fails before any search
     if (!fail) fail = !usable(s) || !usable(t);
@@ -458,7 +564,9 @@ __global__ __launch_bounds__(64) void k_ps_goal(
             hard_q = true;
             break;
         }
-        const uint16_t *bt = bound + static_cast<int64_t>(rw) * V;
+        const uint32_t *bt32 = bound + static_cast<int64_t>(rw) * V;
+        const uint16_t *bt16 = reinterpret_cast<const uint16_t *>(bound) + static_cast<int64_t>(rw) * V;
+        auto bound_of = [&](uint32_t v) -> uint32_t { return wide ? bt32[v] : bt16[v]; };  // in units of 2^shift
         // the empty table with the forbidden switches and the leg's source
         for (int i = lane; i < kSlots / 2; i += 64) reinterpret_cast<ulonglong2 *>(tab)[i] = make_ulonglong2(kEmpty, kEmpty);
         if (lane < kSlots / 32) inq[lane] = 0;
@@ -485,8 +593,8 @@ __global__ __launch_bounds__(64) void k_ps_goal(
         }
         wave_sync();
         uint32_t head = 0, tail = 1;
-        const uint32_t base = static_cast<uint32_t>(bt[from]) << shift;
-        uint64_t B = base;  // limits and sums in 64 bits: a bound may exceed 2^31
+        const uint64_t base = static_cast<uint64_t>(bound_of(static_cast<uint32_t>(from))) << shift;
+        uint64_t B = base;  // limits and sums in 64 bits: a bound may exceed 2^31 (then the leg has no path)
         uint32_t dto = from == to ? 0u : static_cast<uint32_t>(kInf);
         while (true) {
             uint32_t turned = ~0u;  // the smallest distance + bound beyond B (below 2^32 - 1, or saturated)
@@ -520,7 +628,7 @@ __global__ __launch_bounds__(64) void k_ps_goal(
                         const uint32_t x = static_cast<uint32_t>(L[k].x), g = x >> 16;
                         const bool ok = g < 32 && ((A >> (g & 31)) & 1u);
                         if (!ok) L[k].x = static_cast<int>(kNoPeer);
-                        hb[k] = ok ? bt[x & 0xFFFFu] : 0u;
+                        hb[k] = ok ? bound_of(x & 0xFFFFu) : 0u;
                     }
 #pragma unroll
                     for (int k = 0; k < kUn; ++k) {
@@ -1019,9 +1127,8 @@ int run_synthesize(pc_ctx *ctx, int32_t V, const int32_t *port_off, const int32_
     // zeroed together: in-link counts, needed rows, the hard requests' count, the weights' span
     int32_t *cnt, *need, *n_hard, *rin_off, *cursor, *row, *ends, *row_ok, *hard;
     int2 *rin, *link, *range;
-    uint32_t *blink, *wspan;
-    uint16_t *bound;
-    const size_t n_zero = static_cast<size_t>(V) * 2 + 4;
+    uint32_t *blink, *wspan, *bound;
+    const size_t n_zero = static_cast<size_t>(V) * 2 + 5;
     auto carve = [&](Carver &cv, bool with) {
         cnt = cv.take<int32_t>(with ? n_zero : static_cast<size_t>(V) + 1);
         rin_off = cv.take<int32_t>(static_cast<size_t>(V) + 1);
@@ -1038,7 +1145,7 @@ int run_synthesize(pc_ctx *ctx, int32_t V, const int32_t *port_off, const int32_
         link = cv.take<int2>(static_cast<size_t>(n_ports) + 1);
         blink = cv.take<uint32_t>(static_cast<size_t>(n_ports) + 1);
         range = cv.take<int2>(static_cast<size_t>(V));
-        bound = cv.take<uint16_t>(n_rows * V);
+        bound = cv.take<uint32_t>(n_rows * V);
     };
     Carver dry{nullptr, 0};
     carve(dry, directed);
@@ -1081,7 +1188,7 @@ int run_synthesize(pc_ctx *ctx, int32_t V, const int32_t *port_off, const int32_
     if (directed) {
         const unsigned g = static_cast<unsigned>(std::min<int64_t>((std::max<int64_t>(n_ports, V) + 255) / 256, 4096));
         PC_TIMED(ctx, "k_ps_survey", stream,
-                 hipLaunchKernelGGL(k_ps_survey, dim3(std::min(g_all, 1024u)), dim3(256), 0, stream, V, port_peer,
+                 hipLaunchKernelGGL(k_ps_survey, dim3(std::min(g_all, 1024u) + 1), dim3(256), 0, stream, V, port_peer,
                                     n_ports, weight, Q, target, via, Kv, need, wspan));
         launch_scan_i32(need, V, row, nullptr, nullptr, stream);
         PC_TIMED(ctx, "k_ps_links", stream,
@@ -1104,8 +1211,8 @@ int run_synthesize(pc_ctx *ctx, int32_t V, const int32_t *port_off, const int32_
             PC_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(bk),
                                             hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_b)));
             PC_TIMED(ctx, "k_ps_bound", stream,
-                     hipLaunchKernelGGL(bk, dim3(static_cast<unsigned>((V + 2 * words - 1) / (2 * words))), dim3(256 * words), lds_b,
-                                        stream, V, range, blink, ends, row + V, wspan, bound, row_ok));
+                     hipLaunchKernelGGL(bk, dim3(static_cast<unsigned>((V + words - 1) / words)), dim3(256 * words), lds_b,
+                                        stream, V, range, blink, link, ends, row + V, wspan, bound, row_ok));
             PC_TIMED(ctx, "k_ps_goal", stream,
                      hipLaunchKernelGGL(gk, dim3(static_cast<unsigned>(Q)), dim3(64), lds_g, stream, V, n_ports, range,
                                         link, region, rin_off, rin, row, row_ok, bound,

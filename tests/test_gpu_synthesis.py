@@ -212,3 +212,66 @@ def test_overlapping_port_ranges(g, orc, weighted, Q):
     w = synth.port_weights(4, n, 9) if weighted else None
     ho, _, _ = _check(g, orc, 40, off, topo["port_peer"], topo["jur"], req, 5, 20, w)
     assert (ho > 0).any()
+
+
+def _spread(kind, n, rng):
+    """Link weights that no single scale of 16 bits suits, or that one outlier must not spoil."""
+    if kind == "log32":
+        return np.minimum(np.exp2(rng.random(n) * 32), 2**32 - 1).astype(np.uint32)
+    w = rng.integers(1, 11, n).astype(np.uint32)
+    at = rng.permutation(n)
+    if kind == "outlier":
+        w[at[:1]] = 65535
+    elif kind == "drained":      # a link in a hundred
+        w[at[:n // 100]] = 65535
+    elif kind == "two_scales":   # a third of them
+        w[at[:n // 3]] *= 100_000
+    return w
+
+
+@pytest.mark.parametrize("weights", ["log32", "drained", "two_scales"])
+@pytest.mark.parametrize("kind", ["random300", "random1500", "fat_tree12", "fat_tree24", "line700"])
+def test_bound_forms(g, orc, kind, weights):
+    """Bounds of 16 and of 32 bits, clamped links and sums that saturate, with every split of the bounds kernel."""
+    rng = np.random.default_rng(31)
+    size = int("".join(c for c in kind if c.isdigit()))
+    topo = synth.fat_tree(size, 6) if kind.startswith("fat") else _line(size, rng) if kind.startswith("line") else \
+        synth.random_graph(rng, size, 2 * size + size // 3, 2, 6)
+    n = topo["port_peer"].shape[0]
+    Q = (topo["S"] + 25_000_000 // n) // 2 + 40
+    req = synth.synthesis_requests(5, topo, Q, Kv=1, Kf=2, p_other_jur=0.8)
+    ho, _, _ = _check(g, orc, topo["S"], topo["port_off"], topo["port_peer"], topo["jur"], req, 7, 64,
+                      _spread(weights, n, rng))
+    assert (ho >= 0).sum() > 50
+
+
+@pytest.mark.parametrize("weights", ["log32", "outlier", "drained", "two_scales"])
+def test_spread_weights_are_directed(g, orc, weights):
+    """Whatever the weights' range, the directed search settles nearly every request: the workgroup search is left a
+    small share of what it takes for the same requests in batches too small for the directed one, with the same
+    results."""
+    import paper_2602_16100_amd as pc
+    topo = synth.fat_tree(32, 8)
+    w = _spread(weights, topo["port_peer"].shape[0], np.random.default_rng(3))
+    Q, batch = 8000, 900
+    req = synth.synthesis_requests(5, topo, Q, Kv=1, Kf=2)
+    ctx = pc.context()
+
+    def run(q0, q1):
+        r = {k: v[q0:q1] for k, v in req.items()}
+        return g.synthesize(topo["S"], topo["port_off"], topo["port_peer"], topo["jur"], r["src"], r["target"],
+                            r["allowed"], r["via"], r["forbid"], r["key"], r["out_port"], 7, 32, weight=w)[:3]
+
+    run(0, batch)
+    ctx.profile(True)
+    parts = [run(q, min(q + batch, Q)) for q in range(0, Q, batch)]
+    alone = ctx.profile_read()
+    assert "k_ps_goal" not in alone
+    run(0, Q)
+    ctx.profile(True)
+    whole = run(0, Q)
+    left = ctx.profile_read()
+    ctx.profile(False)
+    for x, y in zip(whole, zip(*parts)):
+        assert np.array_equal(x, np.concatenate(y))
+    assert left["k_ps_search"][1] < alone["k_ps_search"][1] / 5, (left, alone)
