@@ -224,7 +224,8 @@ __device__ __forceinline__ int sample_weights(int32_t V, const int32_t *__restri
 // The links' largest weight and the complement of their smallest
 // (wspan[0], wspan[1], both maxima), and the switches that some leg ends at
 // (every target and waypoint that is a switch).  Meanwhile the last workgroup
-// chooses the bounds' form (wspan[2]) from a sample.
+// chooses the bounds' form (wspan[2]) from a sample, and names the sample's lightest
+// weight if 99 links in 100 have it (wspan[3], else 0).
 __global__ __launch_bounds__(256) void k_ps_survey(int32_t V, const int32_t *__restrict__ port_peer, int64_t n_ports,
                                                    const uint32_t *__restrict__ weight, int32_t Q,
                                                    const int32_t *__restrict__ target, const int32_t *__restrict__ via,
@@ -235,7 +236,10 @@ __global__ __launch_bounds__(256) void k_ps_survey(int32_t V, const int32_t *__r
     const unsigned blocks = gridDim.x - 1;
     if (blockIdx.x == blocks) {
         const int n = sample_weights(V, port_peer, n_ports, weight, sorted);
-        if (threadIdx.x == 0) wspan[2] = bound_form(sorted, n);
+        if (threadIdx.x == 0) {
+            wspan[2] = bound_form(sorted, n);
+            wspan[3] = n > 0 && sorted[n * 99 / 100] == sorted[0] ? sorted[0] : 0u;
+        }
         return;
     }
     if (threadIdx.x < 2) top[threadIdx.x] = 0;
@@ -262,12 +266,19 @@ __global__ __launch_bounds__(256) void k_ps_survey(int32_t V, const int32_t *__r
     if (threadIdx.x < 2 && top[threadIdx.x]) atomicMax(wspan + threadIdx.x, top[threadIdx.x]);
 }
 
-// Links of one weight only (or none at all): equally short paths are the
-// rule, a fat-tree's edge switches have one through every core, and a
-// directed search would keep most of the graph.  The workgroup search takes
-// every request then (2,880 switches, 32,768 requests at weight 1: 2.4 ms,
-// directed 3.1 ms; weights 1-2: 2.5 ms, directed 0.8 ms).
-__device__ __forceinline__ bool one_weight(const uint32_t *wspan) { return wspan[0] == ~wspan[1] || wspan[0] == 0; }
+// Links of one weight (or none at all), or nearly all of the lightest:
+// equally short paths are the rule then, a fat-tree's edge switches have one
+// through every core, and a directed search would keep most of the graph.
+// The workgroup search takes every request.  2,880 switches, 32,768 requests,
+// workgroup search / directed: weight 10 and one link of 11 or 65,535 2.4 / 2.6 ms,
+// one link in 1,000 2.4 / 2.6, in 100 2.4 / 2.4, in 33 2.4 / 2.3, in 10 2.5 / 1.6
+// (of 65,535 2.6 / 2.1).  A few lighter links break the ties: one in 1,000 of
+// weight 1 2.6 / 2.1, in 100 2.8 / 1.0.
+__device__ __forceinline__ bool one_weight(const uint32_t *wspan)
+{
+    const uint32_t most = wspan[0], least = ~wspan[1];
+    return most == 0 || most == least || wspan[3] == least;
+}
 
 __device__ __forceinline__ bool wide_bounds(const uint32_t *wspan) { return wspan[2] == kWideBounds; }
 __device__ __forceinline__ uint32_t bound_shift(const uint32_t *wspan) { return wspan[2] & 31u; }
@@ -1128,7 +1139,7 @@ int run_synthesize(pc_ctx *ctx, int32_t V, const int32_t *port_off, const int32_
     int32_t *cnt, *need, *n_hard, *rin_off, *cursor, *row, *ends, *row_ok, *hard;
     int2 *rin, *link, *range;
     uint32_t *blink, *wspan, *bound;
-    const size_t n_zero = static_cast<size_t>(V) * 2 + 5;
+    const size_t n_zero = static_cast<size_t>(V) * 2 + 6;
     auto carve = [&](Carver &cv, bool with) {
         cnt = cv.take<int32_t>(with ? n_zero : static_cast<size_t>(V) + 1);
         rin_off = cv.take<int32_t>(static_cast<size_t>(V) + 1);

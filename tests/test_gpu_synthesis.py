@@ -275,3 +275,30 @@ def test_spread_weights_are_directed(g, orc, weights):
     for x, y in zip(whole, zip(*parts)):
         assert np.array_equal(x, np.concatenate(y))
     assert left["k_ps_search"][1] < alone["k_ps_search"][1] / 5, (left, alone)
+
+
+@pytest.mark.parametrize("share,other,directed", [(0, 11, False), (1e-9, 11, False), (1e-9, 65535, False), (0.002, 11, False),
+                                                  (0.1, 11, True), (0.1, 65535, True), (0.02, 1, True)])
+def test_nearly_equal_weights(g, orc, share, other, directed):
+    """Weight 10 on all links but a share of them (at least one): a few heavier ones leave the ties of equal weights,
+    and the requests with the workgroup search."""
+    import paper_2602_16100_amd as pc
+    topo = synth.fat_tree(32, 8)
+    n = topo["port_peer"].shape[0]
+    links = np.random.default_rng(4).permutation(np.flatnonzero(topo["port_peer"] >= 0))
+    w = np.full(n, 10, np.uint32)
+    w[links[:int(np.ceil(share * links.size))]] = other
+    req = synth.synthesis_requests(5, topo, 8000, Kv=1, Kf=2)
+    args = (topo["S"], topo["port_off"], topo["port_peer"], topo["jur"], req["src"], req["target"], req["allowed"],
+            req["via"], req["forbid"], req["key"], req["out_port"], 7, 32)
+    ctx = pc.context()
+    g.synthesize(*args, weight=w)
+    ctx.profile(True)
+    hg, pg, rg, _ = g.synthesize(*args, weight=w)
+    t = ctx.profile_read()
+    ctx.profile(False)
+    goal, search = t["k_ps_goal"][1], t["k_ps_search"][1]
+    assert search < goal if directed else goal < search / 5, t
+    part = [a[:200] if isinstance(a, np.ndarray) and a.shape[0] == 8000 else a for a in args]
+    ho, po, ro, _ = orc.synthesize(*part, weight=w)
+    assert np.array_equal(hg[:200], ho) and np.array_equal(pg[:200], po) and np.array_equal(rg[:200], ro)
