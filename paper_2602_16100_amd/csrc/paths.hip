@@ -57,7 +57,8 @@ __device__ __forceinline__ int32_t wave_min_i32(int32_t v)
     return v;
 }
 
-// Data-error flags, each a property of the whole input.
+// Data-error flags, each a property of the whole input, and *span += the ports of
+// all valid ranges, which overlapping ranges count more than once.
 __global__ __launch_bounds__(256) void k_ps_validate(int32_t V, const int32_t *__restrict__ port_off,
                                                      const int32_t *__restrict__ port_peer, int64_t n_ports,
                                                      const uint32_t *__restrict__ weight,
@@ -67,9 +68,11 @@ __global__ __launch_bounds__(256) void k_ps_validate(int32_t V, const int32_t *_
                                                      const int32_t *__restrict__ out_port,
                                                      const int32_t *__restrict__ via, int32_t Kv,
                                                      const int32_t *__restrict__ forbid, int32_t Kf,
+                                                     unsigned long long *__restrict__ span,
                                                      uint32_t *__restrict__ d_err)
 {
     uint32_t errs = 0;
+    unsigned long long mine = 0;
     const int64_t per_q = Kv > Kf ? (Kv > 1 ? Kv : 1) : (Kf > 1 ? Kf : 1);
     int64_t tot = static_cast<int64_t>(Q) * per_q;
     if (n_ports > tot) tot = n_ports;
@@ -79,6 +82,7 @@ __global__ __launch_bounds__(256) void k_ps_validate(int32_t V, const int32_t *_
         if (x < V) {
             if (region[x] >= 32) errs |= PC_DERR_JUR;
             if (!pc_range_ok(port_off[x], port_off[x + 1], n_ports)) errs |= PC_DERR_OFFSETS;
+            else mine += static_cast<uint32_t>(port_off[x + 1] - port_off[x]);
         }
         if (x < n_ports) {
             if (port_peer[x] < -1 || port_peer[x] >= V) errs |= PC_DERR_SWITCH;
@@ -97,6 +101,11 @@ __global__ __launch_bounds__(256) void k_ps_validate(int32_t V, const int32_t *_
         if (x < static_cast<int64_t>(Q) * Kf && (forbid[x] < -1 || forbid[x] >= V)) errs |= PC_DERR_SWITCH;
     }
     if (errs) atomicOr(d_err, errs);
+    if (span != nullptr && __ballot(mine != 0)) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off, 64);
+        if ((threadIdx.x & 63) == 0) atomicAdd(span, mine);
+    }
 }
 
 // Weight of port p as a link, or 0 when it is none.
@@ -113,11 +122,22 @@ __device__ __forceinline__ uint32_t link_weight(const int32_t *__restrict__ port
 // 162 us for 138,240 ports, against 15 and 20 us).
 constexpr int kInLanes = 16;
 
+// Do the in-link lists serve?  They hold n_ports entries, and switches whose
+// port ranges overlap can have more links than that, even more than 32 bits count:
+// then no list is written, and the walk-back looks through the switches.
+__device__ __forceinline__ bool in_lists(const unsigned long long *span, int64_t n_ports)
+{
+    return *span <= static_cast<unsigned long long>(n_ports);
+}
+
 // In-link counts: kInLanes lanes per switch u, +1 at the peer of each link.
 __global__ __launch_bounds__(256) void k_ps_in_count(int32_t V, const int32_t *__restrict__ port_off,
                                                      const int32_t *__restrict__ port_peer, int64_t n_ports,
-                                                     const uint32_t *__restrict__ weight, int32_t *__restrict__ cnt)
+                                                     const uint32_t *__restrict__ weight,
+                                                     const unsigned long long *__restrict__ span,
+                                                     int32_t *__restrict__ cnt)
 {
+    if (!in_lists(span, n_ports)) return;
     const int32_t u = (blockIdx.x * blockDim.x + threadIdx.x) / kInLanes;
     if (u >= V) return;
     const int64_t b = port_off[u], e = port_off[u + 1];
@@ -128,20 +148,14 @@ __global__ __launch_bounds__(256) void k_ps_in_count(int32_t V, const int32_t *_
 
 // In-link lists: (u, link weight) pairs in rin[rin_off[v] ..); cursor starts as a
 // copy of rin_off.  The order within a list is arbitrary (only minima are
-// taken over it).  rin holds n_ports entries: switches whose port ranges
-// overlap can have more links than that, and then no list is written (the
-// searches test in_lists).
-__device__ __forceinline__ bool in_lists(const int32_t *rin_off, int32_t V, int64_t n_ports)
-{
-    return rin_off[V] >= 0 && rin_off[V] <= n_ports;
-}
+// taken over it).
 __global__ __launch_bounds__(256) void k_ps_in_fill(int32_t V, const int32_t *__restrict__ port_off,
                                                     const int32_t *__restrict__ port_peer, int64_t n_ports,
                                                     const uint32_t *__restrict__ weight,
-                                                    const int32_t *__restrict__ rin_off,
+                                                    const unsigned long long *__restrict__ span,
                                                     int32_t *__restrict__ cursor, int2 *__restrict__ rin)
 {
-    if (!in_lists(rin_off, V, n_ports)) return;
+    if (!in_lists(span, n_ports)) return;
     const int32_t u = (blockIdx.x * blockDim.x + threadIdx.x) / kInLanes;
     if (u >= V) return;
     const int64_t b = port_off[u], e = port_off[u + 1];
@@ -150,7 +164,7 @@ __global__ __launch_bounds__(256) void k_ps_in_fill(int32_t V, const int32_t *__
         const uint32_t w = link_weight(port_peer, weight, V, p);
         if (w) {
             const int32_t pos = atomicAdd(&cursor[port_peer[p]], 1);
-            if (pos >= 0 && pos < n_ports) rin[pos] = make_int2(u, static_cast<int32_t>(w));  // the weight's bits
+            rin[pos] = make_int2(u, static_cast<int32_t>(w));  // the weight's bits
         }
     }
 }
@@ -278,6 +292,12 @@ __device__ __forceinline__ bool one_weight(const uint32_t *wspan)
 {
     const uint32_t most = wspan[0], least = ~wspan[1];
     return most == 0 || most == least || wspan[3] == least;
+}
+
+// Does the workgroup search take every request?
+__device__ __forceinline__ bool undirected(const uint32_t *wspan, const unsigned long long *span, int64_t n_ports)
+{
+    return one_weight(wspan) || !in_lists(span, n_ports);
 }
 
 __device__ __forceinline__ bool wide_bounds(const uint32_t *wspan) { return wspan[2] == kWideBounds; }
@@ -471,13 +491,14 @@ __global__ __launch_bounds__(256 * kW) void k_ps_bound(int32_t V, const int2 *__
                                                             const int32_t *__restrict__ ends,
                                                             const int32_t *__restrict__ n_ends,
                                                             const uint32_t *__restrict__ wspan,
+                                                            const unsigned long long *__restrict__ span, int64_t n_ports,
                                                             uint32_t *__restrict__ bound, int32_t *__restrict__ row_ok)
 {
     extern __shared__ uint4 ps_bound_lds[];
     const int32_t n = *n_ends;
     const bool wide = wide_bounds(wspan);
     const int32_t r0 = blockIdx.x * (wide ? kW : 2 * kW);
-    if (r0 >= n || one_weight(wspan)) return;
+    if (r0 >= n || undirected(wspan, span, n_ports)) return;
     if (wide)
         bound_rows<(kBv + 1) / 2, kBu, kW, uint32_t, uint32_t>(V, range, link, ends, n, r0, ps_bound_lds, bound, row_ok);
     else
@@ -521,7 +542,8 @@ __global__ __launch_bounds__(64) void k_ps_goal(
     const int32_t *__restrict__ src, const int32_t *__restrict__ target, const uint32_t *__restrict__ allowed,
     const int32_t *__restrict__ via, int32_t Kv, const int32_t *__restrict__ forbid, int32_t Kf,
     const pc_key *__restrict__ key, const int32_t *__restrict__ out_port, int32_t prio, int32_t max_hops,
-    int32_t *__restrict__ hops_out, int32_t *__restrict__ path_out, pc_rule *__restrict__ rules_out, int32_t max_steps,
+    int32_t *__restrict__ hops_out, int32_t *__restrict__ path_out, pc_rule *__restrict__ rules_out,
+    const unsigned long long *__restrict__ span, int32_t max_steps,
     int32_t *__restrict__ hard, int32_t *__restrict__ n_hard)
 {
     constexpr unsigned long long kEmpty = ~0ull;
@@ -538,7 +560,7 @@ __global__ __launch_bounds__(64) void k_ps_goal(
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
     auto slot_of = [](uint32_t u) { return (u * 40503u >> 7) & (kSlots - 1); };
-    if (one_weight(wspan) || !in_lists(rin_off, V, n_ports)) return;
+    if (undirected(wspan, span, n_ports)) return;
     const int32_t q = blockIdx.x;
     const int32_t s = src[q], t = target[q];
     bool fail = s < 0 || s >= V || t < 0 || t >= V;
@@ -836,7 +858,7 @@ __global__ __launch_bounds__(kPsThreads) void k_ps_search(
     const int32_t *__restrict__ forbid, int32_t Kf, const pc_key *__restrict__ key,
     const int32_t *__restrict__ out_port, int32_t prio, int32_t max_hops, int32_t *__restrict__ hops_out,
     int32_t *__restrict__ path_out, pc_rule *__restrict__ rules_out, int32_t Q,
-    const int32_t *__restrict__ list, const int32_t *__restrict__ n_list, const uint32_t *__restrict__ wspan)
+    const unsigned long long *__restrict__ span, const int32_t *__restrict__ list, const int32_t *__restrict__ n_list, const uint32_t *__restrict__ wspan)
 {
     extern __shared__ int32_t ps_lds[];
     const int32_t VW = (V + 31) >> 5;
@@ -852,8 +874,8 @@ __global__ __launch_bounds__(kPsThreads) void k_ps_search(
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int32_t slots = max_hops + 1;
-    const bool lists = in_lists(rin_off, V, n_ports);
-    if (list && (one_weight(wspan) || !lists)) list = nullptr;  // the directed search took none
+    const bool lists = in_lists(span, n_ports);
+    if (list && undirected(wspan, span, n_ports)) list = nullptr;  // the directed search took none
     const int32_t n_req = list ? *n_list : Q;
     for (int32_t at = blockIdx.x; at < n_req; at += gridDim.x) {
     const int32_t q = list ? list[at] : at;
@@ -1029,8 +1051,9 @@ __global__ __launch_bounds__(kPsThreads) void k_ps_search(
                         const int2 in = rin[k];
                         pred(in.x, static_cast<uint32_t>(in.y));
                     }
-                } else {  // overlapping port ranges: every switch's links
+                } else {  // overlapping port ranges: the links of every switch the leg has reached
                     for (int32_t u = lane; u < V; u += 64) {
+                        if (dist[u] == kInf) continue;
                         const int64_t b = port_off[u], e = port_off[u + 1];
                         if (!pc_range_ok(b, e, n_ports)) continue;
                         for (int64_t p = b; p < e; ++p) {
@@ -1135,13 +1158,15 @@ int run_synthesize(pc_ctx *ctx, int32_t V, const int32_t *port_off, const int32_
     bool directed = weight != nullptr && V > 0 && n_ports > 0 && n_ports < (int64_t(1) << 30) &&
                     legs >= V + 25'000'000 / n_ports;
     const size_t n_rows = directed ? static_cast<size_t>(V) : 0;
-    // zeroed together: in-link counts, needed rows, the hard requests' count, the weights' span
+    // zeroed together: the valid ranges' ports, in-link counts, needed rows, the hard requests' count, the weights' span
+    unsigned long long *span;
     int32_t *cnt, *need, *n_hard, *rin_off, *cursor, *row, *ends, *row_ok, *hard;
     int2 *rin, *link, *range;
     uint32_t *blink, *wspan, *bound;
-    const size_t n_zero = static_cast<size_t>(V) * 2 + 6;
+    const size_t n_zero = static_cast<size_t>(V) * 2 + 8;
     auto carve = [&](Carver &cv, bool with) {
-        cnt = cv.take<int32_t>(with ? n_zero : static_cast<size_t>(V) + 1);
+        span = reinterpret_cast<unsigned long long *>(cv.take<int32_t>(n_zero));
+        cnt = reinterpret_cast<int32_t *>(span + 1);
         rin_off = cv.take<int32_t>(static_cast<size_t>(V) + 1);
         cursor = cv.take<int32_t>(static_cast<size_t>(V) + 1);
         rin = cv.take<int2>(static_cast<size_t>(n_ports) + 1);
@@ -1174,26 +1199,28 @@ int run_synthesize(pc_ctx *ctx, int32_t V, const int32_t *port_off, const int32_
 
     int64_t tot = std::max<int64_t>({static_cast<int64_t>(V), n_ports, static_cast<int64_t>(Q) * std::max(Kv, 1),
                                      static_cast<int64_t>(Q) * std::max(Kf, 1)});
+    if (Q > 0) launch_fill_u32(reinterpret_cast<uint32_t *>(span), n_zero, 0, stream);
+    PC_LAUNCH_CHECK(ctx);
     const unsigned g_all = static_cast<unsigned>(std::min<int64_t>((tot + 255) / 256, 8192));
     if (tot > 0) {
         PC_TIMED(ctx, "k_ps_validate", stream,
                  hipLaunchKernelGGL(k_ps_validate, dim3(g_all), dim3(256), 0, stream, V, port_off, port_peer, n_ports,
-                                    weight, region, Q, src, target, out_port, via, Kv, forbid, Kf, ctx->d_err));
+                                    weight, region, Q, src, target, out_port, via, Kv, forbid, Kf,
+                                    Q > 0 ? span : nullptr, ctx->d_err));
         PC_LAUNCH_CHECK(ctx);
     }
     if (Q == 0) return PC_OK;
     if (V > 0) {
-        launch_fill_u32(reinterpret_cast<uint32_t *>(cnt), directed ? n_zero : static_cast<size_t>(V) + 1, 0, stream);
         const unsigned g = static_cast<unsigned>((static_cast<int64_t>(V) * kInLanes + 255) / 256);
         PC_TIMED(ctx, "k_ps_in_count", stream,
                  hipLaunchKernelGGL(k_ps_in_count, dim3(g), dim3(256), 0, stream, V, port_off, port_peer, n_ports,
-                                    weight, cnt));
+                                    weight, span, cnt));
         PC_LAUNCH_CHECK(ctx);
         launch_scan_i32(cnt, V, rin_off, cursor, nullptr, stream);
         PC_LAUNCH_CHECK(ctx);
         PC_TIMED(ctx, "k_ps_in_fill", stream,
                  hipLaunchKernelGGL(k_ps_in_fill, dim3(g), dim3(256), 0, stream, V, port_off, port_peer, n_ports,
-                                    weight, rin_off, cursor, rin));
+                                    weight, span, cursor, rin));
         PC_LAUNCH_CHECK(ctx);
     }
     if (directed) {
@@ -1223,12 +1250,13 @@ int run_synthesize(pc_ctx *ctx, int32_t V, const int32_t *port_off, const int32_
                                             hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_b)));
             PC_TIMED(ctx, "k_ps_bound", stream,
                      hipLaunchKernelGGL(bk, dim3(static_cast<unsigned>((V + words - 1) / words)), dim3(256 * words), lds_b,
-                                        stream, V, range, blink, link, ends, row + V, wspan, bound, row_ok));
+                                        stream, V, range, blink, link, ends, row + V, wspan, span, n_ports, bound,
+                                        row_ok));
             PC_TIMED(ctx, "k_ps_goal", stream,
                      hipLaunchKernelGGL(gk, dim3(static_cast<unsigned>(Q)), dim3(64), lds_g, stream, V, n_ports, range,
                                         link, region, rin_off, rin, row, row_ok, bound,
                                         wspan, src, target, allowed, via, Kv,
-                                        forbid, Kf, key, out_port, prio, max_hops, hops, path, rules, max_steps,
+                                        forbid, Kf, key, out_port, prio, max_hops, hops, path, rules, span, max_steps,
                                         hard, n_hard));
             PC_LAUNCH_CHECK(ctx);
             return PC_OK;
@@ -1249,7 +1277,7 @@ int run_synthesize(pc_ctx *ctx, int32_t V, const int32_t *port_off, const int32_
              hipLaunchKernelGGL(k_ps_search, dim3(grid), dim3(kPsThreads), lds, stream, V,
                                 port_off, port_peer, n_ports, weight, region, rin_off, rin, src, target, allowed, via,
                                 Kv, forbid, Kf, key, out_port, prio, max_hops, hops, path, rules,
-                                Q, directed ? hard : nullptr, directed ? n_hard : nullptr,
+                                Q, span, directed ? hard : nullptr, directed ? n_hard : nullptr,
                                 directed ? wspan : nullptr));
     PC_LAUNCH_CHECK(ctx);
     return PC_OK;

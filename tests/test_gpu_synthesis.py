@@ -302,3 +302,22 @@ def test_nearly_equal_weights(g, orc, share, other, directed):
     part = [a[:200] if isinstance(a, np.ndarray) and a.shape[0] == 8000 else a for a in args]
     ho, po, ro, _ = orc.synthesize(*part, weight=w)
     assert np.array_equal(hg[:200], ho) and np.array_equal(pg[:200], po) and np.array_equal(rg[:200], ro)
+
+
+@pytest.mark.parametrize("weighted", [False, True])
+def test_more_links_than_32_bits_count(g, orc, weighted):
+    """6,144 switches own all 699,051 ports: 2^32 + 2,048 links, a count whose low 32 bits would pass for a list that
+    fits.  Two switches are usable, so that the searches and the walk back stay short."""
+    V, n = 12288, 699_051
+    rng = np.random.default_rng(1)
+    off = np.where(np.arange(V + 1) % 2 == 0, 0, n).astype(np.int32)
+    region = np.full(V, 40, np.uint8)
+    region[[0, 2]] = 0
+    peer = rng.integers(0, V, n).astype(np.int32)
+    req = dict(src=np.array([0, 2, 0, 0, 2], np.int32), target=np.array([2, 0, 0, 2, 4], np.int32),
+               allowed=np.ones(5, np.uint32), via=np.full((5, 1), -1, np.int32),
+               forbid=np.array([[-1], [-1], [-1], [2], [-1]], np.int32), key=synth.random_keys(rng, 5),
+               out_port=np.array([0, n - 1, 9, 0, 0], np.int32))
+    w = synth.port_weights(4, n, 9) if weighted else None
+    ho, _, _ = _check(g, orc, V, off, peer, region, req, 5, 8, w)
+    assert ho.tolist() == [1, 1, 0, -1, -1]
