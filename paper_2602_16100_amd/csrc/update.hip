@@ -289,7 +289,9 @@ __global__ __launch_bounds__(kRowThreads, 4) void k_upd_few(const int32_t *__res
         for (uint64_t k = kept; k; k &= k - 1) pos += __builtin_amdgcn_readlane(n, __builtin_ctzll(k)) < n;
         const int mu = __popcll(kept);
         if (ok && !repeat) ids[pos] = n;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");  // read by other lanes
         __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         const int32_t w = lane < mu ? ids[lane] >> 6 : -1;
         const int32_t before = __shfl_up(w, 1, 64);
         const uint64_t leads = __ballot(lane < mu && (lane == 0 || before != w));

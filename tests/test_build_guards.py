@@ -87,3 +87,15 @@ def test_index_mode_windows_are_the_filter_blocks(match_build):
             assert any(int(v) in (32, 48, 64, 80, 96, 112) for v in src), ln
             bases.update(int(v) for v in src if int(v) in (32, 48, 64, 80, 96, 112))
     assert bases == {32, 48, 64, 80, 96, 112}
+
+
+@pytest.mark.parametrize("name", ["update.hip", "paths.hip", "reach.hip"])
+def test_cross_lane_handovers_are_fenced(name):
+    """What lanes of one wavefront hand each other through LDS is ordered by a release and an acquire fence around
+    the wavefront barrier, which by itself orders no memory."""
+    lines = open(os.path.join(ROOT, "paper_2602_16100_amd", "csrc", name)).read().splitlines()
+    at = [i for i, ln in enumerate(lines) if "__builtin_amdgcn_wave_barrier()" in ln]
+    assert at
+    for i in at:
+        assert "__builtin_amdgcn_fence(__ATOMIC_RELEASE" in lines[i - 1], (name, i + 1)
+        assert "__builtin_amdgcn_fence(__ATOMIC_ACQUIRE" in lines[i + 1], (name, i + 1)
