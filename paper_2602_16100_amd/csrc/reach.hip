@@ -867,6 +867,58 @@ bool takes_bitset(int32_t V, int64_t n_adj, int64_t Q)
     return V > 0 && V <= kMaxBitsetV && !(n_adj / V <= kEll / 2 && V >= 512 && Q <= 1024);
 }
 
+// The search of Q queries (legs).  bits: the bitset search.  Else, with map:
+// the map search, its workgroups, whether neighbour records are formed (up to a
+// mean of kEll / 2 entries nearly all vertices fit one) and its scratch, in the
+// arena.  Else the queue search.
+struct Search {
+    bool bits = false, map = false, records = false;
+    size_t lds = 0;
+    int32_t grid = 0;
+    int32_t *list = nullptr;
+    uint32_t *ell = nullptr;
+};
+
+// The map search asks for more scratch than the others (up to 512 lists and the
+// records): where that is refused, graphs that fit the bitset search take
+// it, which may need none, and larger ones the queue search.  Chosen before the
+// checks: only the bitset search asks for the graph's symmetry.
+// (Targets close to their sources do not repay the records of a large graph: one
+// query two hops away on a million vertices 36 us, by the queue search 21; but
+// where they are is not known, and sixteen queries anywhere 242, by the queue
+// search 864.)
+int choose_search(pc_ctx *ctx, int32_t V, int64_t n_adj, int64_t Q, Search &s)
+{
+    s.bits = takes_bitset(V, n_adj, Q);
+    if (s.bits || V == 0 || Q == 0 || Q > INT32_MAX) return PC_OK;
+    int max_lds = 0;
+    PC_HIP(ctx, hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device));
+    s.lds = (static_cast<size_t>(V) + 127) / 128 * 16;
+    hipFuncAttributes fm{};
+    PC_HIP(ctx, hipFuncGetAttributes(&fm, reinterpret_cast<const void *>(k_rc_map<4, true>)));
+    if (V >= (1 << kVertexBits) || s.lds + fm.sharedSizeBytes > static_cast<size_t>(max_lds)) return PC_OK;
+    s.records = n_adj / V <= kEll / 2;
+    const int per_cu = 2 * (s.lds + fm.sharedSizeBytes) <= static_cast<size_t>(max_lds) ? 2 : 1;
+    s.grid = static_cast<int32_t>(std::min<int64_t>(Q, 256 * per_cu));
+    auto carve = [&](Carver &c) {
+        s.list = c.take<int32_t>(static_cast<size_t>(s.grid) * V);
+        s.ell = c.take<uint32_t>(s.records ? static_cast<size_t>(V) * kEll : 1);
+    };
+    Carver dry{nullptr, 0};
+    carve(dry);
+    const int rc = pc_ensure_arena(ctx, dry.off);
+    if (rc == PC_ENOMEM) {
+        ctx->msg[0] = 0;
+        s.bits = V <= kMaxBitsetV;
+        return PC_OK;
+    }
+    if (rc) return rc;
+    Carver real{ctx->arena, 0};
+    carve(real);
+    s.map = true;
+    return PC_OK;
+}
+
 // Are the queries (legs) ordered by source?  Workgroups then share
 // frontiers and expand each for more of their queries, which pays for the
 // four launches of the sort only with enough workgroups and vertices.
@@ -883,12 +935,12 @@ bool sorts(int32_t V, int64_t Q, bool legs)
 }
 
 // BFS of Q queries; query j's allowed mask is allowed[j / qdiv] and its
-// forbidden list forbid[(j / qdiv) * Kf ...] (Kf = 0: none).  gen: what
-// checks() returned.  via (bitset search, no sort): the queries are walks of
+// forbidden list forbid[(j / qdiv) * Kf ...] (Kf = 0: none).  m: choose_search's.
+// gen: what checks() returned.  via (bitset search, no sort): the queries are walks of
 // Kv + 1 legs.  Takes the context's arena when it needs scratch.
 int bfs(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj, int64_t n_adj, const uint8_t *region,
         int32_t Q, const int32_t *src, const uint32_t *allowed, const int32_t *target, int32_t *dist,
-        const int32_t *forbid, int32_t Kf, int32_t qdiv, int32_t gen, const int32_t *via, int32_t Kv,
+        const int32_t *forbid, int32_t Kf, int32_t qdiv, const Search &m, int32_t gen, const int32_t *via, int32_t Kv,
         hipStream_t stream)
 {
     if (V == 0) {
@@ -897,7 +949,7 @@ int bfs(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj, int6
         return PC_OK;
     }
     const int64_t avg = n_adj / V;
-    if (takes_bitset(V, n_adj, via ? static_cast<int64_t>(Q) * (Kv + 1) : Q)) {
+    if (m.bits) {
         const size_t lds = bitset_lds(V);
         if (!target) launch_fill_u32(reinterpret_cast<uint32_t *>(dist), static_cast<size_t>(Q) * V, 0xFFFFFFFFu, stream);
         PC_LAUNCH_CHECK(ctx);
@@ -953,43 +1005,22 @@ int bfs(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj, int6
         if (gs == 16) return launch(k_rc_bitset<16, false>);
         return launch(k_rc_bitset<32, false>);
     }
-    int max_lds = 0;
-    PC_HIP(ctx, hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device));
-    const size_t lds_m = (static_cast<size_t>(V) + 127) / 128 * 16;
-    hipFuncAttributes fm{};
-    PC_HIP(ctx, hipFuncGetAttributes(&fm, reinterpret_cast<const void *>(k_rc_map<4, true>)));
-    if (V < (1 << kVertexBits) && lds_m + fm.sharedSizeBytes <= static_cast<size_t>(max_lds)) {
-        // records for sparse graphs: up to a mean of kEll / 2 entries nearly all vertices fit one
-        const bool records = avg <= kEll / 2;
-        const int per_cu = 2 * (lds_m + fm.sharedSizeBytes) <= static_cast<size_t>(max_lds) ? 2 : 1;
-        const int32_t grid = std::min(Q, 256 * per_cu);
-        int32_t *list;
-        uint32_t *ell;
-        auto carve = [&](Carver &c) {
-            list = c.take<int32_t>(static_cast<size_t>(grid) * V);
-            ell = c.take<uint32_t>(records ? static_cast<size_t>(V) * kEll : 1);
-        };
-        Carver dry{nullptr, 0};
-        carve(dry);
-        int rc = pc_ensure_arena(ctx, dry.off);
-        if (rc) return rc;
-        Carver real{ctx->arena, 0};
-        carve(real);
-        if (records)
+    if (m.map) {
+        if (m.records)
             PC_TIMED(ctx, "k_rc_records", stream,
                      hipLaunchKernelGGL(k_rc_records, dim3(static_cast<unsigned>((static_cast<int64_t>(V) * 4 + 255) / 256)), dim3(256), 0,
-                                        stream, V, adj_off, adj, n_adj, region, ell));
+                                        stream, V, adj_off, adj, n_adj, region, m.ell));
         auto launch = [&](auto kern) -> int {
             PC_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_m)));
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(m.lds)));
             PC_TIMED(ctx, "k_rc_map", stream,
-                     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(grid)), dim3(kMapThreads), lds_m, stream, V,
-                                        adj_off, adj, n_adj, region, ell, Q, src, allowed, target, dist, list, forbid,
+                     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(m.grid)), dim3(kMapThreads), m.lds, stream, V,
+                                        adj_off, adj, n_adj, region, m.ell, Q, src, allowed, target, dist, m.list, forbid,
                                         Kf, qdiv));
             PC_LAUNCH_CHECK(ctx);
             return PC_OK;
         };
-        if (records) return launch(k_rc_map<4, true>);
+        if (m.records) return launch(k_rc_map<4, true>);
         return avg <= 24 ? launch(k_rc_map<8, false>) : launch(k_rc_map<32, false>);
     }
     if (!target) launch_fill_u32(reinterpret_cast<uint32_t *>(dist), static_cast<size_t>(Q) * V, 0xFFFFFFFFu, stream);
@@ -1001,7 +1032,7 @@ int bfs(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj, int6
     };
     Carver dry{nullptr, 0};
     carve(dry);
-    int rc = pc_ensure_arena(ctx, dry.off);
+    const int rc = pc_ensure_arena(ctx, dry.off);
     if (rc) return rc;
     Carver real{ctx->arena, 0};
     carve(real);
@@ -1043,10 +1074,13 @@ int run_reach(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj
               const uint8_t *region, int32_t Q, const int32_t *src, const uint32_t *allowed, const int32_t *target,
               int32_t *dist, hipStream_t stream)
 {
+    Search m;
+    const int rc = choose_search(ctx, V, n_adj, Q, m);
+    if (rc) return rc;
     const int32_t gen = checks(ctx, V, adj_off, adj, n_adj, region, Q, src, target, nullptr, 0, nullptr, 0,
-                               target && takes_bitset(V, n_adj, Q), stream);
+                               target && m.bits, stream);
     PC_LAUNCH_CHECK(ctx);
-    return bfs(ctx, V, adj_off, adj, n_adj, region, Q, src, allowed, target, dist, nullptr, 0, 1, gen, nullptr, 0,
+    return bfs(ctx, V, adj_off, adj, n_adj, region, Q, src, allowed, target, dist, nullptr, 0, 1, m, gen, nullptr, 0,
                stream);
 }
 
@@ -1056,13 +1090,15 @@ int run_reach_via(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t 
                   int32_t *dist, hipStream_t stream)
 {
     const int64_t nl = static_cast<int64_t>(Q) * (Kv + 1);
-    const bool bits = takes_bitset(V, n_adj, nl);
+    Search m;
+    int rc = choose_search(ctx, V, n_adj, nl, m);
+    if (rc) return rc;
     const int32_t gen = checks(ctx, V, adj_off, adj, n_adj, region, Q, src, target, via, Kv, forbid, Kf,
-                               Q > 0 && (Kv > 0 || bits), stream);
+                               Q > 0 && (Kv > 0 || m.bits), stream);
     PC_LAUNCH_CHECK(ctx);
     if (Q == 0) return PC_OK;
-    if (Kv == 0 || (bits && !sorts(V, nl, true)))
-        return bfs(ctx, V, adj_off, adj, n_adj, region, Q, src, allowed, target, dist, forbid, Kf, 1, gen,
+    if (Kv == 0 || (m.bits && !sorts(V, nl, true)))
+        return bfs(ctx, V, adj_off, adj, n_adj, region, Q, src, allowed, target, dist, forbid, Kf, 1, m, gen,
                    Kv == 0 ? nullptr : via, Kv, stream);
     // legs [Q][Kv + 1] (sources, targets, distances) in the auxiliary
     // buffer; leg j belongs to query j / (Kv + 1)
@@ -1075,7 +1111,7 @@ int run_reach_via(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t 
     };
     Carver dry{nullptr, 0};
     carve(dry);
-    int rc = pc_ensure_aux(ctx, dry.off);
+    rc = pc_ensure_aux(ctx, dry.off);
     if (rc) return rc;
     Carver real{ctx->aux, 0};
     carve(real);
@@ -1085,7 +1121,7 @@ int run_reach_via(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t 
                                 gen, leg_src, leg_tgt));
     PC_LAUNCH_CHECK(ctx);
     rc = bfs(ctx, V, adj_off, adj, n_adj, region, static_cast<int32_t>(nl), leg_src, allowed, leg_tgt, leg_dist,
-             forbid, Kf, Kv + 1, gen, nullptr, 0, stream);
+             forbid, Kf, Kv + 1, m, gen, nullptr, 0, stream);
     if (rc) return rc;
     PC_TIMED(ctx, "k_rc_via_sum", stream,
              hipLaunchKernelGGL(k_rc_via_sum, dim3(qb), dim3(256), 0, stream, Q, via, Kv, leg_dist, dist));

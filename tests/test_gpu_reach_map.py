@@ -70,3 +70,41 @@ def test_map_rows_and_targets(g, orc, kind, V, Q):
     dg = g.reach_via(V, off, adj, region, src, allowed, target, via, forbid)
     do, _ = orc.reach_via(V, off, adj, region, src, allowed, target, via, forbid)
     assert np.array_equal(dg, do), kind
+
+
+@pytest.mark.parametrize("call", ["rows", "targets", "via", "queue_rows"])
+def test_map_scratch_refused(g, orc, monkeypatch, call):
+    """Where the map search's scratch is refused, the searches that need less of it answer: on a new context the
+    bitset search (which needs none), past its sizes the queue search in an arena that holds its lists."""
+    import torch
+    import paper_2602_16100_amd as pc
+    rng = np.random.default_rng(7)
+    V, Q = (8000, 400) if call == "queue_rows" else (1500, 50)
+    off, adj = _graph("mean20" if call == "queue_rows" else "sparse", V, rng)
+    region = rng.integers(0, 4, V).astype(np.uint8)
+    src, target = (rng.integers(0, V, Q).astype(np.int32) for _ in range(2))
+    allowed = rng.integers(1, 16, Q).astype(np.uint32)
+    via, forbid = rng.integers(-1, V, (Q, 1)).astype(np.int32), rng.integers(-1, V, (Q, 2)).astype(np.int32)
+    d = g.dev
+    ctx = pc.Context(0)
+
+    def run(n):
+        a = (V, d(off), d(adj), d(region), d(src[:n]), d(allowed[:n]))
+        if call == "via":
+            return pc.pc_masked_reach_via(*a, d(target[:n]), d(via[:n]), d(forbid[:n]), ctx=ctx)
+        return pc.pc_masked_reach(*a, d(target[:n]) if call == "targets" else None, ctx=ctx)
+
+    if call == "queue_rows":
+        run(256)  # as many lists as the queue search has
+    monkeypatch.setenv("PC_FAIL_ALLOC", "1")
+    ctx.profile(True)
+    got = run(Q)
+    torch.cuda.synchronize()
+    used = ctx.profile_read()
+    ctx.profile(False)
+    assert ("k_rc_queue" if call == "queue_rows" else "k_rc_bitset") in used and "k_rc_map" not in used
+    if call == "via":
+        want, _ = orc.reach_via(V, off, adj, region, src, allowed, target, via, forbid)
+    else:
+        want, _ = orc.reach(V, off, adj, region, src, allowed, target if call == "targets" else None)
+    assert np.array_equal(got.cpu().numpy(), want)
