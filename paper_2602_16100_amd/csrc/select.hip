@@ -348,6 +348,7 @@ constexpr int kSmallThreads = 1024;
 constexpr size_t kSmallLds = 64 * 1024;      // labels of the cluster, at most: two workgroups per CU
 constexpr int64_t kSmallW = 8;               // words of a row, at most
 constexpr int64_t kSmallWork = 400000;       // predicates x (words + 2), at most
+constexpr int64_t small_rows(int64_t W) { return W == 1 ? 1 << 20 : W <= 4 ? 1 << 18 : 1 << 15; }  // rows, at most
 
 // bytes of a label's row: whole pairs of quads, and a dword against bank conflicts
 __host__ __device__ inline int64_t small_pitch(int64_t W) { return (W + 7) / 8 * 8 * 64 + 4; }
@@ -2471,9 +2472,14 @@ int run_selectors(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, cons
     // Few words and predicates: the labels themselves, in one launch.  Planes
     // and programs / labels: 43 to 6,000 rows over 16 nodes 35 / 15 us, 20,000 rows
     // over 64 34 / 20, 6,000 over 300 34 / 18, 20,000 over 300 36 / 35; past the
-    // limits 60,000 rows over 64 nodes 48 / 50, 6,000 over 1,500 35 / 50.
+    // limits 60,000 rows over 64 nodes 48 / 50, 6,000 over 1,500 35 / 50.  Rows
+    // without predicates still take a wavefront each, so their number counts too:
+    // 20,000 predicates in 25,000 rows over 500 nodes 27 / 26, in 50,000 32 / 34, in
+    // 200,000 62 / 81; over 250 nodes 200,000 rows 60 / 56, 500,000 94 / 123; over
+    // 64 500,000 rows 93 / 76, 1,000,000 146 / 151, 2,000,000 255 / 307.
     const size_t small_lds = static_cast<size_t>(L) * static_cast<size_t>(small_pitch(W));
-    const bool small = W > 0 && W <= kSmallW && small_lds <= kSmallLds && n_preds <= kSmallWork / (W + 2);
+    const bool small = W > 0 && W <= kSmallW && small_lds <= kSmallLds && n_preds <= kSmallWork / (W + 2) &&
+                       I <= small_rows(W);
     auto launch_small = [&]() -> int {
         const unsigned blocks = static_cast<unsigned>(std::min(I / (kSmallThreads / 64) + 1, 512));
         const auto kern = W == 1 ? k_sel_small<1> : W <= 4 ? k_sel_small<4> : k_sel_small<8>;

@@ -186,3 +186,26 @@ def test_many_selectors(g, orc, L):
     fo, po, _ = orc.selectors(labels, off, preds)
     fg, pg = g.selectors(labels, off, preds)[:2]
     assert np.array_equal(fg, fo) and np.array_equal(pg, po)
+
+
+@pytest.mark.parametrize("N,I,small", [(500, 32_768, True), (500, 32_769, False), (250, 262_144, True),
+                                       (250, 262_145, False), (64, 1_048_576, True), (60, 1_048_577, False)])
+def test_small_clusters_of_many_rows(g, orc, N, I, small):
+    """A wavefront per row pays up to a number of rows that falls with their words, however few predicates they have."""
+    import paper_2602_16100_amd as pc
+    rng = np.random.default_rng(I)
+    cards = rng.choice([2, 16, 64], size=8)
+    labels = synth.gen_labels(rng, N, cards, 0.1)
+    some_off, preds = synth.gen_preds(rng, 5000, cards, 0, 4, mmax=3)
+    off = np.zeros(I + 1, np.int32)
+    at = np.sort(rng.choice(I, 5000, replace=False))
+    off[at + 1] = np.diff(some_off)
+    off = np.cumsum(off, dtype=np.int64).astype(np.int32)
+    ctx = pc.context()
+    ctx.profile(True)
+    f, p = g.selectors(labels, off, preds)
+    used = ctx.profile_read()
+    ctx.profile(False)
+    assert ("k_sel_small" in used) == small
+    fo, po, _ = orc.selectors(labels, off, preds)
+    assert np.array_equal(f, fo) and np.array_equal(p, po)
