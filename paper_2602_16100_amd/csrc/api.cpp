@@ -171,6 +171,7 @@ int pc_create(pc_ctx **out, int device)
         hipMalloc(reinterpret_cast<void **>(&ctx->d_small), 256) != hipSuccess ||
         hipMemset(ctx->d_small, 0, 256) != hipSuccess ||
         hipHostMalloc(reinterpret_cast<void **>(&ctx->h_small), 256, hipHostMallocDefault) != hipSuccess ||
+        memset(ctx->h_small, 0, 256) == nullptr ||
         hipEventCreateWithFlags(&ctx->lvl_ev[0], hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&ctx->lvl_ev[1], hipEventDisableTiming) != hipSuccess) {
         (void)hipGetLastError();

@@ -17,6 +17,7 @@ struct pc_ctx {
     uint32_t *d_err;     // sticky data-error word (device)
     int32_t *d_small;    // small device counters (live counts, totals)
     int32_t *h_small;    // pinned host mirror of d_small
+    uint32_t direct_call = 0;  // number of the last trace call that asked for its tables' lengths
     int32_t reach_gen = 0;  // number of the last search that checked its graph's symmetry
     char *arena;         // scratch arena (device)
     size_t arena_bytes;

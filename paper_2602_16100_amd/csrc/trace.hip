@@ -71,8 +71,11 @@ static_assert(kItemMin <= kChunk && kChunk <= kMatchWaves * 64, "a wavefront's l
 static_assert((kWideItem + 3) / 4 * 4 <= kWideChunk && kWideChunk <= kWideThreads, "one epilogue thread per lookup");
 constexpr int kCountPad = 32;  // live-trace counters are 128 bytes apart: contended atomics on one line serialise
 constexpr int32_t kDirectRules = 1024;               // mean rules per switch that a walk may match one by one,
-constexpr int64_t kDirectWork = 5000000;             // traces times mean rules
-constexpr int64_t kDirectWorst = int64_t(1) << 26;   // and traces times all rules
+constexpr int64_t kDirectWork = 5000000;             // traces times mean rules,
+constexpr int64_t kDirectWorst = int64_t(1) << 26;   // traces times all rules,
+constexpr int64_t kDirectTable = 40960;              // rules of one table,
+constexpr int64_t kDirectTableWork = int64_t(3) << 23;  // and traces times these
+constexpr int kDirectThreads = 256;                  // k_tr_direct's workgroup
 constexpr int kPortSlots = 64;  // forwarding ports whose moves a match workgroup counts in LDS
 
 // Bit k set iff slot k of trace t's watch list names switch s (K = 0: none).
@@ -135,12 +138,12 @@ struct __align__(32) SwInfo {
     int32_t pb;       // first port
     int32_t np;       // ports, -1 when the port range is invalid
     int32_t R;        // rules
-    int32_t indexed;  // 0: the switch has no chunk sets, its rules are matched one by one
+    int32_t pad;
 };
 
 __device__ __forceinline__ SwInfo make_info(int32_t s, const int32_t *__restrict__ port_off, int64_t n_ports,
                                             const int32_t *__restrict__ rule_off, int64_t n_rules, int32_t gofs,
-                                            uint32_t cpos, bool indexed)
+                                            uint32_t cpos)
 {
     const int64_t pb = port_off[s], pe = port_off[s + 1], rb = rule_off[s], re = rule_off[s + 1];
     const bool rok = pc_range_ok(rb, re, n_rules);
@@ -152,7 +155,7 @@ __device__ __forceinline__ SwInfo make_info(int32_t s, const int32_t *__restrict
     x.rb = rok ? static_cast<int32_t>(rb) : 0;
     x.pb = static_cast<int32_t>(pb);
     x.np = pc_range_ok(pb, pe, n_ports) ? static_cast<int32_t>(pe - pb) : -1;
-    x.indexed = indexed;
+    x.pad = 0;
     return x;
 }
 
@@ -178,7 +181,7 @@ __device__ __forceinline__ void port_infos(int64_t n_ports, const int32_t *__res
         if (p < n_ports) pinfo[p] = make_port(port_peer[p], S, jur);
         if (p < S) {
             const int32_t s = static_cast<int32_t>(p);
-            sinfo[s] = make_info(s, port_off, n_ports, rule_off, n_rules, gofs[s], cpos[s], true);
+            sinfo[s] = make_info(s, port_off, n_ports, rule_off, n_rules, gofs[s], cpos[s]);
         }
     }
 }
@@ -352,23 +355,68 @@ struct Infos {
     }
 };
 
+// The condition of a walk rule by rule on the longest table (word nullptr:
+// none): k_tr_direct sets *word to the call's number if a table has more than
+// most rules (so that nothing is cleared), and the walk ends at once then.  The
+// number and the answer go to the host as early as they are known: from k_tr_direct's
+// first workgroup, which looks at every table (early), else from the walk as it starts.
+struct Guard {
+    uint32_t *word;
+    uint32_t call;
+    int32_t most;
+    unsigned long long *host;  // call << 32 | (1: too long)
+    bool early;
+
+    __device__ __forceinline__ bool too_long(const int32_t *__restrict__ rule_off, int64_t n_rules, int32_t s) const
+    {
+        const int64_t rb = rule_off[s], re = rule_off[s + 1];
+        return word != nullptr && pc_range_ok(rb, re, n_rules) && re - rb > most;
+    }
+    __device__ __forceinline__ void tell(bool stop) const
+    {
+        __hip_atomic_store(host, static_cast<unsigned long long>(call) << 32 | (stop ? 1u : 0u), __ATOMIC_RELEASE,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+};
+
 // Small tables, whose rules a walk matches one by one: everything a trace
-// call prepares, in one launch (a workgroup per switch, the sweeps spread
-// over all of them).
-__global__ __launch_bounds__(64) void k_tr_direct(int32_t S, const int32_t *__restrict__ rule_off, int64_t n_rules,
-                                                  const pc_rule *__restrict__ rules, int64_t n_watch,
-                                                  const int32_t *__restrict__ watch, Infos inf)
+// call prepares, in one launch: a workgroup per switch, the sweeps of the ports and
+// the watch lists spread over these and further workgroups.  (A table that is too
+// long is swept by k_tr_prep.)
+__global__ __launch_bounds__(kDirectThreads) void k_tr_direct(int32_t S, const int32_t *__restrict__ rule_off,
+                                                              int64_t n_rules, const pc_rule *__restrict__ rules,
+                                                              int64_t n_watch, const int32_t *__restrict__ watch,
+                                                              Infos inf, Guard guard)
 {
     const int32_t s = blockIdx.x;
+    if (guard.early && s == 0) {
+        bool stop = false;
+        for (int32_t i = threadIdx.x; i < S; i += kDirectThreads) stop |= guard.too_long(rule_off, n_rules, i);
+        stop = __syncthreads_or(stop);
+        if (threadIdx.x == 0) {
+            if (stop) *guard.word = guard.call;
+            guard.tell(stop);
+        }
+    }
     uint32_t errs = 0;
     if (bad_ids(inf.n_ports, inf.port_peer, S) || bad_ids(n_watch, watch, S)) errs |= PC_DERR_SWITCH;
-    const int64_t rb = rule_off[s], re = rule_off[s + 1];
-    const bool rok = pc_range_ok(rb, re, n_rules);
-    if (inf.jur[s] >= 32) errs |= PC_DERR_JUR;
-    if (!rok || !pc_range_ok(inf.port_off[s], inf.port_off[s + 1], inf.n_ports)) errs |= PC_DERR_OFFSETS;
+    bool rok = false;
+    int64_t rb = 0, re = 0;
+    if (s < S) {
+        rb = rule_off[s];
+        re = rule_off[s + 1];
+        rok = pc_range_ok(rb, re, n_rules);
+        if (inf.jur[s] >= 32) errs |= PC_DERR_JUR;
+        if (!rok || !pc_range_ok(inf.port_off[s], inf.port_off[s + 1], inf.n_ports)) errs |= PC_DERR_OFFSETS;
+    }
     if (errs) atomicOr(inf.d_err, errs);
-    if (threadIdx.x == 0) inf.sinfo[s] = make_info(s, inf.port_off, inf.n_ports, rule_off, n_rules, 0, 0, false);
-    inf.ports(s, S, threadIdx.x, blockDim.x);
+    if (s >= S) return;
+    if (guard.too_long(rule_off, n_rules, s)) {
+        if (!guard.early && threadIdx.x == 0) *guard.word = guard.call;
+        return;
+    }
+    if (threadIdx.x == 0) inf.sinfo[s] = make_info(s, inf.port_off, inf.n_ports, rule_off, n_rules, 0, 0);
+    inf.ports(s, S, threadIdx.x, kDirectThreads);
     if (rok) inf.sweep_actions(s, rules + rb, re - rb);
 }
 
@@ -439,7 +487,7 @@ __global__ __launch_bounds__(256) void k_tr_choose(int32_t S, const int32_t *__r
     if (n == 0) {
         cpos[s] = cp;
         if (inf.sinfo != nullptr)
-            inf.sinfo[s] = make_info(s, inf.port_off, inf.n_ports, rule_off, n_rules, inf.gofs[s], cp, true);
+            inf.sinfo[s] = make_info(s, inf.port_off, inf.n_ports, rule_off, n_rules, inf.gofs[s], cp);
     }
 }
 
@@ -1615,11 +1663,12 @@ struct WalkArgs {
 // One workgroup walks trace t (header h) from switch s to its end, filtering
 // each switch's rule groups with only the kChunks chunk-set words its
 // header selects (coalesced over groups) and reducing the first match in
-// LDS; the rules of a switch without chunk sets are matched one per lane.
+// LDS; without chunk sets (kDirect) the rules are matched one per lane.
 // Bound by the latency of a hop: the switch's record, its ports
 // together with the chunk-set words of two groups per lane, the survivors'
 // rules.  Where 5,200 of 500,009 traces loop until a TTL of 32, 329 us with a hop
 // per link, now 46; 6,001 traces over 777 rules per switch 54 us, now 22.
+template <bool kDirect>
 __device__ __forceinline__ void walk_trace(const WalkArgs &w, unsigned long long *best, int32_t t, const pc_key &h,
                                            int32_t s, uint32_t jm, uint32_t vis, uint64_t vs, int32_t hops)
 {
@@ -1639,7 +1688,7 @@ __device__ __forceinline__ void walk_trace(const WalkArgs &w, unsigned long long
         const pc_rule *rs = w.rules + si.rb;
         // this lane's of the switch's first 64 ports
         const int2 port_lane = lane < si.np ? w.pinfo[si.pb + lane] : make_int2(-2, 0);
-        if (si.indexed) {
+        if constexpr (!kDirect) {
             const uint32_t *fs = w.filt + static_cast<int64_t>(si.gofs) * kPlaneWords;
             int64_t row[kChunks];
 #pragma unroll
@@ -1658,9 +1707,22 @@ __device__ __forceinline__ void walk_trace(const WalkArgs &w, unsigned long long
                     verify_group(surv2, rs + static_cast<int64_t>(g2) * 32, static_cast<uint32_t>(g2) * 32, h, best);
             }
         } else {
-            for (int32_t r = threadIdx.x; r < si.R; r += blockDim.x)
-                if (rule_matches(rs + r, h.w[0], h.w[1], h.w[2], h.w[3]))
-                    atomicMin(best, static_cast<unsigned long long>(rule_key(rs + r, static_cast<uint32_t>(r))));
+            // four rules of a longer table in flight per lane
+            constexpr int kAhead = 4;
+            const int32_t step = static_cast<int32_t>(blockDim.x);
+            auto check = [&](int32_t r, bool hit) {
+                if (hit) atomicMin(best, static_cast<unsigned long long>(rule_key(rs + r, static_cast<uint32_t>(r))));
+            };
+            auto matches = [&](int32_t r) { return rule_matches(rs + r, h.w[0], h.w[1], h.w[2], h.w[3]); };
+            int32_t r = threadIdx.x;
+            for (int32_t left = si.R; left >= kAhead * step; left -= kAhead * step, r += kAhead * step) {
+                bool hit[kAhead];
+#pragma unroll
+                for (int k = 0; k < kAhead; ++k) hit[k] = matches(r + k * step);
+#pragma unroll
+                for (int k = 0; k < kAhead; ++k) check(r + k * step, hit[k]);
+            }
+            for (; r < si.R; r += step) check(r, matches(r));
         }
         __syncthreads();
         const uint64_t key = *best;
@@ -1722,20 +1784,27 @@ __global__ __launch_bounds__(256) void k_tr_walk(WalkArgs w, const LRec *__restr
         while (flying) {
             const LRec e = live[i0 + __builtin_ctzll(flying) * grid];
             flying &= flying - 1;
-            walk_trace(w, &best, e.t, e.key, __builtin_amdgcn_readfirstlane(e.next), e.jm, w.visit ? w.visit[e.t] : 0u,
-                       w.vsum ? w.vsum[e.t] : 0ull, hops0);
+            walk_trace<false>(w, &best, e.t, e.key, __builtin_amdgcn_readfirstlane(e.next), e.jm, w.visit ? w.visit[e.t] : 0u,
+                              w.vsum ? w.vsum[e.t] : 0ull, hops0);
         }
     }
 }
 
 // Few traces: every one (or those of a list) from its ingress (an invalid
-// ingress ends it at once as MISS), without levels or counts.
+// ingress ends it at once as MISS), without levels or counts.  None if the
+// guard found a table too long.
+template <bool kDirect>
 __global__ __launch_bounds__(256) void k_tr_walk_all(WalkArgs w, int32_t T, const pc_key *__restrict__ hdr,
                                                      const int32_t *__restrict__ ingress,
                                                      const uint8_t *__restrict__ jur, uint32_t *__restrict__ d_err,
-                                                     const int32_t *__restrict__ list)
+                                                     const int32_t *__restrict__ list, Guard guard)
 {
     __shared__ unsigned long long best;
+    if (guard.word != nullptr) {
+        const bool stop = *guard.word == guard.call;
+        if (!guard.early && blockIdx.x == 0 && threadIdx.x == 0) guard.tell(stop);
+        if (stop) return;
+    }
     for (int32_t i = blockIdx.x; i < T; i += gridDim.x) {
         const int32_t t = list != nullptr ? list[i] : i;
         const int32_t s = __builtin_amdgcn_readfirstlane(ingress[t]);
@@ -1743,8 +1812,8 @@ __global__ __launch_bounds__(256) void k_tr_walk_all(WalkArgs w, int32_t T, cons
         if (w.walk && threadIdx.x < kWalkSlots)
             w.walk[static_cast<int64_t>(t) * kWalkSlots + threadIdx.x] = in && threadIdx.x == 0 ? s : -1;
         if (in) {
-            walk_trace(w, &best, t, hdr[t], s, jur_bit(jur, s), w.visit ? watch_bits(w.watch, w.K, t, s) : 0u,
-                       sum_bit(s), 0);
+            walk_trace<kDirect>(w, &best, t, hdr[t], s, jur_bit(jur, s), w.visit ? watch_bits(w.watch, w.K, t, s) : 0u,
+                                sum_bit(s), 0);
         } else if (threadIdx.x == 0) {
             write_out(w.out, t, 0, s, PC_NO_PORT, 0, PC_MISS);
             if (w.visit) w.visit[t] = 0;
@@ -2032,6 +2101,23 @@ int layout(pc_ctx *ctx, int32_t S, const int32_t *port_off, int64_t n_ports, con
     return PC_OK;
 }
 
+// Waits for the guard's answer: the host goes on as the walk starts (waiting for
+// its end takes 25 us a call).  Ends at the latest with the stream's work.
+int wait_guard(pc_ctx *ctx, const Guard &g, hipStream_t stream, bool *too_long)
+{
+    for (unsigned n = 1;; ++n) {
+        // (seldom: a query puts a marker into the stream)
+        const bool over = n % (1u << 20) == 0 && hipStreamQuery(stream) != hipErrorNotReady;
+        const unsigned long long x = __atomic_load_n(g.host, __ATOMIC_ACQUIRE);
+        *too_long = x & 1;
+        if (x >> 32 == g.call) return PC_OK;
+        if (over) {
+            PC_HIP(ctx, hipStreamSynchronize(stream));
+            return pc_set_error(ctx, PC_EDEVICE, "pc_trace_flows: no word from the device");
+        }
+    }
+}
+
 }  // namespace
 
 int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *port_peer, int64_t n_ports,
@@ -2060,12 +2146,22 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
     // rule: 1,000 traces over 16 rules per switch 46 / 23 us (k = 16), 4,000
     // over 1,024 rules 61 / 55, 60,000 over 64 rules 145 / 68, 16,000 over 256
     // rules 89 / 54; past the limit 16,000 over 512 rules 93 / 100, over 1,024
-    // 96 / 189.  The host knows no single table's size: the third bound holds
-    // the cost down where one switch has all the rules (67 million matches,
-    // about 0.1 ms a hop).
-    const bool direct = pre == nullptr && !levels && S > 0 && n_rules <= static_cast<int64_t>(kDirectRules) * S &&
-                        static_cast<int64_t>(T) * (n_rules / S + 1) <= kDirectWork &&
-                        static_cast<int64_t>(T) * n_rules <= kDirectWorst;
+    // 96 / 189.
+    bool direct = pre == nullptr && !levels && S > 0 && (T > 0 || n_rules <= kDirectTable) &&
+                  n_rules <= static_cast<int64_t>(kDirectRules) * S &&
+                  static_cast<int64_t>(T) * (n_rules / S + 1) <= kDirectWork &&
+                  static_cast<int64_t>(T) * n_rules <= kDirectWorst;
+    // The host knows the mean table only, and a wavefront takes a hop's rules in
+    // turn: where one table could hold too many, the preparation looks for such a
+    // table, the walk goes on only if there is none, and the host waits for the
+    // answer to see whether the call needs chunk sets after all.  All but 16 rules a switch
+    // (k = 16) in the table that every trace enters, rule by rule / found too long:
+    // 16,384 rules, one trace 29 / 48 us, 1,000 traces 45 / 57; 55,000, one trace
+    // 70 / 49, 1,000 traces 110 / 58; 262,144, one trace 1,989 (the table's
+    // actions swept by one wavefront too) / 69.  Asking costs 0-4 us: 3,000 traces
+    // over 64 rules a switch (k = 16) 15 / 17, 500 over 100 (k = 32) 13 / 17.
+    const int64_t longest = std::min(kDirectTable, kDirectTableWork / std::max(T, 1));
+    const bool guarded = direct && n_rules > longest;
     // work items of a level: at most T / kItemMin + S (see the match launch)
     const int32_t icap = static_cast<int32_t>(std::min<int64_t>(static_cast<int64_t>(T) / kItemMin + S + 1, INT32_MAX));
     auto carve = [&](Carver &c) {
@@ -2088,16 +2184,57 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         B.bucket = c.take<BRec>(T + 1);
         B.imap = c.take<int2>(static_cast<size_t>(icap));
     };
-    Carver dry{nullptr, 0};
-    carve(dry);
-    int rc = pc_ensure_arena(ctx, dry.off);
+    auto reserve = [&]() -> int {
+        Carver dry{nullptr, 0};
+        carve(dry);
+        const int rc = pc_ensure_arena(ctx, dry.off);
+        Carver real{ctx->arena, 0};
+        if (rc == PC_OK) carve(real);
+        return rc;
+    };
+    int rc = reserve();
     if (rc) return rc;
-    Carver real{ctx->arena, 0};
-    carve(real);
     if (!visit) K = 0;
     const int64_t n_watch = static_cast<int64_t>(T) * K;
     Infos inf{B.sinfo, B.pinfo, port_off, port_peer, n_ports, jur, nullptr, ctx->d_err};
     B.filt = nullptr;
+    auto walk_args = [&]() { return WalkArgs{S, B.sinfo, B.pinfo, rules, B.filt, ttl, out, watch, K, visit, vsum, walk}; };
+    auto walk_all = [&](int threads, const Guard &guard) -> int {
+        PC_TIMED(ctx, "k_tr_walk", stream,
+                 hipLaunchKernelGGL(direct ? k_tr_walk_all<true> : k_tr_walk_all<false>,
+                                    dim3(static_cast<unsigned>(std::min(T, 8192))), dim3(threads), 0, stream, walk_args(), T, hdr, ingress, jur, ctx->d_err, nullptr, guard));
+        PC_LAUNCH_CHECK(ctx);
+        return PC_OK;
+    };
+
+    // ---- rule by rule
+    if (direct) {
+        Guard guard{};
+        if (guarded) {
+            ctx->direct_call = ctx->direct_call == UINT32_MAX ? 1 : ctx->direct_call + 1;
+            guard = Guard{reinterpret_cast<uint32_t *>(ctx->d_small + 8), ctx->direct_call,
+                          static_cast<int32_t>(longest), reinterpret_cast<unsigned long long *>(ctx->h_small + 16),
+                          S <= kLayoutS};
+            *guard.host = 0;  // (the last guarded call's has been read)
+        }
+        const int64_t sweep = (std::max(n_ports, n_watch) + 4 * kDirectThreads - 1) / (4 * kDirectThreads);
+        const int64_t blocks = std::max<int64_t>(S, std::min<int64_t>(sweep, 1024));
+        PC_TIMED(ctx, "k_tr_direct", stream,
+                 hipLaunchKernelGGL(k_tr_direct, dim3(static_cast<unsigned>(blocks)), dim3(kDirectThreads), 0, stream, S,
+                                    rule_off, n_rules, rules, n_watch, watch, inf, guard));
+        PC_LAUNCH_CHECK(ctx);
+        if (T == 0) return PC_OK;
+        rc = walk_all(64, guard);
+        if (rc || !guarded) return rc;
+        bool too_long = false;
+        rc = wait_guard(ctx, guard, stream, &too_long);
+        if (rc || !too_long) return rc;
+        direct = false;
+        rc = reserve();
+        if (rc) return rc;
+        inf.sinfo = B.sinfo;
+        inf.pinfo = B.pinfo;
+    }
 
     // ---- prep: per-switch sizes, offsets, chunk sets, data-error sweep
     // (done by the caller when it passes prepared tables)
@@ -2115,11 +2252,6 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
             PC_TIMED(ctx, "k_tr_sweep", stream,
                      hipLaunchKernelGGL(k_tr_sweep, dim3(256), dim3(256), 0, stream, int64_t(0), nullptr, S, n_watch,
                                         watch, nullptr, 0, nullptr, ctx->d_err));
-        PC_LAUNCH_CHECK(ctx);
-    } else if (direct) {
-        PC_TIMED(ctx, "k_tr_direct", stream,
-                 hipLaunchKernelGGL(k_tr_direct, dim3(static_cast<unsigned>(S)), dim3(64), 0, stream, S, rule_off,
-                                    n_rules, rules, n_watch, watch, inf));
         PC_LAUNCH_CHECK(ctx);
     } else if (S > 0) {
         rc = layout(ctx, S, port_off, n_ports, jur, rule_off, n_rules, B.gcount, B.bcount, B.gofs, B.bofs, B.hh, stream);
@@ -2149,15 +2281,8 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         }
     }
     if (T == 0) return PC_OK;
-    const WalkArgs wa{S, B.sinfo, B.pinfo, rules, B.filt, ttl, out, watch, K, visit, vsum, walk};
-    if (!levels) {
-        PC_TIMED(ctx, "k_tr_walk", stream,
-                 hipLaunchKernelGGL(k_tr_walk_all, dim3(static_cast<unsigned>(std::min(T, 8192))),
-                                    dim3(direct ? 64 : walk_threads), 0, stream, wa, T, hdr, ingress, jur, ctx->d_err,
-                                    nullptr));
-        PC_LAUNCH_CHECK(ctx);
-        return PC_OK;
-    }
+    if (!levels) return walk_all(walk_threads, Guard{});
+    const WalkArgs wa = walk_args();
 
     // ---- level-synchronous walk
     int32_t *d_n = ctx->d_small;  // [0], [1]: live counts of the two live lists ([4], [5]: the reach kernels')
@@ -2425,8 +2550,8 @@ int run_trace_delta(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32
         const WalkArgs wa{S, sinfo, pinfo, rules, reinterpret_cast<const uint32_t *>(ctx->tc_filt), ttl, out, nullptr,
                           0, nullptr, vsum, walk};
         PC_TIMED(ctx, "k_tr_walk", stream,
-                 hipLaunchKernelGGL(k_tr_walk_all, dim3(static_cast<unsigned>(std::min(n, 8192))), dim3(rule.threads),
-                                    0, stream, wa, n, hdr, ingress, jur, ctx->d_err, list));
+                 hipLaunchKernelGGL(k_tr_walk_all<false>, dim3(static_cast<unsigned>(std::min(n, 8192))), dim3(rule.threads),
+                                    0, stream, wa, n, hdr, ingress, jur, ctx->d_err, list, Guard{}));
         PC_LAUNCH_CHECK(ctx);
         return PC_OK;
     }

@@ -484,3 +484,120 @@ def test_reach_target_degrees(g, orc, deg):
     dg = g.reach_via(V, off, adj, region, src, allowed, target, none, forbid)
     do, _ = orc.reach_via(V, off, adj, region, src, allowed, target, none, forbid)
     _same(dg, do, "reach_via")
+
+
+def _with_hub(wl, rules, n, rng):
+    """wl with n rules at its switch 0: its own first, then exact ones that match no header drawn."""
+    off = wl["rule_off"].astype(np.int64)
+    more = np.zeros(n - (off[1] - off[0]), synth.RULE_DT)
+    more["value"] = synth.random_keys(rng, more.shape[0])
+    more["mask"] = np.array([0xFFFFFFFF] * 3 + [0xFF], np.uint32)
+    more["priority"] = rng.integers(0, 65536, more.shape[0])
+    off[1:] += more.shape[0]
+    return off.astype(np.int32), np.concatenate([rules[:wl["rule_off"][1]], more, rules[wl["rule_off"][1]:]])
+
+
+@pytest.mark.parametrize("total,T,indexed", [(16_384, 100, False), (30_269, 1000, False), (30_270, 1000, True), (46_064, 1, False),
+                                             (46_065, 1, True), (200_001, 1, True), (262_144, 100, True)])
+@pytest.mark.parametrize("bad", [False, True])
+def test_trace_one_long_table(g, orc, total, T, indexed, bad):
+    """Nearly all rules on the switch where every trace enters (16 on each of the 319 others).  Rule by rule, a wavefront
+    takes 2 ms for the sweep and one hop through 262,144 of them: past 40,960 rules in a table, or 25 million by traces, the
+    call forms chunk sets after all."""
+    import torch
+    import paper_2602_16100_amd as pc
+    rng = np.random.default_rng(total)
+    wl = synth.trace_workload(3, 16, 4, 16, T, 16, 50)
+    S = wl["S"]
+    off, rules = _with_hub(wl, wl["rules"], total - 16 * (S - 1), rng)
+    ingress = np.zeros(T, np.int32)
+    watch = rng.integers(-1, S, (T, 32)).astype(np.int32)
+    if bad:
+        rules["action"][off[1] - 5] = 3000
+        watch[-1, -1] = S
+    assert rules.shape[0] == total
+    a = (S, wl["port_off"], wl["port_peer"], wl["jur"], off, rules, wl["hdr"], ingress, 16)
+    d = [x if isinstance(x, int) else g.dev(np.ascontiguousarray(x)) for x in a]
+    ctx = pc.context()
+    ctx.data_errors(clear=True)
+    for timed in (False, True):
+        ctx.profile(True)
+        out, visit = pc.pc_trace_flows_watch(*d, g.dev(watch))
+        torch.cuda.synchronize()
+        used = ctx.profile_read()
+    ctx.profile(False)
+    flags = ctx.data_errors(clear=True)
+    to, vo, err = orc.trace(*a, watch=watch)
+    _same_traces(pc.records(out, pc.TRACE_OUT_DT), to)
+    _same(visit.cpu().numpy().view(np.uint32), vo, "visit")
+    assert flags == err
+    assert "k_tr_direct" in used and ("k_tr_prep" in used) == indexed
+    assert sum(ms for _, ms in used.values()) < 0.5, used
+
+
+@pytest.mark.parametrize("S,total,T,indexed", [(16_390, 57_349, 600, False), (16_390, 57_350, 600, True),
+                                               (16_384, 57_343, 0, True), (16_384, 40_960, 0, False)])
+def test_trace_one_long_table_of_many_switches(g, orc, S, total, T, indexed):
+    """A rule a switch and one long table, on a ring of more switches than one workgroup looks over; and only the
+    sweeps (no traces)."""
+    import paper_2602_16100_amd as pc
+    rng = np.random.default_rng(total)
+    off = np.arange(S + 1, dtype=np.int32)
+    peer = np.roll(np.arange(S, dtype=np.int32), -1)
+    peer[100::1000] = -1
+    more_off, rules = _with_hub(dict(rule_off=off), np.zeros(S, synth.RULE_DT), total - S + 1, rng)
+    rules["action"][-3] = 7
+    ingress = np.minimum(rng.integers(0, 2 * S, T), S - 1).astype(np.int32)
+    ingress[::2] = 0
+    a = (S, off, peer, (np.arange(S) % 31).astype(np.uint8), more_off, rules, synth.random_keys(rng, T), ingress, 60)
+    ctx = pc.context()
+    for _ in range(3):
+        ctx.data_errors(clear=True)
+        ctx.profile(True)
+        got = g.trace(*a)
+        used = ctx.profile_read()
+        ctx.profile(False)
+        assert ("k_tr_prep" in used) == indexed
+        to, err = orc.trace(*a)
+        _same_traces(got, to)
+        assert ctx.data_errors(clear=True) == err
+
+
+@pytest.mark.parametrize("k,R,T", [(24, 200, 400), (32, 100, 500)])
+def test_trace_many_small_tables(g, orc, k, R, T):
+    """As many rules in all, but none of the tables long: rule by rule, no chunk sets."""
+    import paper_2602_16100_amd as pc
+    wl = synth.trace_workload(R, k, 4, R, T, 16, 50)
+    a = (wl["S"], wl["port_off"], wl["port_peer"], wl["jur"], wl["rule_off"], wl["rules"], wl["hdr"], wl["ingress"], 16)
+    ctx = pc.context()
+    ctx.profile(True)
+    got = g.trace(*a)
+    used = ctx.profile_read()
+    ctx.profile(False)
+    assert set(used) == {"k_tr_direct", "k_tr_walk"}, used
+    _same_traces(got, orc.trace(*a)[0])
+
+
+@pytest.mark.parametrize("bad", [False, True])
+def test_trace_long_watch_lists(g, orc, bad):
+    """Two million watched ids over 20 switches of small tables: the sweep has workgroups of its own."""
+    import paper_2602_16100_amd as pc
+    rng = np.random.default_rng(2)
+    wl = synth.trace_workload(4, 4, 4, 16, 60_000, 16, 500)
+    watch = rng.integers(-1, wl["S"], (60_000, 32)).astype(np.int32)
+    if bad:
+        watch[-1, -1] = wl["S"]
+    a = (wl["S"], wl["port_off"], wl["port_peer"], wl["jur"], wl["rule_off"], wl["rules"], wl["hdr"], wl["ingress"], 16)
+    ctx = pc.context()
+    g.trace_watch(*a, watch)
+    ctx.data_errors(clear=True)
+    ctx.profile(True)
+    tg, vg = g.trace_watch(*a, watch)
+    used = ctx.profile_read()
+    ctx.profile(False)
+    flags = ctx.data_errors(clear=True)
+    to, vo, err = orc.trace(*a, watch=watch)
+    _same_traces(tg, to)
+    _same(vg, vo, "visit")
+    assert flags == err
+    assert used["k_tr_direct"][1] < 0.1, used
