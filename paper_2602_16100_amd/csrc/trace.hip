@@ -109,13 +109,15 @@ __device__ __forceinline__ uint32_t jur_bit(const uint8_t *jur, int32_t s)
     return j < 32 ? (1u << j) : 0u;
 }
 
-// Per switch: validate offsets / jurisdiction, count 32-rule groups and prep blocks.
+// Per switch: validate offsets / jurisdiction, count 32-rule groups and prep
+// blocks; *largest (cleared): the groups of the largest table.
 __global__ void k_tr_switch_info(int32_t S, const int32_t *__restrict__ port_off, int64_t n_ports,
                                  const uint8_t *__restrict__ jur, const int32_t *__restrict__ rule_off,
                                  int64_t n_rules, int32_t *__restrict__ gcount, int32_t *__restrict__ bcount,
-                                 uint32_t *__restrict__ d_err)
+                                 int32_t *__restrict__ largest, uint32_t *__restrict__ d_err)
 {
     uint32_t errs = 0;
+    int32_t most = 0;
     for (int32_t s = blockIdx.x * blockDim.x + threadIdx.x; s < S; s += gridDim.x * blockDim.x) {
         if (jur[s] >= 32) errs |= PC_DERR_JUR;
         const bool pok = pc_range_ok(port_off[s], port_off[s + 1], n_ports);
@@ -125,8 +127,12 @@ __global__ void k_tr_switch_info(int32_t S, const int32_t *__restrict__ port_off
         const int64_t g = rok ? (re - rb + 31) / 32 : 0;
         gcount[s] = static_cast<int32_t>(g);
         bcount[s] = static_cast<int32_t>((g + kPrepGroups - 1) / kPrepGroups);
+        most = max(most, static_cast<int32_t>(g));
     }
     if (errs) atomicOr(d_err, errs);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) most = max(most, __shfl_xor(most, off, 64));
+    if ((threadIdx.x & 63) == 0 && most > 0) atomicMax(largest, most);
 }
 
 // What a lookup at a switch starts from, in one 32-byte record.
@@ -212,6 +218,7 @@ __device__ __forceinline__ bool bad_ids(int64_t n, const int32_t *__restrict__ i
 // kHeaderSample headers: hh[n][x] = sampled headers whose nibble n is x.
 // hh must be zero on entry.
 constexpr int kHeaderSample = 65536;
+constexpr size_t kHistWords = kKeyNibbles * 16 + 1;  // and the groups of the largest table (layout)
 __global__ __launch_bounds__(256) void k_tr_sweep(int64_t n_ports, const int32_t *__restrict__ port_peer, int32_t S,
                                                   int64_t n_watch, const int32_t *__restrict__ watch,
                                                   const pc_key *__restrict__ hdr, int32_t T,
@@ -238,7 +245,7 @@ __global__ __launch_bounds__(256) void k_tr_sweep(int64_t n_ports, const int32_t
 // Per switch the group count and the exclusive scans of group counts
 // (gofs) and prep blocks (bofs), their totals at [S]; offsets and
 // jurisdictions validated; the header histogram cleared for k_tr_sweep; the
-// totals also to host memory.  One workgroup: with the separate kernels, three
+// totals and the groups of the largest table to host memory.  One workgroup: with the separate kernels, three
 // launches, a clear and two copies.
 constexpr int32_t kLayoutS = 16384;  // switches at most
 __global__ __launch_bounds__(1024) void k_tr_layout(int32_t S, const int32_t *__restrict__ port_off, int64_t n_ports,
@@ -250,12 +257,14 @@ __global__ __launch_bounds__(1024) void k_tr_layout(int32_t S, const int32_t *__
 {
     constexpr int kPer = 4;  // consecutive switches per thread and pass
     __shared__ int32_t wsum[2][16];
-    __shared__ int32_t carry_s[2];
+    __shared__ int32_t carry_s[2], most_s;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     if (tid < 2) carry_s[tid] = 0;
+    if (tid == 2) most_s = 0;
     for (int i = tid; i < kKeyNibbles * 16; i += 1024) hh[i] = 0;
     __syncthreads();
     uint32_t errs = 0;
+    int32_t most = 0;
     for (int32_t base = 0; base < S; base += 1024 * kPer) {
         const int32_t i0 = base + tid * kPer;
         int32_t g[kPer], b[kPer];
@@ -274,6 +283,7 @@ __global__ __launch_bounds__(1024) void k_tr_layout(int32_t S, const int32_t *__
             gcount[s] = g[k];
             s0 += g[k];
             s1 += b[k];
+            most = max(most, g[k]);
         }
         int32_t x0 = s0, x1 = s1;
 #pragma unroll
@@ -313,11 +323,16 @@ __global__ __launch_bounds__(1024) void k_tr_layout(int32_t S, const int32_t *__
         if (tid < 2) carry_s[tid] += wsum[tid][15];
         __syncthreads();
     }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) most = max(most, __shfl_xor(most, off, 64));
+    if (lane == 0) atomicMax(&most_s, most);
+    __syncthreads();
     if (tid == 0) {
         gofs[S] = carry_s[0];
         bofs[S] = carry_s[1];
         host[0] = carry_s[0];
         host[1] = carry_s[1];
+        host[2] = most_s;
         __threadfence_system();
     }
     if (errs) atomicOr(d_err, errs);
@@ -2013,15 +2028,25 @@ __global__ __launch_bounds__(256) void k_delta_scatter(const int32_t *__restrict
 // Calls that walk from the start / from 8,192 traces on: 60,000 traces over
 // 512 rules per switch (k = 16) 231 / 258 us, over 2,048 (k = 32) 275 / 302,
 // over 32,768 (k = 16) 908 / 835, 30,000 traces there 527 / 803; 4,194,304
-// traces, of which 8,900 loop until their TTL, 2.4 / 3.2 ms.
+// traces, of which 8,900 loop until their TTL, 2.4 / 3.2 ms; 30,000 over 500,000
+// (k = 4) 4.9 / 7.8 ms.
+// Nor may the walks' passes over the largest table exceed what levels, which read
+// it once per some hundred lookups, take at their worst: one switch with nearly all
+// rules, where every trace enters (half, a fifth of them): 60,000 traces, a million
+// rules 1.8 / 1.6 ms (a tenth: 0.5 / 3.2); past the limit 65,536, two million 4.5 /
+// 3.7; 30,000, four million 7.0 / 6.4; 65,536 there 6.6 / 7.3 (9.5 / 10.9, 3.8 /
+// 11.1); 65,536, ten million 42 / 18.
+constexpr int64_t kWalkLeast = 8192;
+constexpr int64_t kWalkGroups = int64_t(1) << 31;  // traces times the groups of the largest table
 struct WalkRule {
     int64_t most;  // traces at most
     int threads;   // the walks' workgroup: about two rule groups per lane of a mean table
 };
 
-WalkRule walk_rule(int64_t mean_groups)
+WalkRule walk_rule(int64_t mean_groups, int64_t largest)
 {
     WalkRule r{mean_groups <= 128 ? 65536 : 32768, mean_groups <= 128 ? 64 : mean_groups <= 256 ? 128 : 256};
+    r.most = std::max(std::min(r.most, kWalkGroups / std::max<int64_t>(largest, 1)), kWalkLeast);
     if (const char *env = getenv("PC_TRACE_WALK_MAX")) r.most = atoll(env);
     return r;
 }
@@ -2077,8 +2102,8 @@ int sweep_and_choose(pc_ctx *ctx, int32_t S, const int32_t *port_peer, int64_t n
 }
 
 // Group counts and offsets, prep-block offsets (bcount: scratch of the form
-// for many switches) and the zeroed header histogram; the two totals in
-// ctx->h_small[0], [1] once the stream has come so far.
+// for many switches) and the zeroed header histogram; the two totals and the groups
+// of the largest table in ctx->h_small[0..2] once the stream has come so far.
 int layout(pc_ctx *ctx, int32_t S, const int32_t *port_off, int64_t n_ports, const uint8_t *jur,
            const int32_t *rule_off, int64_t n_rules, int32_t *gcount, int32_t *bcount, int32_t *gofs, int32_t *bofs,
            uint32_t *hh, hipStream_t stream)
@@ -2088,12 +2113,14 @@ int layout(pc_ctx *ctx, int32_t S, const int32_t *port_off, int64_t n_ports, con
                  hipLaunchKernelGGL(k_tr_layout, dim3(1), dim3(1024), 0, stream, S, port_off, n_ports, jur, rule_off,
                                     n_rules, gcount, gofs, bofs, hh, ctx->h_small, ctx->d_err));
     } else {
+        int32_t *largest = reinterpret_cast<int32_t *>(hh + kKeyNibbles * 16);
+        launch_fill_u32(hh, kHistWords, 0, stream);
         PC_TIMED(ctx, "k_tr_switch_info", stream,
                  hipLaunchKernelGGL(k_tr_switch_info, dim3(grid_for(S, 256)), dim3(256), 0, stream, S, port_off,
-                                    n_ports, jur, rule_off, n_rules, gcount, bcount, ctx->d_err));
+                                    n_ports, jur, rule_off, n_rules, gcount, bcount, largest, ctx->d_err));
         launch_scan_i32(gcount, S, gofs, nullptr, nullptr, stream);
         launch_scan_i32(bcount, S, bofs, nullptr, nullptr, stream);
-        launch_fill_u32(hh, kKeyNibbles * 16, 0, stream);
+        PC_HIP(ctx, hipMemcpyAsync(ctx->h_small + 2, largest, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
         PC_HIP(ctx, hipMemcpyAsync(ctx->h_small, gofs + S, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
         PC_HIP(ctx, hipMemcpyAsync(ctx->h_small + 1, bofs + S, sizeof(int32_t), hipMemcpyDeviceToHost, stream));
     }
@@ -2136,11 +2163,10 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         uint16_t *prio;
     } B;
     const int64_t mean_groups = S > 0 ? (pre != nullptr ? pre->groups : (n_rules + 31) / 32) / S : 0;
-    const WalkRule rule = walk_rule(mean_groups);
-    const int walk_threads = rule.threads;
-    const int64_t walk_max = rule.most;
-    const bool levels = T > walk_max;
-    const bool ranked = levels && !wide_level(T, S, mean_groups);  // (levels only shrink)
+    // (until the largest table is known, the rule without it)
+    WalkRule rule = walk_rule(mean_groups, pre != nullptr ? pre->largest : 0);
+    bool levels = T > rule.most;
+    const bool may_level = T > walk_rule(mean_groups, kWalkGroups).most;
     // Few enough traces over tables this small are matched rule by rule: no
     // chunk sets, no wait for their count, two launches.  Chunk sets / rule by
     // rule: 1,000 traces over 16 rules per switch 46 / 23 us (k = 16), 4,000
@@ -2169,12 +2195,12 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         B.sinfo = c.take<SwInfo>(static_cast<size_t>(S) + 1);
         if (direct) return;
         B.cpos = c.take<uint32_t>(S + 1);
-        B.hh = c.take<uint32_t>(kKeyNibbles * 16);
+        B.hh = c.take<uint32_t>(kHistWords);
         B.gcount = c.take<int32_t>(S + 1);
         B.bcount = c.take<int32_t>(S + 1);
         B.gofs = c.take<int32_t>(S + 1);
         B.bofs = c.take<int32_t>(S + 1);
-        if (!levels) return;
+        if (!may_level) return;
         B.counts0 = c.take<int32_t>(2 * static_cast<size_t>(S + 1) * kCountPad);
         B.counts1 = B.counts0 + static_cast<size_t>(S + 1) * kCountPad;
         B.boff = c.take<int32_t>(S + 1);
@@ -2269,6 +2295,9 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         const int64_t groups = ctx->h_small[0], prep_blocks = ctx->h_small[1];
         if (groups < 0 || prep_blocks < 0)
             return pc_set_error(ctx, PC_EINVAL, "pc_trace_flows: more than 2^31 rule groups");
+        rule = walk_rule(mean_groups, ctx->h_small[2]);
+        levels = T > rule.most;
+        const bool ranked = levels && !wide_level(T, S, mean_groups);  // (levels only shrink)
         rc = pc_ensure_aux(ctx, chunk_set_bytes(groups, ranked));
         if (rc) return rc;
         B.filt = reinterpret_cast<uint32_t *>(ctx->aux);
@@ -2281,7 +2310,7 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         }
     }
     if (T == 0) return PC_OK;
-    if (!levels) return walk_all(walk_threads, Guard{});
+    if (!levels) return walk_all(rule.threads, Guard{});
     const WalkArgs wa = walk_args();
 
     // ---- level-synchronous walk
@@ -2325,10 +2354,10 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         // the live list this level reads: from k_tr_init (as many entries as
         // traces in flight) or from the previous level's match
         const int32_t *len_cur = level == 0 ? n_cur : d_len + ((level - 1) & 1);
-        if (known <= walk_max) {
+        if (known <= rule.most) {
             const unsigned wb = static_cast<unsigned>(known < 8192 ? known : 8192);
             PC_TIMED(ctx, "k_tr_walk", stream,
-                     hipLaunchKernelGGL(k_tr_walk, dim3(wb), dim3(walk_threads), 0, stream, wa, live_cur, len_cur,
+                     hipLaunchKernelGGL(k_tr_walk, dim3(wb), dim3(rule.threads), 0, stream, wa, live_cur, len_cur,
                                         level));
             PC_LAUNCH_CHECK(ctx);
             break;
@@ -2393,11 +2422,11 @@ TcMeta tc_meta(pc_ctx *ctx, int32_t S)
     m.bofs = c.take<int32_t>(static_cast<size_t>(S) + 1);
     m.sw_bad = c.take<uint32_t>(static_cast<size_t>(S) + 1);
     m.cpos = c.take<uint32_t>(static_cast<size_t>(S) + 1);
-    m.hh = c.take<uint32_t>(kKeyNibbles * 16);
+    m.hh = c.take<uint32_t>(kHistWords);
     return m;
 }
 
-size_t tc_meta_bytes(int32_t S) { return 7 * (256 + (static_cast<size_t>(S) + 1) * 4) + kKeyNibbles * 16 * 4; }
+size_t tc_meta_bytes(int32_t S) { return 7 * (256 + (static_cast<size_t>(S) + 1) * 4) + kHistWords * 4; }
 
 // Prepare every switch's tables into the context's cache (and sweep them
 // for data errors); the cache then describes these tables.
@@ -2409,7 +2438,7 @@ int tc_prepare_all(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_
     int rc = pc_ensure_tc_meta(ctx, tc_meta_bytes(S));
     if (rc) return rc;
     const TcMeta m = tc_meta(ctx, S);
-    int64_t groups = 0, blocks = 0;
+    int64_t groups = 0, blocks = 0, largest = 0;
     if (S > 0) {
         rc = layout(ctx, S, port_off, n_ports, jur, rule_off, n_rules, m.gcount, m.bcount, m.gofs, m.bofs, m.hh, stream);
         if (rc) return rc;
@@ -2422,6 +2451,7 @@ int tc_prepare_all(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_
         PC_HIP(ctx, hipEventSynchronize(ctx->lvl_ev[0]));
         groups = ctx->h_small[0];
         blocks = ctx->h_small[1];
+        largest = ctx->h_small[2];
         if (groups < 0 || blocks < 0)
             return pc_set_error(ctx, PC_EINVAL, "pc_trace_flows_delta: more than 2^31 rule groups");
     }
@@ -2440,6 +2470,7 @@ int tc_prepare_all(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_
     ctx->tc_S = S;
     ctx->tc_groups = groups;
     ctx->tc_blocks = blocks;
+    ctx->tc_largest = largest;
     return PC_OK;
 }
 
@@ -2458,7 +2489,7 @@ int run_trace_delta(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32
         if (T == 0) return PC_OK;
         const TcMeta m = tc_meta(ctx, S);
         const TracePrep pre{reinterpret_cast<const uint32_t *>(ctx->tc_filt), m.gcount, m.gofs, m.cpos,
-                            ctx->tc_groups};
+                            ctx->tc_groups, ctx->tc_largest};
         return run_trace(ctx, S, port_off, port_peer, n_ports, jur, rule_off, rules, n_rules, hdr, ingress, T, ttl,
                          nullptr, 0, out, nullptr, vsum, walk, stream, &pre);
     }
@@ -2539,7 +2570,7 @@ int run_trace_delta(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32
     }
     if (n == 0) return PC_OK;
     const TcMeta m = tc_meta(ctx, S);
-    const WalkRule rule = walk_rule(S > 0 ? ctx->tc_groups / S : 0);
+    const WalkRule rule = walk_rule(S > 0 ? ctx->tc_groups / S : 0, ctx->tc_largest);
     if (n <= rule.most) {  // walked in place
         const int64_t n_info = std::max<int64_t>(n_ports, S);
         if (!serves && n_info > 0)
@@ -2559,7 +2590,7 @@ int run_trace_delta(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32
              hipLaunchKernelGGL(k_delta_gather, dim3(grid_for(n, 256)), dim3(256), 0, stream, list, n, hdr, ingress,
                                 hdr_c, ing_c));
     PC_LAUNCH_CHECK(ctx);
-    const TracePrep pre{reinterpret_cast<const uint32_t *>(ctx->tc_filt), m.gcount, m.gofs, m.cpos, ctx->tc_groups};
+    const TracePrep pre{reinterpret_cast<const uint32_t *>(ctx->tc_filt), m.gcount, m.gofs, m.cpos, ctx->tc_groups, ctx->tc_largest};
     rc = run_trace(ctx, S, port_off, port_peer, n_ports, jur, rule_off, rules, n_rules, hdr_c, ing_c, n, ttl, nullptr,
                    0, out_c, nullptr, vsum_c, walk ? walk_c : nullptr, stream, &pre);
     if (rc) return rc;

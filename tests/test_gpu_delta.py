@@ -317,3 +317,67 @@ def test_delta_forms(g, orc, monkeypatch, walk_max, ring):
             _same_records(rec, ro)
             assert np.array_equal(vs, vo) and np.array_equal(wk, wo) and flags == err | F_SWITCH
             assert n > 0
+
+
+@pytest.mark.parametrize("S,T,walks", [(320, 60_000, True), (320, 65_536, False), (16_390, 60_000, True), (16_390, 65_536, False)])
+def test_walk_limit_with_one_large_table(g, orc, monkeypatch, S, T, walks):
+    """1.1 million rules on the switch where every trace enters (34,376 groups of 32): 60,000 traces are walked, 65,536
+    (past 2^31 groups for all) go by levels; also when the switch's rules change, with the tables kept and anew."""
+    import torch
+    import paper_2602_16100_amd as pc
+    rng = np.random.default_rng(S + T)
+    n = 1_100_000
+    if S == 320:
+        wl = synth.trace_workload(3, 16, 4, 16, T, 12, 50)
+        port_off, peer, jur, off, rules = (wl[k] for k in ("port_off", "port_peer", "jur", "rule_off", "rules"))
+    else:
+        off = port_off = np.arange(S + 1, dtype=np.int32)
+        peer = np.roll(np.arange(S, dtype=np.int32), -1)
+        jur = (np.arange(S) % 31).astype(np.uint8)
+        rules = np.zeros(S, synth.RULE_DT)
+    own = off[1]
+    hub = np.zeros(n, synth.RULE_DT)
+    hub["value"], hub["mask"] = synth.random_keys(rng, n), np.array([0xFFFFFFFF] * 3 + [0xFF], np.uint32)
+    hub["priority"] = rng.integers(0, 65536, n)
+    hub["action"] = rng.integers(0, port_off[1], n)
+    hub[:own] = rules[:own]
+    off = off.copy()
+    off[1:] += n - own
+    rules = np.concatenate([hub, rules[own:]])
+    hdr = synth.random_keys(rng, T)
+    hdr[::2] = hub["value"][rng.integers(own, n, hdr[::2].shape[0])]
+    w = synth.Workload("hub", 0)
+    w.arrays.update(port_off=port_off, port_peer=peer, jur=jur, hdr=hdr, ingress=np.zeros(T, np.int32))
+    w.sizes.update(S=S, ttl=12)
+    ctx = pc.Context(0)
+    ctx.keep_tables(True)
+    some = np.sort(rng.choice(T, 40, replace=False))
+    new = rules.copy()
+    new["action"][:n] = (new["action"][:n] + 1) % port_off[1]
+
+    def call(r, *state, c=ctx):
+        c.profile(True)
+        out = _run(w, off, r, *state[:2], state[2] if len(state) > 2 else None, walk=state[3] if len(state) > 3 else None, ctx=c)
+        used = c.profile_read()
+        c.profile(False)
+        return out[:3], out[3], used
+
+    first, _, used = call(rules, None, None)
+    assert ("k_tr_plan" in used) != walks
+    whole = pc.records(pc.pc_trace_flows(S, *(g.dev(x) for x in (port_off, peer, jur, off, rules, hdr, w["ingress"])), 12), pc.TRACE_OUT_DT)
+    _same_records(whole, first[0])
+    monkeypatch.setenv("PC_TRACE_WALK_MAX", "0" if walks else str(10**9))
+    other, _, used = call(rules, None, None, c=pc.Context(0))
+    assert ("k_tr_plan" in used) == walks
+    for x, y in zip(first, other):
+        assert np.array_equal(x, y)
+    monkeypatch.delenv("PC_TRACE_WALK_MAX")
+    for c in (ctx, pc.Context(0)):
+        again, count, used = call(new, first[0], first[1], [0], first[2], c=c)
+        assert count == T and ("k_delta_gather" in used) != walks
+        ro, vo, wo, _ = _oracle(orc, w, off, new, idx=some)
+        _same_records(again[0][some], ro)
+        assert np.array_equal(again[1][some], vo) and np.array_equal(again[2][some], wo)
+    ro, vo, wo, _ = _oracle(orc, w, off, rules, idx=some)
+    _same_records(first[0][some], ro)
+    assert np.array_equal(first[1][some], vo) and np.array_equal(first[2][some], wo)
