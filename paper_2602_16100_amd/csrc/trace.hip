@@ -2224,6 +2224,7 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
     const int64_t n_watch = static_cast<int64_t>(T) * K;
     Infos inf{B.sinfo, B.pinfo, port_off, port_peer, n_ports, jur, nullptr, ctx->d_err};
     B.filt = nullptr;
+    B.prio = nullptr;
     auto walk_args = [&]() { return WalkArgs{S, B.sinfo, B.pinfo, rules, B.filt, ttl, out, watch, K, visit, vsum, walk}; };
     auto walk_all = [&](int threads, const Guard &guard) -> int {
         PC_TIMED(ctx, "k_tr_walk", stream,
@@ -2297,15 +2298,20 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
             return pc_set_error(ctx, PC_EINVAL, "pc_trace_flows: more than 2^31 rule groups");
         rule = walk_rule(mean_groups, ctx->h_small[2]);
         levels = T > rule.most;
-        const bool ranked = levels && !wide_level(T, S, mean_groups);  // (levels only shrink)
+        bool ranked = levels && !wide_level(T, S, mean_groups);  // (levels only shrink)
         rc = pc_ensure_aux(ctx, chunk_set_bytes(groups, ranked));
+        if (rc == PC_ENOMEM && ranked) {  // no room for the priorities: k_tr_match_wide needs none
+            ranked = false;
+            rc = pc_ensure_aux(ctx, chunk_set_bytes(groups, false));
+            if (rc == PC_OK) ctx->msg[0] = 0;
+        }
         if (rc) return rc;
         B.filt = reinterpret_cast<uint32_t *>(ctx->aux);
-        B.prio = priorities(ctx->aux, groups);
+        if (ranked) B.prio = priorities(ctx->aux, groups);
         if (prep_blocks > 0 && n_rules > 0) {
             PC_TIMED(ctx, "k_tr_prep", stream, hipLaunchKernelGGL(k_tr_prep, dim3(static_cast<unsigned>(prep_blocks)), dim3(kPrepWaves * 64), 0, stream, S,
                                port_off, n_ports, rule_off, rules, B.gcount, B.gofs, B.bofs, B.filt,
-                               ranked ? B.prio : nullptr, ctx->d_err, nullptr, B.cpos));
+                               B.prio, ctx->d_err, nullptr, B.cpos));
             PC_LAUNCH_CHECK(ctx);
         }
     }
@@ -2363,7 +2369,7 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
             break;
         }
         const int32_t nlive = static_cast<int32_t>(known);
-        const bool wide = wide_level(known, S, mean_groups);
+        const bool wide = B.prio == nullptr || wide_level(known, S, mean_groups);
         // Larger items read a table's sets less often, as long as there are enough
         // of them (192 / 256 / 384 lookups: a million over 320 tables of 1,024
         // rules 254 / 232 / 199 us, over 720 of 8,192 816 / 772 / 697).

@@ -601,3 +601,35 @@ def test_trace_long_watch_lists(g, orc, bad):
     _same(vg, vo, "visit")
     assert flags == err
     assert used["k_tr_direct"][1] < 0.1, used
+
+
+def test_priorities_refused(g, orc, monkeypatch):
+    """Where the auxiliary buffer holds the chunk sets but not the rules' priorities, levels of many lookups are
+    matched in registers."""
+    import paper_2602_16100_amd as pc
+    T, part = 100_000, np.arange(0, 100_000, 5000)
+    wl = synth.trace_workload(3, 24, 4, 3000, T, 12, 2000)
+    small = synth.trace_workload(3, 24, 4, 16, 8, 12, 8)
+    d = {k: g.dev(wl[k]) for k in ("port_off", "port_peer", "jur", "rule_off", "rules", "hdr", "ingress")}
+    ctx = pc.Context(0)
+
+    def run(n, rule_off, rules):
+        ctx.profile(True)
+        out = pc.records(pc.pc_trace_flows(wl["S"], d["port_off"], d["port_peer"], d["jur"], rule_off, rules, d["hdr"][:n],
+                                           d["ingress"][:n], 12, ctx=ctx), pc.TRACE_OUT_DT)
+        used = ctx.profile_read()
+        ctx.profile(False)
+        return out, used
+
+    run(T, g.dev(small["rule_off"]), g.dev(small["rules"]))  # the arena
+    run(8000, d["rule_off"], d["rules"])                     # the chunk sets, by walks
+    monkeypatch.setenv("PC_FAIL_ALLOC", "1")
+    refused, used = run(T, d["rule_off"], d["rules"])
+    assert "k_tr_match_wide" in used and "k_tr_match" not in used
+    monkeypatch.delenv("PC_FAIL_ALLOC")
+    normal, used = run(T, d["rule_off"], d["rules"])
+    assert "k_tr_match" in used
+    _same_traces(refused, normal)
+    to, _ = orc.trace(wl["S"], wl["port_off"], wl["port_peer"], wl["jur"], wl["rule_off"], wl["rules"], wl["hdr"],
+                      wl["ingress"], 12, idx=part)
+    _same_traces(refused[part], to)
