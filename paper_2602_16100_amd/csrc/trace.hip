@@ -2502,7 +2502,7 @@ int run_trace_delta(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32
     // compacted traces live in their own buffer: run_trace carves the arena
     const size_t Tn = static_cast<size_t>(T) + 1;
     const size_t words = (static_cast<size_t>(S) + 31) / 32 + 1;
-    const size_t need = 256 * 14 + words * 4 + 2 * (static_cast<size_t>(S) + 1) * 4 +
+    const size_t need = 256 * 9 + words * 4 +
                         Tn * (sizeof(int32_t) * 2 + sizeof(pc_key) + sizeof(pc_trace_out) + 8 + 4 * kWalkSlots);
     int rc = pc_ensure_delta(ctx, need);
     if (rc) return rc;

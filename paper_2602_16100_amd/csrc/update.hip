@@ -479,7 +479,7 @@ int run_update_nodes(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, c
     int64_t full_above = few ? kFewNodes : W / 32;
     if (const char *env = getenv("PC_UPDATE_FULL_ABOVE")) full_above = atoll(env);
     if (few && M <= full_above) {
-        PC_TIMED(ctx, "k_upd_rows", stream,
+        PC_TIMED(ctx, "k_upd_few", stream,
                  hipLaunchKernelGGL(k_upd_few, dim3(static_cast<unsigned>((I + kRowThreads - 1) / kRowThreads)),
                                     dim3(kRowThreads), few_lds, stream, pred_off, preds, n_preds, I, L, nodes, M, N,
                                     labels, W, feasible, popcnt, ctx->d_err));
