@@ -12,6 +12,17 @@ def dev(a):
     return pc.to_device(a, "cuda")
 
 
+def kernels(run):
+    """What run() returns, and the names of the kernels it launched on the default context."""
+    ctx = pc.context()
+    ctx.profile(True)
+    out = run()
+    torch.cuda.synchronize()
+    used = set(ctx.profile_read())
+    ctx.profile(False)
+    return out, used
+
+
 def selectors(labels, pred_off, preds, n_preds=None):
     f, p = pc.pc_eval_selectors(dev(labels), dev(pred_off), dev(preds), n_preds=n_preds)
     torch.cuda.synchronize()

@@ -1,6 +1,6 @@
 """Build guards for the flow-trace filter (CPU only: hipcc cross-compiles).
 
-The match kernel's filter keeps each lane's chunk sets in registers that its
+The filter of k_tr_match_wide keeps each lane's chunk sets in registers that its
 inline asm pins to v32..v127 and reads them in GPR index mode.  These tests
 compile csrc/trace.hip for gfx950 and check, in the compiler's resource report
 and in the kernel's own assembly, that this arrangement still holds under the
@@ -42,8 +42,8 @@ def match_build(tmp_path_factory):
         vals = dict(re.findall(r"remark: \s*([A-Za-z ]+?)(?: \[[^\]]*\])?: (\d+)", block))
         report[name] = vals
     text = open(asm).read()
-    m = re.search(r"^(_ZN\w*k_tr_match\w*):[^\n]*\n(.*?)^\s*s_endpgm", text, re.M | re.S)
-    assert m, "k_tr_match not found in the assembly"
+    m = re.search(r"^(_ZN\w*k_tr_match_wide\w*):[^\n]*\n(.*?)^\s*s_endpgm", text, re.M | re.S)
+    assert m, "k_tr_match_wide not found in the assembly"
     return report, m.group(1), m.group(2)
 
 

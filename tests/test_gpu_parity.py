@@ -334,33 +334,38 @@ def test_trace_malformed_flags(g, orc):
     assert flags == err == (orc.F_JUR | orc.F_SWITCH | orc.F_ACTION)
 
 
+# (1,024 queries and fewer on a sparse graph take the map search)
 @pytest.mark.parametrize("full_rows", [True, False])
 def test_reach_small_graph_bitset(g, orc, full_rows):
-    wl = synth.rgg_workload(4, 3000, 8, 200, mean_degree=6.0, full_rows=full_rows)
-    _check_workload(g, orc, wl)
+    wl = synth.rgg_workload(4, 3000, 8, 1100, mean_degree=6.0, full_rows=full_rows)
+    _, used = g.kernels(lambda: _check_workload(g, orc, wl))
+    assert "k_rc_bitset" in used
 
 
 @pytest.mark.parametrize("V", [700, 1500, 2900, 4000, 5500, 6016, 6200])
 def test_reach_bitset_sizes(g, orc, V):
     """The bitset BFS up to its largest LDS-resident graph (6,016 vertices)
-    and just past it (the queue path), target mode and full rows."""
+    and just past it (the map search), target mode and full rows."""
     for full_rows in (False, True):
-        wl = synth.rgg_workload(V, V, 8, 130, mean_degree=7.0, full_rows=full_rows)
-        _check_workload(g, orc, wl)
+        wl = synth.rgg_workload(V, V, 8, 1030, mean_degree=7.0, full_rows=full_rows)
+        _, used = g.kernels(lambda: _check_workload(g, orc, wl))
+        assert ("k_rc_bitset" if V <= 6016 else "k_rc_map") in used
 
 
 @pytest.mark.parametrize("deg", [7.0, 20.0, 40.0, 80.0])
 def test_reach_bitset_lane_groups(g, orc, deg):
     """Mean degrees that select 4, 8, 16 and 32 lanes per frontier vertex."""
     for full_rows in (False, True):
-        wl = synth.rgg_workload(int(deg), 1500, 8, 150, mean_degree=deg, full_rows=full_rows)
-        _check_workload(g, orc, wl)
+        wl = synth.rgg_workload(int(deg), 1500, 8, 1050, mean_degree=deg, full_rows=full_rows)
+        _, used = g.kernels(lambda: _check_workload(g, orc, wl))
+        assert "k_rc_bitset" in used
 
 
 @pytest.mark.parametrize("full_rows", [True, False])
-def test_reach_large_graph_queue(g, orc, full_rows):
+def test_reach_large_graph_map(g, orc, full_rows):
     wl = synth.rgg_workload(5, 40000, 16, 40, mean_degree=5.0, full_rows=full_rows)
-    _check_workload(g, orc, wl)
+    _, used = g.kernels(lambda: _check_workload(g, orc, wl))
+    assert "k_rc_map" in used
 
 
 def test_reach_fat_tree_targets(g, orc):
@@ -382,7 +387,7 @@ def test_reach_targets_on_one_way_graphs(g, orc, kind):
     exact only when the lists are symmetric: one-way entries, unsorted lists
     (which switch the shortcut off) and a vertex with invalid offsets (named
     by lists it cannot name back) must match the oracle's plain search."""
-    wl = synth.rgg_workload(11, 1200, 4, 130, mean_degree=9.0, full_rows=False)
+    wl = synth.rgg_workload(11, 1200, 4, 1130, mean_degree=9.0, full_rows=False)
     adj_off, adj = wl["adj_off"].copy(), wl["adj"].copy()
     rng = np.random.default_rng(1)
     if kind == "asymmetric":
@@ -396,9 +401,10 @@ def test_reach_targets_on_one_way_graphs(g, orc, kind):
     else:
         hub = int(np.argmax(np.diff(adj_off)))
         adj_off[hub + 1] = adj_off[hub] - 1 if adj_off[hub] > 0 else adj.shape[0] + 5
-    dg = g.reach(wl["V"], adj_off, adj, wl["region"], wl["src"], wl["allowed"], wl["target"])
+    dg, used = g.kernels(lambda: g.reach(wl["V"], adj_off, adj, wl["region"], wl["src"], wl["allowed"], wl["target"]))
     do, _ = orc.reach(wl["V"], adj_off, adj, wl["region"], wl["src"], wl["allowed"], wl["target"])
     _same(dg, do, "dist")
+    assert "k_rc_bitset" in used
 
 
 def test_reach_malformed_flags(g, orc):

@@ -1,8 +1,8 @@
 """Parity of the waypoint and forbidden-switch checks (pc_trace_flows_watch,
 pc_masked_reach_via, pc_report_paths) with the CPU oracle, bit-exact, on
 seeded inputs: the tiny end-to-end case, small combined workloads, fat-trees
-with long and full watch lists, both BFS paths (LDS bitset and queue), and
-malformed lists."""
+with long and full watch lists, the bitset and the map search, and malformed
+lists."""
 import numpy as np
 import pytest
 
@@ -161,8 +161,8 @@ def _via_lists(rng, Q, V, Kv, Kf, src, target):
 @pytest.mark.parametrize("Kv,Kf", [(0, 0), (0, 3), (1, 2), (3, 5)])
 @pytest.mark.parametrize("V", [1500, 40000])
 def test_reach_via_rgg(g, orc, V, Kv, Kf):
-    """Bitset (1,500 vertices) and queue (40,000) BFS paths."""
-    Q = 300 if V <= 6016 else 40
+    """The bitset search (1,500 vertices) and the map search (40,000)."""
+    Q = 1100 if V <= 6016 else 40
     wl = synth.rgg_workload(V + Kv + Kf, V, 8, Q, mean_degree=7.0, full_rows=False)
     rng = np.random.default_rng(V + 10 * Kv + Kf)
     via, forbid = _via_lists(rng, Q, V, Kv, Kf, wl["src"], wl["target"])
@@ -170,11 +170,12 @@ def test_reach_via_rgg(g, orc, V, Kv, Kf):
         # waypoints near the source, so that many walks exist
         near = wl["adj"][wl["adj_off"][wl["src"]]]
         via[::2, 0] = near[::2]
-    dg = g.reach_via(wl["V"], wl["adj_off"], wl["adj"], wl["region"], wl["src"], wl["allowed"], wl["target"], via,
-                     forbid)
+    dg, used = g.kernels(lambda: g.reach_via(wl["V"], wl["adj_off"], wl["adj"], wl["region"], wl["src"], wl["allowed"],
+                                             wl["target"], via, forbid))
     do, _ = orc.reach_via(wl["V"], wl["adj_off"], wl["adj"], wl["region"], wl["src"], wl["allowed"], wl["target"],
                           via, forbid)
     _same(dg, do, "reach_via")
+    assert ("k_rc_bitset" if V <= 6016 else "k_rc_map") in used
     if V <= 6016:
         assert (do >= 0).sum() > 10 and (do == -1).sum() > 10
 
@@ -237,13 +238,15 @@ def test_report_paths_cfg1_visit_patterns(g, orc):
     _same(sg["no_path"], so["no_path"], "no_path")
 
 
+# legs of the map search, of the bitset search, and of the bitset search in source order
+@pytest.mark.parametrize("Q", [130, 500, 4700])
 @pytest.mark.parametrize("kind", ["symmetric", "asymmetric", "unsorted", "bad_offsets"])
-def test_reach_via_leg_direction(g, orc, kind):
+def test_reach_via_leg_direction(g, orc, kind, Q):
     """Legs are searched from their far end only on symmetric graphs with
     sorted lists; one-way entries, unsorted lists, or a vertex whose offsets
     are invalid (push never expands it, yet a neighbour's list names it) must
     give the forward results."""
-    wl = synth.rgg_workload(11, 1200, 4, 130, mean_degree=9.0, full_rows=False)
+    wl = synth.rgg_workload(11, 1200, 4, Q, mean_degree=9.0, full_rows=False)
     adj_off, adj = wl["adj_off"].copy(), wl["adj"].copy()
     rng = np.random.default_rng(1)
     if kind == "asymmetric":
@@ -257,12 +260,13 @@ def test_reach_via_leg_direction(g, orc, kind):
     elif kind == "bad_offsets":
         hub = int(np.argmax(np.diff(adj_off)))
         adj_off[hub + 1] = adj_off[hub] - 1 if adj_off[hub] > 0 else adj.shape[0] + 5
-    Q = 130
     near = adj[np.clip(adj_off[wl["src"]], 0, adj.shape[0] - 1)]
     via = np.stack([near, rng.integers(0, wl["V"], size=Q)], axis=1).astype(np.int32)
     via[::3, 1] = -1
     forbid = rng.integers(-1, wl["V"], size=(Q, 2)).astype(np.int32)
-    dg = g.reach_via(wl["V"], adj_off, adj, wl["region"], wl["src"], wl["allowed"], wl["target"], via, forbid)
+    dg, used = g.kernels(lambda: g.reach_via(wl["V"], adj_off, adj, wl["region"], wl["src"], wl["allowed"], wl["target"],
+                                             via, forbid))
+    assert ("k_rc_map" if Q == 130 else "k_rc_bitset") in used and ("k_rc_legs" in used) == (Q != 500)
     do, _ = orc.reach_via(wl["V"], adj_off, adj, wl["region"], wl["src"], wl["allowed"], wl["target"], via, forbid)
     _same(dg, do, "reach_via")
     assert (do >= 0).sum() > 5
