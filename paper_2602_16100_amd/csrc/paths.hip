@@ -9,10 +9,12 @@
 //   2. in-links : the reverse of the port graph -- per switch v the (u, port)
 //                 pairs of the links u -> v -- counted, scanned and filled --
 //                 and packed link records for the directed search.
-//   3. bounds   : with many more legs than switches, for every switch that a
-//                 leg ends at, a lower bound of every switch's distance to
-//                 it: the distances of the whole port graph, which no
-//                 request's restrictions can shorten.
+//   3. bounds   : with many more legs than switches and weights that differ
+//                 (one_weight), for every switch that a leg ends at, a lower
+//                 bound of every switch's distance to it: the distances of
+//                 the whole port graph, which no request's restrictions can
+//                 shorten, in units taken from a sample of the weights
+//                 (bound_form), 16 or 32 bits each.
 //   4. goal     : one wavefront per request.  A leg relaxes only switches
 //                 whose distance plus bound stays within a limit, which starts
 //                 at the bound of the leg's source and grows until the leg's
@@ -27,10 +29,11 @@
 //                 lanes over a switch's ports with LDS atomic minima,
 //                 loading the next switch's links while the current one's
 //                 are relaxed; a switch whose distance drops joins the next
-//                 round's frontier once (a flag bit per switch).  A frontier switch at or beyond the target's
-//                 current distance is skipped: with weights >= 1 it cannot
-//                 shorten the target's path, so every switch nearer than
-//                 the target ends with its exact distance.  The leg is then
+//                 round's frontier once (a flag bit per switch).  A frontier
+//                 switch at or beyond the target's current distance is
+//                 skipped: with weights >= 1 it cannot shorten the target's
+//                 path, so every switch nearer than the target ends with its
+//                 exact distance.  The leg is then
 //                 walked back from its end by one wavefront: the
 //                 predecessor of v is the lowest-numbered u among v's
 //                 in-links with dist(u) + w = dist(v) (a wavefront minimum;

@@ -170,6 +170,9 @@ __global__ __launch_bounds__(256) void k_sel_presence_flat(const uint8_t *__rest
     // An atomic that has returned its old value has been performed, so the
     // count below comes after this workgroup's sets without a fence (an
     // agent-wide release writes the L2 back: 100,000 nodes 89 us with one).
+    // That is how this hardware orders them, not a release and an acquire: what
+    // the last workgroup reads here it must read with atomic loads, and other
+    // kernels read it only after this launch has ended.
     uint32_t seen = 0;
     for (int32_t i = threadIdx.x; i < L * 8; i += 256)
         if (ptab[i] & ~present32[i]) seen |= atomicOr(&present32[i], ptab[i]);

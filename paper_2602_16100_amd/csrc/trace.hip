@@ -36,9 +36,11 @@
 //            port and workgroup, which also gives each trace its rank in its
 //            next switch's bucket) and writes their live-list entries in its
 //            own share of the list, grouped by port.
-//   tail   : once few traces are left in flight, one workgroup per trace
-//            walks it to its end, reading only the chunk-set words its
+//   tail   : once few traces are left in flight (walk_rule), one workgroup per
+//            trace walks it to its end, reading only the chunk-set words its
 //            header selects, and skipping whole turns of a loop.
+//   direct : few traces over small tables are walked rule by rule in one
+//            launch, without chunk sets.
 #include <stdlib.h>
 
 #include <algorithm>
