@@ -40,8 +40,8 @@
  *   - `stream` is a hipStream_t (NULL = the legacy default stream).  Every
  *     entry point is asynchronous and stream-ordered, except
  *     pc_trace_flows(_watch), which waits for the size of its rule index (where it
- *     matches small tables rule by rule, at most to learn that none is too long) and
- *     for one live-trace count per hop level it walks by levels,
+ *     matches small tables rule by rule, at most to learn that none is too long, and not while
+ *     the stream is captured) and for one live-trace count per hop level it walks by levels,
  *     pc_trace_flows_delta, which waits for the number
  *     of traces to trace again and of its rule index, and pc_data_errors and
  *     pc_profile_read, which wait for the stream.

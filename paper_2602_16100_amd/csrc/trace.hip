@@ -2130,6 +2130,13 @@ int layout(pc_ctx *ctx, int32_t S, const int32_t *port_off, int64_t n_ports, con
     return PC_OK;
 }
 
+bool capturing(hipStream_t stream)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) (void)hipGetLastError();
+    return status != hipStreamCaptureStatusNone;
+}
+
 // Waits for the guard's answer: the host goes on as the walk starts (waiting for
 // its end takes 25 us a call).  Ends at the latest with the stream's work.
 int wait_guard(pc_ctx *ctx, const Guard &g, hipStream_t stream, bool *too_long)
@@ -2189,7 +2196,8 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
     // actions swept by one wavefront too) / 69.  Asking costs 0-4 us: 3,000 traces
     // over 64 rules a switch (k = 16) 15 / 17, 500 over 100 (k = 32) 13 / 17.
     const int64_t longest = std::min(kDirectTable, kDirectTableWork / std::max(T, 1));
-    const bool guarded = direct && n_rules > longest;
+    // (A stream under capture cannot be waited for: no question then.)
+    const bool guarded = direct && n_rules > longest && !capturing(stream);
     // work items of a level: at most T / kItemMin + S (see the match launch)
     const int32_t icap = static_cast<int32_t>(std::min<int64_t>(static_cast<int64_t>(T) / kItemMin + S + 1, INT32_MAX));
     auto carve = [&](Carver &c) {

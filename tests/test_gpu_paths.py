@@ -637,3 +637,32 @@ def test_priorities_refused(g, orc, monkeypatch):
     to, _ = orc.trace(wl["S"], wl["port_off"], wl["port_peer"], wl["jur"], wl["rule_off"], wl["rules"], wl["hdr"],
                       wl["ingress"], 12, idx=part)
     _same_traces(refused[part], to)
+
+
+def test_trace_many_rules_captured(g, orc):
+    """A call that would ask for its tables' lengths waits for nothing while its stream is captured: the graph's replays
+    trace the headers of the moment."""
+    import torch
+    import paper_2602_16100_amd as pc
+    wl = synth.trace_workload(5, 16, 4, 100, 1000, 16, 50)
+    names = ("port_off", "port_peer", "jur", "rule_off", "rules", "hdr", "ingress")
+    d = {k: g.dev(wl[k]) for k in names}
+    ctx = pc.Context(0)
+
+    def call():
+        return pc.pc_trace_flows(wl["S"], *(d[k] for k in names), 16, ctx=ctx)
+
+    call()  # the scratch
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = call()
+    first, hdr = d["hdr"].clone(), wl["hdr"]
+    for turn in (0, 17, 500):
+        d["hdr"].copy_(first.roll(turn, 0))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = pc.records(out, pc.TRACE_OUT_DT)
+        to, _ = orc.trace(wl["S"], *(wl[k] for k in names[:5]), np.roll(hdr, turn, 0), wl["ingress"], 16)
+        _same_traces(got, to)
+        _same_traces(pc.records(call(), pc.TRACE_OUT_DT), to)
