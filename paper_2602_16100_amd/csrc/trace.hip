@@ -2245,6 +2245,27 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
     };
 
     // ---- rule by rule
+    auto by_rule = [&](const Guard &guard) -> int {
+        const int64_t sweep = (std::max(n_ports, n_watch) + 4 * kDirectThreads - 1) / (4 * kDirectThreads);
+        const int64_t blocks = std::max<int64_t>(S, std::min<int64_t>(sweep, 1024));
+        PC_TIMED(ctx, "k_tr_direct", stream,
+                 hipLaunchKernelGGL(k_tr_direct, dim3(static_cast<unsigned>(blocks)), dim3(kDirectThreads), 0, stream, S,
+                                    rule_off, n_rules, rules, n_watch, watch, inf, guard));
+        PC_LAUNCH_CHECK(ctx);
+        return T > 0 ? walk_all(64, guard) : PC_OK;
+    };
+    // where the chunk sets of a call whose longest table asks for them are
+    // refused, its rules are matched one by one all the same
+    auto refused = [&](int rc) -> int {
+        if (rc != PC_ENOMEM || !guarded) return rc;
+        direct = true;
+        rc = reserve();
+        if (rc) return rc;
+        ctx->msg[0] = 0;
+        inf.sinfo = B.sinfo;
+        inf.pinfo = B.pinfo;
+        return by_rule(Guard{});
+    };
     if (direct) {
         Guard guard{};
         if (guarded) {
@@ -2254,21 +2275,14 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
                           S <= kLayoutS};
             *guard.host = 0;  // (the last guarded call's has been read)
         }
-        const int64_t sweep = (std::max(n_ports, n_watch) + 4 * kDirectThreads - 1) / (4 * kDirectThreads);
-        const int64_t blocks = std::max<int64_t>(S, std::min<int64_t>(sweep, 1024));
-        PC_TIMED(ctx, "k_tr_direct", stream,
-                 hipLaunchKernelGGL(k_tr_direct, dim3(static_cast<unsigned>(blocks)), dim3(kDirectThreads), 0, stream, S,
-                                    rule_off, n_rules, rules, n_watch, watch, inf, guard));
-        PC_LAUNCH_CHECK(ctx);
-        if (T == 0) return PC_OK;
-        rc = walk_all(64, guard);
+        rc = by_rule(guard);
         if (rc || !guarded) return rc;
         bool too_long = false;
         rc = wait_guard(ctx, guard, stream, &too_long);
         if (rc || !too_long) return rc;
         direct = false;
         rc = reserve();
-        if (rc) return rc;
+        if (rc) return refused(rc);
         inf.sinfo = B.sinfo;
         inf.pinfo = B.pinfo;
     }
@@ -2315,7 +2329,7 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
             rc = pc_ensure_aux(ctx, chunk_set_bytes(groups, false));
             if (rc == PC_OK) ctx->msg[0] = 0;
         }
-        if (rc) return rc;
+        if (rc) return refused(rc);
         B.filt = reinterpret_cast<uint32_t *>(ctx->aux);
         if (ranked) B.prio = priorities(ctx->aux, groups);
         if (prep_blocks > 0 && n_rules > 0) {

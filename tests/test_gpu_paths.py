@@ -666,3 +666,32 @@ def test_trace_many_rules_captured(g, orc):
         to, _ = orc.trace(wl["S"], *(wl[k] for k in names[:5]), np.roll(hdr, turn, 0), wl["ingress"], 16)
         _same_traces(got, to)
         _same_traces(pc.records(call(), pc.TRACE_OUT_DT), to)
+
+
+def test_trace_one_long_table_refused(g, orc, monkeypatch):
+    """Where the chunk sets of a call with one long table are refused, its rules are matched one by one all the same."""
+    import paper_2602_16100_amd as pc
+    wl = synth.trace_workload(3, 16, 4, 16, 100, 16, 50)
+    off, rules = _with_hub(wl, wl["rules"], 50_000, np.random.default_rng(1))
+    rules["action"][off[1] - 5] = 3000
+    a = (wl["S"], wl["port_off"], wl["port_peer"], wl["jur"])
+    hdr, ingress = wl["hdr"], np.zeros(100, np.int32)
+    ctx = pc.Context(0)
+
+    def run(off, rules):
+        ctx.profile(True)
+        out = pc.pc_trace_flows(a[0], *(g.dev(x) for x in (*a[1:], off, rules, hdr, ingress)), 16, ctx=ctx)
+        used = ctx.profile_read()
+        ctx.profile(False)
+        return pc.records(out, pc.TRACE_OUT_DT), ctx.data_errors(clear=True), used
+
+    run(wl["rule_off"], wl["rules"])  # the arena
+    monkeypatch.setenv("PC_FAIL_ALLOC", "1")
+    got, flags, used = run(off, rules)
+    monkeypatch.delenv("PC_FAIL_ALLOC")
+    to, err = orc.trace(*a, off, rules, hdr, ingress, 16)
+    _same_traces(got, to)
+    assert flags == err and used["k_tr_walk"][0] == 2 and "k_tr_prep" not in used
+    got, flags, used = run(off, rules)
+    _same_traces(got, to)
+    assert flags == err and "k_tr_prep" in used
