@@ -2175,7 +2175,7 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
     // (until the largest table is known, the rule without it)
     WalkRule rule = walk_rule(mean_groups, pre != nullptr ? pre->largest : 0);
     bool levels = T > rule.most;
-    const bool may_level = T > walk_rule(mean_groups, kWalkGroups).most;
+    bool may_level = pre != nullptr ? levels : T > walk_rule(mean_groups, kWalkGroups).most;
     // Few enough traces over tables this small are matched rule by rule: no
     // chunk sets, no wait for their count, two launches.  Chunk sets / rule by
     // rule: 1,000 traces over 16 rules per switch 46 / 23 us (k = 16), 4,000
@@ -2229,6 +2229,12 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         return rc;
     };
     int rc = reserve();
+    if (rc == PC_ENOMEM && may_level && T <= walk_rule(mean_groups, 0).most) {
+        // no room for levels, which only the largest table asks for: walks, which need none
+        may_level = levels = false;
+        rc = reserve();
+        if (rc == PC_OK) ctx->msg[0] = 0;
+    }
     if (rc) return rc;
     if (!visit) K = 0;
     const int64_t n_watch = static_cast<int64_t>(T) * K;
@@ -2321,7 +2327,7 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         if (groups < 0 || prep_blocks < 0)
             return pc_set_error(ctx, PC_EINVAL, "pc_trace_flows: more than 2^31 rule groups");
         rule = walk_rule(mean_groups, ctx->h_small[2]);
-        levels = T > rule.most;
+        levels = may_level && T > rule.most;
         bool ranked = levels && !wide_level(T, S, mean_groups);  // (levels only shrink)
         rc = pc_ensure_aux(ctx, chunk_set_bytes(groups, ranked));
         if (rc == PC_ENOMEM && ranked) {  // no room for the priorities: k_tr_match_wide needs none

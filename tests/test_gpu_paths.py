@@ -695,3 +695,29 @@ def test_trace_one_long_table_refused(g, orc, monkeypatch):
     got, flags, used = run(off, rules)
     _same_traces(got, to)
     assert flags == err and "k_tr_prep" in used
+
+
+def test_trace_levels_refused(g, orc, monkeypatch):
+    """60,000 traces are walked unless a table is large, and need no room for levels: they are where that is refused."""
+    import paper_2602_16100_amd as pc
+    T, part = 60_000, np.arange(0, 60_000, 3000)
+    wl = synth.trace_workload(3, 24, 4, 300, T, 12, 2000)
+    names = ("port_off", "port_peer", "jur", "rule_off", "rules", "hdr", "ingress")
+    d = {k: g.dev(wl[k]) for k in names}
+    ctx = pc.Context(0)
+
+    def run(n):
+        ctx.profile(True)
+        out = pc.pc_trace_flows(wl["S"], *(d[k] for k in names[:5]), d["hdr"][:n], d["ingress"][:n], 12, ctx=ctx)
+        used = ctx.profile_read()
+        ctx.profile(False)
+        return pc.records(out, pc.TRACE_OUT_DT), used
+
+    run(8000)  # the chunk sets, and an arena without levels
+    monkeypatch.setenv("PC_FAIL_ALLOC", "1")
+    got, used = run(T)
+    assert "k_tr_prep" in used and "k_tr_plan" not in used
+    to, _ = orc.trace(wl["S"], *(wl[k] for k in names), 12, idx=part)
+    _same_traces(got[part], to)
+    monkeypatch.delenv("PC_FAIL_ALLOC")
+    _same_traces(got, run(T)[0])
