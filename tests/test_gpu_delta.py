@@ -381,3 +381,49 @@ def test_walk_limit_with_one_large_table(g, orc, monkeypatch, S, T, walks):
     ro, vo, wo, _ = _oracle(orc, w, off, rules, idx=some)
     _same_records(first[0][some], ro)
     assert np.array_equal(first[1][some], vo) and np.array_equal(first[2][some], wo)
+
+
+@pytest.mark.parametrize("form,kernel", [("one", "listed"), ("few", "marked"), ("all", "marked"), ("repeated", "marked"), ("others", "listed")])
+def test_delta_one_large_table_changed(g, orc, form, kernel):
+    """300,000 rules on one of 320 switches: a delta on kept tables prepares them with a workgroup for each of their
+    blocks (by those of the mean table 310 us), by the list or, past all tables' blocks, by the marked switches."""
+    import paper_2602_16100_amd as pc
+    rng = np.random.default_rng(4)
+    wl = synth.trace_workload(3, 16, 4, 16, 1000, 12, 50)
+    S, n = wl["S"], 300_000
+    extra = np.zeros(n, synth.RULE_DT)
+    extra["value"], extra["mask"] = synth.random_keys(rng, n), np.array([0xFFFFFFFF] * 3 + [0xFF], np.uint32)
+    extra["priority"] = rng.integers(0, 65536, n)
+    extra["action"] = rng.integers(0, wl["port_off"][1], n)
+    own = wl["rule_off"][1]
+    rules = np.concatenate([wl["rules"][:own], extra, wl["rules"][own:]])
+    off = wl["rule_off"].copy()
+    off[1:] += n
+    hdr = wl["hdr"].copy()
+    hdr[::2] = extra["value"][rng.integers(0, n, 500)]
+    w = synth.Workload("hub", 0)
+    w.arrays.update(port_off=wl["port_off"], port_peer=wl["port_peer"], jur=wl["jur"], hdr=hdr,
+                    ingress=np.where(rng.random(1000) < 0.5, 0, wl["ingress"]).astype(np.int32))
+    w.sizes.update(S=S, ttl=12)
+    changed = dict(one=[0], few=[5, 0, S + 1, 7, -1, *range(10, 20)], all=np.arange(S), repeated=[0] * 500,
+                   others=[3, 4])[form]
+    inside = np.unique([c for c in changed if 0 <= c < S])
+    new = rules.copy()
+    for s in inside:
+        t = new[off[s]:off[s + 1]]
+        t["action"] = (t["action"] + 1) % (wl["port_off"][s + 1] - wl["port_off"][s])
+    new["action"][off[inside[0]] + 3] = 5000
+    ctx = pc.Context(0)
+    ctx.keep_tables(True)
+    first = _run(w, off, rules, None, None, None, ctx=ctx)
+    for _ in range(2):
+        ctx.profile(True)
+        again = _run(w, off, new, *first[:2], changed, walk=first[2], ctx=ctx)
+        used = ctx.profile_read()
+        ctx.profile(False)
+        ro, vo, wo, err = _oracle(orc, w, off, new)
+        _same_records(again[0], ro)
+        assert np.array_equal(again[1], vo) and np.array_equal(again[2], wo)
+        assert again[4] == err | (F_SWITCH if form == "few" else 0)
+        assert "k_tr_prep" not in used
+    assert used["k_tr_prep_" + kernel][1] < 0.15, used
