@@ -2059,14 +2059,15 @@ __global__ __launch_bounds__(256) void k_delta_scatter(const int32_t *__restrict
 // over 32,768 (k = 16) 908 / 835, 30,000 traces there 527 / 803; 4,194,304
 // traces, of which 8,900 loop until their TTL, 2.4 / 3.2 ms; 30,000 over 500,000
 // (k = 4) 4.9 / 7.8 ms.
-// Nor may the walks' passes over the largest table exceed what levels, which read
-// it once per some hundred lookups, take at their worst: one switch with nearly all
-// rules, where every trace enters (half, a fifth of them): 60,000 traces, a million
-// rules 1.8 / 1.6 ms (a tenth: 0.5 / 3.2); past the limit 65,536, two million 4.5 /
-// 3.7; 30,000, four million 7.0 / 6.4; 65,536 there 6.6 / 7.3 (9.5 / 10.9, 3.8 /
-// 11.1); 65,536, ten million 42 / 18.
+// Nor may the walks' passes over the largest table take much longer than the levels'
+// at their worst, one switch of 320 with nearly all rules where every trace enters
+// (in brackets a fifth of them, then none more than elsewhere): 16,000 traces, two
+// million rules 1,351 / 3,234 us; 30,000, 1.1 million 1,306 / 1,842; 60,000, half a
+// million 1,157 / 886 (492 / 872, 164 / 650); past the limit 60,000, 1.1 million
+// 3,216 / 1,760 (1,190 / 1,749, 280 / 1,286); 30,000, two million 3,132 / 3,243; 60,000
+// there 7,679 / 3,742 (2,331 / 3,699, 462 / 1,869).
 constexpr int64_t kWalkLeast = 8192;
-constexpr int64_t kWalkGroups = int64_t(1) << 31;  // traces times the groups of the largest table
+constexpr int64_t kWalkGroups = int64_t(1) << 30;  // traces times the groups of the largest table
 struct WalkRule {
     int64_t most;  // traces at most
     int threads;   // the walks' workgroup: about two rule groups per lane of a mean table

@@ -321,12 +321,12 @@ def test_delta_forms(g, orc, monkeypatch, walk_max, ring):
 
 @pytest.mark.parametrize("S,T,walks", [(320, 60_000, True), (320, 65_536, False), (16_390, 60_000, True), (16_390, 65_536, False)])
 def test_walk_limit_with_one_large_table(g, orc, monkeypatch, S, T, walks):
-    """1.1 million rules on the switch where every trace enters (34,376 groups of 32): 60,000 traces are walked, 65,536
-    (past 2^31 groups for all) go by levels; also when the switch's rules change, with the tables kept and anew."""
+    """550,000 rules on the switch where every trace enters (17,188 groups of 32): 60,000 traces are walked, 65,536
+    (past 2^30 groups for all) go by levels; also when the switch's rules change, with the tables kept and anew."""
     import torch
     import paper_2602_16100_amd as pc
     rng = np.random.default_rng(S + T)
-    n = 1_100_000
+    n = 550_000
     if S == 320:
         wl = synth.trace_workload(3, 16, 4, 16, T, 12, 50)
         port_off, peer, jur, off, rules = (wl[k] for k in ("port_off", "port_peer", "jur", "rule_off", "rules"))
