@@ -36,7 +36,7 @@
 //            port and workgroup, which also gives each trace its rank in its
 //            next switch's bucket) and writes their live-list entries in its
 //            own share of the list, grouped by port.
-//   tail   : once few traces are left in flight (walk_rule), one workgroup per
+//   tail   : once few traces are left in flight (walk_most), one workgroup per
 //            trace walks it to its end, reading only the chunk-set words its
 //            header selects, and skipping whole turns of a loop.
 //   direct : few traces over small tables are walked rule by rule in one
@@ -2068,17 +2068,22 @@ __global__ __launch_bounds__(256) void k_delta_scatter(const int32_t *__restrict
 // there 7,679 / 3,742 (2,331 / 3,699, 462 / 1,869).
 constexpr int64_t kWalkLeast = 8192;
 constexpr int64_t kWalkGroups = int64_t(1) << 30;  // traces times the groups of the largest table
-struct WalkRule {
-    int64_t most;  // traces at most
-    int threads;   // the walks' workgroup: about two rule groups per lane of a mean table
-};
-
-WalkRule walk_rule(int64_t mean_groups, int64_t largest)
+int64_t walk_most(int64_t mean_groups, int64_t largest)
 {
-    WalkRule r{mean_groups <= 128 ? 65536 : 32768, mean_groups <= 128 ? 64 : mean_groups <= 256 ? 128 : 256};
-    r.most = std::max(std::min(r.most, kWalkGroups / std::max<int64_t>(largest, 1)), kWalkLeast);
-    if (const char *env = getenv("PC_TRACE_WALK_MAX")) r.most = atoll(env);
-    return r;
+    if (const char *env = getenv("PC_TRACE_WALK_MAX")) return atoll(env);
+    return std::max(std::min<int64_t>(mean_groups <= 128 ? 65536 : 32768, kWalkGroups / std::max<int64_t>(largest, 1)),
+                    kWalkLeast);
+}
+
+// The walks' workgroup: about two rule groups per lane of a mean table; all of it
+// for few walks where the largest table is long (1.1 million rules on one of 320
+// switches, where every / no more than its share of the traces enter, 64 / 256 threads:
+// 300 traces 169 / 84 us and 155 / 78, 2,000 170 / 151 and 162 / 81; past the
+// limit 4,000 195 / 267 and 162 / 83; 60,000 rules there, 2,000 traces 49 / 47).
+int walk_threads(int64_t walks, int64_t mean_groups, int64_t largest)
+{
+    if (walks <= 2048 && largest > 1024) return 256;
+    return mean_groups <= 128 ? 64 : mean_groups <= 256 ? 128 : 256;
 }
 
 // The chunk sets' buffer: the sets of every group, then (for levels matched
@@ -2201,9 +2206,10 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
     } B;
     const int64_t mean_groups = S > 0 ? (pre != nullptr ? pre->groups : (n_rules + 31) / 32) / S : 0;
     // (until the largest table is known, the rule without it)
-    WalkRule rule = walk_rule(mean_groups, pre != nullptr ? pre->largest : 0);
-    bool levels = T > rule.most;
-    bool may_level = pre != nullptr ? levels : T > walk_rule(mean_groups, kWalkGroups).most;
+    int64_t largest = pre != nullptr ? pre->largest : 0;
+    int64_t most_walks = walk_most(mean_groups, largest);
+    bool levels = T > most_walks;
+    bool may_level = pre != nullptr ? levels : T > walk_most(mean_groups, kWalkGroups);
     // Few enough traces over tables this small are matched rule by rule: no
     // chunk sets, no wait for their count, two launches.  Chunk sets / rule by
     // rule: 1,000 traces over 16 rules per switch 46 / 23 us (k = 16), 4,000
@@ -2257,7 +2263,7 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         return rc;
     };
     int rc = reserve();
-    if (rc == PC_ENOMEM && may_level && T <= walk_rule(mean_groups, 0).most) {
+    if (rc == PC_ENOMEM && may_level && T <= walk_most(mean_groups, 0)) {
         // no room for levels, which only the largest table asks for: walks, which need none
         may_level = levels = false;
         rc = reserve();
@@ -2354,8 +2360,9 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         const int64_t groups = ctx->h_small[0], prep_blocks = ctx->h_small[1];
         if (groups < 0 || prep_blocks < 0)
             return pc_set_error(ctx, PC_EINVAL, "pc_trace_flows: more than 2^31 rule groups");
-        rule = walk_rule(mean_groups, ctx->h_small[2]);
-        levels = may_level && T > rule.most;
+        largest = ctx->h_small[2];
+        most_walks = walk_most(mean_groups, largest);
+        levels = may_level && T > most_walks;
         bool ranked = levels && !wide_level(T, S, mean_groups);  // (levels only shrink)
         rc = pc_ensure_aux(ctx, chunk_set_bytes(groups, ranked));
         if (rc == PC_ENOMEM && ranked) {  // no room for the priorities: k_tr_match_wide needs none
@@ -2374,7 +2381,7 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         }
     }
     if (T == 0) return PC_OK;
-    if (!levels) return walk_all(rule.threads, Guard{});
+    if (!levels) return walk_all(walk_threads(T, mean_groups, largest), Guard{});
     const WalkArgs wa = walk_args();
 
     // ---- level-synchronous walk
@@ -2418,11 +2425,11 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
         // the live list this level reads: from k_tr_init (as many entries as
         // traces in flight) or from the previous level's match
         const int32_t *len_cur = level == 0 ? n_cur : d_len + ((level - 1) & 1);
-        if (known <= rule.most) {
+        if (known <= most_walks) {
             const unsigned wb = static_cast<unsigned>(known < 8192 ? known : 8192);
             PC_TIMED(ctx, "k_tr_walk", stream,
-                     hipLaunchKernelGGL(k_tr_walk, dim3(wb), dim3(rule.threads), 0, stream, wa, live_cur, len_cur,
-                                        level));
+                     hipLaunchKernelGGL(k_tr_walk, dim3(wb), dim3(walk_threads(known, mean_groups, largest)), 0, stream, wa,
+                                        live_cur, len_cur, level));
             PC_LAUNCH_CHECK(ctx);
             break;
         }
@@ -2646,8 +2653,8 @@ int run_trace_delta(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32
     }
     if (n == 0) return PC_OK;
     const TcMeta m = tc_meta(ctx, S);
-    const WalkRule rule = walk_rule(S > 0 ? ctx->tc_groups / S : 0, ctx->tc_largest);
-    if (n <= rule.most) {  // walked in place
+    const int64_t mean_groups = S > 0 ? ctx->tc_groups / S : 0;
+    if (n <= walk_most(mean_groups, ctx->tc_largest)) {  // walked in place
         const int64_t n_info = std::max<int64_t>(n_ports, S);
         if (!serves && n_info > 0)
             PC_TIMED(ctx, "k_tr_port_info", stream,
@@ -2657,8 +2664,8 @@ int run_trace_delta(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32
         const WalkArgs wa{S, sinfo, pinfo, rules, reinterpret_cast<const uint32_t *>(ctx->tc_filt), ttl, out, nullptr,
                           0, nullptr, vsum, walk};
         PC_TIMED(ctx, "k_tr_walk", stream,
-                 hipLaunchKernelGGL(k_tr_walk_all<false>, dim3(static_cast<unsigned>(std::min(n, 8192))), dim3(rule.threads),
-                                    0, stream, wa, n, hdr, ingress, jur, ctx->d_err, list, Guard{}));
+                 hipLaunchKernelGGL(k_tr_walk_all<false>, dim3(static_cast<unsigned>(std::min(n, 8192))),
+                                    dim3(walk_threads(n, mean_groups, ctx->tc_largest)), 0, stream, wa, n, hdr, ingress, jur, ctx->d_err, list, Guard{}));
         PC_LAUNCH_CHECK(ctx);
         return PC_OK;
     }

@@ -427,3 +427,43 @@ def test_delta_one_large_table_changed(g, orc, form, kernel):
         assert again[4] == err | (F_SWITCH if form == "few" else 0)
         assert "k_tr_prep" not in used
     assert used["k_tr_prep_" + kernel][1] < 0.15, used
+
+
+@pytest.mark.parametrize("T", [2048, 2049])
+def test_walks_through_one_large_table(g, orc, T):
+    """1.1 million rules on the switch where every trace enters: up to 2,048 traces walk with a whole workgroup each
+    (1,000 traces 47 us, with a wavefront 122)."""
+    import paper_2602_16100_amd as pc
+    rng = np.random.default_rng(T)
+    wl = synth.trace_workload(3, 16, 4, 16, T, 12, 50)
+    n, own = 1_100_000, wl["rule_off"][1]
+    hub = np.zeros(n, synth.RULE_DT)
+    hub["value"], hub["mask"] = synth.random_keys(rng, n), np.array([0xFFFFFFFF] * 3 + [0xFF], np.uint32)
+    hub["priority"] = rng.integers(0, 65536, n)
+    hub["action"] = rng.integers(0, wl["port_off"][1], n)
+    off = wl["rule_off"].copy()
+    off[1:] += n
+    rules = np.concatenate([wl["rules"][:own], hub, wl["rules"][own:]])
+    hdr = wl["hdr"].copy()
+    hdr[::2] = hub["value"][rng.integers(0, n, hdr[::2].shape[0])]
+    w = synth.Workload("hub", 0)
+    w.arrays.update(port_off=wl["port_off"], port_peer=wl["port_peer"], jur=wl["jur"], hdr=hdr, ingress=np.zeros(T, np.int32))
+    w.sizes.update(S=wl["S"], ttl=12)
+    some = np.sort(rng.choice(T, 60, replace=False))
+    ro, vo, wo, _ = _oracle(orc, w, off, rules, idx=some)
+    d = [g.dev(x) for x in (w["port_off"], w["port_peer"], w["jur"], off, rules, hdr)]
+    ctx = pc.Context(0)
+    for k in (1000, T):
+        for _ in range(2):
+            ctx.profile(True)
+            got = pc.records(pc.pc_trace_flows(w["S"], *d[:5], d[5][:k], g.dev(w["ingress"][:k]), 12, ctx=ctx), pc.TRACE_OUT_DT)
+            used = ctx.profile_read()
+            ctx.profile(False)
+        _same_records(got[some[some < k]], ro[some < k])
+        if k == 1000:
+            assert used["k_tr_walk"][1] < 0.09, used
+    first = _run(w, off, rules, None, None, None)
+    again = _run(w, off, rules, *first[:2], [0], walk=first[2])
+    for r in (first, again):
+        _same_records(r[0][some], ro)
+        assert np.array_equal(r[1][some], vo) and np.array_equal(r[2][some], wo)
