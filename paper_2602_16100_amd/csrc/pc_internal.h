@@ -36,6 +36,7 @@ struct pc_ctx {
     int64_t tc_groups = 0;
     int64_t tc_blocks = 0;
     int64_t tc_largest = 0;  // groups of the largest table
+    bool tc_ranked = false;  // the rules' priorities lie behind the chunk sets
     bool tc_keep = false;  // pc_trace_keep_tables: delta calls may reuse the kept tables
     hipEvent_t lvl_ev[2];  // trace level loop: completion of a level's live count copy
     // optional per-kernel timing (pc_profile)
@@ -138,6 +139,7 @@ struct TracePrep {
     const uint32_t *cpos;  // per switch: the key nibbles its chunk sets filter on (5 bits each)
     int64_t groups;        // groups of all switches
     int64_t largest;       // groups of the largest table
+    uint16_t *prio;        // the rules' priorities, or nullptr
 };
 
 int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *port_peer, int64_t n_ports,

@@ -2331,7 +2331,7 @@ int run_trace(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *po
     // (done by the caller when it passes prepared tables)
     if (pre != nullptr) {
         B.filt = const_cast<uint32_t *>(pre->filt);
-        B.prio = priorities(B.filt, pre->groups);
+        B.prio = pre->prio;
         B.gcount = const_cast<int32_t *>(pre->gcount);
         const int64_t n_info = std::max<int64_t>(n_ports, S);
         if (n_info > 0)
@@ -2499,6 +2499,12 @@ TcMeta tc_meta(pc_ctx *ctx, int32_t S)
 
 size_t tc_meta_bytes(int32_t S) { return 7 * (256 + (static_cast<size_t>(S) + 1) * 4) + kHistWords * 4; }
 
+// The kept tables' priorities (nullptr: there was no room for them).
+uint16_t *kept_priorities(pc_ctx *ctx)
+{
+    return ctx->tc_ranked ? priorities(ctx->tc_filt, ctx->tc_groups) : nullptr;
+}
+
 // Prepare every switch's tables into the context's cache (and sweep them
 // for data errors); the cache then describes these tables.
 int tc_prepare_all(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_t *port_peer, int64_t n_ports,
@@ -2526,15 +2532,22 @@ int tc_prepare_all(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32_
         if (groups < 0 || blocks < 0)
             return pc_set_error(ctx, PC_EINVAL, "pc_trace_flows_delta: more than 2^31 rule groups");
     }
+    ctx->tc_ranked = true;
     rc = pc_ensure_tc_filt(ctx, chunk_set_bytes(groups, true));
+    if (rc == PC_ENOMEM) {  // no room for the priorities: k_tr_match_wide needs none
+        ctx->tc_ranked = false;
+        rc = pc_ensure_tc_filt(ctx, chunk_set_bytes(groups, false));
+        if (rc == PC_OK) ctx->msg[0] = 0;
+    }
     if (rc) return rc;
     if (S > 0) {
         if (blocks > 0) {
             PC_TIMED(ctx, "k_tr_prep", stream,
                      hipLaunchKernelGGL(k_tr_prep, dim3(static_cast<unsigned>(blocks)), dim3(kPrepWaves * 64), 0,
                                         stream, S, port_off, n_ports, rule_off, rules, m.gcount, m.gofs, m.bofs,
-                                        reinterpret_cast<uint32_t *>(ctx->tc_filt), priorities(ctx->tc_filt, groups),
-                                        ctx->d_err, m.sw_bad, m.cpos));
+                                        reinterpret_cast<uint32_t *>(ctx->tc_filt),
+                                        ctx->tc_ranked ? priorities(ctx->tc_filt, groups) : nullptr, ctx->d_err,
+                                        m.sw_bad, m.cpos));
             PC_LAUNCH_CHECK(ctx);
         }
     }
@@ -2560,7 +2573,7 @@ int run_trace_delta(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32
         if (T == 0) return PC_OK;
         const TcMeta m = tc_meta(ctx, S);
         const TracePrep pre{reinterpret_cast<const uint32_t *>(ctx->tc_filt), m.gcount, m.gofs, m.cpos,
-                            ctx->tc_groups, ctx->tc_largest};
+                            ctx->tc_groups, ctx->tc_largest, kept_priorities(ctx)};
         return run_trace(ctx, S, port_off, port_peer, n_ports, jur, rule_off, rules, n_rules, hdr, ingress, T, ttl,
                          nullptr, 0, out, nullptr, vsum, walk, stream, &pre);
     }
@@ -2629,7 +2642,7 @@ int run_trace_delta(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32
         // rules on each of 1,280, 16 / 1,280 changed: 9 / 22 us.
         const int64_t most = (ctx->tc_largest + kPrepGroups - 1) / kPrepGroups;
         uint32_t *filt = reinterpret_cast<uint32_t *>(ctx->tc_filt);
-        uint16_t *prio = priorities(filt, ctx->tc_groups);
+        uint16_t *prio = kept_priorities(ctx);
         if (C <= 65535 && C * most <= ctx->tc_blocks)
             PC_TIMED(ctx, "k_tr_prep_listed", stream,
                      hipLaunchKernelGGL(k_tr_prep_listed, dim3(static_cast<unsigned>(most), static_cast<unsigned>(C)),
@@ -2673,7 +2686,8 @@ int run_trace_delta(pc_ctx *ctx, int32_t S, const int32_t *port_off, const int32
              hipLaunchKernelGGL(k_delta_gather, dim3(grid_for(n, 256)), dim3(256), 0, stream, list, n, hdr, ingress,
                                 hdr_c, ing_c));
     PC_LAUNCH_CHECK(ctx);
-    const TracePrep pre{reinterpret_cast<const uint32_t *>(ctx->tc_filt), m.gcount, m.gofs, m.cpos, ctx->tc_groups, ctx->tc_largest};
+    const TracePrep pre{reinterpret_cast<const uint32_t *>(ctx->tc_filt), m.gcount, m.gofs, m.cpos,
+                        ctx->tc_groups, ctx->tc_largest, kept_priorities(ctx)};
     rc = run_trace(ctx, S, port_off, port_peer, n_ports, jur, rule_off, rules, n_rules, hdr_c, ing_c, n, ttl, nullptr,
                    0, out_c, nullptr, vsum_c, walk ? walk_c : nullptr, stream, &pre);
     if (rc) return rc;

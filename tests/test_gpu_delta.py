@@ -467,3 +467,41 @@ def test_walks_through_one_large_table(g, orc, T):
     for r in (first, again):
         _same_records(r[0][some], ro)
         assert np.array_equal(r[1][some], vo) and np.array_equal(r[2][some], wo)
+
+
+def test_delta_priorities_refused(g, orc, monkeypatch):
+    """Where the kept tables' buffer holds the chunk sets but not the rules' priorities, levels of many lookups are matched
+    in registers, also by the deltas that follow."""
+    import paper_2602_16100_amd as pc
+    T, S = 100_000, 720
+    small, wl = (synth.trace_workload(3, 24, 4, R, T, 12, 2000) for R in (2016, 2400))
+    some = np.arange(0, T, 5000)
+    changed = np.arange(0, S, 3)
+    off2, new = synth.mutate_tables(4, wl["port_off"], wl["rule_off"], wl["rules"], changed)
+    ctx, other = pc.Context(0), pc.Context(0)
+    for c in (ctx, other):
+        c.keep_tables(True)
+
+    def call(c, off, rules, *state):
+        c.profile(True)
+        r = _run(wl, off, rules, *(state[:2] or (None, None)), changed if state else None, walk=state[2] if state else None, ctx=c)
+        used = c.profile_read()
+        c.profile(False)
+        return r, used
+
+    _run(small, small["rule_off"], small["rules"], None, None, None, ctx=ctx)  # all buffers; 504 bytes a group for the sets'
+    _run(small, small["rule_off"], small["rules"], np.zeros(T, pc.TRACE_OUT_DT), np.zeros(T, np.uint64), [], walk=np.full((T, 8), -1), ctx=ctx)
+    monkeypatch.setenv("PC_FAIL_ALLOC", "1")
+    first, used = call(ctx, wl["rule_off"], wl["rules"])
+    assert "k_tr_match_wide" in used and "k_tr_match" not in used
+    again, used = call(ctx, off2, new, *first[:3])
+    monkeypatch.delenv("PC_FAIL_ALLOC")
+    first2, used = call(other, wl["rule_off"], wl["rules"])
+    assert "k_tr_match" in used
+    again2, used = call(other, off2, new, *first2[:3])
+    for a, b, off, rules in ((first, first2, wl["rule_off"], wl["rules"]), (again, again2, off2, new)):
+        for x, y in zip(a, b):
+            assert np.array_equal(x, y)
+        ro, vo, wo, _ = _oracle(orc, wl, off, rules, idx=some)
+        _same_records(a[0][some], ro)
+        assert np.array_equal(a[1][some], vo) and np.array_equal(a[2][some], wo)
