@@ -535,7 +535,12 @@ __global__ __launch_bounds__(256) void k_rc_records(int32_t V, const int32_t *__
 // 0.28 ms against 2.0 ms.
 constexpr int kMapThreads = 1024;
 constexpr int kNarrow = 256;
-constexpr int kDeferred = 1024;  // levels walked at most while the row is filled
+// Vertices of more than kHubDegree entries wait, up to kHubs at a time, for the whole
+// workgroup (5,000 vertices joined to four of them: one query with a target 132 us with
+// a hub's entries by the wavefront that takes its level, 27 so; 1,000 rows 812 and 155).
+constexpr int kHubs = 64;
+constexpr int kHubDegree = 256;
+constexpr int kDeferred = 1023 - kHubs;    // levels walked at most while the row is filled
 template <int GS, bool kRecords>
 __global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t *__restrict__ adj_off,
                                                         const int32_t *__restrict__ adj, int64_t n_adj,
@@ -552,7 +557,8 @@ __global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t
     uint32_t *bm = reinterpret_cast<uint32_t *>(map_lds);  // [ceil(V / 128) * 4]
     __shared__ int32_t near_q[2][kNarrow];  // a narrow frontier and the next one
     __shared__ int32_t starts[kDeferred + 1];
-    __shared__ int32_t s_lo, s_hi, s_d, s_tail;
+    __shared__ int32_t hubs[kHubs];  // with their entries not yet looked at
+    __shared__ int32_t s_lo, s_hi, s_d, s_tail, s_hubs;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool rows = target == nullptr;
@@ -582,6 +588,7 @@ __global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t
             s_lo = 0;
             s_hi = go ? 1 : 0;
             s_d = 0;
+            s_hubs = 0;
             starts[0] = 0;
             if (go) {
                 list[0] = s;
@@ -592,10 +599,11 @@ __global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t
         __syncthreads();
         // Narrow levels, by wavefront 0: the frontier in near_q[0], ids
         // list[lo .. hi).  Ends with the frontier empty, too wide, the target
-        // reached, or (deferred) kDeferred levels behind it.
+        // reached, (deferred) kDeferred levels behind it, or hubs among the
+        // last level's vertices.
         auto narrow = [&](bool deferred) {
-            int32_t lo = s_lo, hi = s_hi, d = s_d, cur = 0;
-            while (hi > lo && hi - lo <= kNarrow && !(deferred && d >= kDeferred) && !(!rows && bit(tgt))) {
+            int32_t lo = s_lo, hi = s_hi, d = s_d, cur = 0, nh = 0;
+            while (nh == 0 && hi > lo && hi - lo <= kNarrow && !(deferred && d >= kDeferred) && !(!rows && bit(tgt))) {
                 const int32_t n = hi - lo;
                 int32_t *nq = near_q[cur ^ 1];
                 int32_t nn = 0;
@@ -637,7 +645,13 @@ __global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t
                             const int32_t w = __builtin_amdgcn_readlane(v[k], static_cast<int>(__builtin_ctzll(big)));
                             big &= big - 1;
                             const int64_t e = adj_off[w + 1];
-                            for (int64_t p = adj_off[w]; p < e; p += 64) {
+                            int64_t p = adj_off[w];
+                            if (e - p > kHubDegree && nh < kHubs) {
+                                if (lane == 0) hubs[nh] = w;
+                                ++nh;
+                                continue;
+                            }
+                            for (; p < e; p += 64) {
                                 const int32_t u = p + lane < e ? adj[p + lane] : -1;
                                 const uint32_t g = u >= 0 && u < V ? region[u] : 32u;
                                 claim(g < 32 ? static_cast<uint32_t>(u) | g << kVertexBits : kHole);
@@ -658,6 +672,39 @@ __global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t
                 s_lo = lo;
                 s_hi = hi;
                 s_d = d;
+                s_hubs = nh;
+            }
+        };
+        // the whole workgroup's: r's vertex is on level d unless it was reached before
+        auto claim_wide = [&](uint32_t r, int32_t d) {
+            const bool ok = !(r >> 31) && ((A >> (r >> kVertexBits)) & 1u);
+            const uint32_t u = r & ((1u << kVertexBits) - 1);
+            if (!__ballot(ok)) return;
+            bool fresh = false;
+            if (ok && !bit(static_cast<int32_t>(u)))
+                fresh = !((atomicOr(&bm[u >> 5], 1u << (u & 31)) >> (u & 31)) & 1u);
+            const uint64_t m = __ballot(fresh);
+            if (!m) return;
+            const int lead = static_cast<int>(__builtin_ctzll(m));
+            int32_t at = 0;
+            if (lane == lead) at = atomicAdd(&s_tail, static_cast<int32_t>(__popcll(m)));
+            at = __builtin_amdgcn_readlane(at, lead);
+            if (fresh) {
+                list[at + rank_in(m)] = static_cast<int32_t>(u);
+                if (rows) row[u] = d;
+            }
+        };
+        // the waiting hubs' neighbours, on level d (between barriers)
+        auto expand_hubs = [&](int32_t d) {
+            const int32_t nh = min(s_hubs, kHubs);
+            for (int32_t h = 0; h < nh; ++h) {
+                const int32_t w = hubs[h];
+                const int64_t e = adj_off[w + 1];
+                for (int64_t p = adj_off[w] + wave * 64; p < e; p += kMapThreads) {
+                    const int32_t u = p + lane < e ? adj[p + lane] : -1;
+                    const uint32_t g = u >= 0 && u < V ? region[u] : 32u;
+                    claim_wide(g < 32 ? static_cast<uint32_t>(u) | g << kVertexBits : kHole, d);
+                }
             }
         };
         auto fill = [&](int32_t first, int32_t step) {  // -1 over the row: 16-byte stores between its unaligned ends
@@ -688,6 +735,17 @@ __global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t
             __syncthreads();
         }
         while (true) {
+            if (kRecords && s_hubs) {  // left by narrow()
+                if (tid == 0) s_tail = s_hi;
+                __syncthreads();
+                expand_hubs(s_d);
+                __syncthreads();
+                if (tid == 0) {
+                    s_hi = s_tail;
+                    s_hubs = 0;
+                }
+                __syncthreads();
+            }
             const int32_t lo = s_lo, hi = s_hi, d = s_d;
             if (hi <= lo || (!rows && bit(tgt))) break;
             __syncthreads();
@@ -704,24 +762,6 @@ __global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t
             }
             if (tid == 0) s_tail = hi;
             __syncthreads();
-            auto claim = [&](uint32_t r) {
-                const bool ok = !(r >> 31) && ((A >> (r >> kVertexBits)) & 1u);
-                const uint32_t u = r & ((1u << kVertexBits) - 1);
-                if (!__ballot(ok)) return;
-                bool fresh = false;
-                if (ok && !bit(static_cast<int32_t>(u)))
-                    fresh = !((atomicOr(&bm[u >> 5], 1u << (u & 31)) >> (u & 31)) & 1u);
-                const uint64_t m = __ballot(fresh);
-                if (!m) return;
-                const int lead = static_cast<int>(__builtin_ctzll(m));
-                int32_t at = 0;
-                if (lane == lead) at = atomicAdd(&s_tail, static_cast<int32_t>(__popcll(m)));
-                at = __builtin_amdgcn_readlane(at, lead);
-                if (fresh) {
-                    list[at + rank_in(m)] = static_cast<int32_t>(u);
-                    if (rows) row[u] = d + 1;
-                }
-            };
             constexpr int kPerWave = 64 / GS;
             for (int32_t i0 = lo + wave * kPerWave; i0 < hi; i0 += kMapThreads / GS) {
                 const int32_t i = i0 + lane / GS;
@@ -731,10 +771,10 @@ __global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t
                     uint4 R = make_uint4(kHole, kHole, kHole, kHole);
                     if (w >= 0) R = reinterpret_cast<const uint4 *>(ell)[static_cast<int64_t>(w) * 4 + (lane & 3)];
                     lists = __shfl(R.x == kUseLists ? 1 : 0, lane & ~3, 64) != 0;
-                    claim(R.x);
-                    claim(R.y);
-                    claim(R.z);
-                    claim(R.w);
+                    claim_wide(R.x, d + 1);
+                    claim_wide(R.y, d + 1);
+                    claim_wide(R.z, d + 1);
+                    claim_wide(R.w, d + 1);
                 }
                 int64_t p = 0, e = 0;
                 if (lists) {
@@ -742,17 +782,28 @@ __global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t
                     e = adj_off[w + 1];
                     if (!pc_range_ok(p, e, n_adj)) e = p;
                 }
+                if constexpr (kRecords) {
+                    int32_t at = kHubs;
+                    if (e - p > kHubDegree && (lane & 3) == 0) at = atomicAdd(&s_hubs, 1);
+                    if (at < kHubs) hubs[at] = w;
+                    if (__shfl(at, lane & ~3, 64) < kHubs) e = p;  // (all four lanes')
+                }
                 for (p += lane % GS; __ballot(p < e); p += GS) {
                     const int32_t u = p < e ? adj[p] : -1;
                     const uint32_t g = u >= 0 && u < V ? region[u] : 32u;
-                    claim(g < 32 ? static_cast<uint32_t>(u) | g << kVertexBits : kHole);
+                    claim_wide(g < 32 ? static_cast<uint32_t>(u) | g << kVertexBits : kHole, d + 1);
                 }
             }
             __syncthreads();
+            if (kRecords && s_hubs) {
+                expand_hubs(d + 1);
+                __syncthreads();
+            }
             if (tid == 0) {
                 s_lo = hi;
                 s_hi = s_tail;
                 s_d = d + 1;
+                s_hubs = 0;
             }
             __syncthreads();
         }

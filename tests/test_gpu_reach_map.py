@@ -35,13 +35,18 @@ def _graph(kind, V, rng):
         spokes = np.concatenate([np.stack([np.full(n, h), rng.integers(0, V, n)], 1)
                                  for h, n in zip(hubs, rng.integers(17, 400, 40))])
         return _csr(V, np.concatenate([np.stack([v[:-1], v[1:]], 1), spokes[spokes[:, 0] != spokes[:, 1]]]))
+    if kind == "star":      # hubs of V entries: on narrow levels, then, past 64 of 300 entries, on wide ones
+        a, b = np.arange(100), rng.integers(100, V, (100, 300))
+        return _csr(V, np.concatenate([np.stack([np.full(V - 1, 0), v[1:]], 1), np.stack([np.full(V - 2, 1), v[2:]], 1),
+                                       np.stack([np.repeat(a, 300), b.ravel()], 1)]))
     deg = {"sparse": 3, "mixed": 8, "mean20": 20, "dense": 60}[kind]  # random: wide levels
     return _csr(V, np.stack([rng.integers(0, V, V * deg // 2), rng.integers(0, V, V * deg // 2)], 1))
 
 
 @pytest.mark.parametrize("kind,V,Q", [
     ("line", 6017, 5), ("line", 7003, 3), ("hubs", 9001, 9), ("sparse", 20001, 300), ("mixed", 12007, 40),
-    ("mean20", 8191, 20), ("dense", 6100, 12), ("sparse", 512, 1000), ("sparse", 4001, 1024), ("sparse", 4001, 1025), ("blocks", 1_259_000, 4), ("blocks", 1_300_001, 4)])
+    ("mean20", 8191, 20), ("dense", 6100, 12), ("sparse", 512, 1000), ("sparse", 4001, 1024), ("sparse", 4001, 1025), ("blocks", 1_259_000, 4), ("blocks", 1_300_001, 4),
+    ("star", 40_001, 30), ("star", 12_000, 600)])
 def test_map_rows_and_targets(g, orc, kind, V, Q):
     rng = np.random.default_rng(V)
     off, adj = _graph(kind, V, rng)
@@ -108,3 +113,25 @@ def test_map_scratch_refused(g, orc, monkeypatch, call):
     else:
         want, _ = orc.reach(V, off, adj, region, src, allowed, target if call == "targets" else None)
     assert np.array_equal(got.cpu().numpy(), want)
+
+
+def test_map_hubs_at_once(g, orc):
+    """5,000 vertices joined to four hubs: a hub's 5,000 entries are the whole workgroup's (64 queries 107 us by one
+    wavefront, which took them 64 at a time)."""
+    import paper_2602_16100_amd as pc
+    rng = np.random.default_rng(2)
+    V, Q = 5000, 64
+    v = np.arange(4, V)
+    off, adj = _csr(V, np.concatenate([np.stack([np.full(V - 4, h), v], 1) for h in range(4)]))
+    region = np.zeros(V, np.uint8)
+    src, target = (rng.integers(0, V, Q).astype(np.int32) for _ in range(2))
+    allowed = np.ones(Q, np.uint32)
+    ctx = pc.context()
+    for _ in range(2):
+        ctx.profile(True)
+        dg = g.reach(V, off, adj, region, src, allowed, target)
+        used = ctx.profile_read()
+        ctx.profile(False)
+    do, _ = orc.reach(V, off, adj, region, src, allowed, target)
+    assert np.array_equal(dg, do)
+    assert used["k_rc_map"][1] < 0.06, used
