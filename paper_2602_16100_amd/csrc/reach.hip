@@ -897,14 +897,19 @@ int32_t checks(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *ad
     return c.gen;
 }
 
-// Does the bitset search take Q queries (legs)?  The graph has to fit its
-// LDS.  Few queries on a sparse graph would leave most of the
-// chip idle and pass over every vertex on each of many levels (bitset /
-// map, rows: 6,000 vertices of mean degree 4, 256 queries 272 / 80 us, 1,024
-// queries 280 / 145 us, 4,096 queries 309 / 424 us; 1,000 vertices, 64 queries
-// 46 / 33 us, 1,024 queries 75 / 77 us; 100 vertices, 64 queries 20 / 33 us).
-// Denser graphs have few levels (1,280 switches of degree 32, 64 queries
-// 41 / 36 us; 2,880 of degree 48 80 / 84 us): the bitset search keeps them.
+// Does the bitset search take Q queries (rows, or targets and legs)?  The graph
+// has to fit its LDS.  Few queries on a sparse graph would leave most of the chip
+// idle and pass over every vertex on each of many levels; the map search pays for
+// every query, and past 512 workgroups a second round.  How many levels there are
+// the host does not know.  Bitset / map on geometric graphs of mean degree 4 (many
+// levels) and random ones of mean degree 8 (few): rows, 256 queries on 1,000
+// vertices 86 / 49 and 55 / 38 us, 512 there 91 / 83 and 55 / 62, 512 on 2,000
+// 149 / 89 and 95 / 70, 1,024 on 6,000 436 / 252 and 265 / 240; past the limit 1,024 on
+// 1,000 92 / 148 and 57 / 101.  Targets, 256 queries on 1,000 vertices 86 / 50 and
+// 23 / 32, 512 on 6,000 387 / 144 and 102 / 95; past the limit 512 on 1,000 88 / 85
+// and 23 / 45, 1,024 on 6,000 386 / 231 and 76 / 166.  Denser graphs have few levels
+// (1,280 switches of degree 32, 64 queries 41 / 36; 2,880 of degree 48 80 / 84):
+// the bitset search keeps them.
 size_t bitset_lds(int32_t V)
 {
     // visited / frontier / next (8 B each), region (1 B) and list (2 B) per vertex
@@ -912,10 +917,11 @@ size_t bitset_lds(int32_t V)
            static_cast<size_t>(V) * 2;
 }
 
-bool takes_bitset(int32_t V, int64_t n_adj, int64_t Q)
+bool takes_bitset(int32_t V, int64_t n_adj, int64_t Q, bool rows)
 {
     static_assert(kMaxBitsetV * 27 + 256 + kBitsetStatic <= 160 * 1024, "within a workgroup's LDS");
-    return V > 0 && V <= kMaxBitsetV && !(n_adj / V <= kEll / 2 && V >= 512 && Q <= 1024);
+    const int64_t few = std::min(std::max(V / (rows ? 4 : 12), 256), 1024);
+    return V > 0 && V <= kMaxBitsetV && !(n_adj / V <= kEll / 2 && V >= 512 && Q <= few);
 }
 
 // The search of Q queries (legs).  bits: the bitset search.  Else, with map:
@@ -938,9 +944,9 @@ struct Search {
 // query two hops away on a million vertices 36 us, by the queue search 21; but
 // where they are is not known, and sixteen queries anywhere 242, by the queue
 // search 864.)
-int choose_search(pc_ctx *ctx, int32_t V, int64_t n_adj, int64_t Q, Search &s)
+int choose_search(pc_ctx *ctx, int32_t V, int64_t n_adj, int64_t Q, bool rows, Search &s)
 {
-    s.bits = takes_bitset(V, n_adj, Q);
+    s.bits = takes_bitset(V, n_adj, Q, rows);
     if (s.bits || V == 0 || Q == 0 || Q > INT32_MAX) return PC_OK;
     int max_lds = 0;
     PC_HIP(ctx, hipDeviceGetAttribute(&max_lds, hipDeviceAttributeMaxSharedMemoryPerBlock, ctx->device));
@@ -1126,7 +1132,7 @@ int run_reach(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t *adj
               int32_t *dist, hipStream_t stream)
 {
     Search m;
-    const int rc = choose_search(ctx, V, n_adj, Q, m);
+    const int rc = choose_search(ctx, V, n_adj, Q, target == nullptr, m);
     if (rc) return rc;
     const int32_t gen = checks(ctx, V, adj_off, adj, n_adj, region, Q, src, target, nullptr, 0, nullptr, 0,
                                target && m.bits, stream);
@@ -1142,7 +1148,7 @@ int run_reach_via(pc_ctx *ctx, int32_t V, const int32_t *adj_off, const int32_t 
 {
     const int64_t nl = static_cast<int64_t>(Q) * (Kv + 1);
     Search m;
-    int rc = choose_search(ctx, V, n_adj, nl, m);
+    int rc = choose_search(ctx, V, n_adj, nl, false, m);
     if (rc) return rc;
     const int32_t gen = checks(ctx, V, adj_off, adj, n_adj, region, Q, src, target, via, Kv, forbid, Kf,
                                Q > 0 && (Kv > 0 || m.bits), stream);

@@ -239,7 +239,7 @@ def test_report_paths_cfg1_visit_patterns(g, orc):
 
 
 # legs of the map search, of the bitset search, and of the bitset search in source order
-@pytest.mark.parametrize("Q", [130, 500, 4700])
+@pytest.mark.parametrize("Q", [80, 130, 500, 4700])
 @pytest.mark.parametrize("kind", ["symmetric", "asymmetric", "unsorted", "bad_offsets"])
 def test_reach_via_leg_direction(g, orc, kind, Q):
     """Legs are searched from their far end only on symmetric graphs with
@@ -266,7 +266,7 @@ def test_reach_via_leg_direction(g, orc, kind, Q):
     forbid = rng.integers(-1, wl["V"], size=(Q, 2)).astype(np.int32)
     dg, used = g.kernels(lambda: g.reach_via(wl["V"], adj_off, adj, wl["region"], wl["src"], wl["allowed"], wl["target"],
                                              via, forbid))
-    assert ("k_rc_map" if Q == 130 else "k_rc_bitset") in used and ("k_rc_legs" in used) == (Q != 500)
+    assert ("k_rc_map" if Q == 80 else "k_rc_bitset") in used and ("k_rc_legs" in used) == (Q in (80, 4700))
     do, _ = orc.reach_via(wl["V"], adj_off, adj, wl["region"], wl["src"], wl["allowed"], wl["target"], via, forbid)
     _same(dg, do, "reach_via")
     assert (do >= 0).sum() > 5

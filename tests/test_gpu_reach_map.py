@@ -45,7 +45,8 @@ def _graph(kind, V, rng):
 
 @pytest.mark.parametrize("kind,V,Q", [
     ("line", 6017, 5), ("line", 7003, 3), ("hubs", 9001, 9), ("sparse", 20001, 300), ("mixed", 12007, 40),
-    ("mean20", 8191, 20), ("dense", 6100, 12), ("sparse", 512, 1000), ("sparse", 4001, 1024), ("sparse", 4001, 1025), ("blocks", 1_259_000, 4), ("blocks", 1_300_001, 4),
+    ("mean20", 8191, 20), ("dense", 6100, 12), ("sparse", 512, 1000), ("sparse", 4001, 1024), ("sparse", 4001, 1025), ("sparse", 4001, 1000), ("sparse", 4001, 1001),
+    ("sparse", 4001, 333), ("sparse", 4001, 334), ("sparse", 512, 256), ("sparse", 600, 257), ("blocks", 1_259_000, 4), ("blocks", 1_300_001, 4),
     ("star", 40_001, 30), ("star", 12_000, 600)])
 def test_map_rows_and_targets(g, orc, kind, V, Q):
     rng = np.random.default_rng(V)
@@ -135,3 +136,26 @@ def test_map_hubs_at_once(g, orc):
     do, _ = orc.reach(V, off, adj, region, src, allowed, target)
     assert np.array_equal(dg, do)
     assert used["k_rc_map"][1] < 0.06, used
+
+
+@pytest.mark.parametrize("V,Q,rows,targets", [(1000, 256, True, True), (1000, 257, False, False), (3600, 300, True, True),
+                                              (3600, 301, True, False), (3600, 900, True, False), (3600, 901, False, False)])
+def test_few_queries_of_sparse_graphs(g, orc, V, Q, rows, targets):
+    """The map search takes rows up to a quarter of the vertices, targets and legs up to a twelfth, and 256 either way."""
+    rng = np.random.default_rng(V + Q)
+    off, adj = _graph("mixed", V, rng)
+    region = rng.integers(0, 4, V).astype(np.uint8)
+    src, target = (rng.integers(0, V, Q).astype(np.int32) for _ in range(2))
+    allowed = rng.integers(1, 16, Q).astype(np.uint32)
+    none = np.zeros((Q, 0), np.int32)
+    for t, by_map in ((None, rows), (target, targets)):
+        dg, used = g.kernels(lambda: g.reach(V, off, adj, region, src, allowed, t))
+        assert ("k_rc_map" in used) == by_map and ("k_rc_bitset" in used) != by_map
+        do, _ = orc.reach(V, off, adj, region, src, allowed, t)
+        assert np.array_equal(dg, do)
+    via = rng.integers(-1, V, (Q // 2, 1)).astype(np.int32)
+    args = (V, off, adj, region, *(x[:Q // 2] for x in (src, allowed, target)), via, none[:Q // 2])
+    dg, used = g.kernels(lambda: g.reach_via(*args))
+    assert ("k_rc_map" in used) == (Q // 2 * 2 <= max(256, V // 12))
+    do, _ = orc.reach_via(*args)
+    assert np.array_equal(dg, do)
