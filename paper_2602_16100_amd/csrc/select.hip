@@ -2479,7 +2479,9 @@ int run_selectors(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, cons
     // without predicates still take a wavefront each, so their number counts too:
     // 20,000 predicates in 25,000 rows over 500 nodes 27 / 26, in 50,000 32 / 34, in
     // 200,000 62 / 81; over 250 nodes 200,000 rows 60 / 56, 500,000 94 / 123; over
-    // 64 500,000 rows 93 / 76, 1,000,000 146 / 151, 2,000,000 255 / 307.
+    // 64 500,000 rows 93 / 76, 1,000,000 146 / 151, 2,000,000 255 / 307.  (Where one row
+    // has most of the predicates a wavefront tests them in turn, as the compile did: a row of
+    // 5,000 over 64 nodes 2,330 / 1,790, over 300 2,340 / 2,880; of 300 163 / 113, 160 / 179.)
     const size_t small_lds = static_cast<size_t>(L) * static_cast<size_t>(small_pitch(W));
     const bool small = W > 0 && W <= kSmallW && small_lds <= kSmallLds && n_preds <= kSmallWork / (W + 2) &&
                        I <= small_rows(W);

@@ -473,7 +473,8 @@ int run_update_nodes(pc_ctx *ctx, const uint8_t *labels, int32_t N, int32_t L, c
     // Up to 64 nodes the listed form is the faster one at every size: listed
     // / every row in full, 64 nodes, 3,000 rows of 313 words 39 / 46 us,
     // 200,003 rows of 16 words 56 / 93, of 313 words 192 / 190, of 782 words
-    // 296 / 333.  Longer lists: above W / 32 nodes the scattered word updates
+    // 296 / 333.  (One row of 20,000 predicates, which either form gives one thread, nine
+    // nodes: in three launches 9.2 ms, so 13.0; of 300 168 us and 203.)  Longer lists: above W / 32 nodes the scattered word updates
     // cost about as much as rewriting every row, which gives the same result.
     // PC_UPDATE_FULL_ABOVE overrides the threshold.
     int64_t full_above = few ? kFewNodes : W / 32;
