@@ -538,6 +538,8 @@ constexpr int kNarrow = 256;
 // Vertices of more than kHubDegree entries wait, up to kHubs at a time, for the whole
 // workgroup (5,000 vertices joined to four of them: one query with a target 132 us with
 // a hub's entries by the wavefront that takes its level, 27 so; 1,000 rows 812 and 155).
+// Marked as unlikely, which keeps it out of the way of graphs without (256 rows of a
+// million vertices 392 us in line, 389 so and without it).
 constexpr int kHubs = 64;
 constexpr int kHubDegree = 256;
 constexpr int kDeferred = 1023 - kHubs;    // levels walked at most while the row is filled
@@ -603,7 +605,7 @@ __global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t
         // last level's vertices.
         auto narrow = [&](bool deferred) {
             int32_t lo = s_lo, hi = s_hi, d = s_d, cur = 0, nh = 0;
-            while (nh == 0 && hi > lo && hi - lo <= kNarrow && !(deferred && d >= kDeferred) && !(!rows && bit(tgt))) {
+            while (hi > lo && hi - lo <= kNarrow && !(deferred && d >= kDeferred) && !(!rows && bit(tgt))) {
                 const int32_t n = hi - lo;
                 int32_t *nq = near_q[cur ^ 1];
                 int32_t nn = 0;
@@ -641,12 +643,12 @@ __global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t
                         claim(R[k].y);
                         claim(R[k].z);
                         claim(R[k].w);
-                        while (big) {  // a vertex of many entries: its list, across the wavefront
+                        while (__builtin_expect(big != 0, 0)) {  // a vertex of many entries: its list, across the wavefront
                             const int32_t w = __builtin_amdgcn_readlane(v[k], static_cast<int>(__builtin_ctzll(big)));
                             big &= big - 1;
                             const int64_t e = adj_off[w + 1];
                             int64_t p = adj_off[w];
-                            if (e - p > kHubDegree && nh < kHubs) {
+                            if (__builtin_expect(e - p > kHubDegree && nh < kHubs, 0)) {
                                 if (lane == 0) hubs[nh] = w;
                                 ++nh;
                                 continue;
@@ -666,6 +668,7 @@ __global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t
                 hi += nn;
                 ++d;
                 if (deferred && lane == 0) starts[d] = lo;
+                if (nh) break;
                 cur ^= 1;
             }
             if (lane == 0) {
@@ -695,9 +698,8 @@ __global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t
             }
         };
         // the waiting hubs' neighbours, on level d (between barriers)
-        auto expand_hubs = [&](int32_t d) {
-            const int32_t nh = min(s_hubs, kHubs);
-            for (int32_t h = 0; h < nh; ++h) {
+        auto expand_hubs = [&](int32_t n, int32_t d) {
+            for (int32_t h = 0; h < min(n, kHubs); ++h) {
                 const int32_t w = hubs[h];
                 const int64_t e = adj_off[w + 1];
                 for (int64_t p = adj_off[w] + wave * 64; p < e; p += kMapThreads) {
@@ -735,18 +737,19 @@ __global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t
             __syncthreads();
         }
         while (true) {
-            if (kRecords && s_hubs) {  // left by narrow()
-                if (tid == 0) s_tail = s_hi;
+            const int32_t lo = s_lo, d = s_d, waiting = kRecords ? s_hubs : 0;
+            int32_t hi = s_hi;
+            if (__builtin_expect(waiting != 0, 0)) {  // left by narrow()
+                if (tid == 0) s_tail = hi;
                 __syncthreads();
-                expand_hubs(s_d);
+                expand_hubs(waiting, d);
                 __syncthreads();
+                hi = s_tail;
                 if (tid == 0) {
-                    s_hi = s_tail;
+                    s_hi = hi;
                     s_hubs = 0;
                 }
-                __syncthreads();
             }
-            const int32_t lo = s_lo, hi = s_hi, d = s_d;
             if (hi <= lo || (!rows && bit(tgt))) break;
             __syncthreads();
             if (kRecords && hi - lo <= kNarrow / 2) {
@@ -782,7 +785,7 @@ __global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t
                     e = adj_off[w + 1];
                     if (!pc_range_ok(p, e, n_adj)) e = p;
                 }
-                if constexpr (kRecords) {
+                if (kRecords && __ballot(e - p > kHubDegree)) {
                     int32_t at = kHubs;
                     if (e - p > kHubDegree && (lane & 3) == 0) at = atomicAdd(&s_hubs, 1);
                     if (at < kHubs) hubs[at] = w;
@@ -795,9 +798,12 @@ __global__ __launch_bounds__(kMapThreads) void k_rc_map(int32_t V, const int32_t
                 }
             }
             __syncthreads();
-            if (kRecords && s_hubs) {
-                expand_hubs(d + 1);
-                __syncthreads();
+            if (kRecords) {
+                const int32_t found = s_hubs;
+                if (found) {
+                    expand_hubs(found, d + 1);
+                    __syncthreads();
+                }
             }
             if (tid == 0) {
                 s_lo = hi;
