@@ -34,63 +34,64 @@ VALU_PEAK_LANE_OPS = 256 * 128 * 2.4e9
 # scalar ALU: one instruction per CU per clock (measured 0.96 of it)
 SALU_PEAK_INSTR = 256 * 2.4e9
 
-# HBM bytes per launch of k_sel_eval, k_aff_eval and k_tr_prep (per step of
-# k_tr_match) on the combined workload, from one rocprofv3 FETCH_SIZE pass and
-# one WRITE_SIZE pass each, scaled by what the same counter reads for a plain
-# copy of known size (the command lines and counter values are in
-# profiles/k_sel_eval_k_tr_prep_cfg5_hbm_counters.md).  Valid only for the
-# kernel source they were measured on.
+# HBM bytes per launch of k_sel_eval, k_aff_eval, the four k_pref_eval launches
+# and k_tr_prep (per step of the match) on the combined workload, from one
+# rocprofv3 FETCH_SIZE pass and one WRITE_SIZE pass each, scaled by what the
+# same counter reads for a plain copy of known size (the command lines and
+# counter values are in profiles/k_sel_eval_k_tr_prep_cfg5_hbm_counters.md).
+# Valid only for the kernel source they were measured on.
 TRAFFIC = [
     {"source": "paper_2602_16100_amd/csrc/select.hip",
-     "sha256": "3ba266f186a97c69f5525e79cbd1aa8e8de7774ba0177ee4f0f28a75ebc43f74",
+     "sha256": "ed10233eacdfb9690f5c7b077ffed58e520b96641cbcf89720215938a77a8779",
      "workload": "cfg5",
-     "bytes_per_launch": {"k_sel_eval": 680_687_937 + 4_407_406_605,
-                          "k_aff_eval": 1_360_481_846 + 4_407_121_613}},
+     "bytes_per_launch": {"k_sel_eval": 684_323_438 + 4_407_204_557,
+                          "k_aff_eval": 1_391_696_871 + 4_406_970_778,
+                          "k_pref_eval": 7_632_870_361 + 317_199_053}},
     {"source": "paper_2602_16100_amd/csrc/trace.hip",
-     "sha256": "c9b11ae36f815781b39e2ccddb1fca6cd58dc757cfef139cb8fdfc38042cac7d",
+     "sha256": "6c879bbe2138a3b09ea7694d4c038050651b5876bac498cf3f2f170aa554efcf",
      "workload": "cfg5",
-     # k_tr_match: per step (its 6 launches), like the hop-loop roofline
-     "bytes_per_launch": {"k_tr_prep": 1_888_686_134 + 566_231_040,
-                          "k_tr_match": 2_325_285_696 + 142_260_102}},
+     # k_tr_match_wide: per step (its 6 launches), like the hop-loop roofline
+     "bytes_per_launch": {"k_tr_prep": 1_888_818_359 + 566_231_040,
+                          "k_tr_match_wide": 2_324_476_813 + 142_258_586}},
     # the single-kernel configurations (profiles/cfg2_cfg3_cfg4_hbm_counters.md)
     {"source": "paper_2602_16100_amd/csrc/select.hip",
-     "sha256": "3ba266f186a97c69f5525e79cbd1aa8e8de7774ba0177ee4f0f28a75ebc43f74",
+     "sha256": "ed10233eacdfb9690f5c7b077ffed58e520b96641cbcf89720215938a77a8779",
      "workload": "cfg2",
-     "bytes_per_launch": {"k_sel_eval": 61_279_026 + 206_234_144}},
+     "bytes_per_launch": {"k_sel_eval": 54_978_636 + 206_353_818}},
     {"source": "paper_2602_16100_amd/csrc/trace.hip",
-     "sha256": "c9b11ae36f815781b39e2ccddb1fca6cd58dc757cfef139cb8fdfc38042cac7d",
+     "sha256": "6c879bbe2138a3b09ea7694d4c038050651b5876bac498cf3f2f170aa554efcf",
      "workload": "cfg3-rpath",
-     "bytes_per_launch": {"k_tr_match": 1_056_617_428 + 793_564_755}},  # per call (its 7 launches)
+     "bytes_per_launch": {"k_tr_match": 1_058_834_651 + 776_572_006}},  # per call (its 6 launches)
     {"source": "paper_2602_16100_amd/csrc/reach.hip",
-     "sha256": "c5686db7947fd48ea645f261a5cf397dcff66e0567c993962d5520fdb59c8dee",
+     "sha256": "1bbf33a160fad785eab8aa6761ca72ffb20d52f01fe5a32cbffe869d7a254740",
      "workload": "cfg4",
-     # per call: k_rc_validate, the -1 fill and k_rc_queue
-     "bytes_per_launch": {"pc_masked_reach": 47_662_753 + 1_047_437_664}},
+     # per call: k_rc_checks, k_rc_records and k_rc_map
+     "bytes_per_launch": {"pc_masked_reach": 64_333_634 + 1_092_269_568}},
 ]
 
 
-# Issue counters of k_tr_match on the combined workload (one rocprofv3 pass
+# Issue counters of k_tr_match_wide on the combined workload (one rocprofv3 pass
 # per counter group; the command and the per-step values are in the profiles
 # folder).  Valid only for the kernel source they were measured on.
 MATCH_COUNTERS = {
     "cfg5": {"source": "paper_2602_16100_amd/csrc/trace.hip",
-             "sha256": "c9b11ae36f815781b39e2ccddb1fca6cd58dc757cfef139cb8fdfc38042cac7d",
-             "SQ_INSTS_VALU_per_step": 3.895e8, "SQ_INSTS_SALU_per_step": 3.235e8},
+             "sha256": "6c879bbe2138a3b09ea7694d4c038050651b5876bac498cf3f2f170aa554efcf",
+             "SQ_INSTS_VALU_per_step": 3.932e8, "SQ_INSTS_SALU_per_step": 3.253e8},
 }
 
 
-# Issue counters of the instruction-bound kernels of two passes on the
-# combined workload, per launch (one rocprofv3 pass; the command and values
-# are in the profiles folder): the preferred-affinity evaluator of rows of at
-# most three terms, and the path search.  Valid only for the kernel source
-# they were measured on.
+# Issue counters of two passes' main kernels on the combined workload, per
+# launch (one rocprofv3 pass; the command and values are in the profiles
+# folder): the preferred-affinity evaluator of rows of at most three terms, and
+# the directed path search.  Valid only for the kernel source they were measured
+# on.
 PASS_COUNTERS = {
     "k_pref_eval3": {"source": "paper_2602_16100_amd/csrc/select.hip",
-                     "sha256": "3ba266f186a97c69f5525e79cbd1aa8e8de7774ba0177ee4f0f28a75ebc43f74",
-                     "SQ_INSTS_VALU_per_launch": 1.1454e9, "SQ_INSTS_SALU_per_launch": 7.263e8},
-    "k_ps_search": {"source": "paper_2602_16100_amd/csrc/paths.hip",
-                    "sha256": "2cd6a2ef3bef6e4dbc6d79785967370e9c75b27ef64d4f64f685999d7c9ac81e",
-                    "SQ_INSTS_VALU_per_launch": 4.129e9, "SQ_INSTS_SALU_per_launch": 3.355e9},
+                     "sha256": "ed10233eacdfb9690f5c7b077ffed58e520b96641cbcf89720215938a77a8779",
+                     "SQ_INSTS_VALU_per_launch": 6.992e8, "SQ_INSTS_SALU_per_launch": 5.586e8},
+    "k_ps_goal": {"source": "paper_2602_16100_amd/csrc/paths.hip",
+                  "sha256": "44be860c6cf267051e7a50a6399f1ba262e7032061744ebc92902f738c8d099a",
+                  "SQ_INSTS_VALU_per_launch": 1.730e8, "SQ_INSTS_SALU_per_launch": 1.585e8},
 }
 
 
@@ -629,7 +630,7 @@ def time_preferred(args, wl, pc, ctx, feasible):
                      "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": measured_traffic(args.workload, "k_pref_eval"), "alg_bytes_per_launch": alg,
                      "avg_launch_ms": avg_ms,
-                     # the class that takes every row at this size is instruction bound
+                     # the class that takes every row at this size
                      "alu": alu_view("k_pref_eval3", prof["k_pref_eval3"][1] / max(prof["k_pref_eval3"][0], 1)
                                      if "k_pref_eval3" in prof else None)},
         "placed_rows": int((b >= 0).sum()),

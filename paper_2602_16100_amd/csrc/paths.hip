@@ -353,10 +353,11 @@ __global__ __launch_bounds__(256) void k_ps_links(int32_t V, const int32_t *__re
 // lane, so sweeps read whatever is newest.  Saturated sums are lower
 // bounds like the rest.  A graph that needs more than kSweeps sweeps is too
 // long for this: its rows are marked as missing.
-// Bound by vector instructions (two packed adds and minima per link, word and
-// sweep): 2,880 rows over 138,240 links, 7-8 sweeps, in 0.31 ms with eight
-// rows per workgroup, 0.33 ms with four; in 32 bits, over weights of a range
-// that needs them, 0.53-1.2 ms.
+// Bound by the chains link -> LDS words -> packed add and minimum of each link and
+// word: of 315 us the vector units issue 28 % of what they could, and waves wait 45 %
+// of their cycles, 31 % for an operand.  2,880 rows over 138,240 links, 7-8 sweeps,
+// in 0.31 ms with eight rows per workgroup, 0.33 ms with four; in 32 bits, over weights
+// of a range that needs them, 0.53-1.2 ms.
 constexpr int kSweeps = 40;
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 template <class T>
@@ -526,7 +527,8 @@ __global__ __launch_bounds__(256 * kW) void k_ps_bound(int32_t V, const int2 *__
 // lanes share a switch's links, so 64 / GS switches are relaxed at once, kUn
 // links per lane in flight.  Requests that need more than kFull slots or
 // max_steps rounds of links go to the list `hard`.
-// Bound by the latency of the link and bound reads, so the wave slots have
+// Bound by the latency of the link and bound reads (waves wait 61 % of their
+// cycles; vector units 22 %, scalar units 41 % of their issue rates), so the wave slots have
 // to fill: 512 slots keep 5 KB of LDS per wavefront (1,024 slots: 0.96 ms
 // instead of 0.60 at the time).  Three links per lane in flight and 16 lanes a
 // switch fit 48-port switches (0.51 ms; four links 0.54, 8 lanes 0.64, 32 lanes

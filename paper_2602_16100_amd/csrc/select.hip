@@ -1987,10 +1987,13 @@ __device__ Words pref_term_decoded(const pc_pred *__restrict__ preds, int64_t b,
 // score bits: a node's score is fixed by the set of terms that hold for it,
 // so the lane's best score is the largest weight sum of a set of terms that
 // hold together for some candidate.
-// Bound by vector instructions: class 3 takes the term sets in one pass of
-// positive intersections (two passes of exact patterns before), one maximum
-// for score and node, and skips the tiles without a feasible node; six
-// waves per SIMD hide its plane loads better than five or seven.  233,017 rows
+// Bound by no unit alone: of 699,051 rows over 50,000 nodes in 1.54 ms, HBM moves
+// 7.9 GB (0.64 of its peak: the feasible words, and plane words that miss L2), the
+// scalar units issue at 59 % and the vector units at 37 % of their rates, and waves wait 55 %
+// of their cycles.  Class 3 takes the term sets in one pass of
+// positive intersections (two passes of exact patterns before: 1.6 times the vector
+// instructions), one maximum for score and node, and skips the tiles without a feasible node;
+// six waves per SIMD hide its plane loads better than five or seven.  233,017 rows
 // x 50,000 nodes, a third of the rows without a feasible node: 1.35 -> 0.52
 // ms; 100,000 three-term rows with every node feasible: the call 0.82 -> 0.48 ms.
 template <bool kBuf, int kCls>
